@@ -13,8 +13,8 @@
 // epilogue is fused: bias + ReLU, or SiLU(gate)*up from two accumulator sets,
 // writing the fp32 score matrix and/or the element-type hidden matrix; or
 // bias + convert for the down projection.
-// gemm_f32_kernel: plain fp32 FMA tiles for the fp32 element type.
-#include "common.hpp"
+// The fp32 element type has its own kernels (gemm_f32.hip).
+#include "gemm_common.hpp"
 
 namespace ci {
 
@@ -23,21 +23,6 @@ namespace {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-enum { EPI_RELU = 0, EPI_SWIGLU = 1, EPI_LINEAR = 2 };
-
-struct GemmArgs {
-  const void* A;
-  const void* B0;  // EPI_SWIGLU: gate
-  const void* B1;  // EPI_SWIGLU: up
-  const void* bias;
-  void* out_e;     // [M, Nn] element type, may be null
-  float* out_f;    // [M, Nn] fp32, may be null
-  int64_t lda, ldb, ldo;
-  int M, Nn, Kk;
-  int k_chunk;     // k range handled by one workgroup along blockIdx.y (a multiple of the k tile)
-  float* partial;  // split-K only: [gridDim.y][M][Nn] fp32 partial products (epilogue skipped)
-};
 
 template <class D>
 __device__ __forceinline__ f32x16 mfma32(const uint4& a, const uint4& b, f32x16 c);
@@ -54,13 +39,6 @@ __device__ __forceinline__ f32x16 mfma32<BF16>(const uint4& a, const uint4& b, f
 
 constexpr int BM = 128, BN = 128, BK = 64;
 constexpr int LDK = BK + 8;  // LDS row stride in elements (144 bytes)
-
-// Spreads consecutive tiles over one XCD (workgroup ids go round-robin over the
-// 8 XCDs, each with its own L2), so that tiles sharing a B panel share an L2.
-__device__ __forceinline__ int xcd_swizzle(int id, int n) {
-  if (n % 8 != 0) return id;
-  return (id % 8) * (n / 8) + id / 8;
-}
 
 // Fused epilogue shared by the two MFMA kernels.  Accumulator element v of lane
 // l is C[row, col] with col = l % 32, row = 8 * (v / 4) + 4 * (l / 32) + v % 4
@@ -781,101 +759,6 @@ __global__ __launch_bounds__(512) void gemm_mfma_big_kernel(GemmArgs g) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 element type: 64x64x16 tiles, 256 threads, 4x4 outputs per thread.
-template <int EPI, bool BNN>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  constexpr int NB = DUAL ? 2 : 1;
-  __shared__ float sA[16][68];
-  __shared__ float sB[NB][16][68];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int tiles_m = (g.M + 63) / 64;
-  const int m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64;
-  const float* A = reinterpret_cast<const float*>(g.A);
-  const float* Bp[2] = {reinterpret_cast<const float*>(g.B0), reinterpret_cast<const float*>(g.B1)};
-  float acc[NB][4][4];
-#pragma unroll
-  for (int q = 0; q < NB; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[q][i][j] = 0.f;
-
-  for (int k0 = 0; k0 < g.Kk; k0 += 16) {
-    // 64 rows x 16 k: thread -> (row = tid / 4, k quad = tid % 4)
-    {
-      const int row = tid >> 2, kq = (tid & 3) * 4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + kq + e;
-        sA[kq + e][row] = (m0 + row < g.M && k < g.Kk) ? A[(size_t)(m0 + row) * g.lda + k] : 0.f;
-      }
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        if (!BNN) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int k = k0 + kq + e;
-            sB[q][kq + e][row] = (n0 + row < g.Nn && k < g.Kk) ? Bp[q][(size_t)(n0 + row) * g.ldb + k] : 0.f;
-          }
-        } else {
-          const int kr = tid >> 4, nq = (tid & 15) * 4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int n = n0 + nq + e;
-            sB[q][kr][nq + e] = (k0 + kr < g.Kk && n < g.Nn) ? Bp[q][(size_t)(k0 + kr) * g.ldb + n] : 0.f;
-          }
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[NB][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[k][ty * 4 + i];
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[q][j] = sB[q][k][tx * 4 + j];
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[q][i][j] = fmaf(a[i], b[q][j], acc[q][i][j]);
-    }
-    __syncthreads();
-  }
-  const float* bias = reinterpret_cast<const float*>(g.bias);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= g.M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= g.Nn) continue;
-      const float bv = bias ? bias[col] : 0.f;
-      float h, score;
-      if (EPI == EPI_SWIGLU) {
-        h = silu(acc[0][i][j]) * acc[NB - 1][i][j];
-        score = fabsf(h);
-      } else if (EPI == EPI_RELU) {
-        h = fmaxf(acc[0][i][j] + bv, 0.f);
-        score = h;
-      } else {
-        h = acc[0][i][j] + bv;
-        score = h;
-      }
-      const size_t o = (size_t)row * g.ldo + col;
-      if (g.out_f) g.out_f[o] = score;
-      if (g.out_e) reinterpret_cast<float*>(g.out_e)[o] = h;
-    }
-  }
-}
-
 // Y[m, n] = sum_s partial[s][m][n] + bias[n], converted to the element type.
 template <class D>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial,
@@ -977,17 +860,9 @@ int launch_mfma(const GemmArgs& g, hipStream_t s) {
 }
 
 template <int EPI, bool BNN>
-int launch_f32(const GemmArgs& g, hipStream_t s) {
-  const int tiles = ((g.M + 63) / 64) * ((g.Nn + 63) / 64);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, BNN>), dim3(tiles), dim3(256), 0, s, g);
-  CI_HIP_CHECK_LAUNCH();
-  return CI_OK;
-}
-
-template <int EPI, bool BNN>
 int launch_any(int dtype, const GemmArgs& g, hipStream_t s) {
   switch (dtype) {
-    case CI_F32: return launch_f32<EPI, BNN>(g, s);
+    case CI_F32: return launch_gemm_f32(EPI, BNN, g, s);
     case CI_F16: return launch_mfma<F16, EPI, BNN>(g, s);
     case CI_BF16: return launch_mfma<BF16, EPI, BNN>(g, s);
   }
