@@ -107,6 +107,8 @@ int coreinfer_dev_set_param(const char* name, int value) {
   else if (!strcmp(name, "gemm_ring") && (value == 0 || value == 1)) p.gemm_ring = value;
   else if (!strcmp(name, "gemm_direct") && (value == 0 || value == 1)) p.gemm_direct = value;
   else if (!strcmp(name, "gemm_big") && value >= 0 && value <= 2) p.gemm_big = value;
+  else if (!strcmp(name, "gemm_tile") && value >= -1 && value <= 4) p.gemm_tile = value;
+  else if (!strcmp(name, "gemm_splits") && value >= 0 && value <= 8) p.gemm_splits = value;
   else if (!strcmp(name, "gemv_wgs_per_cu") && value >= 1 && value <= 32) p.gemv_wgs_per_cu = value;
   else if (!strcmp(name, "union_depth") && (value == 8 || value == 16)) p.union_depth = value;
   else if (!strcmp(name, "union_down_threads") && value >= 64 && value <= 512) p.union_down_threads = value;

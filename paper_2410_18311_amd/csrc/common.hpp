@@ -125,9 +125,10 @@ struct Params {
   Knob select_wgs_per_cu{2};
   Knob select_def2_single{0};  // Def. 2 in one workgroup even where the parallel kernel applies
   Knob gemv_wgs_per_cu{4};
-  Knob gemm_ring{1};         // register-ring GEMM kernel where it applies
-  Knob gemm_direct{1};       // 128 x 128 tiles loaded straight into LDS instead of through the register ring
-  Knob gemm_big{1};          // 256 x 256 tiles: 0 never, 1 when there are enough of them, 2 whenever the shape divides
+  Knob gemm_ring{1}, gemm_direct{1};  // either 0: the guarded two-stage GEMM kernel instead of the planned tiles
+  Knob gemm_big{1};          // 256 x 256 tiles: 0 never, 1 where the plan takes them, 2 always
+  Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256)
+  Knob gemm_splits{0};       // k splits of the last round of the down projection: 0 planned
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)
   Knob reduce_cq{8};         // column quads per reduce workgroup (4, 8, 16)
   Knob decode_nt_store{1};   // non-temporal stores for the partial sums
@@ -224,7 +225,6 @@ int launch_down_rows(const float* H, int64_t M, const void* w_down, const void* 
                      int64_t d, int64_t N, void* Y, hipStream_t s);
 int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,
                    int dtype, int act, int64_t d, int64_t N, void* H, float* A, hipStream_t s);
-int gemm_down_splits(int64_t M, int64_t d, int64_t N, int dtype);
 int gemm_down_splits_max(int64_t M, int64_t d, int64_t N, int dtype);  // what the workspace is sized for
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,
                      int down_layout, int dtype, int64_t d, int64_t N, void* Y, float* partial,

@@ -25,10 +25,11 @@
  *   compute unit also for prompts longer than the chip has compute units),
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
- *   "gemv_wgs_per_cu" (1..32), "gemm_ring" (0/1: pipelined 128 x 128 GEMM kernels),
- *   "gemm_direct" (0/1: those tiles loaded straight into LDS, else through a
- *   register ring), "gemm_big" (0 never, 1 when the grid is large enough, 2
- *   whenever the shape divides: the 256 x 256-tile GEMM kernel);
+ *   "gemv_wgs_per_cu" (1..32), "gemm_ring", "gemm_direct" (0/1: either 0
+ *   selects the guarded two-stage GEMM kernel instead of the planned tiles),
+ *   "gemm_big" (0 never, 1 where the plan takes them, 2 always: 256 x 256 tiles),
+ *   "gemm_tile" (-1 planned, 0 .. 4: tile shape), "gemm_splits" (0 planned, 1 .. 8:
+ *   k splits of the last round of tiles of the down projection);
  *   "union_depth" (8, 16), "union_down_threads" (64..512), "union_up_wgs_per_cu"
  *   (1..8), "union_down_wgs_per_cu" (1..16), "union_super" (0 = default, 16..256:
  *   cap on the rows between two drains of the load ring): union-batched decode.

@@ -16,8 +16,9 @@ struct GemmArgs {
   float* out_f;    // [M, Nn] fp32, may be null
   int64_t lda, ldb, ldo;
   int M, Nn, Kk;
-  int k_chunk;     // k range handled by one workgroup along blockIdx.y (a multiple of the k tile)
-  float* partial;  // split-K only: [gridDim.y][M][Nn] fp32 partial products (epilogue skipped)
+  float* partial;  // where the k of a product may be split: [splits][M][Nn] fp32 partial products
+  // tiles computed whole, tiles computed by `splits` workgroups of k_chunk each (a multiple of the k tile)
+  int full, tail, splits, k_chunk;
 };
 
 // Spreads consecutive tiles over one XCD (workgroup ids go round-robin over the
@@ -27,6 +28,30 @@ __device__ __forceinline__ int xcd_swizzle(int id, int n) {
   return (id % 8) * (n / 8) + id / 8;
 }
 
+// The same for any n (workgroup id -> place in an order of which each XCD walks one stretch).
+__device__ __forceinline__ int xcd_spread(int id, int n) {
+  const int x = id & 7, q = n >> 3, r = n & 7;
+  return x * q + (x < r ? x : r) + (id >> 3);
+}
+
+// Place t in the order of the tiles -> tile, such that tiles that run at the same time are close to square:
+// groups of eight tile rows, columns outermost.  The 32 compute units of an XCD then read eight row panels and
+// four column panels through their L2 at a time (all 16 row panels of a 4096-row product first would make
+// that 18 panels).
+__device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n, int* tm, int* tn) {
+  constexpr int G = 8;
+  const int per_group = G * tiles_n;
+  const int grp = t / per_group, in = t % per_group;
+  const int rows = tiles_m - grp * G < G ? tiles_m - grp * G : G;
+  *tm = grp * G + in % rows;
+  *tn = in / rows;
+}
+
+// 256x256-tile kernel for 16-bit types (gemm_wide.hip).
+int launch_gemm_wide(int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
+// Smaller tiles for 16-bit types (gemm_mid.hip): rows of A x rows of B per workgroup.
+enum { kMid128x128 = 0, kMid128x256 = 1, kMid256x64 = 2, kMid128x64 = 3 };
+int launch_gemm_mid(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
 // fp32 kernels (gemm_f32.hip); epi: EPI_*, b_kmajor: B given as [Kk, Nn].
 int launch_gemm_f32(int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
 

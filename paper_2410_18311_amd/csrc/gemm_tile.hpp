@@ -1,0 +1,143 @@
+// Device code that the LDS-tiled GEMM kernels for 16-bit types share (gemm_wide.hip, gemm_mid.hip).
+#pragma once
+
+#include "gemm_common.hpp"
+
+namespace ci {
+
+namespace {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+constexpr int WK = 64;             // k per tile
+
+template <class D>
+__device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c) {
+  if constexpr (D::VEC == 8 && __is_same(D, F16))
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Four consecutive columns of one output row: epilogue, then one 16-byte and / or one 8-byte store.
+template <class D, int EPI>
+__device__ __forceinline__ void store_quad(const GemmArgs& g, float4 c0, float4 c1, const float (&bv)[4], size_t o) {
+  using T = typename D::T;
+  const float z[4] = {c0.x, c0.y, c0.z, c0.w}, u[4] = {c1.x, c1.y, c1.z, c1.w};
+  float h[4], score[4];
+  T e[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (EPI == EPI_SWIGLU) {
+      h[k] = silu(z[k]) * u[k];
+      score[k] = fabsf(h[k]);
+    } else {
+      h[k] = EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
+      score[k] = h[k];
+    }
+    e[k] = from_float<D>(h[k]);
+  }
+  if (g.out_f) *reinterpret_cast<float4*>(g.out_f + o) = make_float4(score[0], score[1], score[2], score[3]);
+  if (g.out_e) {
+    uint2 pack;
+    __builtin_memcpy(&pack, e, 8);
+    *reinterpret_cast<uint2*>(reinterpret_cast<T*>(g.out_e) + o) = pack;
+  }
+}
+
+// Buffer descriptor over everything from a uniform address on: a load then takes one 32-bit offset per lane.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ i32x4 rsrc_at(const char* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return i32x4{(int)a, (int)((a >> 32) & 0xffffu), -1, 0x00020000};
+}
+
+// 16 bytes per lane from `rsrc` + `off` to LDS at `lds` + 16 * lane.  Written out, because the compiler
+// orders transposing LDS reads behind every such load it knows of; nothing is returned to a register, and
+// the waits for its arrival are the kernel's own (s_waitcnt vmcnt ahead of a barrier).
+__device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t off, i32x4 rsrc) {
+  const uint32_t m = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lds;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(m), "v"(off), "s"(rsrc)
+               : "memory");
+}
+
+// Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
+// column l % 32 of a 32x32 block) -> LDS -> rows, four columns per lane, so that a row's columns are whole
+// cache lines.  PITCH (words) is 8 modulo 16: the two half-waves of a store, four rows apart, then lie in
+// different halves of the banks.  acc: TI x TJ blocks; SwiGLU: the second half of the column blocks holds the
+// up values of the first half's columns.  part: 32 * PITCH floats of LDS of this wave's own; row0, col0: the
+// wave's first output row and column; partial: raw sums of split `split` instead of outputs.
+template <class D, int EPI, int TI, int TJ>
+__device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc)[TI][TJ], float* part, int row0, int col0,
+                                           bool partial, int split, int lane) {
+  using T = typename D::T;
+  constexpr bool DUAL = (EPI == EPI_SWIGLU);
+  constexpr int PITCH = TJ * 32 + 8;
+  constexpr int CW = DUAL ? TJ * 16 : TJ * 32;  // output columns of this wave
+  constexpr int LPR = CW / 4;                   // lanes per row
+  const int l31 = lane & 31, hi = lane >> 5;
+  const int col = col0 + 4 * (lane % LPR);
+  float bv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (g.bias && !partial && col < g.Nn) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bv[k] = to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]);
+  }
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[(8 * (v >> 2) + 4 * hi + (v & 3)) * PITCH + 32 * j + l31] = acc[i][j][v];
+#pragma unroll 4
+    for (int r = lane / LPR; r < 32; r += 64 / LPR) {
+      const int row = row0 + 32 * i + r;
+      const float4 c0 = *reinterpret_cast<const float4*>(part + r * PITCH + 4 * (lane % LPR));
+      const float4 c1 = DUAL ? *reinterpret_cast<const float4*>(part + r * PITCH + CW + 4 * (lane % LPR)) : c0;
+      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
+        if (partial) *reinterpret_cast<float4*>(g.partial + ((size_t)split * g.M + row) * g.Nn + col) = c0;
+        else store_quad<D, EPI>(g, c0, c1, bv, (size_t)row * g.ldo + col);
+      }
+    }
+  }
+}
+
+// Which tile and which part of k a workgroup has: the first g.full tiles are computed whole, each of the
+// g.tail tiles behind them by g.splits workgroups.
+struct TileWork {
+  int tm, tn;
+  bool partial;
+  int split, k_begin, k_end;
+};
+__device__ __forceinline__ TileWork tile_work(const GemmArgs& g, int bm, int bn) {
+  const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.Nn + bn - 1) / bn;
+  const int id = blockIdx.x;
+  TileWork w;
+  int t;
+  if (id < g.full) {
+    t = xcd_spread(id, g.full);
+    w.partial = false;
+    w.split = 0;
+    w.k_begin = 0;
+    w.k_end = g.Kk;
+  } else {
+    const int local = xcd_spread(id - g.full, g.tail * g.splits);
+    t = g.full + local % g.tail;
+    w.partial = true;
+    w.split = local / g.tail;
+    w.k_begin = w.split * g.k_chunk;
+    w.k_end = min(g.Kk, w.k_begin + g.k_chunk);
+  }
+  tile_of(t, tiles_m, tiles_n, &w.tm, &w.tn);
+  return w;
+}
+
+}  // namespace
+
+}  // namespace ci

@@ -34,7 +34,11 @@ def _check_dense(lib, dtype, act, layout, M, d, N, hidden=False):
     assert bool((S[n:] == -7.0).all()) and bool((Y[M * d:] == -7.0).all()), "stored past the end"
     got = S[:n].view(M, N)
     if hidden:
-        assert_close_rms(got.abs(), A_ref, dtype, "hidden values")
+        # one rounding of the fp32 value: half a unit in the last place, at most 2^-8 (bf16, 8 bits) or 2^-11
+        # (fp16, 11 bits) of it and, for fp16, 2^-25 below its normal range, on top of the scores' own bound
+        half_ulp = {torch.bfloat16: 2.0 ** -8, torch.float16: 2.0 ** -11}[dtype]
+        bound = half_ulp * A_ref + 2.0 ** -25 + score_bound(dtype, act, A_ref, X, w)
+        assert np.all(np.abs(np.abs(f64(got)) - A_ref) <= bound), "hidden values"
     else:
         assert np.max(np.abs(f64(got) - A_ref)) <= score_bound(dtype, act, A_ref, X, w), "scores"
     assert_close_rms(Y[:M * d].view(M, d), y_ref, dtype, "Y")
@@ -47,3 +51,39 @@ def _check_dense(lib, dtype, act, layout, M, d, N, hidden=False):
                                    (1025, 36, 1924), (2049, 1028, 68)])
 def test_dense_f32_tiles(lib, act, layout, M, d, N):
     _check_dense(lib, torch.float32, act, layout, M, d, N)
+
+
+# The LDS-tiled kernels for 16-bit types, every tile shape forced (0 .. 3: 128x128, 128x256, 256x64, 128x64
+# rows of A x rows of B; 4: 256x256), whole and with k split over 3 workgroups per tile: one row and column
+# past a tile, k shorter than the ring, k that ends inside a 64-k tile, an odd number of k-tiles, several
+# tiles per XCD.
+TILE_CASES = [(5, 8, 8), (129, 264, 136), (257, 328, 520), (64, 1608, 776), (300, 1152, 1032)]
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("act,layout,dtype", [("relu", "out_major", torch.float16), ("swiglu", "out_major", torch.bfloat16),
+                                              ("relu", "neuron_major", torch.bfloat16)])
+@pytest.mark.parametrize("splits", [0, 3])
+def test_dense_tile_shapes(lib, tile, act, layout, dtype, splits):
+    lib.dev_set_param("gemm_tile", tile)
+    lib.dev_set_param("gemm_splits", splits)
+    try:
+        for M, d, N in TILE_CASES:
+            _check_dense(lib, dtype, act, layout, M, d, N)
+            _check_dense(lib, dtype, act, layout, M, d, N, hidden=True)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+
+
+@pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
+def test_dense_split_last_round_only(lib, layout):
+    """A down projection of more than 256 tiles whose last round is split along k: 17 x 16 tiles of
+    128x64, whole rounds and split tiles side by side, the last row of tiles ragged."""
+    lib.dev_set_param("gemm_tile", 3)
+    lib.dev_set_param("gemm_splits", 2)
+    try:
+        _check_dense(lib, torch.float16, "relu", layout, 2090, 1024, 648)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
