@@ -318,7 +318,10 @@ typedef struct {
  * Two kernel paths, chosen by the layout of the compact down matrix:
  *   CI_DOWN_NEURON_MAJOR (and every gathered call): neuron slices produce fp32
  *     partial outputs in ws, a second launch sums them in a fixed order.  ws
- *     needs no initialisation.
+ *     needs no initialisation.  A gathered call of up to
+ *     CI_MAX_UNION_SENTENCES large, overlapping lists reads each row of their
+ *     union once, as coreinfer_ffn_decode_union does (a rule on B, K, N, d and
+ *     the types; a neuron that a list names r times still counts r times).
  *   CI_DOWN_OUT_MAJOR: one launch, no partial outputs; the hidden values cross
  *     workgroups through ws as self-validating words.  For this path ws must
  *     have been ZEROED ONCE (hipMemsetAsync) before its first use and must not

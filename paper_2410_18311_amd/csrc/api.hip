@@ -110,6 +110,7 @@ int coreinfer_dev_set_param(const char* name, int value) {
   else if (!strcmp(name, "gemm_tile") && value >= -1 && value <= 4) p.gemm_tile = value;
   else if (!strcmp(name, "gemm_splits") && value >= 0 && value <= 8) p.gemm_splits = value;
   else if (!strcmp(name, "gemv_wgs_per_cu") && value >= 1 && value <= 32) p.gemv_wgs_per_cu = value;
+  else if (!strcmp(name, "gathered_union") && value >= 0 && value <= 2) p.gathered_union = value;
   else if (!strcmp(name, "union_depth") && (value == 8 || value == 16)) p.union_depth = value;
   else if (!strcmp(name, "union_down_threads") && value >= 64 && value <= 512) p.union_down_threads = value;
   else if (!strcmp(name, "union_up_wgs_per_cu") && value >= 1 && value <= 8) p.union_up_wgs_per_cu = value;
@@ -478,7 +479,7 @@ int coreinfer_ffn_decode_static(const void* x, int64_t B, const ci_ffn_weights* 
   const bool single = w->down_layout == CI_DOWN_OUT_MAJOR && w->K > 0;
   // what THIS call needs (not the device-independent bound of coreinfer_ffn_decode_workspace_size)
   const size_t need = single ? fused_decode_ws_bytes(w->K)
-                             : (size_t)B * (size_t)decode_splits(B, w->K) * (size_t)w->d * sizeof(float);
+                             : (size_t)B * (size_t)decode_splits_bound(B, w->K) * (size_t)w->d * sizeof(float);
   if (need > (single ? kStaticWords : kStaticPartial)) return CI_ERR_WORKSPACE;
   unsigned char* base = nullptr;
   const int rs = static_scratch(&base);
@@ -529,7 +530,7 @@ int coreinfer_union_build(const int32_t* core_idx, int64_t B, int64_t K, int64_t
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (!aligned16(ws)) return CI_ERR_BAD_LAYOUT;
   return launch_union_build(core_idx, B, K, N, max_rows, union_idx, union_mask, union_count,
-                            reinterpret_cast<uint32_t*>(ws), (hipStream_t)stream);
+                            reinterpret_cast<uint32_t*>(ws), nullptr, (hipStream_t)stream);
 }
 
 int coreinfer_ffn_decode_union_workspace_size(int64_t B, int64_t max_rows, int64_t d, int dtype, int act,

@@ -132,10 +132,11 @@ struct Params {
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)
   Knob reduce_cq{8};         // column quads per reduce workgroup (4, 8, 16)
   Knob decode_nt_store{1};   // non-temporal stores for the partial sums
+  Knob gathered_union{1};         // gathered decode through the union of the lists: 0 never, 1 by the rule, 2 wherever it can
   Knob union_depth{8};            // union-batched decode: rows in flight per thread (8 or 16)
-  Knob union_down_threads{384};   // threads (= 16-byte column vectors) per down-phase workgroup
+  Knob union_down_threads{512};   // threads per down-phase workgroup
   Knob union_up_wgs_per_cu{1};
-  Knob union_down_wgs_per_cu{2};
+  Knob union_down_wgs_per_cu{1};
   Knob union_super{0};            // cap on the rows between two ring drains (0: 256 or what LDS holds)
   Knob fused_depth{4};     // single-launch decode: rows in flight per thread (4, 8 or 16)
   Knob fused_threads{0};   // 0 = derived from d
@@ -203,6 +204,7 @@ int launch_compact_update(const void* w_up, const void* w_gate, const void* b_up
                           int64_t K, int32_t* slot_idx, void* w_up_c, void* w_gate_c, void* b_up_c,
                           void* w_down_c, int down_c_layout, int32_t* changed, uint32_t* ws, hipStream_t s);
 int decode_splits(int64_t B, int64_t K);
+int decode_splits_bound(int64_t B, int64_t K);  // at least decode_splits; what scratch limits are stated in
 int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
                       void* y, float* partial, hipStream_t s);
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
@@ -213,11 +215,14 @@ int launch_ffn_decode_fused(const void* x, int64_t B, const ci_ffn_weights* w, i
                             void* ws, hipStream_t s);
 int union_up_chunks(int64_t vecs);
 int launch_union_build(const int32_t* core_idx, int64_t B, int64_t K, int64_t N, int64_t cap,
-                       int32_t* uidx, uint32_t* umask, int32_t* ucount, uint32_t* owners,
+                       int32_t* uidx, uint32_t* umask, int32_t* ucount, uint32_t* owners, uint32_t* dup,
                        hipStream_t s);
 int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, const int32_t* uidx,
                             const uint32_t* umask, const int32_t* ucount, int64_t cap, int dtype,
-                            int act, void* y, float* ws, hipStream_t s);
+                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup = nullptr);
+bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act);
+int launch_gathered_union(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, float* ws,
+                          hipStream_t s);
 // h[M, N] fp32 = act(X w^T ...) and y = W h + b by row-dot GEMVs (small M).
 int launch_up_rows(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,
                    int dtype, int act, int64_t d, int64_t N, float* H, float* A, hipStream_t s);

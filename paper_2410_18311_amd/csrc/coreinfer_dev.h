@@ -30,6 +30,8 @@
  *   "gemm_big" (0 never, 1 where the plan takes them, 2 always: 256 x 256 tiles),
  *   "gemm_tile" (-1 planned, 0 .. 4: tile shape), "gemm_splits" (0 planned, 1 .. 8:
  *   k splits of the last round of tiles of the down projection);
+ *   "gathered_union" (0 never, 1 by the rule, 2 wherever it can: gathered decode
+ *   through the union of its lists);
  *   "union_depth" (8, 16), "union_down_threads" (64..512), "union_up_wgs_per_cu"
  *   (1..8), "union_down_wgs_per_cu" (1..16), "union_super" (0 = default, 16..256:
  *   cap on the rows between two drains of the load ring): union-batched decode.

@@ -5,12 +5,15 @@
 // sets is read ONCE and applied to the sentences that own it (a bit mask per
 // row).  The result per sentence is exactly its own sparse FFN (Sec. 4.2).
 //
-//   union_scatter / union_count / union_place : owner masks [N] -> ascending row list + masks + count
-//   union_up_kernel   : partial dots of the up (and gate) rows with every owner's x,
-//                       per column chunk -> hp[chunk][matrix][row][sentence]
-//   union_down_kernel : h = act(sum of chunks [+ bias]) for the owners, then
-//                       y_s += h[row][s] * W_down[row, :] -> partial[s][slice][d]
+//   union_scatter / union_place : owner masks [N] -> ascending row list + masks + count
+//   union_up_kernel   : dots of the up (and gate) rows with every owner's x, then the
+//                       hidden values h[row][sentence] (rows wider than 2048 vectors:
+//                       partial dots per column chunk, union_act_kernel adds them up)
+//   union_down_kernel : y_s += h[row][s] * W_down[row, :] -> partial[s][slice][d]
 //   (decode_reduce_kernel of the single-sentence path sums the slices.)
+// The gathered decode (core_idx = [B, K]) of several sentences runs the same way
+// where that is the faster order (gathered_union_bytes): sentences that share
+// resident weights share most of their rows.
 //
 // The number of union rows lives in device memory: the kernels slice the rows
 // themselves, so no host synchronisation separates building the union from
@@ -23,7 +26,7 @@ namespace ci {
 namespace {
 
 constexpr int SB = 8;  // sentences per batch (bits of the owner mask that the kernels look at)
-constexpr int kSuperMax = 256;  // most rows of a slice between two drains of the load ring
+constexpr int kSuperMax = 256;  // up phase: most rows of a slice between two drains of the load ring
 
 struct UnionArgs {
   const void* x;
@@ -34,12 +37,14 @@ struct UnionArgs {
   const int32_t* uidx;
   const uint32_t* umask;
   const int32_t* ucount;
-  float* hp;       // [c_up][NDOT][cap][SB]
+  const uint32_t* dup;  // NULL, or: dup[0] != 0 if a list names a neuron more than once, dup[1 + SB n + s] how often
+                        // beyond the first time sentence s does (gathered lists: every time counts)
+  float* hp;       // [cap][SB] hidden values; c_up > 1: partial dots [c_up][NDOT][cap][SB] first
   float* partial;  // [B][n_down][d]
   int B, d, N, cap, vecs;
   int vc;  // up phase: 16-byte vectors of a row per column chunk
   int n_up, c_up, n_down, c_down;
-  int ks_up, ks_down;  // most rows of a slice handled between two drains of the load ring
+  int ks_up;  // up phase: most rows of a slice handled between two drains of the load ring
 };
 
 __global__ void union_zero_kernel(uint32_t* owners, int64_t n) {
@@ -47,19 +52,27 @@ __global__ void union_zero_kernel(uint32_t* owners, int64_t n) {
   if (i < n) owners[i] = 0u;
 }
 
-// owners[n] |= 1 << s for every valid member n of sentence s's list
+// owners[n] |= 1 << s for every valid member n of sentence s's list; dup as in UnionArgs
 __global__ void union_scatter_kernel(const int32_t* __restrict__ core_idx, int64_t n_idx, int64_t K,
-                                     int64_t N, uint32_t* __restrict__ owners) {
+                                     int64_t N, uint32_t* __restrict__ owners, uint32_t* __restrict__ dup) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_idx) return;
   const int n = core_idx[i];
-  if (n >= 0 && n < N) atomicOr(&owners[n], 1u << (uint32_t)(i / K));
+  if (n < 0 || n >= N) return;
+  const uint32_t t = (uint32_t)(i / K), bit = 1u << t;
+  const uint32_t old = atomicOr(&owners[n], bit);
+  if (dup && (old & bit)) {
+    dup[0] = 1u;
+    atomicAdd(&dup[1 + (size_t)n * SB + t], 1u);
+  }
 }
 
-// Ordered compaction of the neurons with a non-empty owner mask, in two launches over blocks of 1024
-// neurons: the number of owned neurons per block, then every block adds up the blocks before it and
-// places its own neurons behind them (ascending, so the result does not depend on the scheduling).
+// Ordered compaction of the neurons with a non-empty owner mask over blocks of 1024 neurons: every block adds
+// up the owned neurons of the blocks before it and places its own behind them (ascending, so the result does
+// not depend on the scheduling).  Up to kUnionRecount blocks a block counts those before it itself (they are
+// at most 256 KB in cache, and a launch that counts costs 2 us); above that, union_count_kernel has done so.
 constexpr int kUnionBlock = 1024;
+constexpr int kUnionRecount = 64;
 
 __global__ __launch_bounds__(kUnionBlock) void union_count_kernel(const uint32_t* __restrict__ owners, int N,
                                                                   uint32_t* __restrict__ blkcnt) {
@@ -92,7 +105,13 @@ __global__ __launch_bounds__(kUnionBlock) void union_place_kernel(const uint32_t
   const int before = __popcll(bal & lanemask_lt());
   if (lane == 0) wsum[wave] = __popcll(bal);
   // owned neurons in the blocks before mine (at most 1024 blocks: one per thread)
-  int c = tid < blk ? (int)blkcnt[tid] : 0;
+  int c = 0;
+  if (blkcnt) {
+    c = tid < blk ? (int)blkcnt[tid] : 0;
+  } else {
+#pragma unroll 8
+    for (int q = 0; q < blk; ++q) c += owners[q * kUnionBlock + tid] != 0u ? 1 : 0;
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
   if (lane == 0) bsum[wave] = c;
@@ -160,6 +179,17 @@ __device__ __forceinline__ float dot16<BF16>(const uint4& w, const uint4& x, flo
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.y), __builtin_bit_cast(bf16x2_t, x.y), acc, false);
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.z), __builtin_bit_cast(bf16x2_t, x.z), acc, false);
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.w), __builtin_bit_cast(bf16x2_t, x.w), acc, false);
+}
+
+// Hidden value of (row n, sentence t) from its dots (SwiGLU: z0 gate, z1 up); 0 where t does not own the row.
+template <class D, bool SWIGLU>
+__device__ __forceinline__ float union_hidden(const UnionArgs& a, int n, bool owns, int t, float z0, float z1) {
+  using T = typename D::T;
+  float h;
+  if (SWIGLU) h = silu(z0) * z1;
+  else h = fmaxf(z0 + (a.b_up ? to_float<D>(reinterpret_cast<const T*>(a.b_up)[n]) : 0.f), 0.f);
+  if (a.dup && a.dup[0]) h *= (float)(1u + a.dup[1 + (size_t)n * SB + t]);
+  return owns ? h : 0.f;
 }
 
 // One thread owns NI 16-byte column vectors of its chunk and keeps the matching
@@ -274,128 +304,149 @@ __global__ __launch_bounds__(512) void union_up_kernel(UnionArgs a) {
     __syncthreads();
 #undef CI_UISSUE
     // sum over the waves; gate rows are matrix 0, up rows matrix 1 (SwiGLU), else matrix 0
-    for (int o = tid; o < QB * SB; o += nt) {
-      const int q = o / SB, t = o % SB;
-      float z = 0.f;
-      for (int w = 0; w < nw; ++w) z += red[((w * NDOT * ks) + q) * SB + t];
-      const int mat = (SWIGLU && q >= Rs) ? 1 : 0;
-      const int r = q - mat * Rs;
-      a.hp[(((size_t)chunk * NDOT + mat) * a.cap + (size_t)(r0 + s0 + r)) * SB + t] = z;
+    for (int o = tid; o < Rs * SB; o += nt) {
+      const int r = o / SB, t = o % SB;
+      float z[NDOT];
+#pragma unroll
+      for (int m = 0; m < NDOT; ++m) {
+        z[m] = 0.f;
+        for (int w = 0; w < nw; ++w) z[m] += red[((w * NDOT * ks) + m * Rs + r) * SB + t];
+      }
+      const size_t u = (size_t)(r0 + s0 + r);
+      if (a.c_up == 1) {
+        a.hp[u * SB + t] = union_hidden<D, SWIGLU>(a, sidx[r], (smask[r] >> t) & 1u, t, z[0], z[NDOT - 1]);
+      } else {
+#pragma unroll
+        for (int m = 0; m < NDOT; ++m) a.hp[(((size_t)chunk * NDOT + m) * a.cap + u) * SB + t] = z[m];
+      }
     }
   }
 }
 
-// ---- down phase ----------------------------------------------------------------
-__device__ __forceinline__ uint4 union_down_issue(int pos, int Rs, const char* __restrict__ down,
-                                                  const char* __restrict__ filler, size_t rowbytes,
-                                                  const int* sidx, uint32_t coff) {
-  const int r = pos > Rs - 1 ? Rs - 1 : pos;
-  const char* prow = down + (size_t)sidx[r] * rowbytes;
-  prow = pos < Rs ? prow : filler;
-  return ld16_stream(prow + coff);
+// c_up > 1: hidden values from the column chunks' partial dots, over the first of them in place.
+template <class D, bool SWIGLU>
+__global__ __launch_bounds__(256) void union_act_kernel(UnionArgs a) {
+  constexpr int NDOT = SWIGLU ? 2 : 1;
+  const int Ku = union_rows_clamped(a);
+  const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (o >= (int64_t)Ku * SB) return;
+  const size_t u = (size_t)(o / SB);
+  const int t = (int)(o % SB), n = a.uidx[u];
+  const bool ok = n >= 0 && n < a.N;
+  float z[NDOT];
+#pragma unroll
+  for (int m = 0; m < NDOT; ++m) {
+    z[m] = 0.f;
+    for (int c = 0; c < a.c_up; ++c) z[m] += a.hp[(((size_t)c * NDOT + m) * a.cap + u) * SB + t];
+  }
+  a.hp[o] = union_hidden<D, SWIGLU>(a, ok ? n : 0, ok && t < a.B && ((a.umask[u] >> t) & 1u), t, z[0], z[NDOT - 1]);
 }
 
-template <class D, bool SWIGLU, int DEPTH>
+// ---- down phase ----------------------------------------------------------------
+// A workgroup has 64 column vectors (1 KB of a row) and a slice of the rows; its waves split the slice, each
+// lane holding one vector for all eight sentences, and are added up through LDS at the end, so that a slice
+// leaves one partial sum per column: with 384 vectors per workgroup and six times as many slices, 50 MB of them
+// were written and read back per step at 36864 x 9216 and 8 sentences (13 us to add them up; now 8 MB, 4.5 us).
+// What a wave needs to know of a group of eight rows -- indices, owners, 8 x 8 hidden values, one per lane --
+// are three small loads that run ahead in the same in-order queue as the rows, and reach scalar registers by
+// lane reads: nothing is staged ahead of the stream and no barrier interrupts it.  (Scalar loads instead cost
+// a wait per owner: 173 us for the phase at 8 sentences and a keep fraction of 0.6.)
+template <class D, int DEPTH>
 __global__ __launch_bounds__(512) void union_down_kernel(UnionArgs a) {
   using T = typename D::T;
   constexpr int VEC = D::VEC;
-  constexpr int NDOT = SWIGLU ? 2 : 1;
-
-  __shared__ float hbuf[kSuperMax * SB];
-  __shared__ int sidx[kSuperMax];
-  __shared__ uint32_t smask[kSuperMax];
-  const int tid = threadIdx.x, nt = blockDim.x;
+  __shared__ float red[8][64 * VEC];
+  const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.x, chunk = blockIdx.y;
-  const int Ku = union_rows_clamped(a);
-  const int r0 = (int)(((int64_t)slice * Ku) / a.n_down);
-  const int r1 = (int)(((int64_t)(slice + 1) * Ku) / a.n_down);
-  const int R = r1 - r0;
+  const int Ku = __builtin_amdgcn_readfirstlane(union_rows_clamped(a));
+  // the slice's rows [.., r1) go to the waves in groups of DEPTH, turn by turn
+  const int step = nw * DEPTH;
+  const int r0 = (int)((int64_t)slice * Ku / a.n_down) + wave * DEPTH, r1 = (int)((int64_t)(slice + 1) * Ku / a.n_down);
 
   const size_t rowbytes = (size_t)a.d * sizeof(T);
   const char* down = reinterpret_cast<const char*>(a.w_down);
-  const char* filler = reinterpret_cast<const char*>(a.x);
-  const int vec = chunk * nt + tid;
+  const int vec = chunk * 64 + lane;
   const bool cv = vec < a.vecs;
   const uint32_t coff = cv ? (uint32_t)vec * 16u : 0u;
-
   float acc[SB][VEC];
 #pragma unroll
   for (int t = 0; t < SB; ++t)
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[t][v] = 0.f;
 
-  const int nsc = (R + a.ks_down - 1) / a.ks_down;
-  const int step = nsc > 0 ? (R + nsc - 1) / nsc : 1;
-  for (int s0 = 0; s0 < R; s0 += step) {
-    const int Rs = min(step, R - s0);
-    const int QBp = (Rs + DEPTH - 1) / DEPTH * DEPTH;
-    __syncthreads();  // previous super-chunk done with hbuf / sidx / smask
-    union_stage(a, r0 + s0, Rs, sidx, smask);
-    // hidden value of (row, sentence): sum of the column chunks' partial dots
-    for (int o = tid; o < Rs * SB; o += nt) {
-      const int r = o / SB, t = o % SB;
-      const size_t u = (size_t)(r0 + s0 + r);
-      const int n = a.uidx[u];
-      const bool ok = n >= 0 && n < a.N && t < a.B && ((a.umask[u] >> t) & 1u);
-      float z0 = 0.f, z1 = 0.f;
-      for (int c = 0; c < a.c_up; ++c) {
-        z0 += a.hp[(((size_t)c * NDOT) * a.cap + u) * SB + t];
-        if (SWIGLU) z1 += a.hp[(((size_t)c * NDOT + 1) * a.cap + u) * SB + t];
-      }
-      float h;
-      if (SWIGLU) h = silu(z0) * z1;  // z0: gate, z1: up
-      else {
-        const float bias = (a.b_up && ok) ? to_float<D>(reinterpret_cast<const T*>(a.b_up)[n]) : 0.f;
-        h = fmaxf(z0 + bias, 0.f);
-      }
-      hbuf[o] = ok ? h : 0.f;
-    }
-    __syncthreads();
-
+  if (r0 < r1) {
+    const uint32_t all = (1u << a.B) - 1u;
+    // indices and owners of the rows from `g` on, one per lane (DEPTH <= 64); rows past the end belong to nobody
+    auto load_idx = [&](int g) { return a.uidx[min(g + (lane & (DEPTH - 1)), r1 - 1)]; };
+    auto load_mask = [&](int g) { return a.umask[min(g + (lane & (DEPTH - 1)), r1 - 1)]; };
+    // hidden values of the rows from `g` on: lane 8 i + t holds row i, sentence t
+    auto load_h = [&](int g, float (&h)[DEPTH / 8]) {
+#pragma unroll
+      for (int q = 0; q < DEPTH / 8; ++q) h[q] = a.hp[(size_t)min(g + 8 * q + (lane >> 3), r1 - 1) * SB + (lane & 7)];
+    };
+    // row s of the group whose indices are in `idx`; past the end: x, which is in cache
+    auto row_ptr = [&](int idx, int g, int s) {
+      const int n = __builtin_amdgcn_readlane(idx, s);
+      return g + s < r1 ? down + (size_t)((n >= 0 && n < a.N) ? n : 0) * rowbytes : reinterpret_cast<const char*>(a.x);
+    };
+    int idx0 = load_idx(r0), idx1 = load_idx(r0 + step);
+    uint32_t mask = load_mask(r0);
+    float h[DEPTH / 8];
+    load_h(r0, h);
     uint4 buf[DEPTH];
-#define CI_DISSUE(pos) union_down_issue((pos), Rs, down, filler, rowbytes, sidx, coff)
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) {
-      buf[s] = CI_DISSUE(s);
+      buf[s] = ld16_stream(row_ptr(idx0, r0, s) + coff);
       __builtin_amdgcn_sched_barrier(0);
     }
-    for (int g0 = 0; g0 < QBp; g0 += DEPTH) {
+    for (int g0 = r0; g0 < r1; g0 += step) {
+      const int idx2 = load_idx(g0 + 2 * step);
+      const uint32_t mask_next = load_mask(g0 + step);
+      float h_next[DEPTH / 8];
+      load_h(g0 + step, h_next);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int s = 0; s < DEPTH; ++s) {
-        const int pos = g0 + s;
-        const int r = pos > Rs - 1 ? Rs - 1 : pos;
-        const uint32_t m = __builtin_amdgcn_readfirstlane(pos < Rs ? smask[r] : 0u);
         float f[VEC];
         unpack<D>(buf[s], f);
         __builtin_amdgcn_sched_barrier(0);
-        buf[s] = CI_DISSUE(pos + DEPTH);
+        buf[s] = ld16_stream(row_ptr(idx1, g0 + step, s) + coff);
         __builtin_amdgcn_sched_barrier(0);
+        const int n = __builtin_amdgcn_readlane(idx0, s);
+        const uint32_t own = (uint32_t)__builtin_amdgcn_readlane((int)mask, s) & all;
+        const uint32_t m = (g0 + s < r1 && n >= 0 && n < a.N) ? own : 0u;
 #pragma unroll
         for (int t = 0; t < SB; ++t) {
           if (m & (1u << t)) {  // uniform
-            const float hj = hbuf[r * SB + t];
+            const float ht = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(h[s >> 3]), 8 * (s & 7) + t));
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[t][v] = fmaf(hj, f[v], acc[t][v]);
+            for (int v = 0; v < VEC; ++v) acc[t][v] = fmaf(ht, f[v], acc[t][v]);
           }
         }
       }
+      idx0 = idx1;
+      idx1 = idx2;
+      mask = mask_next;
+#pragma unroll
+      for (int q = 0; q < DEPTH / 8; ++q) h[q] = h_next[q];
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
-#undef CI_DISSUE
   }
 
-  if (cv) {
-    const int col = vec * VEC;
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
+  // sum over the waves, in wave order, one sentence after the other; thread -> columns
 #pragma unroll
-    for (int t = 0; t < SB; ++t) {
-      if (t < a.B) {
-        float* out = a.partial + ((size_t)t * a.n_down + slice) * a.d + col;
+  for (int t = 0; t < SB; ++t) {
+    if (t < a.B) {  // uniform
+      __syncthreads();
 #pragma unroll
-        for (int v = 0; v < VEC; v += 4) {
-          const f32x4 o = {acc[t][v], acc[t][v + 1], acc[t][v + 2], acc[t][v + 3]};
-          __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(out + v));
-        }
+      for (int v = 0; v < VEC; ++v) red[wave][v * 64 + lane] = acc[t][v];
+      __syncthreads();
+      for (int o = tid; o < 64 * VEC; o += blockDim.x) {
+        float z = 0.f;
+        for (int w = 0; w < nw; ++w) z += red[w][o];
+        const int col = (chunk * 64 + (o & 63)) * VEC + (o >> 6);
+        if (chunk * 64 + (o & 63) < a.vecs) a.partial[((size_t)t * a.n_down + slice) * a.d + col] = z;
       }
     }
   }
@@ -425,11 +476,11 @@ int launch_union_typed(const UnionArgs& a, int ni, int t_up, int t_down, hipStre
     case 4: launch_union_up<D, 4, SWIGLU>(a, t_up, s); break;
     default: return CI_ERR_UNSUPPORTED;
   }
+  if (a.c_up > 1)
+    hipLaunchKernelGGL((union_act_kernel<D, SWIGLU>), dim3((unsigned)(((int64_t)a.cap * SB + 255) / 256)), dim3(256), 0, s, a);
   const dim3 gd(a.n_down, a.c_down);
-  if (params().union_depth == 16)
-    hipLaunchKernelGGL((union_down_kernel<D, SWIGLU, 16>), gd, dim3(t_down), 0, s, a);
-  else
-    hipLaunchKernelGGL((union_down_kernel<D, SWIGLU, 8>), gd, dim3(t_down), 0, s, a);
+  if (params().union_depth == 16) hipLaunchKernelGGL((union_down_kernel<D, 16>), gd, dim3(t_down), 0, s, a);
+  else hipLaunchKernelGGL((union_down_kernel<D, 8>), gd, dim3(t_down), 0, s, a);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
@@ -441,26 +492,109 @@ int launch_union_typed(const UnionArgs& a, int ni, int t_up, int t_down, hipStre
 int union_up_chunks(int64_t vecs) { return (int)((vecs + 2047) / 2048); }
 
 int launch_union_build(const int32_t* core_idx, int64_t B, int64_t K, int64_t N, int64_t cap,
-                       int32_t* uidx, uint32_t* umask, int32_t* ucount, uint32_t* owners,
+                       int32_t* uidx, uint32_t* umask, int32_t* ucount, uint32_t* owners, uint32_t* dup,
                        hipStream_t s) {
-  hipLaunchKernelGGL(union_zero_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, owners, N);
+  // owner masks, and behind them dup if there is one (gathered_union_layout keeps the two adjacent)
+  const int64_t n_zero = dup ? (dup - owners) + 1 + N * SB : N;
+  hipLaunchKernelGGL(union_zero_kernel, dim3((unsigned)((n_zero + 255) / 256)), dim3(256), 0, s, owners, n_zero);
   const int64_t n_idx = B * K;
   if (n_idx > 0)
     hipLaunchKernelGGL(union_scatter_kernel, dim3((unsigned)((n_idx + 255) / 256)), dim3(256), 0, s,
-                       core_idx, n_idx, K, N, owners);
+                       core_idx, n_idx, K, N, owners, dup);
   const unsigned nblk = (unsigned)((N + kUnionBlock - 1) / kUnionBlock);  // <= 1024: N <= CI_MAX_NEURONS
-  uint32_t* blkcnt = owners + (N + 63) / 64 * 64;
-  hipLaunchKernelGGL(union_count_kernel, dim3(nblk), dim3(kUnionBlock), 0, s, owners, (int)N, blkcnt);
+  uint32_t* blkcnt = nullptr;
+  if (nblk > kUnionRecount) {
+    blkcnt = owners + (N + 63) / 64 * 64;
+    hipLaunchKernelGGL(union_count_kernel, dim3(nblk), dim3(kUnionBlock), 0, s, owners, (int)N, blkcnt);
+  }
   hipLaunchKernelGGL(union_place_kernel, dim3(nblk), dim3(kUnionBlock), 0, s, owners, (int)N, (int)cap, blkcnt, uidx,
                      umask, ucount);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
 
+namespace {
+
+// Slices of the down phase: one workgroup of eight waves per compute unit over all column chunks, at most 256 (what the
+// workspace holds) and not so many that a wave has fewer than about 16 rows.
+int down_slices(int64_t vecs, int64_t cap, int cus) {
+  const int64_t chunks = (vecs + 63) / 64;
+  int64_t n = (int64_t)cus * params().union_down_wgs_per_cu / chunks;
+  const int64_t most = (cap + 127) / 128;
+  if (n > 256) n = 256;
+  if (n > most) n = most;
+  return n < 1 ? 1 : (int)n;
+}
+
+int chip_cus() {
+  DeviceInfo di;
+  return device_info(&di) == CI_OK ? di.cus : 256;
+}
+
+// Scratch of a gathered decode that goes through the union of its lists, in 4-byte words from the start:
+// hidden values, partial outputs, then owner masks with dup right behind them, then the row list.
+struct GatheredUnion {
+  size_t partial, owners, dup, uidx, umask, ucount, total;
+  int64_t cap;
+};
+GatheredUnion gathered_union_layout(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act) {
+  GatheredUnion g;
+  auto up64 = [](size_t n) { return (n + 63) / 64 * 64; };
+  const int64_t vecs = d / (dtype == CI_F32 ? 4 : 8);
+  g.cap = B * K < N ? B * K : N;
+  g.partial = up64((size_t)union_up_chunks(vecs) * (act == CI_ACT_SWIGLU ? 2 : 1) * (size_t)g.cap * SB);
+  g.owners = g.partial + up64((size_t)B * down_slices(vecs, g.cap, chip_cus()) * (size_t)d);
+  g.dup = g.owners + up64((size_t)N) + 1024;  // 1024: counts per block of union_place_kernel
+  g.uidx = g.dup + up64(1 + (size_t)N * SB);
+  g.umask = g.uidx + up64((size_t)g.cap);
+  g.ucount = g.umask + up64((size_t)g.cap);
+  g.total = g.ucount + 64;
+  return g;
+}
+
+}  // namespace
+
+// Whether a gathered decode of B lists goes through their union.  Reading every list's rows separately runs at
+// about 7 TB/s (sentences in flight together find shared rows in the caches), the union at 5.6 TB/s (gated layers
+// 5.0) and 23 us for building it, two more dependent launches and the ends of the kernels.  Lists are taken to
+// overlap as random ones do -- core sets of one model overlap more -- and the union has to win by a tenth.
+// Measured, separate / union (us): 36864 x 9216 ReLU: 8 lists at a keep fraction of 0.4 573 / 241, 4 at 0.4
+// 304 / 217, 3 at 0.4 236 / 194, 4 at 0.2 163 / 153 (stays separate); 13824 x 5120 gated: 8 at 0.3 134 / 109,
+// 8 at 0.2 95 / 100, 4 at 0.4 94 / 98 (stay separate); 16384 x 4096 ReLU: 8 at 0.3 87 / 67, 8 at 0.2 60 / 63 (stays);
+// 3840 x 1280: separate throughout (15 / 28).  Its scratch has to fit what both gathered entry points offer for any
+// such call: the workspace by its published size, and the 16 MiB of library scratch.
+bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act) {
+  if (params().gathered_union == 0 || B < 2 || B > SB || K < 1 || K > N) return false;
+  if (d / (dtype == CI_F32 ? 4 : 8) > 4096) return false;  // wider rows are turned down by the gathered kernel, and stay so
+  const size_t bytes = gathered_union_layout(B, K, N, d, dtype, act).total * 4;
+  const size_t ws = (size_t)B * (size_t)(K < 1024 ? K : 1024) * (size_t)d * sizeof(float);
+  if (bytes > ws || bytes > ((size_t)16 << 20)) return false;
+  if (params().gathered_union == 2) return true;
+  const double row = (double)d * elem_bytes(dtype) * (act == CI_ACT_SWIGLU ? 3 : 2);
+  double miss = 1.0;
+  for (int64_t b = 0; b < B; ++b) miss *= 1.0 - (double)K / (double)N;
+  const double t_lists = (double)(B * K) * row / 7.0e12 + 4e-6;
+  const double t_union = (double)N * (1.0 - miss) * row / (act == CI_ACT_SWIGLU ? 5.0e12 : 5.6e12) + 23e-6;
+  return t_union * 1.1 < t_lists;
+}
+
+int launch_gathered_union(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, float* ws,
+                          hipStream_t s) {
+  const GatheredUnion g = gathered_union_layout(B, w->K, w->N, w->d, dtype, act);
+  uint32_t* base = reinterpret_cast<uint32_t*>(ws);
+  int32_t* uidx = reinterpret_cast<int32_t*>(base + g.uidx);
+  int32_t* ucount = reinterpret_cast<int32_t*>(base + g.ucount);
+  const int rc = launch_union_build(w->core_idx, B, w->K, w->N, g.cap, uidx, base + g.umask, ucount, base + g.owners,
+                                    base + g.dup, s);
+  if (rc != CI_OK) return rc;
+  return launch_ffn_decode_union(x, B, w, uidx, base + g.umask, ucount, g.cap, dtype, act, y, ws, s, base + g.dup);
+}
+
 int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, const int32_t* uidx,
                             const uint32_t* umask, const int32_t* ucount, int64_t cap, int dtype,
-                            int act, void* y, float* ws, hipStream_t s) {
+                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup) {
   UnionArgs a;
+  a.dup = dup;
   a.x = x;
   a.w_up = w->w_up;
   a.w_gate = w->w_gate;
@@ -476,9 +610,7 @@ int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, c
   a.vecs = (int)(w->d / (dtype == CI_F32 ? 4 : 8));
   const int ndot = act == CI_ACT_SWIGLU ? 2 : 1;
 
-  DeviceInfo di;
-  int cus = 256;
-  if (device_info(&di) == CI_OK) cus = di.cus;
+  const int cus = chip_cus();
   a.c_up = union_up_chunks(a.vecs);
   a.vc = (a.vecs + a.c_up - 1) / a.c_up;
   // vectors per thread: the choice that pads the chunk least, the larger one on ties (one
@@ -489,31 +621,23 @@ int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, c
     if (t > 512) continue;
     if (t * n - a.vc < waste) { waste = t * n - a.vc; ni = n; t_up = t; }
   }
-  // down phase: column chunks of about union_down_threads vectors, evenly sized
-  int want = params().union_down_threads;
-  if (want < 64) want = 64;
-  if (want > 512) want = 512;
-  a.c_down = (a.vecs + want - 1) / want;
-  const int t_down = ((a.vecs + a.c_down - 1) / a.c_down + 63) / 64 * 64;
-  a.c_down = (a.vecs + t_down - 1) / t_down;
-  a.n_up = cus * params().union_up_wgs_per_cu / a.c_up;
-  a.n_down = cus * params().union_down_wgs_per_cu / a.c_down;
+  int t_down = params().union_down_threads / 64 * 64;
+  if (t_down < 64) t_down = 64;
+  if (t_down > 512) t_down = 512;
+  a.c_down = (a.vecs + 63) / 64;
+  a.n_down = down_slices(a.vecs, a.cap, cus);
+  // up phase: about 384 threads per compute unit (at d = 4096 the two waves of four vectors per lane that a
+  // workgroup has were alone on theirs: 36 us for 13650 rows, now 25)
+  a.n_up = cus * params().union_up_wgs_per_cu * ((384 + t_up / 2) / t_up > 1 ? (384 + t_up / 2) / t_up : 1) / a.c_up;
   if (a.n_up > 1024) a.n_up = 1024;
-  if (a.n_down > 256) a.n_down = 256;  // bounds the partial sums of the workspace
   if (a.n_up > a.cap) a.n_up = a.cap;
-  if (a.n_down > a.cap) a.n_down = a.cap;
   if (a.n_up < 1) a.n_up = 1;
-  if (a.n_down < 1) a.n_down = 1;
 
   // rows between two drains: as many as 64 KB of LDS hold (wave sums of the up phase)
   a.ks_up = kSuperMax;
   while (a.ks_up > 64 && union_up_lds(t_up, ndot, a.ks_up) > 65536) a.ks_up >>= 1;
-  a.ks_down = kSuperMax;
   const int ks_cap = params().union_super;
-  if (ks_cap > 0) {
-    if (a.ks_up > ks_cap) a.ks_up = ks_cap;
-    if (a.ks_down > ks_cap) a.ks_down = ks_cap;
-  }
+  if (ks_cap > 0 && a.ks_up > ks_cap) a.ks_up = ks_cap;
 
   a.hp = ws;
   const size_t hp_floats = ((size_t)a.c_up * ndot * (size_t)a.cap * SB + 63) / 64 * 64;

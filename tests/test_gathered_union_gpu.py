@@ -1,0 +1,85 @@
+"""Gathered decode of several sentences through the union of their lists: forced at small sizes,
+against the oracle and against the kernel that reads every list's rows separately."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import coreinfer_oracle as orc
+from tests._util import assert_close_rms, down_out_major64, f64, rand_weights
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _reference(act, x, S, w):
+    Wd = down_out_major64(w, "neuron_major")
+    if act == "relu":
+        return orc.ffn_relu(f64(x), S, f64(w["w_up"]), f64(w["b_up"]), Wd, f64(w["b_down"]))
+    return orc.ffn_swiglu(f64(x), S, f64(w["w_gate"]), f64(w["w_up"]), Wd, f64(w["b_down"]))
+
+
+# widths around the 64-vector column chunks of the down phase and (16384 fp32 elements = 4096 vectors) rows of
+# more than one column chunk in the up phase; row counts around the blocks of 1024 neurons and, with 65537
+# and more, above the limit up to which a block counts the ones before it
+@pytest.mark.parametrize("dt,act", [(torch.float16, "relu"), (torch.bfloat16, "swiglu"), (torch.float32, "relu")])
+@pytest.mark.parametrize("d,N,K,B", [(512, 2000, 801, 4), (520, 1024, 300, 8), (1016, 1025, 1025, 2), (8, 700, 699, 3),
+                                     (64, 66000, 30000, 2), (16384, 400, 200, 2)])
+def test_gathered_through_the_union(lib, dt, act, d, N, K, B):
+    print("gathered union case", dt, act, d, N, K, B, flush=True)
+    if d == 16384 and dt != torch.float32:
+        pytest.skip("two column chunks need rows of more than 2048 vectors: fp32 only")
+    w = rand_weights(d, N, dt, act, "neuron_major", seed=d + N + B, device=DEV)
+    rng = np.random.default_rng(K + B)
+    sets = np.stack([rng.permutation(N)[:K] for _ in range(B)]).astype(np.int32)   # in no order
+    idx = torch.from_numpy(sets).to(DEV)
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(N)).to(dt).to(DEV)
+    desc = lib.make_weights(w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], core_idx=idx)
+    ys = []
+    for mode in (0, 2):
+        lib.dev_set_param("gathered_union", mode)
+        try:
+            ys.append(lib.ffn_decode(x, desc, act))
+            if mode == 2:
+                y_st = lib.ffn_decode_static(x, desc, act)
+            torch.cuda.synchronize()
+        finally:
+            lib.dev_set_param("gathered_union", 1)
+    assert torch.equal(ys[1], y_st), "the library's own scratch gives other results"
+    rows = range(B) if N < 10000 else [0]
+    for b in rows:
+        ref = _reference(act, x[b], np.sort(sets[b]).astype(np.int64), w)
+        assert_close_rms(ys[0][b], ref, dt, f"separate rows, sentence {b}")
+        assert_close_rms(ys[1][b], ref, dt, f"union, sentence {b}")
+    # the same sums in another order, rounded once to the element type
+    rms = float(ys[0].float().pow(2).mean().sqrt())
+    assert float((ys[1].float() - ys[0].float()).abs().max()) <= {torch.float32: 1e-5, torch.float16: 1e-2,
+                                                                    torch.bfloat16: 5e-2}[dt] * rms
+
+
+def test_repeated_and_invalid_entries_count_as_before(lib):
+    """A neuron named r times by a list contributes r times, an entry outside [0, N) nothing -- also when
+    another sentence names the same neuron once."""
+    d, N, K, B = 256, 3000, 900, 3
+    w = rand_weights(d, N, torch.float32, "relu", "neuron_major", seed=5, device=DEV)
+    rng = np.random.default_rng(3)
+    sets = np.stack([np.sort(rng.choice(N, size=K, replace=False)) for _ in range(B)]).astype(np.int32)
+    sets[0, 10:310] = sets[0, 9]          # 301 times the same neuron
+    sets[1, [0, 5, 899]] = [-1, N, 2 ** 30]
+    sets[2, :9] = sets[0, 9]
+    idx = torch.from_numpy(sets).to(DEV)
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(1)).to(DEV)
+    desc = lib.make_weights(w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], core_idx=idx)
+    out = []
+    for mode in (0, 2):
+        lib.dev_set_param("gathered_union", mode)
+        try:
+            out.append(f64(lib.ffn_decode(x, desc, "relu")))
+        finally:
+            lib.dev_set_param("gathered_union", 1)
+    Wu, Wd = f64(w["w_up"]), f64(w["w_down"])
+    for b in range(B):
+        S = sets[b][(sets[b] >= 0) & (sets[b] < N)]
+        ref = np.maximum(f64(x[b]) @ Wu[S].T + f64(w["b_up"])[S], 0.0) @ Wd[S] + f64(w["b_down"])
+        rms = np.sqrt(np.mean(ref ** 2))
+        for y in out:
+            assert np.max(np.abs(y[b] - ref)) <= 1e-5 * rms
