@@ -121,8 +121,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without the Stream object that torch.cuda.current_stream builds around it: 0.15
+# instead of 3.4 us of a call, which for small layers is a fifth of what a decode call costs the host
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream(t: torch.Tensor):
-    return torch.cuda.current_stream(t.device).cuda_stream if t.is_cuda else None
+    device = t.get_device()     # -1: host memory
+    return _raw_stream(device) if device >= 0 else None
 
 
 def _workspace(nbytes: int, like: torch.Tensor) -> torch.Tensor:
