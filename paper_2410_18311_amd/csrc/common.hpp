@@ -176,7 +176,7 @@ inline int allow_dynamic_lds(std::atomic<uint64_t>& seen, const void* kernel, si
 // ---- launchers (one per translation unit) ----------------------------------
 enum { kSelZero = 1, kSelTokens = 2, kSelFinal = 4, kSelAccumulate = 8 };
 struct SelectWs {
-  size_t off_thr, off_hist, off_counts, total;
+  size_t off_thr, off_hist, off_counts, off_part, total;
 };
 void select_ws_layout(int64_t M, int64_t N, SelectWs* w, int64_t B = 1);
 bool select_batch_ok(int64_t M, int64_t N);

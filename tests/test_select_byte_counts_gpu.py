@@ -1,0 +1,53 @@
+"""Token counts that the per-token kernel keeps a byte per neuron and workgroup, at the edges of what a
+byte, a register of four neurons and a workgroup's share of tokens hold: bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import coreinfer_oracle as orc
+from paper_2410_18311_amd.workloads import activation_like
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# one neuron; one past a multiple of 4096 (a new register of counts); a workgroup with one and with several
+# tokens; 64 sentences of 2045 tokens = 256 tokens for each of 8 workgroups (one more than a byte holds, so the
+# counting kernel over the activations runs) and 2040 (255: the most a byte holds); 65 sentences and 40961 neurons
+# (no byte counts); 36869 neurons (nine registers and five neurons)
+@pytest.mark.parametrize("B,M,N,levels", [(1, 1, 1, 0), (1, 3, 4097, 0), (3, 130, 5000, 6), (1, 700, 16384, 0),
+                                          (64, 2045, 12, 3), (64, 2040, 12, 3), (65, 9, 40, 0), (1, 20, 40961, 0),
+                                          (1, 300, 36869, 5), (1, 513, 2048, 1)])
+@pytest.mark.parametrize("kind", ["relu", "abs"])
+def test_counts_of_all_sentences(lib, B, M, N, levels, kind):
+    print("byte counts case", B, M, N, levels, kind, flush=True)
+    A = activation_like(B * M, N, seed=B + M + N, kind=kind, levels=levels)
+    if kind == "abs" and N <= 12:
+        A = np.abs(A) + np.float32(0.25)   # every token takes every place it can: counts reach the number of tokens
+    alpha = 1.0 if N <= 12 else 0.2
+    idx, counts = lib.select_batch(torch.from_numpy(A).to(DEV), B, alpha, 0.4)
+    torch.cuda.synchronize()
+    for b in (range(B) if N > 12 else (0, B // 2, B - 1)):
+        S_ref, c_ref = orc.select(A[b * M:(b + 1) * M], alpha, 0.4)
+        assert np.array_equal(counts[b].cpu().numpy(), c_ref), f"counts, sentence {b}"
+        assert np.array_equal(idx[b].cpu().numpy(), S_ref), f"core set, sentence {b}"
+
+
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,N", [(300, 5003), (40, 36864)])
+def test_counts_of_hidden_values(lib, dt, M, N):
+    H = torch.from_numpy(activation_like(M, N, seed=N, kind="raw", levels=40)).to(dt).to(DEV)
+    for act in ("relu", "swiglu"):
+        idx, counts = lib.select_hidden(H, act, 0.2, 0.3)
+        A = H.float().abs() if act == "swiglu" else H.float()
+        S_ref, c_ref = orc.select(A.cpu().numpy(), 0.2, 0.3)
+        assert np.array_equal(counts.cpu().numpy(), c_ref) and np.array_equal(idx.cpu().numpy(), S_ref)
+
+
+def test_running_counts_add_up(lib):
+    A = activation_like(90, 6000, seed=4)
+    dev = torch.from_numpy(A).to(DEV)
+    counts = lib.count_tokens(dev[:37], 0.2)
+    lib.count_tokens(dev[37:], 0.2, counts=counts, accumulate=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(counts.cpu().numpy(), orc.select(A, 0.2, 0.4)[1])
