@@ -32,10 +32,10 @@
 // count_partial_kernel -- Eq. 3 from those bytes: one byte per neuron and workgroup
 //     instead of every activation again (1024 x 13824 fp32 scores: 7 MB instead of
 //     57 MB read, counting 13.0 -> 4.5 us, the
-//     per-token kernel 24.4 -> 26.3 us; 256 x 16384 fp16 values: 6.3 -> 4.6 and 11.0 -> 12.5 us).
-// count_kernel -- Eq. 3 where there are no such bytes (rows of more than 40960
-//     neurons, more than 64 sentences).  Counting is then a second pass over the activations by
-//     neuron: a workgroup owns 64 neurons (256 when that still gives more
+//     per-token kernel 24.4 -> 26.3 us).
+// count_kernel -- Eq. 3 where there are no such bytes (middling sizes, see
+//     launch_tokens; rows of more than 40960 neurons, more than 64 sentences).
+//     Counting is then a second pass over the activations by neuron: a workgroup owns 64 neurons (256 when that still gives more
 //     workgroups than half the compute units), walks all tokens, compares every
 //     activation with its token's (T, cut) and keeps the tallies in registers
 //     -- no atomics on the counters, and the counts are the same whatever the
@@ -292,10 +292,10 @@ __device__ __forceinline__ void radix_pass(KeyAt key_at, int n_iter, int shift, 
   n_eq = sh->in_bin;
 }
 
-// The workgroup (x, b) takes the tokens x, x + gridDim.x, ... of sentence b (M rows each).  `part`: NULL, or
+// The workgroup (x, b) takes the tokens x, x + gridDim.x, ... of sentence b (M rows each).  BYTES: `part` gets
 // the counts of its tokens' core neurons, row b * gridDim.x + x: word q * 1024 + t holds, a byte each, those of the
 // neurons (4 q + j) * 1024 + t, j = 0 .. 3 (at most 255 tokens per workgroup).
-template <int ITEMS, bool TWO, class IN>  // TWO: registers capped so that two workgroups of 16 waves share a compute unit
+template <int ITEMS, bool TWO, bool BYTES, class IN>  // TWO: registers capped so that two workgroups of 16 waves share a compute unit
 __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(const typename IN::T* __restrict__ act,
                                                                int M, int N, int64_t ld, int64_t q_alpha,
                                                                uint32_t sign_mask, uint32_t* __restrict__ thr,
@@ -321,9 +321,10 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       ghist[j] = 0u;
   act += (size_t)blockIdx.y * M * ld;
   thr += (size_t)blockIdx.y * M * 2;
-  uint32_t cp[ITEMS > 0 ? ITEMS / 4 : 1];  // counts of this thread's neurons, a byte each
+  static_assert(!BYTES || ITEMS > 0, "byte counts come from keys in registers");
+  uint32_t cp[BYTES ? ITEMS / 4 : 1];  // counts of this thread's neurons, a byte each
 #pragma unroll
-  for (int q = 0; q < (ITEMS > 0 ? ITEMS / 4 : 1); ++q) cp[q] = 0u;
+  for (int q = 0; q < (BYTES ? ITEMS / 4 : 1); ++q) cp[q] = 0u;
 
   for (int m = blockIdx.x; m < M; m += gridDim.x) {
     const TI* row = act + (size_t)m * ld;
@@ -479,22 +480,20 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       }
       __syncthreads();  // cut_s is final, and the tables in the histogram's place are done with
     }
-    if constexpr (ITEMS > 0) {
-      if (part) {
-        // keys that are not positive are all-ones, negative as signed numbers; T is not negative
-        const uint32_t cut = need == n_eq ? 0x7fffffffu : cut_s;  // uniform
-        // a tie past the cut is not taken: thread tid takes the ties of its items i with i * 1024 + tid <= cut
-        const int last = (int)cut - tid >= 0 ? ((int)cut - tid) / nt : -1;
+    if constexpr (BYTES) {
+      // keys that are not positive are all-ones, negative as signed numbers; T is not negative
+      const uint32_t cut = need == n_eq ? 0x7fffffffu : cut_s;  // uniform
+      // a tie past the cut is not taken: thread tid takes the ties of its items i with i * 1024 + tid <= cut
+      const int last = (int)cut - tid >= 0 ? ((int)cut - tid) / nt : -1;
 #pragma unroll
-        for (int q = 0; q < ITEMS / 4; ++q) {
+      for (int q = 0; q < ITEMS / 4; ++q) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int i = 4 * q + j;
-            const int t = (int)T + (i <= last ? 0 : 1);  // the least key that is taken
-            cp[q] += (int)kc[i] >= t ? 1u << (8 * j) : 0u;
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < 4; ++j) {
+          const int i = 4 * q + j;
+          const int t = (int)T + (i <= last ? 0 : 1);  // the least key that is taken
+          cp[q] += (int)kc[i] >= t ? 1u << (8 * j) : 0u;
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     if (tid == 0) { thr[2 * m] = T; thr[2 * m + 1] = cut_s; }
@@ -502,14 +501,12 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
     // thread 0 alone resets cut_s, behind barriers of its own; everything else in LDS is written again only
     // after barriers
   }
-  if constexpr (ITEMS > 0) {
-    if (part) {
-      const int words = (n_iter + 3) / 4;
-      uint32_t* p = part + (size_t)(blockIdx.y * gridDim.x + blockIdx.x) * words * kThreads + tid;
+  if constexpr (BYTES) {
+    const int words = (n_iter + 3) / 4;
+    uint32_t* p = part + (size_t)(blockIdx.y * gridDim.x + blockIdx.x) * words * kThreads + tid;
 #pragma unroll
-      for (int q = 0; q < ITEMS / 4; ++q)
-        if (q < words) p[q * kThreads] = cp[q];
-    }
+    for (int q = 0; q < ITEMS / 4; ++q)
+      if (q < words) p[q * kThreads] = cp[q];
   }
 }
 
@@ -1011,13 +1008,13 @@ __global__ __launch_bounds__(1024) void best_group_kernel(const int32_t* __restr
   if (threadIdx.x == 0) best[0] = sg[0];
 }
 
-template <int ITEMS, bool TWO, class IN>
+template <int ITEMS, bool TWO, bool BYTES, class IN>
 int launch_threshold(const typename IN::T* act, int M, int N, int64_t ld, int64_t q_alpha, uint32_t sign_mask,
                      uint32_t* thr, uint32_t* ghist, int ghist_words, uint32_t* part, dim3 grid, hipStream_t s) {
   static std::atomic<uint64_t> attr_seen{0};  // raise the dynamic-LDS ceiling once (64 KB by default)
-  if (allow_dynamic_lds(attr_seen, reinterpret_cast<const void*>(&token_threshold_kernel<ITEMS, TWO, IN>), 156 * 1024) != CI_OK)
+  if (allow_dynamic_lds(attr_seen, reinterpret_cast<const void*>(&token_threshold_kernel<ITEMS, TWO, BYTES, IN>), 156 * 1024) != CI_OK)
     return CI_ERR_HIP;
-  hipLaunchKernelGGL((token_threshold_kernel<ITEMS, TWO, IN>), grid, dim3(kThreads),
+  hipLaunchKernelGGL((token_threshold_kernel<ITEMS, TWO, BYTES, IN>), grid, dim3(kThreads),
                      (size_t)(kHistWords + kHist2Words) * 4, s, act,
                      M, N, ld, q_alpha, sign_mask, thr, ghist, ghist_words, part);
   CI_HIP_CHECK_LAUNCH();
@@ -1038,8 +1035,17 @@ int launch_tokens(const void* act_v, int B, int M_each, int N, int64_t ld, int64
   // unit (a token round is half instruction issue, half barriers and latency; the register cap
   // this needs costs a single workgroup about 10 %, so it is not used for short prompts)
   const bool two = M > cus && items <= 16 && params().select_wgs_per_cu >= 2;
+  // four activations per load of the counting kernel: 16 bytes of fp32 or 8 bytes of a 16-bit type
+  const uintptr_t quad = 4 * sizeof(TI);
+  const int vec_ok = ((reinterpret_cast<uintptr_t>(act) & (quad - 1)) == 0 && ld % 4 == 0) ? 1 : 0;
+  // Byte counts cost the per-token kernel 1 to 2 us and save reading the activations again: worth it where those
+  // are many (1024 x 13824 fp32 39.4 -> 34.2 us, 512 x 36864 fp16 58.0 -> 51.6) or come in loads of one element
+  // (300 x 13825 27.5 -> 24.9), and where the second pass is all latency (32 x 1024 13.7 -> 12.8); in between it is
+  // in cache and its loads are wide (512 x 11008 fp32 24.9 against 25.5 us, fp16 25.2 against 27.0).
+  const size_t act_bytes = (size_t)M * (size_t)N * sizeof(TI);
+  if (vec_ok && act_bytes > ((size_t)2 << 20) && act_bytes < ((size_t)24 << 20)) part = nullptr;
   int wgs = cus * (two ? 2 : 1);
-  if (wgs > kPartRows) wgs = kPartRows;
+  if (part && wgs > kPartRows) wgs = kPartRows;
   // workgroups per sentence when they leave byte counts (each has one sentence's tokens only); else the
   // rows of all sentences are alike
   int per = part ? wgs / B : wgs;
@@ -1053,7 +1059,10 @@ int launch_tokens(const void* act_v, int B, int M_each, int N, int64_t ld, int64
   const int rows_each = part ? M_each : M;
   int rc = CI_OK;
 #define CI_THR(I, W) \
-  launch_threshold<I, W, IN>(act, rows_each, N, ld, q_alpha, sign_mask, thr, ghist, ghist_words, part, grid, s)
+  (part ? launch_threshold<I, W, true, IN>(act, rows_each, N, ld, q_alpha, sign_mask, thr, ghist, ghist_words, part, grid, s) \
+        : launch_threshold<I, W, false, IN>(act, rows_each, N, ld, q_alpha, sign_mask, thr, ghist, ghist_words, part, grid, s))
+#define CI_THR0() \
+  launch_threshold<0, false, false, IN>(act, rows_each, N, ld, q_alpha, sign_mask, thr, ghist, ghist_words, part, grid, s)
   if constexpr (sizeof(TI) == 4) {
     if (two && items <= 8) rc = CI_THR(8, true);
     else if (two) rc = CI_THR(16, true);
@@ -1064,14 +1073,15 @@ int launch_tokens(const void* act_v, int B, int M_each, int N, int64_t ld, int64
     else if (items <= 32) rc = CI_THR(32, false);
     else if (items <= 36) rc = CI_THR(36, false);
     else if (items <= 40) rc = CI_THR(40, false);
-    else rc = CI_THR(0, false);
+    else rc = CI_THR0();
   } else {
     if (two) rc = CI_THR(16, true);
     else if (items <= 16) rc = CI_THR(16, false);
     else if (items <= 40) rc = CI_THR(40, false);
-    else rc = CI_THR(0, false);
+    else rc = CI_THR0();
   }
 #undef CI_THR
+#undef CI_THR0
   if (rc != CI_OK) return rc;
   if (part) {
     const int words = (items + 3) / 4 * kThreads;
@@ -1080,9 +1090,6 @@ int launch_tokens(const void* act_v, int B, int M_each, int N, int64_t ld, int64
     CI_HIP_CHECK_LAUNCH();
     return CI_OK;
   }
-  // four activations per load: 16 bytes of fp32 or 8 bytes of a 16-bit type
-  const uintptr_t quad = 4 * sizeof(TI);
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(act) & (quad - 1)) == 0 && ld % 4 == 0) ? 1 : 0;
   // 64 neurons per workgroup when blocks of 256 would leave more than half of the chip idle
   if (nblocks * B <= cus / 2)
     hipLaunchKernelGGL((count_kernel<64, IN>), dim3((N + 63) / 64, B), dim3(nt), 0, s, act, M_each, N, ld, sign_mask,
