@@ -317,10 +317,13 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
   const int n_iter = (N + nt - 1) / nt;
   init_shared(&sh);
   if (ghist)  // cleared here, a slice per workgroup, for the counting launch that follows
-    for (int j = (blockIdx.y * gridDim.x + blockIdx.x) * nt + tid; j < ghist_words; j += gridDim.y * gridDim.x * nt)
+    for (int j = ((BYTES ? blockIdx.y * gridDim.x : 0) + blockIdx.x) * nt + tid; j < ghist_words;
+         j += (BYTES ? gridDim.y : 1) * gridDim.x * nt)
       ghist[j] = 0u;
-  act += (size_t)blockIdx.y * M * ld;
-  thr += (size_t)blockIdx.y * M * 2;
+  if constexpr (BYTES) {  // without byte counts the rows of all sentences are one range
+    act += (size_t)blockIdx.y * M * ld;
+    thr += (size_t)blockIdx.y * M * 2;
+  }
   static_assert(!BYTES || ITEMS > 0, "byte counts come from keys in registers");
   uint32_t cp[BYTES ? ITEMS / 4 : 1];  // counts of this thread's neurons, a byte each
 #pragma unroll
