@@ -110,6 +110,7 @@ int coreinfer_dev_set_param(const char* name, int value) {
   else if (!strcmp(name, "gemm_tile") && value >= -1 && value <= 4) p.gemm_tile = value;
   else if (!strcmp(name, "gemm_splits") && value >= 0 && value <= 8) p.gemm_splits = value;
   else if (!strcmp(name, "gemv_wgs_per_cu") && value >= 1 && value <= 32) p.gemv_wgs_per_cu = value;
+  else if (!strcmp(name, "gemv_cols_wgs_per_cu") && value >= 1 && value <= 4) p.gemv_cols_wgs_per_cu = value;
   else if (!strcmp(name, "gathered_union") && value >= 0 && value <= 2) p.gathered_union = value;
   else if (!strcmp(name, "union_depth") && (value == 8 || value == 16)) p.union_depth = value;
   else if (!strcmp(name, "union_down_threads") && value >= 64 && value <= 512) p.union_down_threads = value;
@@ -587,6 +588,17 @@ int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtyp
   return CI_OK;
 }
 
+// Up to four tokens over neuron-major weights: hidden values first, then the down rows, each weight read once;
+// or the decode kernel with all neurons as the core set, which reads the weights once per token and, for the
+// scores, the up matrices once more.  The latter has one launch fewer where no scores are asked for: a single
+// token, two below 200 MB (2048 x 8192 fp32 30 against 36 us; 4096 x 16384 fp16 55 against 48), three and four
+// below 8 MB.  (Rows that the decode kernel does not take are refused in either case.)
+static bool dense_cols_pays(int64_t M, int64_t d, int64_t N, int dtype, int act, bool scores) {
+  if (d / vec_of(dtype) > 4096) return false;
+  const double bytes = (double)(act == CI_ACT_SWIGLU ? 3 : 2) * (double)d * (double)N * (double)elem_bytes(dtype);
+  return scores || (M == 2 && bytes >= 200e6) || (M > 2 && bytes >= 8e6);
+}
+
 int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* w_gate,
                         const void* b_up, const void* w_down, const void* b_down, int down_layout,
                         int dtype, int act, int64_t d, int64_t N, void* Y, float* A, void* ws,
@@ -608,6 +620,12 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
 
   if (M <= 4) {
     float* H = reinterpret_cast<float*>(ws);
+    float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
+                                              round256((size_t)M * (size_t)N * sizeof(float)));
+    if (down_layout == CI_DOWN_NEURON_MAJOR && Y && dense_cols_pays(M, d, N, dtype, act, A != nullptr)) {
+      const int rc = launch_up_rows(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, A, s);
+      return rc != CI_OK ? rc : launch_down_cols(H, M, w_down, b_down, dtype, d, N, Y, partial, s);
+    }
     if (down_layout == CI_DOWN_NEURON_MAJOR && Y) {
       // all three matrices are neuron-major: this is the decode kernel with S = all neurons
       if (A) {
@@ -618,8 +636,6 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
       w.w_up = w_up; w.w_gate = w_gate; w.b_up = b_up; w.w_down = w_down; w.b_down = b_down;
       w.core_idx = nullptr; w.K = N; w.d = d; w.N = N;
       w.ld_down = 0; w.down_layout = CI_DOWN_NEURON_MAJOR;
-      float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
-                                                round256((size_t)M * (size_t)N * sizeof(float)));
       return launch_ffn_decode(X, M, &w, dtype, act, Y, partial, s);
     }
     int rc = launch_up_rows(X, M, w_up, w_gate, b_up, dtype, act, d, N, Y ? H : nullptr, A, s);

@@ -124,7 +124,8 @@ struct Params {
   Knob decode_depth{4};      // weight rows in flight per thread (4, 8 or 16)
   Knob select_wgs_per_cu{2};
   Knob select_def2_single{0};  // Def. 2 in one workgroup even where the parallel kernel applies
-  Knob gemv_wgs_per_cu{4};
+  Knob gemv_wgs_per_cu{8};
+  Knob gemv_cols_wgs_per_cu{1};
   Knob gemm_ring{1}, gemm_direct{1};  // either 0: the guarded two-stage GEMM kernel instead of the planned tiles
   Knob gemm_big{1};          // 256 x 256 tiles: 0 never, 1 where the plan takes them, 2 always
   Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256)
@@ -226,6 +227,8 @@ int launch_gathered_union(const void* x, int64_t B, const ci_ffn_weights* w, int
 // h[M, N] fp32 = act(X w^T ...) and y = W h + b by row-dot GEMVs (small M).
 int launch_up_rows(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,
                    int dtype, int act, int64_t d, int64_t N, float* H, float* A, hipStream_t s);
+int launch_down_cols(const float* H, int64_t M, const void* w_down, const void* b_down, int dtype,
+                     int64_t d, int64_t N, void* Y, float* partial, hipStream_t s);
 int launch_down_rows(const float* H, int64_t M, const void* w_down, const void* b_down, int dtype,
                      int64_t d, int64_t N, void* Y, hipStream_t s);
 int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,

@@ -25,7 +25,7 @@
  *   compute unit also for prompts longer than the chip has compute units),
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
- *   "gemv_wgs_per_cu" (1..32), "gemm_ring", "gemm_direct" (0/1: either 0
+ *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4), "gemm_ring", "gemm_direct" (0/1: either 0
  *   selects the guarded two-stage GEMM kernel instead of the planned tiles),
  *   "gemm_big" (0 never, 1 where the plan takes them, 2 always: 256 x 256 tiles),
  *   "gemm_tile" (-1 planned, 0 .. 4: tile shape), "gemm_splits" (0 planned, 1 .. 8:

@@ -87,3 +87,25 @@ def test_dense_split_last_round_only(lib, layout):
     finally:
         lib.dev_set_param("gemm_tile", -1)
         lib.dev_set_param("gemm_splits", 0)
+
+
+# up to four tokens: groups of 4 (8) rows that end inside a group, rows shorter and longer than one pass of 256
+# threads, columns that end inside a chunk of 64 vectors, pieces of the neurons that are empty or end inside a batch
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("act,layout", [("relu", "out_major"), ("swiglu", "out_major"), ("relu", "neuron_major"),
+                                        ("swiglu", "neuron_major")])
+@pytest.mark.parametrize("M", [1, 2, 3, 4])
+def test_dense_few_tokens(lib, M, act, layout, dtype):
+    for d, N in [(8, 8), (24, 40), (520, 1032), (2056, 2824), (4104, 264)]:
+        _check_dense(lib, dtype, act, layout, M, d, N)
+
+
+def test_dense_few_tokens_infinite_weight(lib):
+    """Rows that are loaded again to fill a batch take no part: an infinite weight gives an infinity, not a NaN."""
+    d, N, dt = 64, 8 * 19, torch.float16
+    X = torch.ones(2, d, dtype=dt, device=DEV)
+    w_up = torch.full((N, d), 0.01, dtype=dt, device=DEV)
+    w_down = torch.full((N, d), 0.01, dtype=dt, device=DEV)
+    w_down[N - 1, 3] = float("inf")
+    Y = lib.ffn_dense(X, w_up, None, None, w_down, None, "neuron_major", "relu", want_y=True, want_a=True)[0]
+    assert bool(torch.isinf(Y[:, 3]).all()) and int(torch.isfinite(Y).sum()) == 2 * (d - 1)
