@@ -263,8 +263,8 @@ struct GemmPlan {
 // filled round can be split along k into `splits` parts each, whose fp32 sums are written, read back and
 // added by another launch (about 4.5 TB/s and 5 us).  The shape and split of the least estimated time are
 // taken; out_bytes: written per output.  Examples (both projections, former kernels -> these): 77 tokens, 4096 x 11008
-// gated 96 -> 80 us; 700 tokens, 4096 x 16384, neuron-major down 702 -> 210 us; 1000 tokens, 5448 x 17768,
-// neuron-major 1656 -> 600 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
+// gated 97 -> 71 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000 tokens, 7168 x 28672,
+// neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
 GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, bool can_split) {
   GemmPlan best{};
