@@ -379,7 +379,8 @@ def run_workload(inp: Inputs, beta: float, steps: int, warmup: int, args, cpu_se
                      "not a bandwidth claim for HBM alone" if traffic is not None else
                      "no committed counter summary for this launch size: algorithmic bytes / time, which counts "
                      "rows shared between sentences once per sentence; not a bandwidth claim")
-        kernels = "ffn_decode_kernel + decode_reduce_kernel (gathered rows of resident weights)"
+        kernels = ("everything coreinfer_ffn_decode launches (gathered rows of resident weights; large overlapping lists: "
+                   "union build, union_up_kernel, union_down_kernel, decode_reduce_kernel)")
     else:
         achieved_gbps = bytes_per_launch / (kernel_ms * 1e-3) / 1e9
         roof_note = "achieved = algorithmic bytes of one layer-token / time of everything coreinfer_ffn_decode launches"
