@@ -100,6 +100,8 @@ _lib.coreinfer_dev_set_param.restype = _int
 _lib.coreinfer_dev_set_param.argtypes = [ctypes.c_char_p, _int]
 _lib.coreinfer_dev_fused_plan.restype = _int
 _lib.coreinfer_dev_fused_plan.argtypes = [_i64, _i64, _int, _int, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_select_layout.restype = _int
+_lib.coreinfer_dev_select_layout.argtypes = [_i64, _i64, _i64, ctypes.POINTER(_i64)]
 _lib.coreinfer_dev_stream_probe.restype = _int
 _lib.coreinfer_dev_stream_probe.argtypes = [_vp, _i64, _i64, _int, _int, _int, _int, _int, _vp, _vp]
 _lib.coreinfer_dev_tile_probe.restype = _int
@@ -153,6 +155,13 @@ def dev_fused_plan(K: int, d: int, dtype: torch.dtype, act: str) -> dict:
     out = (_int * 5)()
     _check(_lib.coreinfer_dev_fused_plan(K, d, DTYPE_CODE[dtype], ACT_CODE[act], out), "coreinfer_dev_fused_plan")
     return dict(zip(("chunks", "chunk_neurons", "compute_waves", "loads_per_row", "workgroups"), list(out)))
+
+
+def dev_select_layout(B: int, M: int, N: int) -> dict:
+    """Byte offsets of the pieces of coreinfer_select_batch's workspace (part: -1 if there are no byte counts)."""
+    out = (_i64 * 4)()
+    _check(_lib.coreinfer_dev_select_layout(B, M, N, out), "coreinfer_dev_select_layout")
+    return dict(zip(("thresholds", "histograms", "counts", "part"), list(out)))
 
 
 def dev_stream_probe(buf: torch.Tensor, window_bytes: int, per_workgroup: bool, workgroups: int, threads: int,

@@ -80,6 +80,17 @@ int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out)
   return fused_decode_plan(K, d, dtype, act, out);
 }
 
+int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out) {
+  size_t need = 0;
+  if (!out || coreinfer_select_batch_workspace_size(B, M, N, &need) != CI_OK) return CI_ERR_INVALID_ARG;
+  const SelectScratch sc = select_scratch(nullptr, M, N, B);
+  out[0] = (int64_t)reinterpret_cast<uintptr_t>(sc.thr);
+  out[1] = (int64_t)reinterpret_cast<uintptr_t>(sc.hist);
+  out[2] = (int64_t)reinterpret_cast<uintptr_t>(sc.counts);
+  out[3] = sc.part ? (int64_t)reinterpret_cast<uintptr_t>(sc.part) : -1;
+  return CI_OK;
+}
+
 // Development hook (coreinfer_dev.h), not part of the installed interface: launch-shape
 // parameters for tuning sweeps.  Returns CI_ERR_INVALID_ARG for unknown names.
 int coreinfer_dev_set_param(const char* name, int value) {
@@ -137,15 +148,6 @@ int coreinfer_select_workspace_size(int64_t M, int64_t N, size_t* bytes) {
   return CI_OK;
 }
 
-namespace {
-// counters inside the workspace, for callers that pass none
-int32_t* ws_counts(void* ws, int64_t M, int64_t N) {
-  SelectWs w;
-  select_ws_layout(M, N, &w);
-  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + w.off_counts);
-}
-}  // namespace
-
 int coreinfer_select(const float* act, int64_t M, int64_t N, int64_t ld, double alpha, double beta,
                      int32_t* core_idx, int32_t* counts, void* ws, size_t ws_bytes, void* stream) {
   size_t need = 0;
@@ -159,8 +161,9 @@ int coreinfer_select(const float* act, int64_t M, int64_t N, int64_t ld, double 
     return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  int32_t* cnt = counts ? counts : ws_counts(ws, M, N);
-  return launch_select(act, CI_F32, 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, ws, kSelTokens | kSelFinal,
+  const SelectScratch sc = select_scratch(ws, M, N);
+  int32_t* cnt = counts ? counts : sc.counts;
+  return launch_select(act, CI_F32, 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, &sc, kSelTokens | kSelFinal,
                        (hipStream_t)stream);
 }
 
@@ -188,16 +191,16 @@ int coreinfer_select_batch(const float* act, int64_t B, int64_t M, int64_t N, in
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
   const int64_t K = keep(qb, N);
-  SelectWs w;
-  select_ws_layout(M, N, &w, B);
-  int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + w.off_counts);
+  const SelectScratch sc = select_scratch(ws, M, N, B);
+  int32_t* cnt = counts ? counts : sc.counts;
   if (B == 1 || select_batch_ok(M, N))
-    return launch_select(act, CI_F32, 0, M, N, ld, qa, K, M, core_idx, cnt, ws, kSelTokens | kSelFinal,
+    return launch_select(act, CI_F32, 0, M, N, ld, qa, K, M, core_idx, cnt, &sc, kSelTokens | kSelFinal,
                          (hipStream_t)stream, (int)B, N);
-  // one sentence after the other; a sentence's thresholds and histogram fit the front of the batch's workspace
+  // one sentence after the other, each in the batch's layout: its thresholds and histogram take the front of theirs,
+  // and its byte counts lie behind the counters of all sentences
   for (int64_t b = 0; b < B; ++b) {
     const int rc = launch_select(act + (size_t)b * M * ld, CI_F32, 0, M, N, ld, qa, K, M, core_idx + b * K, cnt + b * N,
-                                 ws, kSelTokens | kSelFinal, (hipStream_t)stream);
+                                 &sc, kSelTokens | kSelFinal, (hipStream_t)stream);
     if (rc != CI_OK) return rc;
   }
   return CI_OK;
@@ -219,8 +222,9 @@ int coreinfer_select_hidden(const void* hidden, int dtype, int act, int64_t M, i
     return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  int32_t* cnt = counts ? counts : ws_counts(ws, M, N);
-  return launch_select(hidden, dtype, act == CI_ACT_SWIGLU ? 1 : 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, ws,
+  const SelectScratch sc = select_scratch(ws, M, N);
+  int32_t* cnt = counts ? counts : sc.counts;
+  return launch_select(hidden, dtype, act == CI_ACT_SWIGLU ? 1 : 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, &sc,
                        kSelTokens | kSelFinal, (hipStream_t)stream);
 }
 
@@ -235,7 +239,8 @@ int coreinfer_count_tokens(const float* act, int64_t M, int64_t N, int64_t ld, d
   if ((reinterpret_cast<uintptr_t>(act) & 3u) || (reinterpret_cast<uintptr_t>(counts) & 3u)) return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  return launch_select(act, CI_F32, 0, M, N, ld, qa, 1, M, nullptr, counts, ws,
+  const SelectScratch sc = select_scratch(ws, M, N);
+  return launch_select(act, CI_F32, 0, M, N, ld, qa, 1, M, nullptr, counts, &sc,
                        kSelTokens | (accumulate ? kSelAccumulate : 0), (hipStream_t)stream);
 }
 
@@ -265,7 +270,8 @@ int coreinfer_group_select(const int32_t* core_sets, int64_t G, int64_t K, int64
     return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  int32_t* cnt = counts ? counts : ws_counts(ws, G, N);
+  const SelectScratch sc = select_scratch(ws, G, N);
+  int32_t* cnt = counts ? counts : sc.counts;
   hipStream_t s = (hipStream_t)stream;
   // clear the counters, count the groups' members, then Def. 2 with gamma on the counters
   int rc = launch_select(nullptr, CI_F32, 0, 0, N, N, 1, 1, G, nullptr, cnt, nullptr, kSelZero, s);

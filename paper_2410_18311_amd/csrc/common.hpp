@@ -180,10 +180,19 @@ struct SelectWs {
   size_t off_thr, off_hist, off_counts, off_part, total;
 };
 void select_ws_layout(int64_t M, int64_t N, SelectWs* w, int64_t B = 1);
+// Where the pieces of one selection lie.  One layout serves an entry point from its size check to its last launch:
+// sentences that are taken one after the other use the batch's, whose counters have to outlast them all.
+struct SelectScratch {
+  uint32_t* thr;    // (T, cut) per token
+  uint32_t* hist;   // histogram of the counts
+  int32_t* counts;  // for callers that pass none
+  uint32_t* part;   // byte counts, min(B M, 512) rows; NULL where the layout has none
+};
+SelectScratch select_scratch(void* ws, int64_t M, int64_t N, int64_t B = 1);
 bool select_batch_ok(int64_t M, int64_t N);
-// ws: laid out by select_ws_layout (may be null when only kSelZero is asked for)
+// scratch: null where no tokens are counted
 int launch_select(const void* act, int act_dtype, int take_abs, int64_t M, int64_t N, int64_t ld, int64_t q_alpha,
-                  int64_t K, int64_t max_count, int32_t* core_idx, int32_t* counts, void* ws, int what,
+                  int64_t K, int64_t max_count, int32_t* core_idx, int32_t* counts, const SelectScratch* scratch, int what,
                   hipStream_t s, int B = 1, int64_t counts_stride = 0);
 int launch_scatter_count(const int32_t* idx, int64_t n_idx, int64_t N, int32_t* counts, hipStream_t s);
 int launch_similarity(const int32_t* a, int64_t Ka, const int32_t* b, int64_t Kb, int32_t* out, hipStream_t s);

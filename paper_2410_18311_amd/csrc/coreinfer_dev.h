@@ -58,6 +58,11 @@ int coreinfer_dev_set_param(const char* name, int value);
  * apply. */
 int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out);
 
+/* Where coreinfer_select_batch lays the pieces of its workspace, in bytes from
+ * its start: out[0..3] = thresholds, histograms, counters, byte counts (-1:
+ * none).  Host array. */
+int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out);
+
 /* Measurement aid: `workgroups` workgroups of `threads` threads (a multiple of
  * 64 up to 512) each stream 16-byte loads, `depth` (2, 4, 8, 16) in flight per
  * thread, `iters` * depth per thread in all, round and round over a window of

@@ -1138,6 +1138,15 @@ void select_ws_layout(int64_t M, int64_t N, SelectWs* w, int64_t B) {
   }
 }
 
+SelectScratch select_scratch(void* ws, int64_t M, int64_t N, int64_t B) {
+  SelectWs w;
+  select_ws_layout(M, N, &w, B);
+  char* base = reinterpret_cast<char*>(ws);
+  return SelectScratch{reinterpret_cast<uint32_t*>(base + w.off_thr), reinterpret_cast<uint32_t*>(base + w.off_hist),
+                       reinterpret_cast<int32_t*>(base + w.off_counts),
+                       select_has_part(B, N) ? reinterpret_cast<uint32_t*>(base + w.off_part) : nullptr};
+}
+
 // The stages of the selection, individually switchable:
 //   kSelZero       clear the counters (before members are scattered into them)
 //   kSelTokens     Def. 1 over the M rows of act, then Eq. 3 (kSelAccumulate: added to the counters)
@@ -1150,7 +1159,7 @@ bool select_batch_ok(int64_t M, int64_t N) {
 }
 
 int launch_select(const void* act, int act_dtype, int take_abs, int64_t M64, int64_t N64, int64_t ld,
-                  int64_t q_alpha, int64_t K64, int64_t max_count, int32_t* core_idx, int32_t* counts, void* ws,
+                  int64_t q_alpha, int64_t K64, int64_t max_count, int32_t* core_idx, int32_t* counts, const SelectScratch* scratch,
                   int what, hipStream_t s, int B, int64_t counts_stride) {
   const int M = (what & kSelTokens) ? (int)M64 : 0, N = (int)N64, K = (int)K64;
   DeviceInfo di;
@@ -1170,15 +1179,12 @@ int launch_select(const void* act, int act_dtype, int take_abs, int64_t M64, int
   const bool parallel_final = (what & kSelTokens) && (what & kSelFinal) && !(what & kSelAccumulate) &&
                               max_count < kCountBins && nblocks <= 256 && params().select_def2_single == 0;
   if (what & kSelTokens) {
-    SelectWs w;
-    select_ws_layout(M, N, &w, B);
     if (B > 1 && !parallel_final) return CI_ERR_UNSUPPORTED;
-    char* base = reinterpret_cast<char*>(ws);
-    uint32_t* thr = reinterpret_cast<uint32_t*>(base + w.off_thr);
-    uint32_t* ghist = parallel_final ? reinterpret_cast<uint32_t*>(base + w.off_hist) : nullptr;
+    uint32_t* thr = scratch->thr;
+    uint32_t* ghist = parallel_final ? scratch->hist : nullptr;
     const uint32_t sign_mask = take_abs ? 0x7fffffffu : 0xffffffffu;
     const int acc = (what & kSelAccumulate) ? 1 : 0;
-    uint32_t* part = select_has_part(B, N) ? reinterpret_cast<uint32_t*>(base + w.off_part) : nullptr;
+    uint32_t* part = scratch->part;
     if (act_dtype == CI_F16)
       rc = launch_tokens<InF16>(act, B, M, N, ld, q_alpha, sign_mask, thr, ghist, part, counts, counts_stride, acc, nt, items,
                                nblocks, di.cus, s);

@@ -65,6 +65,28 @@ def test_workspace_sizes(lib):
     assert lib.raw.coreinfer_ffn_dense_workspace_size(4, 64, 64, 9, ctypes.byref(b)) == lib.CI_ERR_BAD_DTYPE
 
 
+@pytest.mark.parametrize("B", [1, 2, 8, 64, 65, 300])
+@pytest.mark.parametrize("M", [1, 7, 511, 2047, 2048, 3000])
+@pytest.mark.parametrize("N", [1, 1025, 12289, 13824, 40960, 40961, 70000])
+def test_select_batch_keeps_the_pieces_of_its_workspace_apart(lib, B, M, N):
+    """Thresholds, histograms, the counters of all B sentences and the byte counts follow each other inside the
+    size that is asked for -- also where the sentences are taken one after the other (M >= 2048 or N > 65536) and
+    every one of them writes byte counts while the counters of those before it have to stay."""
+    if B * M > 65535 * 64:
+        pytest.skip("more tokens than a batch may have")
+    at = lib.dev_select_layout(B, M, N)
+    size = lib.select_batch_workspace_size(B, M, N)
+    assert at["thresholds"] == 0 and at["histograms"] >= B * M * 8
+    assert at["counts"] >= at["histograms"] + B * 2048 * 8 * 4
+    end = at["counts"] + B * N * 4
+    if at["part"] >= 0:
+        assert at["part"] >= end and at["part"] % 16 == 0
+        end = at["part"] + min(B * M, 512) * -(-N // 4096) * 4096   # a byte per neuron, whole registers of four
+    assert size >= end
+    if B <= 64 and N <= 40960:
+        assert at["part"] >= 0
+
+
 FAKE = 0x10000  # a non-null, 16-byte aligned address that is never dereferenced on these paths
 
 

@@ -51,3 +51,30 @@ def test_running_counts_add_up(lib):
     lib.count_tokens(dev[37:], 0.2, counts=counts, accumulate=True)
     torch.cuda.synchronize()
     assert np.array_equal(counts.cpu().numpy(), orc.select(A, 0.2, 0.4)[1])
+
+
+# Counters that the caller does not ask for live in the workspace, behind them the byte counts: sentences of 2048 tokens
+# and more are taken one after the other, each with byte counts of its own (2048 x 13824 fp32: 113 MB), and must leave
+# the counters of those before them alone.  65 sentences: no byte counts.  Guard words: nothing past the workspace.
+@pytest.mark.parametrize("B,M,N", [(2, 2048, 13824), (3, 2100, 4100), (2, 2048, 36864), (65, 2048, 130), (2, 2049, 12289)])
+def test_batch_without_counts(lib, B, M, N):
+    print("batch without counts case", B, M, N, flush=True)
+    base = activation_like(M + 5 * (B - 1), N, seed=M + N)
+    A = torch.from_numpy(np.concatenate([base[5 * b:5 * b + M] for b in range(B)])).to(DEV)   # no two sentences alike
+    K = lib.keep_count(0.4, N)
+    size = lib.select_batch_workspace_size(B, M, N)
+    ws = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    idx = torch.full((B, K), -1, dtype=torch.int32, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+    for _ in range(3):
+        rc = lib.raw.coreinfer_select_batch(A.data_ptr(), B, M, N, N, 0.2, 0.4, idx.data_ptr(), None, ws.data_ptr(), size,
+                                            stream)
+        assert rc == lib.CI_OK
+    torch.cuda.synchronize()
+    assert bool((ws[size:] == 0xA5).all()), "stored past the workspace"
+    at = lib.dev_select_layout(B, M, N)["counts"]
+    counts = ws[at:at + B * N * 4].view(torch.int32).view(B, N).cpu().numpy()
+    for b in range(B) if B < 10 else (0, B // 2, B - 1):
+        S_ref, c_ref = orc.select(base[5 * b:5 * b + M], 0.2, 0.4)
+        assert np.array_equal(counts[b], c_ref), f"counters in the workspace, sentence {b}"
+        assert np.array_equal(idx[b].cpu().numpy(), S_ref), f"core set, sentence {b}"
