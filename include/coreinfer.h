@@ -101,7 +101,10 @@ int coreinfer_keep_count(double frac, int64_t n, int64_t* k);
  *            come first in the order (count descending, index ascending).
  *   core_idx [K] int32 out: S in ascending index order.
  *   counts   [N] int32 out, may be NULL (then it lives in the workspace).
- *   ws       at least coreinfer_select_workspace_size(M, N) bytes.
+ *   ws       coreinfer_select_workspace_size(M, N) bytes.  For N <= 40960 the
+ *            last min(M, 512) * N of them (N rounded up to 4096) let long
+ *            prompts read their activations once instead of twice; a workspace
+ *            without them is accepted too, with the same results.
  * Limits: 1 <= M <= CI_MAX_TOKENS, 1 <= N <= CI_MAX_NEURONS.
  */
 int coreinfer_select_workspace_size(int64_t M, int64_t N, size_t* bytes);

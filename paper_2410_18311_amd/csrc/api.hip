@@ -83,7 +83,7 @@ int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out)
 int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out) {
   size_t need = 0;
   if (!out || coreinfer_select_batch_workspace_size(B, M, N, &need) != CI_OK) return CI_ERR_INVALID_ARG;
-  const SelectScratch sc = select_scratch(nullptr, M, N, B);
+  const SelectScratch sc = select_scratch(nullptr, need, M, N, B);
   out[0] = (int64_t)reinterpret_cast<uintptr_t>(sc.thr);
   out[1] = (int64_t)reinterpret_cast<uintptr_t>(sc.hist);
   out[2] = (int64_t)reinterpret_cast<uintptr_t>(sc.counts);
@@ -159,9 +159,9 @@ int coreinfer_select(const float* act, int64_t M, int64_t N, int64_t ld, double 
   if ((reinterpret_cast<uintptr_t>(act) & 3u) || (reinterpret_cast<uintptr_t>(core_idx) & 3u) ||
       (reinterpret_cast<uintptr_t>(counts) & 3u))
     return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < select_ws_least(M, N)) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  const SelectScratch sc = select_scratch(ws, M, N);
+  const SelectScratch sc = select_scratch(ws, ws_bytes, M, N);
   int32_t* cnt = counts ? counts : sc.counts;
   return launch_select(act, CI_F32, 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, &sc, kSelTokens | kSelFinal,
                        (hipStream_t)stream);
@@ -188,10 +188,10 @@ int coreinfer_select_batch(const float* act, int64_t B, int64_t M, int64_t N, in
   if ((reinterpret_cast<uintptr_t>(act) & 3u) || (reinterpret_cast<uintptr_t>(core_idx) & 3u) ||
       (reinterpret_cast<uintptr_t>(counts) & 3u))
     return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < select_ws_least(M, N, B)) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
   const int64_t K = keep(qb, N);
-  const SelectScratch sc = select_scratch(ws, M, N, B);
+  const SelectScratch sc = select_scratch(ws, ws_bytes, M, N, B);
   int32_t* cnt = counts ? counts : sc.counts;
   if (B == 1 || select_batch_ok(M, N))
     return launch_select(act, CI_F32, 0, M, N, ld, qa, K, M, core_idx, cnt, &sc, kSelTokens | kSelFinal,
@@ -220,9 +220,9 @@ int coreinfer_select_hidden(const void* hidden, int dtype, int act, int64_t M, i
   if ((reinterpret_cast<uintptr_t>(hidden) & (elem - 1)) || (reinterpret_cast<uintptr_t>(core_idx) & 3u) ||
       (reinterpret_cast<uintptr_t>(counts) & 3u))
     return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < select_ws_least(M, N)) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  const SelectScratch sc = select_scratch(ws, M, N);
+  const SelectScratch sc = select_scratch(ws, ws_bytes, M, N);
   int32_t* cnt = counts ? counts : sc.counts;
   return launch_select(hidden, dtype, act == CI_ACT_SWIGLU ? 1 : 0, M, N, ld, qa, keep(qb, N), M, core_idx, cnt, &sc,
                        kSelTokens | kSelFinal, (hipStream_t)stream);
@@ -237,9 +237,9 @@ int coreinfer_count_tokens(const float* act, int64_t M, int64_t N, int64_t ld, d
   if (qa == 0) return CI_ERR_INVALID_ARG;
   if (ld < N) return CI_ERR_BAD_LAYOUT;
   if ((reinterpret_cast<uintptr_t>(act) & 3u) || (reinterpret_cast<uintptr_t>(counts) & 3u)) return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < select_ws_least(M, N)) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  const SelectScratch sc = select_scratch(ws, M, N);
+  const SelectScratch sc = select_scratch(ws, ws_bytes, M, N);
   return launch_select(act, CI_F32, 0, M, N, ld, qa, 1, M, nullptr, counts, &sc,
                        kSelTokens | (accumulate ? kSelAccumulate : 0), (hipStream_t)stream);
 }
@@ -268,9 +268,9 @@ int coreinfer_group_select(const int32_t* core_sets, int64_t G, int64_t K, int64
   if ((reinterpret_cast<uintptr_t>(core_sets) & 3u) || (reinterpret_cast<uintptr_t>(core_idx) & 3u) ||
       (reinterpret_cast<uintptr_t>(counts) & 3u))
     return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < select_ws_least(G, N)) return CI_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) & 15u) return CI_ERR_BAD_LAYOUT;
-  const SelectScratch sc = select_scratch(ws, G, N);
+  const SelectScratch sc = select_scratch(ws, ws_bytes, G, N);
   int32_t* cnt = counts ? counts : sc.counts;
   hipStream_t s = (hipStream_t)stream;
   // clear the counters, count the groups' members, then Def. 2 with gamma on the counters

@@ -186,9 +186,11 @@ struct SelectScratch {
   uint32_t* thr;    // (T, cut) per token
   uint32_t* hist;   // histogram of the counts
   int32_t* counts;  // for callers that pass none
-  uint32_t* part;   // byte counts, min(B M, 512) rows; NULL where the layout has none
+  uint32_t* part;   // byte counts, min(B M, 512) rows; NULL where the layout has none or the workspace ends before them
 };
-SelectScratch select_scratch(void* ws, int64_t M, int64_t N, int64_t B = 1);
+SelectScratch select_scratch(void* ws, size_t ws_bytes, int64_t M, int64_t N, int64_t B = 1);
+// The least a selection works with: everything but the byte counts, without which the activations are read twice.
+size_t select_ws_least(int64_t M, int64_t N, int64_t B = 1);
 bool select_batch_ok(int64_t M, int64_t N);
 // scratch: null where no tokens are counted
 int launch_select(const void* act, int act_dtype, int take_abs, int64_t M, int64_t N, int64_t ld, int64_t q_alpha,

@@ -1138,13 +1138,20 @@ void select_ws_layout(int64_t M, int64_t N, SelectWs* w, int64_t B) {
   }
 }
 
-SelectScratch select_scratch(void* ws, int64_t M, int64_t N, int64_t B) {
+size_t select_ws_least(int64_t M, int64_t N, int64_t B) {
+  SelectWs w;
+  select_ws_layout(M, N, &w, B);
+  return w.off_part;
+}
+
+SelectScratch select_scratch(void* ws, size_t ws_bytes, int64_t M, int64_t N, int64_t B) {
   SelectWs w;
   select_ws_layout(M, N, &w, B);
   char* base = reinterpret_cast<char*>(ws);
   return SelectScratch{reinterpret_cast<uint32_t*>(base + w.off_thr), reinterpret_cast<uint32_t*>(base + w.off_hist),
                        reinterpret_cast<int32_t*>(base + w.off_counts),
-                       select_has_part(B, N) ? reinterpret_cast<uint32_t*>(base + w.off_part) : nullptr};
+                       select_has_part(B, N) && ws_bytes >= w.total ? reinterpret_cast<uint32_t*>(base + w.off_part)
+                                                                    : nullptr};
 }
 
 // The stages of the selection, individually switchable:

@@ -87,6 +87,20 @@ def test_select_batch_keeps_the_pieces_of_its_workspace_apart(lib, B, M, N):
         assert at["part"] >= 0
 
 
+@pytest.mark.parametrize("B,M,N", [(1, 256, 16384), (1, 4, 10), (8, 512, 36864), (2, 2048, 13824), (65, 9, 40)])
+def test_select_refuses_a_workspace_that_ends_before_its_counters(lib, B, M, N):
+    """What a selection cannot do without: everything in front of the byte counts."""
+    F, at = 0x10000, lib.dev_select_layout(B, M, N)
+    least = at["part"] if at["part"] >= 0 else lib.select_batch_workspace_size(B, M, N)
+    r = lib.raw
+    assert r.coreinfer_select_batch(F, B, M, N, N, 0.2, 0.4, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
+    if B == 1:
+        assert r.coreinfer_select(F, M, N, N, 0.2, 0.4, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
+        assert r.coreinfer_select_hidden(F, 1, 0, M, N, N, 0.2, 0.4, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
+        assert r.coreinfer_count_tokens(F, M, N, N, 0.2, F, 0, F, least - 1, None) == lib.CI_ERR_WORKSPACE
+        assert r.coreinfer_group_select(F, M, 1, N, 0.2, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
+
+
 FAKE = 0x10000  # a non-null, 16-byte aligned address that is never dereferenced on these paths
 
 

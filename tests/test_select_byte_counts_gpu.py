@@ -78,3 +78,33 @@ def test_batch_without_counts(lib, B, M, N):
         S_ref, c_ref = orc.select(base[5 * b:5 * b + M], 0.2, 0.4)
         assert np.array_equal(counts[b], c_ref), f"counters in the workspace, sentence {b}"
         assert np.array_equal(idx[b].cpu().numpy(), S_ref), f"core set, sentence {b}"
+
+
+# a workspace that ends where the byte counts would begin serves every call with the same results
+@pytest.mark.parametrize("B,M,N", [(1, 700, 16384), (1, 40, 36864), (3, 130, 5001), (2, 2048, 4100), (1, 5, 7)])
+def test_workspace_without_byte_counts(lib, B, M, N):
+    print("short workspace case", B, M, N, flush=True)
+    A = activation_like(B * M, N, seed=N)
+    dev = torch.from_numpy(A).to(DEV)
+    least = lib.dev_select_layout(B, M, N)["part"]
+    ws = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    idx, counts = lib.select_batch(dev, B, 0.2, 0.4, ws=ws[:least])
+    refs = [orc.select(A[b * M:(b + 1) * M], 0.2, 0.4) for b in range(B)]
+    for b, (S_ref, c_ref) in enumerate(refs):
+        assert np.array_equal(counts[b].cpu().numpy(), c_ref) and np.array_equal(idx[b].cpu().numpy(), S_ref)
+    if B == 1:
+        i1, c1 = lib.select(dev, 0.2, 0.4, ws=ws[:least])
+        c2 = lib.count_tokens(dev, 0.2, ws=ws[:least])
+        H = dev.to(torch.float16)
+        i3, c3 = lib.select_hidden(H, "relu", 0.2, 0.4, ws=ws[:least])
+        S3, r3 = orc.select(H.float().cpu().numpy(), 0.2, 0.4)
+        sets = i1[None].repeat(M, 1).contiguous()          # M groups that all name the same neurons
+        i4, c4 = lib.group_select(sets, N, 0.3, ws=ws[:least])
+        torch.cuda.synchronize()
+        assert np.array_equal(c1.cpu().numpy(), refs[0][1]) and np.array_equal(i1.cpu().numpy(), refs[0][0])
+        assert np.array_equal(c2.cpu().numpy(), refs[0][1])
+        assert np.array_equal(c3.cpu().numpy(), r3) and np.array_equal(i3.cpu().numpy(), S3)
+        S4, r4 = orc.group_core_neurons(sets.cpu().numpy(), N, 0.3)
+        assert np.array_equal(c4.cpu().numpy(), r4) and np.array_equal(i4.cpu().numpy(), S4)
+    torch.cuda.synchronize()
+    assert bool((ws[least:] == 0xA5).all()), "stored past the workspace"
