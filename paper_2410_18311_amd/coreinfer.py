@@ -100,6 +100,8 @@ _lib.coreinfer_dev_set_param.restype = _int
 _lib.coreinfer_dev_set_param.argtypes = [ctypes.c_char_p, _int]
 _lib.coreinfer_dev_fused_plan.restype = _int
 _lib.coreinfer_dev_fused_plan.argtypes = [_i64, _i64, _int, _int, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_decode_slices.restype = _int
+_lib.coreinfer_dev_decode_slices.argtypes = [_i64, _i64, _i64, _int, _int, ctypes.POINTER(_int)]
 _lib.coreinfer_dev_select_layout.restype = _int
 _lib.coreinfer_dev_select_layout.argtypes = [_i64, _i64, _i64, ctypes.POINTER(_i64)]
 _lib.coreinfer_dev_stream_probe.restype = _int
@@ -155,6 +157,14 @@ def dev_fused_plan(K: int, d: int, dtype: torch.dtype, act: str) -> dict:
     out = (_int * 5)()
     _check(_lib.coreinfer_dev_fused_plan(K, d, DTYPE_CODE[dtype], ACT_CODE[act], out), "coreinfer_dev_fused_plan")
     return dict(zip(("chunks", "chunk_neurons", "compute_waves", "loads_per_row", "workgroups"), list(out)))
+
+
+def dev_decode_slices(B: int, K: int, d: int, dtype: torch.dtype, gathered: bool) -> int:
+    """Neuron slices per sentence of the two-launch decode under the current development settings."""
+    out = _int(0)
+    _check(_lib.coreinfer_dev_decode_slices(B, K, d, DTYPE_CODE[dtype], int(bool(gathered)), ctypes.byref(out)),
+           "coreinfer_dev_decode_slices")
+    return out.value
 
 
 def dev_select_layout(B: int, M: int, N: int) -> dict:

@@ -80,6 +80,13 @@ int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out)
   return fused_decode_plan(K, d, dtype, act, out);
 }
 
+int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int gathered, int* slices) {
+  if (!slices || B < 1 || B > 65535 || K < 1 || K > CI_MAX_NEURONS || d < 1 || d > CI_MAX_DMODEL || !dtype_ok(dtype))
+    return CI_ERR_INVALID_ARG;
+  *slices = decode_splits(B, K, d * elem_bytes(dtype), gathered != 0);
+  return CI_OK;
+}
+
 int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out) {
   size_t need = 0;
   if (!out || coreinfer_select_batch_workspace_size(B, M, N, &need) != CI_OK) return CI_ERR_INVALID_ARG;

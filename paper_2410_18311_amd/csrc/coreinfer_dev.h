@@ -58,6 +58,10 @@ int coreinfer_dev_set_param(const char* name, int value);
  * apply. */
 int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out);
 
+/* Neuron slices per sentence of the two-launch decode under the current
+ * settings: *slices (host). */
+int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int gathered, int* slices);
+
 /* Where coreinfer_select_batch lays the pieces of its workspace, in bytes from
  * its start: out[0..3] = thresholds, histograms, counters, byte counts (-1:
  * none).  Host array. */

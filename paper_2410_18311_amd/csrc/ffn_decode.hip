@@ -444,13 +444,31 @@ int decode_splits_bound(int64_t B, int64_t K) {
   return (int)n;
 }
 
-// Of several sentences, slice i of each should run on the same XCD at the same time: the rows that
-// their ascending lists share are then neighbours in one L2.  Workgroups go to the XCDs round-robin, so
-// the number of slices is kept a multiple of eight (3 sentences at a keep fraction of 0.4 of
-// 36864 x 9216: 86 slices 353 us, 80 slices 236 us; 5 at 0.3: 52 slices 435 us, 48 slices 290 us).
-int decode_splits(int64_t B, int64_t K) {
+// Of several sentences, slice i of each should run on the same XCD at the same time: the rows that they share
+// are then neighbours in one L2.  Workgroups go to the XCDs round-robin, so the number of slices is kept a
+// multiple of eight (gathered, 3 sentences at a keep fraction of 0.4 of 36864 x 9216: 86 slices 353 us, 80 slices
+// 236 us; 5 at 0.3: 52 slices 435 us, 48 slices 290 us) -- as long as that leaves no more than a quarter of the compute
+// units without work; else one workgroup per compute unit, fewer than the bound, whose last few workgroups share a
+// compute unit with another one and end last (18 sentences, 36864 x 9216 at 0.4 gathered: 15 slices 1965, 8 slices
+// 1557, 14 slices 1342 us; 6554 x 4096 compacted: 297, 288, 180).  Wide gathered rows gain more by the shared L2:
+// 8 of 11 slices still 1646 against 1734 us (23 sentences, 36864 x 9216 at 0.4; 6554 x 4096 compacted 289 against 240).
+// That holds for rows that fill a compute unit's loads with one workgroup.  Of narrower ones (a 16-byte vector per
+// thread: fewer waves) two workgroups on a compute unit run as fast as one, and more slices are better: 18 sentences
+// of 1638 x 2048 in 16 bits, compacted: 15 slices 21.8, 8 slices 32.6 us; of 1228 x 1024 in fp32, gathered: 40.6
+// and 57.8.  The line lies between 4096 bytes (multiples of eight up to 1.6 times slower; up to 1.15 times faster where
+// compacted rows lose less than a sixth of the slices) and 6144 (up to 1.6 times faster); fewer than eight slices, only
+// from 8192 on (6144 bytes, 33 sentences gathered: 8 slices 1.16 times faster than 7).
+int decode_splits(int64_t B, int64_t K, int64_t row_bytes, bool gathered) {
   const int n = decode_splits_bound(B, K);
-  return B > 1 && n > 8 && params().decode_wgs == 0 ? n / 8 * 8 : n;
+  DeviceInfo di;
+  const int64_t cus = device_info(&di) == CI_OK ? di.cus : 256;
+  const int64_t whole = cus * params().decode_wgs_per_cu / B;  // slices with at most that many workgroups per compute unit
+  if (params().decode_wgs > 0 || whole < 1 || whole >= n) return n;  // B == 1 among them
+  const int64_t eights = whole / 8 * 8;
+  const bool wide = row_bytes >= 8192;
+  if (row_bytes < 6144) return !gathered && row_bytes >= 4096 && eights * 6 >= n * 5 ? (int)eights : n;
+  if (whole < 8 && !wide) return n;
+  return (int)(eights * 100 >= whole * (wide && gathered ? 72 : 75) ? eights : whole);
 }
 
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
@@ -478,7 +496,7 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   a.K = (int)w->K;
   a.d = (int)w->d;
   a.N = (int)w->N;
-  a.n_wg = decode_splits(B, w->K);
+  a.n_wg = decode_splits(B, w->K, w->d * (dtype == CI_F32 ? 4 : 2), w->core_idx != nullptr);
   a.nt_store = params().decode_nt_store;
   switch (dtype) {
     case CI_F32: return launch_dtype<F32>(a, (int)B, act, w->b_down, y, s);

@@ -101,6 +101,28 @@ def test_select_refuses_a_workspace_that_ends_before_its_counters(lib, B, M, N):
         assert r.coreinfer_group_select(F, M, 1, N, 0.2, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("gathered", [False, True])
+def test_decode_slices_leave_few_compute_units_idle(lib, gathered):
+    """On 256 compute units: narrow rows keep every slice (two workgroups on a compute unit cost them nothing) but a
+    sixth at most; wide ones of several sentences have at most one workgroup per compute unit, a multiple of eight
+    where that idles little of the chip; and never more slices than the scratch is sized for."""
+    import torch
+    for dtype, e in ((torch.float16, 2), (torch.float32, 4)):
+        for d in (256, 1024, 2048, 3072, 4096, 9216):
+            for K in (5, 410, 14746):
+                for B in list(range(1, 70)) + [200, 256, 257, 1000]:
+                    bound = min(-(-256 // B), K)
+                    n = lib.dev_decode_slices(B, K, d, dtype, gathered)
+                    assert 1 <= n <= bound
+                    if B == 1 or K < 256 // B:
+                        assert n == bound
+                    elif d * e < 6144:
+                        assert n == bound if gathered or d * e < 4096 else 6 * n >= 5 * bound
+                    elif d * e >= 8192 and B <= 256:
+                        assert n * B <= 256 and n * B >= (0.72 if gathered else 0.75) * (256 // B * B)
+                        assert n == 256 // B or n % 8 == 0
+
+
 FAKE = 0x10000  # a non-null, 16-byte aligned address that is never dereferenced on these paths
 
 
