@@ -59,11 +59,15 @@ __device__ __forceinline__ i32x4 rsrc_at(const char* p) {
 
 // 16 bytes per lane from `rsrc` + `off` to LDS at `lds` + 16 * lane.  Written out, because the compiler
 // orders transposing LDS reads behind every such load it knows of; nothing is returned to a register, and
-// the waits for its arrival are the kernel's own (s_waitcnt vmcnt ahead of a barrier).
+// the waits for its arrival are the kernel's own (s_waitcnt vmcnt ahead of a barrier).  The compiler does not
+// look for hazards inside: five wait states have to lie between a vector instruction that writes a scalar register
+// (a lane read that makes a descriptor uniform or fetches a spilled one) and a load that reads it, and the move to
+// m0 and four idle ones are those five, whatever stands before.
 __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t off, i32x4 rsrc) {
   const uint32_t m = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lds;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
+  uint32_t m0;  // says that m0 is written (as a clobber it is refused with a warning)
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 3\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+               : "={m0}"(m0)
                : "s"(m), "v"(off), "s"(rsrc)
                : "memory");
 }
