@@ -412,7 +412,10 @@ int coreinfer_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w
  * be NULL); at least one of Y, A must be given.  b_up may be NULL and must be
  * NULL for CI_ACT_SWIGLU (CI_ERR_INVALID_ARG).  For Y, H is rounded to
  * `dtype` before the second product when M > 4 (matrix-core path).
- * ws: at least coreinfer_ffn_dense_workspace_size(M, d, N, dtype) bytes.
+ * ws: coreinfer_ffn_dense_workspace_size(M, d, N, dtype) bytes.  For M > 4 what
+ * goes beyond the hidden matrix (4 M N bytes, whole 256-byte blocks, and 256)
+ * holds partial sums of Y where tiles are split along N; a workspace without
+ * room for them is accepted, and no tile is split.
  */
 int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes);
 int coreinfer_ffn_dense(const void* X, int64_t M,
@@ -429,7 +432,8 @@ int coreinfer_ffn_dense(const void* X, int64_t M,
  * SiLU(X w_gate^T) * (X w_up^T), rounded once from the fp32 accumulator; Y
  * (nullable) = H w_down^T + b_down as in coreinfer_ffn_dense.  No fp32 matrix
  * of size M x N is written.  Arguments, layouts and errors as for
- * coreinfer_ffn_dense; the workspace only holds split partial products of Y.
+ * coreinfer_ffn_dense; the workspace (at least 256 bytes) only holds partial
+ * sums of Y where tiles are split along N.
  */
 int coreinfer_ffn_dense_hidden_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes);
 int coreinfer_ffn_dense_hidden(const void* X, int64_t M, const void* w_up, const void* w_gate,

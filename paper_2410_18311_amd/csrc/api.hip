@@ -594,8 +594,7 @@ int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtyp
   if (M <= 4) {
     b += round256((size_t)M * (size_t)(N < kMaxSplits ? N : kMaxSplits) * (size_t)d * sizeof(float));
   } else {
-    const int splits = gemm_down_splits_max(M, d, N, dtype);  // split-K partial products of Y
-    if (splits > 1) b += round256((size_t)splits * (size_t)M * (size_t)d * sizeof(float));
+    b += round256(gemm_plan_bytes(gemm_down_plan(M, d, N, dtype, SIZE_MAX)));  // sums of tiles split along k
   }
   *bytes = b + 256;
   return CI_OK;
@@ -620,6 +619,8 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
   if (!layout_ok(down_layout)) return CI_ERR_BAD_LAYOUT;
   size_t need = 0;
   if (coreinfer_ffn_dense_workspace_size(M, d, N, dtype, &need) != CI_OK) return CI_ERR_INVALID_ARG;
+  const size_t hidden = round256((size_t)M * (size_t)N * sizeof(float));
+  if (M > 4) need = hidden + 256;  // without room for the sums of split tiles none is split
   if (!X || !w_up || (!Y && !A) || (Y && !w_down)) return CI_ERR_INVALID_ARG;
   if ((act == CI_ACT_SWIGLU) != (w_gate != nullptr)) return CI_ERR_INVALID_ARG;
   if (act == CI_ACT_SWIGLU && b_up) return CI_ERR_INVALID_ARG;
@@ -633,8 +634,7 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
 
   if (M <= 4) {
     float* H = reinterpret_cast<float*>(ws);
-    float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
-                                              round256((size_t)M * (size_t)N * sizeof(float)));
+    float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + hidden);
     if (down_layout == CI_DOWN_NEURON_MAJOR && Y && dense_cols_pays(M, d, N, dtype, act, A != nullptr)) {
       const int rc = launch_up_rows(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, A, s);
       return rc != CI_OK ? rc : launch_down_cols(H, M, w_down, b_down, dtype, d, N, Y, partial, s);
@@ -655,20 +655,19 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
     if (rc != CI_OK || !Y) return rc;
     return launch_down_rows(H, M, w_down, b_down, dtype, d, N, Y, s);
   }
+  const GemmPlan plan = gemm_down_plan(M, d, N, dtype, ws_bytes - hidden);
   void* H = Y ? ws : nullptr;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, A, s);
   if (rc != CI_OK || !Y) return rc;
-  float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
-                                            round256((size_t)M * (size_t)N * sizeof(float)));
-  return launch_gemm_down(H, M, w_down, b_down, down_layout, dtype, d, N, Y, partial, s);
+  float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + hidden);
+  return launch_gemm_down(H, M, w_down, b_down, down_layout, dtype, d, N, Y, partial, plan, s);
 }
 
 int coreinfer_ffn_dense_hidden_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes) {
   if (!dtype_ok(dtype)) return CI_ERR_BAD_DTYPE;
   if (!bytes || M < 1 || M > CI_MAX_TOKENS || d < 1 || d > CI_MAX_DMODEL || N < 1 || N > CI_MAX_NEURONS)
     return CI_ERR_INVALID_ARG;
-  const int splits = gemm_down_splits_max(M, d, N, dtype);  // split-K partial products of Y
-  *bytes = (splits > 1 ? round256((size_t)splits * (size_t)M * (size_t)d * sizeof(float)) : 0) + 256;
+  *bytes = round256(gemm_plan_bytes(gemm_down_plan(M, d, N, dtype, SIZE_MAX))) + 256;  // sums of tiles split along k
   return CI_OK;
 }
 
@@ -686,12 +685,13 @@ int coreinfer_ffn_dense_hidden(const void* X, int64_t M, const void* w_up, const
   if (!aligned16(X) || !aligned16(w_up) || !aligned16(w_gate) || !aligned16(w_down) || !aligned16(Y) ||
       !aligned16(H))
     return CI_ERR_BAD_LAYOUT;
-  if (!ws || ws_bytes < need) return CI_ERR_WORKSPACE;
+  if (!ws || ws_bytes < 256) return CI_ERR_WORKSPACE;  // without room for the sums of split tiles none is split
   if (!aligned16(ws)) return CI_ERR_BAD_LAYOUT;
+  const GemmPlan plan = gemm_down_plan(M, d, N, dtype, ws_bytes);
   hipStream_t s = (hipStream_t)stream;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, nullptr, s);
   if (rc != CI_OK || !Y) return rc;
-  return launch_gemm_down(H, M, w_down, b_down, down_layout, dtype, d, N, Y, reinterpret_cast<float*>(ws), s);
+  return launch_gemm_down(H, M, w_down, b_down, down_layout, dtype, d, N, Y, reinterpret_cast<float*>(ws), plan, s);
 }
 
 }  // extern "C"

@@ -244,9 +244,15 @@ int launch_down_rows(const float* H, int64_t M, const void* w_down, const void* 
                      int64_t d, int64_t N, void* Y, hipStream_t s);
 int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,
                    int dtype, int act, int64_t d, int64_t N, void* H, float* A, hipStream_t s);
-int gemm_down_splits_max(int64_t M, int64_t d, int64_t N, int dtype);  // what the workspace is sized for
+struct GemmPlan {
+  int shape, bm, bn;                // tile shape; bn: output columns
+  int full, tail, splits, k_chunk;  // tiles computed whole, tiles split along k, by how many workgroups, k of each
+};
+// Plan of the down projection whose sums of split tiles take at most `room` bytes, and what they take.
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int dtype, size_t room);
+size_t gemm_plan_bytes(const GemmPlan& p);
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,
                      int down_layout, int dtype, int64_t d, int64_t N, void* Y, float* partial,
-                     hipStream_t s);
+                     const GemmPlan& p, hipStream_t s);
 
 }  // namespace ci

@@ -16,7 +16,7 @@ struct GemmArgs {
   float* out_f;    // [M, Nn] fp32, may be null
   int64_t lda, ldb, ldo;
   int M, Nn, Kk;
-  float* partial;  // where the k of a product may be split: [splits][M][Nn] fp32 partial products
+  float* partial;  // where the k of a product is split: [splits][tail] tiles of fp32 partial products, whole tiles each
   // tiles computed whole, tiles computed by `splits` workgroups of k_chunk each (a multiple of the k tile)
   int full, tail, splits, k_chunk;
 };

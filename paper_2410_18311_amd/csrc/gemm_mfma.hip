@@ -193,27 +193,29 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
   gemm_epilogue<D, EPI>(g, acc, m0, n0, wm, wn, lane);
 }
 
-// Y[m, n] = sum_s partial[s][m][n] + bias[n], converted to the element type, over the tiles that were split
-// (bm x bn, from place `first` in the order of tile_of).  A workgroup takes 16 rows of a tile, a thread four
+// Y[m, n] = sum_s partial[s][tile][m, n] + bias[n], converted to the element type, over the `tail` tiles that were
+// split (bm x bn, from place `first` in the order of tile_of).  A workgroup takes 16 rows of a tile, a thread four
 // columns of a row at a time; all splits' loads of it are in flight together.
 template <class D>
 __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ partial, const void* __restrict__ bias,
                                                            void* __restrict__ out, int splits, int M, int Nn, int bm,
-                                                           int bn, int first) {
+                                                           int bn, int first, int tail) {
   using T = typename D::T;
   const int strips = bm / 16;
   int tm, tn;
-  tile_of(first + blockIdx.x / strips, (M + bm - 1) / bm, (Nn + bn - 1) / bn, &tm, &tn);
-  const int row0 = tm * bm + (blockIdx.x % strips) * 16, col0 = tn * bn;
+  const int tile = blockIdx.x / strips, r0 = (blockIdx.x % strips) * 16;
+  const size_t stride = (size_t)tail * bm * bn;  // a split's tiles
+  tile_of(first + tile, (M + bm - 1) / bm, (Nn + bn - 1) / bn, &tm, &tn);
+  const int row0 = tm * bm + r0, col0 = tn * bn;
   const int quads = bn / 4;
   for (int i = threadIdx.x; i < 16 * quads; i += 256) {
     const int row = row0 + i / quads, col = col0 + (i % quads) * 4;
     if (row >= M || col >= Nn) continue;
-    const float* p = partial + (size_t)row * Nn + col;
+    const float* p = partial + ((size_t)tile * bm + r0 + i / quads) * bn + (i % quads) * 4;
     float4 a = *reinterpret_cast<const float4*>(p);
 #pragma unroll 4
     for (int s = 1; s < splits; ++s) {
-      const float4 v = *reinterpret_cast<const float4*>(p + (size_t)s * M * Nn);
+      const float4 v = *reinterpret_cast<const float4*>(p + s * stride);
       a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
     }
     const float o[4] = {a.x, a.y, a.z, a.w};
@@ -254,19 +256,14 @@ constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12},
                                  {kMid128x64, 128, 64, 2.7e12},
                                  {kWide, 256, 256, 5.5e12}};
 
-struct GemmPlan {
-  int shape, bm, bn;            // bn: output columns
-  int full, tail, splits, k_chunk;
-};
-
 // Every workgroup takes all of a compute unit's LDS, so tiles run in rounds of 256.  Tiles of the last, partly
 // filled round can be split along k into `splits` parts each, whose fp32 sums are written, read back and
-// added by another launch (about 4.5 TB/s and 5 us).  The shape and split of the least estimated time are
-// taken; out_bytes: written per output.  Examples (both projections, former kernels -> these): 77 tokens, 4096 x 11008
+// added by another launch (about 4.5 TB/s and 5 us).  The shape and split of the least estimated time whose sums fit
+// `room` bytes are taken; out_bytes: written per output.  Examples (both projections, former kernels -> these): 77 tokens, 4096 x 11008
 // gated 97 -> 71 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000 tokens, 7168 x 28672,
 // neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
-GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, bool can_split) {
+GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, size_t room) {
   GemmPlan best{};
   double best_t = 1e30;
   const int force = params().gemm_tile, force_splits = params().gemm_splits, big = params().gemm_big;
@@ -278,14 +275,14 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, 
     // first loads; results of a round, which nothing overlaps
     const double t_fixed = 3e-6 + (double)ts.bm * bn * out_bytes * kFullChip / 4.5e12;
     for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && (!can_split || Kk / ((int64_t)sp * BK) < 4)) break;  // at least four k tiles per split
+      if (sp > 1 && Kk / ((int64_t)sp * BK) < 4) break;  // at least four k tiles per split
       const int64_t full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
-      if (sp > 1 && tail == 0) break;
+      if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * ts.bm * bn * sizeof(float) > room)) break;
       const double t_full = (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed);
       const double t_tail = (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed);
       const double t_sum = tail == 0 ? 0.0 : 2.0 * sp * (double)tail * ts.bm * bn * 4.0 / 4.5e12 + 5e-6;
       const double t = t_full + t_tail + t_sum;
-      if (force_splits > 0 && can_split ? sp == force_splits : t < best_t) {
+      if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
         best_t = t;
         best = GemmPlan{ts.shape, ts.bm, bn, (int)full, (int)tail, sp, (int)Kk};
         if (sp > 1) best.k_chunk = (int)(((Kk + sp - 1) / sp + BK - 1) / BK * BK);
@@ -298,12 +295,8 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, 
 }
 
 template <class D, int EPI, bool BNN>
-int launch_mfma(GemmArgs& g, hipStream_t s) {
-  if (!params().gemm_ring || !params().gemm_direct) {
-    g.partial = nullptr;
-    return launch_guarded<D, EPI, BNN>(g, s);
-  }
-  const GemmPlan p = plan_gemm(g.M, g.Nn, g.Kk, EPI == EPI_SWIGLU, EPI == EPI_LINEAR ? 2 : 6, g.partial != nullptr);
+int launch_mfma(GemmArgs& g, const GemmPlan& p, hipStream_t s) {
+  if (!params().gemm_ring || !params().gemm_direct) return launch_guarded<D, EPI, BNN>(g, s);
   g.full = p.full;
   g.tail = p.tail;
   g.splits = p.splits;
@@ -312,17 +305,17 @@ int launch_mfma(GemmArgs& g, hipStream_t s) {
   const int rc = p.shape == kWide ? launch_gemm_wide(dtype, EPI, BNN, g, s) : launch_gemm_mid(p.shape, dtype, EPI, BNN, g, s);
   if (rc != CI_OK || p.tail == 0) return rc;
   hipLaunchKernelGGL((split_reduce_kernel<D>), dim3((unsigned)(p.tail * (p.bm / 16))), dim3(256), 0, s, g.partial, g.bias,
-                     g.out_e, p.splits, g.M, g.Nn, p.bm, p.bn, p.full);
+                     g.out_e, p.splits, g.M, g.Nn, p.bm, p.bn, p.full, p.tail);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
 
 template <int EPI, bool BNN>
-int launch_any(int dtype, GemmArgs& g, hipStream_t s) {
+int launch_any(int dtype, GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   switch (dtype) {
     case CI_F32: return launch_gemm_f32(EPI, BNN, g, s);
-    case CI_F16: return launch_mfma<F16, EPI, BNN>(g, s);
-    case CI_BF16: return launch_mfma<BF16, EPI, BNN>(g, s);
+    case CI_F16: return launch_mfma<F16, EPI, BNN>(g, p, s);
+    case CI_BF16: return launch_mfma<BF16, EPI, BNN>(g, p, s);
   }
   return CI_ERR_BAD_DTYPE;
 }
@@ -343,27 +336,31 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
   g.out_f = A;
   g.k_chunk = (int)d;
   g.partial = nullptr;
+  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, 6, 0);
   if (act == CI_ACT_SWIGLU) {
     g.B0 = w_gate;
     g.B1 = w_up;
     g.bias = nullptr;
-    return launch_any<EPI_SWIGLU, false>(dtype, g, s);
+    return launch_any<EPI_SWIGLU, false>(dtype, g, p, s);
   }
   g.B0 = w_up;
   g.B1 = nullptr;
   g.bias = b_up;
-  return launch_any<EPI_RELU, false>(dtype, g, s);
+  return launch_any<EPI_RELU, false>(dtype, g, p, s);
 }
 
-// Number of k splits of the down projection: a function of the shape (and the development settings), which
-// sizes the workspace.
-int gemm_down_splits_max(int64_t M, int64_t d, int64_t N, int dtype) {
-  return dtype == CI_F32 ? 1 : plan_gemm(M, d, N, false, 2, true).splits;
+// The down projection's plan, made once per call: the size check, the place of the sums and the launches all go by it.
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int dtype, size_t room) {
+  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, d, N, false, 2, room);
+}
+
+size_t gemm_plan_bytes(const GemmPlan& p) {
+  return p.tail > 0 ? (size_t)p.splits * (size_t)p.tail * p.bm * p.bn * sizeof(float) : 0;
 }
 
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,
                      int down_layout, int dtype, int64_t d, int64_t N, void* Y, float* partial,
-                     hipStream_t s) {
+                     const GemmPlan& p, hipStream_t s) {
   GemmArgs g;
   g.A = H;
   g.lda = N;
@@ -380,10 +377,10 @@ int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b
   g.partial = partial;
   if (down_layout == CI_DOWN_OUT_MAJOR) {
     g.ldb = N;
-    return launch_any<EPI_LINEAR, false>(dtype, g, s);
+    return launch_any<EPI_LINEAR, false>(dtype, g, p, s);
   }
   g.ldb = d;
-  return launch_any<EPI_LINEAR, true>(dtype, g, s);
+  return launch_any<EPI_LINEAR, true>(dtype, g, p, s);
 }
 
 }  // namespace ci

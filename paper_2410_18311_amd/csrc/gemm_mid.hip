@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __syncthreads();
   constexpr int PITCH = TJ * 32 + 8;
   store_wave<D, EPI, TI, TJ>(g, acc, reinterpret_cast<float*>(smem) + wave * 32 * PITCH, m0 + wm * TI * 32,
-                             n0 + wn * (DUAL ? TJ * 16 : TJ * 32), w.partial, w.split, lane);
+                             n0 + wn * (DUAL ? TJ * 16 : TJ * 32), w.sums, BNO, lane);
 }
 
 template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ>

@@ -77,10 +77,11 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t o
 // cache lines.  PITCH (words) is 8 modulo 16: the two half-waves of a store, four rows apart, then lie in
 // different halves of the banks.  acc: TI x TJ blocks; SwiGLU: the second half of the column blocks holds the
 // up values of the first half's columns.  part: 32 * PITCH floats of LDS of this wave's own; row0, col0: the
-// wave's first output row and column; partial: raw sums of split `split` instead of outputs.
+// wave's first output row and column; sums: not null where raw sums are stored instead of outputs, by row and column of
+// the product `sums_ld` apart.
 template <class D, int EPI, int TI, int TJ>
 __device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc)[TI][TJ], float* part, int row0, int col0,
-                                           bool partial, int split, int lane) {
+                                           float* sums, int sums_ld, int lane) {
   using T = typename D::T;
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr int PITCH = TJ * 32 + 8;
@@ -89,7 +90,7 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc
   const int l31 = lane & 31, hi = lane >> 5;
   const int col = col0 + 4 * (lane % LPR);
   float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (g.bias && !partial && col < g.Nn) {
+  if (g.bias && !sums && col < g.Nn) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) bv[k] = to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]);
   }
@@ -105,7 +106,7 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc
       const float4 c0 = *reinterpret_cast<const float4*>(part + r * PITCH + 4 * (lane % LPR));
       const float4 c1 = DUAL ? *reinterpret_cast<const float4*>(part + r * PITCH + CW + 4 * (lane % LPR)) : c0;
       if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
-        if (partial) *reinterpret_cast<float4*>(g.partial + ((size_t)split * g.M + row) * g.Nn + col) = c0;
+        if (sums) *reinterpret_cast<float4*>(sums + (ptrdiff_t)row * sums_ld + col) = c0;
         else store_quad<D, EPI>(g, c0, c1, bv, (size_t)row * g.ldo + col);
       }
     }
@@ -116,8 +117,8 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc
 // g.tail tiles behind them by g.splits workgroups.
 struct TileWork {
   int tm, tn;
-  bool partial;
-  int split, k_begin, k_end;
+  int k_begin, k_end;
+  float* sums;  // null, or where store_wave finds row 0, column 0 of the product for this workgroup's tile of sums
 };
 __device__ __forceinline__ TileWork tile_work(const GemmArgs& g, int bm, int bn) {
   const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.Nn + bn - 1) / bn;
@@ -126,19 +127,19 @@ __device__ __forceinline__ TileWork tile_work(const GemmArgs& g, int bm, int bn)
   int t;
   if (id < g.full) {
     t = xcd_spread(id, g.full);
-    w.partial = false;
-    w.split = 0;
+    w.sums = nullptr;
     w.k_begin = 0;
     w.k_end = g.Kk;
   } else {
     const int local = xcd_spread(id - g.full, g.tail * g.splits);
     t = g.full + local % g.tail;
-    w.partial = true;
-    w.split = local / g.tail;
-    w.k_begin = w.split * g.k_chunk;
+    w.k_begin = local / g.tail * g.k_chunk;
     w.k_end = min(g.Kk, w.k_begin + g.k_chunk);
   }
   tile_of(t, tiles_m, tiles_n, &w.tm, &w.tn);
+  if (id >= g.full)  // sums are stored tile after tile, in the order of the workgroups' tiles and splits
+    w.sums = g.partial + ((ptrdiff_t)(w.k_begin / g.k_chunk * g.tail + (t - g.full)) * bm - (ptrdiff_t)w.tm * bm) * bn -
+             (ptrdiff_t)w.tn * bn;
   return w;
 }
 

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __builtin_amdgcn_s_waitcnt(0x0070);  // nothing of mine is still on its way into LDS
   __syncthreads();  // the units are free: each wave turns its outputs to rows in one of its own
   store_wave<D, EPI, 4, 4>(g, acc, reinterpret_cast<float*>(smem + wave * kOperand), m0 + wm * 128,
-                           n0 + wn * (DUAL ? 64 : 128), w.partial, w.split, lane);
+                           n0 + wn * (DUAL ? 64 : 128), w.sums, BNO, lane);
 }
 
 template <class D, int EPI, bool BNN>

@@ -123,6 +123,27 @@ def test_decode_slices_leave_few_compute_units_idle(lib, gathered):
                         assert n == 256 // B or n % 8 == 0
 
 
+def test_dense_workspace_holds_the_sums_of_split_tiles_only(lib):
+    """At most a few rounds of 256 workgroups leave partial sums, whatever the product's size: 4096 x 9216 from 36864
+    (576 tiles of 256 x 256, 64 of them split in four) takes 67 MB beside the hidden matrix."""
+    import torch
+    b = ctypes.c_size_t(0)
+    for M, d, N in [(5, 4096, 16384), (77, 4096, 11008), (256, 4096, 16384), (700, 4096, 16384), (1024, 5120, 13824),
+                    (2090, 1024, 648), (4096, 9216, 36864), (8000, 9216, 36864), (65535, 8192, 28672)]:
+        assert lib.raw.coreinfer_ffn_dense_hidden_workspace_size(M, d, N, lib.CI_F16, ctypes.byref(b)) == lib.CI_OK
+        sums = b.value
+        assert 256 <= sums <= 8 * 256 * 256 * 256 * 4 + 256
+        if M == 4096:
+            assert sums == 64 * 4 * 256 * 256 * 4 + 256
+        hidden = -(-M * N * 4 // 256) * 256
+        assert lib.ffn_dense_workspace_size(M, d, N, torch.float16) == hidden + sums
+    r, F = lib.raw.coreinfer_ffn_dense, 0x10000
+    hidden = 256 * 16384 * 4
+    assert r(F, 256, F, None, None, F, None, 0, 1, 0, 4096, 16384, F, None, F, hidden + 255, None) == lib.CI_ERR_WORKSPACE
+    r = lib.raw.coreinfer_ffn_dense_hidden
+    assert r(F, 256, F, None, None, F, None, 0, 1, 0, 4096, 16384, F, F, F, 255, None) == lib.CI_ERR_WORKSPACE
+
+
 FAKE = 0x10000  # a non-null, 16-byte aligned address that is never dereferenced on these paths
 
 

@@ -1,5 +1,7 @@
 """The dense GEMM kernels at the sizes where a tile, a remainder or a split of the reduction can go
 wrong, against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -109,3 +111,64 @@ def test_dense_few_tokens_infinite_weight(lib):
     w_down[N - 1, 3] = float("inf")
     Y = lib.ffn_dense(X, w_up, None, None, w_down, None, "neuron_major", "relu", want_y=True, want_a=True)[0]
     assert bool(torch.isinf(Y[:, 3]).all()) and int(torch.isfinite(Y).sum()) == 2 * (d - 1)
+
+
+def _hidden_ws_size(lib, M, d, N):
+    b = ctypes.c_size_t(0)
+    assert lib.raw.coreinfer_ffn_dense_hidden_workspace_size(M, d, N, lib.CI_F16, ctypes.byref(b)) == lib.CI_OK
+    return b.value
+
+
+def _hidden_layer(M, d, N, dt):
+    w = rand_weights(d, N, dt, "relu", "neuron_major", seed=M, device=DEV)
+    X = torch.randn(M, d, generator=torch.Generator().manual_seed(d)).to(dt).to(DEV)
+    y = orc.ffn_relu(f64(X), None, f64(w["w_up"]), f64(w["b_up"]), down_out_major64(w, "neuron_major"), f64(w["b_down"]))
+    return w, X, y
+
+
+# workspaces with room for all sums of split tiles, for some of a plan of fewer splits, and for none
+@pytest.mark.parametrize("M,d,N", [(64, 1608, 1032), (300, 1152, 1032), (129, 264, 2056)])
+def test_dense_hidden_takes_what_room_there_is(lib, M, d, N):
+    w, X, y_ref = _hidden_layer(M, d, N, torch.float16)
+    size = _hidden_ws_size(lib, M, d, N)
+    for room in sorted({256, size // 2, size - 256, size, 4 * size}):
+        print("dense room case", M, d, N, room, "of", size, flush=True)
+        ws = torch.full((max(room, 256) + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+        Y, H = lib.ffn_dense_hidden(X, w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], "neuron_major", "relu",
+                                    ws=ws[:max(room, 256)])
+        torch.cuda.synchronize()
+        assert bool((ws[max(room, 256):] == 0xA5).all()), "stored past the workspace"
+        assert_close_rms(Y, y_ref, torch.float16, f"room {room}")
+
+
+def test_settings_that_change_during_a_call_stay_inside_its_workspace(lib):
+    """A development setting may be changed by another thread at any time: the plan a call's workspace was checked
+    for is the plan it runs."""
+    import threading
+    M, d, N = 64, 512, 2056
+    w, X, y_ref = _hidden_layer(M, d, N, torch.float16)
+    size = _hidden_ws_size(lib, M, d, N)
+    ws = torch.full((size + (1 << 20),), 0xA5, dtype=torch.uint8, device=DEV)
+    stop = threading.Event()
+
+    def flip():
+        i = 0
+        while not stop.is_set():
+            lib.dev_set_param("gemm_splits", i % 9)
+            lib.dev_set_param("gemm_tile", i % 6 - 1)
+            i += 1
+
+    t = threading.Thread(target=flip)
+    t.start()
+    try:
+        ys = [lib.ffn_dense_hidden(X, w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], "neuron_major", "relu",
+                                   ws=ws[:size])[0] for _ in range(200)]
+        torch.cuda.synchronize()
+    finally:
+        stop.set()
+        t.join()
+        lib.dev_set_param("gemm_splits", 0)
+        lib.dev_set_param("gemm_tile", -1)
+    assert bool((ws[size:] == 0xA5).all()), "stored past the workspace"
+    for y in ys:
+        assert_close_rms(y, y_ref, torch.float16, "while settings change")
