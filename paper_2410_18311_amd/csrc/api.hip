@@ -482,7 +482,7 @@ int coreinfer_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int 
   if (!aligned16(ws)) return CI_ERR_BAD_LAYOUT;
   if (w->down_layout == CI_DOWN_OUT_MAJOR && w->K > 0)
     return launch_ffn_decode_fused(x, B, w, dtype, act, y, ws, (hipStream_t)stream);
-  return launch_ffn_decode(x, B, w, dtype, act, y, reinterpret_cast<float*>(ws), (hipStream_t)stream);
+  return launch_ffn_decode(x, B, w, dtype, act, y, reinterpret_cast<float*>(ws), kMaxSplits, (hipStream_t)stream);
 }
 
 int coreinfer_ffn_decode_static(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
@@ -500,7 +500,8 @@ int coreinfer_ffn_decode_static(const void* x, int64_t B, const ci_ffn_weights* 
   if (rs != CI_OK) return rs;
   hipStream_t s = (hipStream_t)stream;
   if (!single) {
-    const int rl = launch_ffn_decode(x, B, w, dtype, act, y, reinterpret_cast<float*>(base + kStaticWords), s);
+    const int room = (int)std::min<size_t>(kMaxSplits, kStaticPartial / ((size_t)B * (size_t)w->d * sizeof(float)));
+    const int rl = launch_ffn_decode(x, B, w, dtype, act, y, reinterpret_cast<float*>(base + kStaticWords), room, s);
     if (rl != CI_OK || !status_out) return rl;
     // the two-launch path has no bounded waits: nothing to report.  A copy, not a memset: callers may
     // be under graph capture, and base + 8 is a word of the header that no kernel writes.
@@ -649,7 +650,7 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
       w.w_up = w_up; w.w_gate = w_gate; w.b_up = b_up; w.w_down = w_down; w.b_down = b_down;
       w.core_idx = nullptr; w.K = N; w.d = d; w.N = N;
       w.ld_down = 0; w.down_layout = CI_DOWN_NEURON_MAJOR;
-      return launch_ffn_decode(X, M, &w, dtype, act, Y, partial, s);
+      return launch_ffn_decode(X, M, &w, dtype, act, Y, partial, kMaxSplits, s);
     }
     int rc = launch_up_rows(X, M, w_up, w_gate, b_up, dtype, act, d, N, Y ? H : nullptr, A, s);
     if (rc != CI_OK || !Y) return rc;

@@ -217,8 +217,9 @@ int launch_compact_update(const void* w_up, const void* w_gate, const void* b_up
                           void* w_down_c, int down_c_layout, int32_t* changed, uint32_t* ws, hipStream_t s);
 int decode_splits(int64_t B, int64_t K, int64_t row_bytes, bool gathered);
 int decode_splits_bound(int64_t B, int64_t K);  // at least decode_splits; what scratch limits are stated in
+// max_slices: how many slices per sentence the partial sums have room for
 int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
-                      void* y, float* partial, hipStream_t s);
+                      void* y, float* partial, int max_slices, hipStream_t s);
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
                          int dtype, hipStream_t s);
 size_t fused_decode_ws_bytes(int64_t K);
@@ -229,12 +230,21 @@ int union_up_chunks(int64_t vecs);
 int launch_union_build(const int32_t* core_idx, int64_t B, int64_t K, int64_t N, int64_t cap,
                        int32_t* uidx, uint32_t* umask, int32_t* ucount, uint32_t* owners, uint32_t* dup,
                        hipStream_t s);
+// dup, n_down: of a gathered decode (its count of repeated entries, its slices of the down phase), else NULL and 0
 int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, const int32_t* uidx,
                             const uint32_t* umask, const int32_t* ucount, int64_t cap, int dtype,
-                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup = nullptr);
-bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act);
+                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup = nullptr, int n_down = 0);
+// Scratch of a gathered decode that goes through the union of its lists, in 4-byte words from the start: hidden
+// values, partial outputs, then owner masks with dup right behind them, then the row list.  Made once per call: what is
+// checked against the scratch is what runs.
+struct GatheredUnion {
+  size_t partial, owners, dup, uidx, umask, ucount, total;
+  int64_t cap;
+  int n_down;  // slices of the down phase
+};
+bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act, GatheredUnion* plan);
 int launch_gathered_union(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, float* ws,
-                          hipStream_t s);
+                          const GatheredUnion& plan, hipStream_t s);
 // h[M, N] fp32 = act(X w^T ...) and y = W h + b by row-dot GEMVs (small M).
 int launch_up_rows(const void* X, int64_t M, const void* w_up, const void* w_gate, const void* b_up,
                    int dtype, int act, int64_t d, int64_t N, float* H, float* A, hipStream_t s);

@@ -482,9 +482,10 @@ int launch_decode_reduce(const float* partial, const void* b_down, void* y, int 
 }
 
 int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
-                      void* y, float* partial, hipStream_t s) {
-  if (w->core_idx && gathered_union_pays(B, w->K, w->N, w->d, dtype, act))
-    return launch_gathered_union(x, B, w, dtype, act, y, partial, s);
+                      void* y, float* partial, int max_slices, hipStream_t s) {
+  GatheredUnion plan;
+  if (w->core_idx && gathered_union_pays(B, w->K, w->N, w->d, dtype, act, &plan))
+    return launch_gathered_union(x, B, w, dtype, act, y, partial, plan, s);
   DecodeArgs a;
   a.x = x;
   a.w_up = w->w_up;
@@ -497,6 +498,7 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   a.d = (int)w->d;
   a.N = (int)w->N;
   a.n_wg = decode_splits(B, w->K, w->d * (dtype == CI_F32 ? 4 : 2), w->core_idx != nullptr);
+  if (a.n_wg > max_slices) a.n_wg = max_slices;
   a.nt_store = params().decode_nt_store;
   switch (dtype) {
     case CI_F32: return launch_dtype<F32>(a, (int)B, act, w->b_down, y, s);

@@ -532,19 +532,14 @@ int chip_cus() {
   return device_info(&di) == CI_OK ? di.cus : 256;
 }
 
-// Scratch of a gathered decode that goes through the union of its lists, in 4-byte words from the start:
-// hidden values, partial outputs, then owner masks with dup right behind them, then the row list.
-struct GatheredUnion {
-  size_t partial, owners, dup, uidx, umask, ucount, total;
-  int64_t cap;
-};
 GatheredUnion gathered_union_layout(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act) {
   GatheredUnion g;
   auto up64 = [](size_t n) { return (n + 63) / 64 * 64; };
   const int64_t vecs = d / (dtype == CI_F32 ? 4 : 8);
   g.cap = B * K < N ? B * K : N;
   g.partial = up64((size_t)union_up_chunks(vecs) * (act == CI_ACT_SWIGLU ? 2 : 1) * (size_t)g.cap * SB);
-  g.owners = g.partial + up64((size_t)B * down_slices(vecs, g.cap, chip_cus()) * (size_t)d);
+  g.n_down = down_slices(vecs, g.cap, chip_cus());
+  g.owners = g.partial + up64((size_t)B * g.n_down * (size_t)d);
   g.dup = g.owners + up64((size_t)N) + 1024;  // 1024: counts per block of union_place_kernel
   g.uidx = g.dup + up64(1 + (size_t)N * SB);
   g.umask = g.uidx + up64((size_t)g.cap);
@@ -564,10 +559,11 @@ GatheredUnion gathered_union_layout(int64_t B, int64_t K, int64_t N, int64_t d, 
 // 8 at 0.2 95 / 100, 4 at 0.4 94 / 98 (stay separate); 16384 x 4096 ReLU: 8 at 0.3 87 / 67, 8 at 0.2 60 / 63 (stays);
 // 3840 x 1280: separate throughout (15 / 28).  Its scratch has to fit what both gathered entry points offer for any
 // such call: the workspace by its published size, and the 16 MiB of library scratch.
-bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act) {
+bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, int act, GatheredUnion* plan) {
   if (params().gathered_union == 0 || B < 2 || B > SB || K < 1 || K > N) return false;
   if (d / (dtype == CI_F32 ? 4 : 8) > 4096) return false;  // wider rows are turned down by the gathered kernel, and stay so
-  const size_t bytes = gathered_union_layout(B, K, N, d, dtype, act).total * 4;
+  *plan = gathered_union_layout(B, K, N, d, dtype, act);
+  const size_t bytes = plan->total * 4;
   const size_t ws = (size_t)B * (size_t)(K < 1024 ? K : 1024) * (size_t)d * sizeof(float);
   if (bytes > ws || bytes > ((size_t)16 << 20)) return false;
   if (params().gathered_union == 2) return true;
@@ -580,20 +576,19 @@ bool gathered_union_pays(int64_t B, int64_t K, int64_t N, int64_t d, int dtype, 
 }
 
 int launch_gathered_union(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, float* ws,
-                          hipStream_t s) {
-  const GatheredUnion g = gathered_union_layout(B, w->K, w->N, w->d, dtype, act);
+                          const GatheredUnion& g, hipStream_t s) {
   uint32_t* base = reinterpret_cast<uint32_t*>(ws);
   int32_t* uidx = reinterpret_cast<int32_t*>(base + g.uidx);
   int32_t* ucount = reinterpret_cast<int32_t*>(base + g.ucount);
   const int rc = launch_union_build(w->core_idx, B, w->K, w->N, g.cap, uidx, base + g.umask, ucount, base + g.owners,
                                     base + g.dup, s);
   if (rc != CI_OK) return rc;
-  return launch_ffn_decode_union(x, B, w, uidx, base + g.umask, ucount, g.cap, dtype, act, y, ws, s, base + g.dup);
+  return launch_ffn_decode_union(x, B, w, uidx, base + g.umask, ucount, g.cap, dtype, act, y, ws, s, base + g.dup, g.n_down);
 }
 
 int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, const int32_t* uidx,
                             const uint32_t* umask, const int32_t* ucount, int64_t cap, int dtype,
-                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup) {
+                            int act, void* y, float* ws, hipStream_t s, const uint32_t* dup, int n_down) {
   UnionArgs a;
   a.dup = dup;
   a.x = x;
@@ -626,7 +621,7 @@ int launch_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w, c
   if (t_down < 64) t_down = 64;
   if (t_down > 512) t_down = 512;
   a.c_down = (a.vecs + 63) / 64;
-  a.n_down = down_slices(a.vecs, a.cap, cus);
+  a.n_down = n_down > 0 ? n_down : down_slices(a.vecs, a.cap, cus);
   // up phase: about 384 threads per compute unit (at d = 4096 the two waves of four vectors per lane that a
   // workgroup has were alone on theirs: 36 us for 13650 rows, now 25)
   a.n_up = cus * params().union_up_wgs_per_cu * ((384 + t_up / 2) / t_up > 1 ? (384 + t_up / 2) / t_up : 1) / a.c_up;

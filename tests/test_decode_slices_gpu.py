@@ -22,11 +22,11 @@ def test_decode_of_many_sentences(lib, d, dt, B, gathered):
     x = torch.randn(B, d, generator=torch.Generator().manual_seed(B)).to(dt).to(DEV)
     if gathered:
         sets = np.stack([np.sort(rng.permutation(N)[:K]) for _ in range(B)]).astype(np.int32)
-        desc = lib.make_weights(w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], core_idx=torch.from_numpy(sets).to(DEV))
+        idx = torch.from_numpy(sets).to(DEV)     # a descriptor holds addresses only
+        desc = lib.make_weights(w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], core_idx=idx)
     else:
         sets = np.tile(np.arange(K, dtype=np.int32), (B, 1))
-        desc = lib.make_weights(w["w_up"][:K].contiguous(), None, w["b_up"][:K].contiguous(), w["w_down"][:K].contiguous(),
-                                w["b_down"])
+        desc = lib.make_weights(w["w_up"][:K], None, w["b_up"][:K], w["w_down"][:K], w["b_down"])   # the first K rows
     y = lib.ffn_decode(x, desc, "relu")
     torch.cuda.synchronize()
     Wd = down_out_major64(w, "neuron_major")

@@ -83,3 +83,51 @@ def test_repeated_and_invalid_entries_count_as_before(lib):
         rms = np.sqrt(np.mean(ref ** 2))
         for y in out:
             assert np.max(np.abs(y[b] - ref)) <= 1e-5 * rms
+
+
+@pytest.mark.parametrize("knob,values", [("union_down_wgs_per_cu", (1, 16)), ("gathered_union", (0, 2)), ("decode_wgs", (16, 1024))])
+def test_settings_that_change_during_a_call_stay_inside_its_scratch(lib, knob, values):
+    """A development setting may be changed by another thread at any time: the slices that a call's scratch was laid
+    out or checked for are the slices it runs.  (The library's own scratch turns a call down where they do not fit.)"""
+    import threading
+    d, N, K, B, dt = 4096, 12000, 6000, 4, torch.float16
+    w = rand_weights(d, N, dt, "relu", "neuron_major", seed=9, device=DEV)
+    rng = np.random.default_rng(4)
+    sets = np.stack([np.sort(rng.permutation(N)[:K]) for _ in range(B)]).astype(np.int32)
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(2)).to(dt).to(DEV)
+    idx = torch.from_numpy(sets).to(DEV)     # a descriptor holds addresses only
+    desc = lib.make_weights(w["w_up"], None, w["b_up"], w["w_down"], w["b_down"], core_idx=idx)
+    size = lib.ffn_decode_workspace_size(B, K, d)
+    ws = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    stop = threading.Event()
+
+    def flip():
+        i = 0
+        while not stop.is_set():
+            lib.dev_set_param(knob, values[i % 2])
+            i += 1
+
+    lib.dev_set_param("gathered_union", 0 if knob == "decode_wgs" else 2)
+    t = threading.Thread(target=flip)
+    t.start()
+    ys, refused = [], 0
+    try:
+        for _ in range(60):
+            ys.append(lib.ffn_decode(x, desc, "relu", ws=ws[:size]))
+            try:
+                ys.append(lib.ffn_decode_static(x, desc, "relu"))
+            except lib.CoreInferError as e:
+                assert e.status == lib.CI_ERR_WORKSPACE
+                refused += 1
+        torch.cuda.synchronize()
+    finally:
+        stop.set()
+        t.join()
+        for name, default in (("union_down_wgs_per_cu", 1), ("gathered_union", 1), ("decode_wgs", 0)):
+            lib.dev_set_param(name, default)
+    assert bool((ws[size:] == 0xA5).all()), "stored past the workspace"
+    assert refused == 0 or knob == "decode_wgs"
+    refs = [_reference("relu", x[b], sets[b].astype(np.int64), w) for b in range(B)]
+    for y in ys:
+        for b in range(B):
+            assert_close_rms(y[b], refs[b], dt, f"sentence {b}")
