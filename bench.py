@@ -8,10 +8,11 @@ Inputs are resident in HBM before the timed region.
 
 A run with no --workload times every workload of the build -- the Llama-2-13B
 shape at each of its four keep fractions, the OPT-6.7B and Llama-2-7B shapes
-and the OPT-66B shape with eight sentences -- and prints ONE JSON line: its
-top-level fields are the Llama-2-13B shape at its first keep fraction (timed
-with --steps / --warmup), `workloads` carries the same fields for the others
-(at fewer steps, stated in each record).
+and the OPT-66B shape with eight sentences -- and prints ONE short JSON line on
+stdout: its top-level fields are the Llama-2-13B shape at its first keep fraction
+(timed with --steps / --warmup), `workloads` has the main figures of the others
+(at fewer steps, stated in each).  Everything that was measured goes to stderr, one
+JSON line per workload, and to --details FILE as one document.
 
     python bench.py --gpus 1 --steps 20 --warmup 5
     python bench.py --workload opt6.7b_relu_f16 [--beta 0.4] [--layers 8] ...
@@ -50,6 +51,7 @@ def parse_args():
                    help="layout of the compact down matrix (auto: the library's preference for the shape)")
     p.add_argument("--no-graph", action="store_true", help="launch decode kernels directly instead of a HIP graph")
     p.add_argument("--kernel-reps", type=int, default=20, help="replays of the kernel-only timing graph")
+    p.add_argument("--details", default=None, metavar="FILE", help="write the full records of all workloads here")
     p.add_argument("--cpu-seconds", type=float, default=12.0, help="oracle time of the top-level cpu_baseline sample")
     return p.parse_args()
 
@@ -494,6 +496,33 @@ def run_workload(inp: Inputs, beta: float, steps: int, warmup: int, args, cpu_se
     }
 
 
+def short(x, digits=5):
+    """Figures of the printed line: five digits."""
+    return float(f"{x:.{digits}g}") if isinstance(x, float) else x
+
+
+def printed_line(top: dict, others) -> dict:
+    """The line on stdout: the fields that name and time the headline workload, and the main figures of the rest.  Kept
+    short (a reader of the last two thousand characters of the output has to find all of it)."""
+    keys = ("metric", "value", "unit", "steps", "warmup", "ms_per_step", "dtype", "config")
+    out = {k: top[k] for k in keys}
+    out.update({"n_gpus": 1, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "data": "synthetic"})
+    roof = top["roofline"]
+    out["roofline"] = {k: short(roof[k]) for k in ("bound", "achieved", "peak", "unit", "frac", "us_per_launch")}
+    out["select_us_per_layer"] = short(top["select_us_per_layer"])
+    out["dense_prefill_tflops"] = short(top["dense_prefill_tflops"])
+    if top["parity"] is not None:
+        out["parity"] = {"core_set_bit_exact": top["parity"]["core_set_bit_exact"],
+                         "decode_max_abs_err_over_rms": short(top["parity"]["decode_max_abs_err_over_rms"], 2)}
+    if top["cpu_baseline"] is not None:
+        out["cpu_baseline"] = {k: short(top["cpu_baseline"][k], 3) for k in ("value", "unit", "cores", "kind")}
+    if others is not None:
+        out["workloads"] = [{"workload": o["config"]["workload"], "beta": o["config"]["beta"], "steps": o["steps"],
+                             "tokens_per_s": short(o["value"]), "ms_per_step": short(o["ms_per_step"]),
+                             "prefill_tflops": short(o["dense_prefill_tflops"], 4)} for o in others]
+    return out
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -551,11 +580,12 @@ def main():
             torch.cuda.empty_cache()
         note(f"done in {time.perf_counter() - t_start:.0f} s")
 
-    out = dict(top)
-    out.update({"n_gpus": 1, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "data": "synthetic"})
-    if others is not None:
-        out["workloads"] = others
-    print(json.dumps(out))
+    for record in [top] + (others or []):
+        print(json.dumps(record), file=sys.stderr, flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump([top] + (others or []), f, indent=1)
+    print(json.dumps(printed_line(top, others)))
 
 
 if __name__ == "__main__":

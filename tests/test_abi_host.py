@@ -531,3 +531,36 @@ def test_bench_line_fields_are_built_from_the_documented_pieces():
     assert bench.read_traffic_note("opt6.7b_relu_f16", 0.4, 107410228) is not None
     assert bench.read_traffic_note("opt6.7b_relu_f16", 0.4, 2 * 107410228) is None
     assert bench.read_traffic_note("no_such_workload", 0.4, 1) is None
+
+
+def test_bench_prints_one_short_line_with_every_field_of_its_contract():
+    import importlib.util
+    import json
+    spec = importlib.util.spec_from_file_location("bench_module", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    x = 12345.678901234567
+
+    def record(name, beta):
+        return {"metric": "decode_sparse_ffn_tokens_per_s", "value": x, "unit": "tokens/s", "steps": 20, "warmup": 5,
+                "ms_per_step": x, "dtype": "bf16",
+                "config": {"workload": name, "act": "swiglu", "d_model": 5120, "d_ff": 13824, "layers": 40,
+                           "prefill_tokens": 1024, "decode_tokens": 256, "sentences": 1, "alpha": 0.2, "beta": beta,
+                           "core_neurons": 13824, "decode_mode": "compacted, w_down_c neuron_major",
+                           "decode_launch": "hip_graph_per_token",
+                           "value_definition": "decode tokens of a step / GPU time of the step's decode phase (HIP events)"},
+                "roofline": {"kernel": "k" * 200, "bound": "hbm", "achieved": x, "peak": 8000.0, "unit": "GB/s", "frac": x / 3e4,
+                             "traffic": None, "bytes_per_launch": 1 << 40, "us_per_launch": x, "note": "n" * 400},
+                "select_us_per_layer": x, "dense_prefill_tflops": x,
+                "parity": {"core_set_bit_exact": True, "decode_max_abs_err_over_rms": x, "layers": list(range(99))},
+                "cpu_baseline": {"value": x, "unit": "tokens/s", "cores": 256, "kind": "oracle", "sample": "s" * 300}}
+    others = [record(n, 0.2 if b is None else b) for n, b, _, _ in bench.OTHER_WORKLOADS]
+    line = json.dumps(bench.printed_line(record(bench.TOP_WORKLOAD, 0.2), others))
+    assert "\n" not in line and len(line) < 2000, len(line)
+    got = json.loads(line)
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config"):
+        assert key in got
+    assert got["value"] == x and got["ms_per_step"] == x and len(got["workloads"]) == len(bench.OTHER_WORKLOADS)
+    alone = bench.printed_line({**record(bench.TOP_WORKLOAD, 0.2), "parity": None, "cpu_baseline": None}, None)
+    assert "workloads" not in alone and "parity" not in alone
