@@ -120,6 +120,7 @@ int coreinfer_dev_set_param(const char* name, int value) {
   else if (!strcmp(name, "fused_window_slots") && value >= 0 && value <= 1000) p.fused_window_slots = value;
   else if (!strcmp(name, "fused_ablate") && value >= 0 && value <= 2) p.fused_ablate = value;
   else if (!strcmp(name, "fused_aux") && (value == -1 || value == -2 || value == 0 || value == 16)) p.fused_aux = value;
+  else if (!strcmp(name, "select_bytes") && value >= 0 && value <= 2) p.select_bytes = value;
   else if (!strcmp(name, "select_def2_single") && (value == 0 || value == 1)) p.select_def2_single = value;
   else if (!strcmp(name, "select_wgs_per_cu") && value >= 1 && value <= 8) p.select_wgs_per_cu = value;
   else if (!strcmp(name, "gemm_ring") && (value == 0 || value == 1)) p.gemm_ring = value;

@@ -123,6 +123,7 @@ struct Params {
   Knob decode_threads{0};    // 0 = derived from d
   Knob decode_depth{4};      // weight rows in flight per thread (4, 8 or 16)
   Knob select_wgs_per_cu{2};
+  Knob select_bytes{1};        // byte counts of the per-token kernel: 0 never, 1 by the rule, 2 wherever they can be
   Knob select_def2_single{0};  // Def. 2 in one workgroup even where the parallel kernel applies
   Knob gemv_wgs_per_cu{8};
   Knob gemv_cols_wgs_per_cu{1};

@@ -23,6 +23,8 @@
  *   scope), "fused_ablate" (timing builds only): single-launch decode;
  *   "select_wgs_per_cu" (1..8; 1 keeps the per-token kernel at one workgroup per
  *   compute unit also for prompts longer than the chip has compute units),
+ *   "select_bytes" (0 never, 1 by the rule, 2 wherever they can be: byte counts
+ *   of the per-token kernel instead of a second pass over the activations),
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
  *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4), "gemm_ring", "gemm_direct" (0/1: either 0

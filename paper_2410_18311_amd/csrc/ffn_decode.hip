@@ -460,10 +460,11 @@ int decode_splits_bound(int64_t B, int64_t K) {
 // from 8192 on (6144 bytes, 33 sentences gathered: 8 slices 1.16 times faster than 7).
 int decode_splits(int64_t B, int64_t K, int64_t row_bytes, bool gathered) {
   const int n = decode_splits_bound(B, K);
+  if (B == 1 || params().decode_wgs > 0) return n;
   DeviceInfo di;
   const int64_t cus = device_info(&di) == CI_OK ? di.cus : 256;
   const int64_t whole = cus * params().decode_wgs_per_cu / B;  // slices with at most that many workgroups per compute unit
-  if (params().decode_wgs > 0 || whole < 1 || whole >= n) return n;  // B == 1 among them
+  if (whole < 1 || whole >= n) return n;
   const int64_t eights = whole / 8 * 8;
   const bool wide = row_bytes >= 8192;
   if (row_bytes < 6144) return !gathered && row_bytes >= 4096 && eights * 6 >= n * 5 ? (int)eights : n;

@@ -33,8 +33,8 @@
 //     instead of every activation again (1024 x 13824 fp32 scores: 7 MB instead of
 //     57 MB read, counting 13.0 -> 4.5 us, the
 //     per-token kernel 24.4 -> 26.3 us).
-// count_kernel -- Eq. 3 where there are no such bytes (middling sizes, see
-//     launch_tokens; rows of more than 40960 neurons, more than 64 sentences).
+// count_kernel -- Eq. 3 where there are no such bytes (see byte_counts_pay; rows
+//     of more than 40960 neurons, more than 64 sentences).
 //     Counting is then a second pass over the activations by neuron: a workgroup owns 64 neurons (256 when that still gives more
 //     workgroups than half the compute units), walks all tokens, compares every
 //     activation with its token's (T, cut) and keeps the tallies in registers
@@ -1024,6 +1024,33 @@ int launch_threshold(const typename IN::T* act, int M, int N, int64_t ld, int64_
   return CI_OK;
 }
 
+// Whether the per-token kernel leaves byte counts, so that the activations need not be read again.  They cost it 1 to 2
+// us, and, as each workgroup then has one sentence's tokens only, sometimes a round of tokens more (rounds, rounds_part:
+// without and with them).  Measured, counting kernel / byte counts (us):
+//  - rows of fewer than 4096 neurons fill a row of byte counts (words of four neurons, 1024 apart) badly: one or two
+//    sentences 113 / 57 (4096 x 1024), 17 / 16 (32 x 1024); from three on 17.8 / 19.7 (12 x 33 x 1024), 19 / 29 (64 x 4 x 1024),
+//    but for few tokens in all (14.1 / 13.6, 3 x 11 x 1024) and for many each (96 / 87, 24 x 256 x 3072);
+//  - a counting kernel of 64 neurons per workgroup takes two rounds once it has more workgroups than there are compute units:
+//    21.2 / 18.5 (5 x 64 x 4096), 27.7 / 25.3 (256 x 22016), 23.4 / 20.7 (2 x 128 x 16384); with loads of one element
+//    it is slower still: 27.5 / 24.9 (300 x 13825; few tokens of many sentences 43 / 49, 64 x 4 x 4097);
+//  - several rounds of tokens make the second pass long: one sentence from two on (1024 x 13824 39.4 / 34.2, 1024 x 11008 fp16
+//    39.8 / 36.8), more from four on (8 x 512 x 16384 96 / 73), or from two where it misses the caches (8 x 128 x 11008
+//    0.89, but 3 x 256 x 11008, 34 MB, 31.7 / 34.8);
+//  - one round of tokens, all in cache, is a matter of latency: at most 8192 neurons, or 100 tokens, 3 to 6 % faster;
+//    128 to 512 tokens of 11008 to 16384 neurons 2 to 8 % slower; above 32768 neurons (keys of nine or ten registers of
+//    counts) 25.9 / 27.9 (1 x 36864), from 256 tokens on faster (512 x 36864 fp16 58.0 / 51.6).
+bool byte_counts_pay(int64_t B, int64_t M, int64_t N, size_t bytes, bool vec_ok, int rounds, int rounds_part, int cus) {
+  const bool few = B * M <= 100;
+  if (B > 2 && N < 4096) return (B <= 5 && few) || (N >= 2048 && M >= 256 && rounds >= 4);
+  if (!vec_ok && (B <= 2 || M >= 32 || N > 8 * kThreads || (B <= 5 && few))) return true;
+  if (B > 2 && M >= 64 && bytes >= ((size_t)40 << 20) && rounds >= 2 && (rounds_part == rounds || M >= 512)) return true;
+  if (rounds_part * 5 > rounds * 6) return false;
+  const int64_t blocks = (N + 255) / 256 * B;  // of the counting kernel; with 64 neurons each up to half a chip full of them
+  if ((blocks <= cus / 2 && 4 * blocks > cus) || rounds >= (B <= 2 ? 2 : 4)) return true;
+  if (N > 32 * kThreads) return B <= 2 && B * M >= cus;
+  return B <= 2 && (N <= 8 * kThreads || few);
+}
+
 // Def. 1 and Eq. 3 for an activation matrix of element type IN::T.  The fp32 path has a kernel for
 // every keys-per-thread step; the 16-bit types share three of them (16, 40, streaming).
 template <class IN>
@@ -1041,23 +1068,17 @@ int launch_tokens(const void* act_v, int B, int M_each, int N, int64_t ld, int64
   // four activations per load of the counting kernel: 16 bytes of fp32 or 8 bytes of a 16-bit type
   const uintptr_t quad = 4 * sizeof(TI);
   const int vec_ok = ((reinterpret_cast<uintptr_t>(act) & (quad - 1)) == 0 && ld % 4 == 0) ? 1 : 0;
-  // Byte counts cost the per-token kernel 1 to 2 us and save reading the activations again: worth it where those
-  // are many (1024 x 13824 fp32 39.4 -> 34.2 us, 512 x 36864 fp16 58.0 -> 51.6) or come in loads of one element
-  // (300 x 13825 27.5 -> 24.9), and where the second pass is all latency (32 x 1024 13.7 -> 12.8); in between it is
-  // in cache and its loads are wide (512 x 11008 fp32 24.9 against 25.5 us, fp16 25.2 against 27.0).
-  const size_t act_bytes = (size_t)M * (size_t)N * sizeof(TI);
-  if (vec_ok && act_bytes > ((size_t)2 << 20) && act_bytes < ((size_t)24 << 20)) part = nullptr;
-  int wgs = cus * (two ? 2 : 1);
-  if (part && wgs > kPartRows) wgs = kPartRows;
-  // workgroups per sentence when they leave byte counts (each has one sentence's tokens only); else the
-  // rows of all sentences are alike
-  int per = part ? wgs / B : wgs;
-  if (per > (part ? M_each : M)) per = part ? M_each : M;
-  if (per < 1) per = 1;
-  if (part && (M_each + per - 1) / per > 255) {  // a byte would not hold the counts
+  const int wgs = cus * (two ? 2 : 1);
+  const int flat = wgs > M ? M : wgs;  // workgroups without byte counts: the rows of all sentences are alike
+  // with them, each workgroup has one sentence's tokens only, at most as many as a byte counts
+  int per = (wgs > kPartRows ? kPartRows : wgs) / B;
+  per = per < 1 ? 1 : (per > M_each ? M_each : per);
+  const int rounds = (M + flat - 1) / flat, rounds_part = (M_each + per - 1) / per;
+  const int mode = params().select_bytes;
+  if (mode == 0 || rounds_part > 255 ||
+      (mode == 1 && !byte_counts_pay(B, M_each, N, (size_t)M * (size_t)N * sizeof(TI), vec_ok, rounds, rounds_part, cus)))
     part = nullptr;
-    per = wgs > M ? M : wgs;
-  }
+  if (!part) per = flat;
   const dim3 grid((unsigned)per, (unsigned)(part ? B : 1));
   const int rows_each = part ? M_each : M;
   int rc = CI_OK;

@@ -11,12 +11,21 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+# every test here with byte counts wherever they can be, with none, and by the rule
+@pytest.fixture(params=[2, 0, 1], ids=["bytes", "second_pass", "rule"], autouse=True)
+def _mode(request, lib):
+    lib.dev_set_param("select_bytes", request.param)
+    yield
+    lib.dev_set_param("select_bytes", 1)
+
+
 # one neuron; one past a multiple of 4096 (a new register of counts); a workgroup with one and with several
 # tokens; 64 sentences of 2045 tokens = 256 tokens for each of 8 workgroups (one more than a byte holds, so the
-# counting kernel over the activations runs) and 2040 (255: the most a byte holds); 65 sentences and 40961 neurons
+# counting kernel over the activations runs) and 2040 (255: the most a byte holds; one sentence of the most tokens
+# a call takes: 128 a workgroup, sums near the end of their 16-bit fields); 65 sentences and 40961 neurons
 # (no byte counts); 36869 neurons (nine registers and five neurons)
 @pytest.mark.parametrize("B,M,N,levels", [(1, 1, 1, 0), (1, 3, 4097, 0), (3, 130, 5000, 6), (1, 700, 16384, 0),
-                                          (64, 2045, 12, 3), (64, 2040, 12, 3), (65, 9, 40, 0), (1, 20, 40961, 0),
+                                          (64, 2045, 12, 3), (64, 2040, 12, 3), (1, 65535, 12, 3), (65, 9, 40, 0), (1, 20, 40961, 0),
                                           (1, 300, 36869, 5), (1, 513, 2048, 1)])
 @pytest.mark.parametrize("kind", ["relu", "abs"])
 def test_counts_of_all_sentences(lib, B, M, N, levels, kind):
