@@ -604,13 +604,17 @@ int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtyp
 
 // Up to four tokens over neuron-major weights: hidden values first, then the down rows, each weight read once;
 // or the decode kernel with all neurons as the core set, which reads the weights once per token and, for the
-// scores, the up matrices once more.  The latter has one launch fewer where no scores are asked for: a single
-// token, two below 200 MB (2048 x 8192 fp32 30 against 36 us; 4096 x 16384 fp16 55 against 48), three and four
-// below 8 MB.  (Rows that the decode kernel does not take are refused in either case.)
+// scores, the up matrices once more.  The latter has shorter launches, and one fewer where no scores are asked for.
+// With scores it stays for one token below 60 MB (1024 x 4096 fp32, 34 MB: 14.8 against 20.3 us; 4096 x 16384 fp16,
+// 268 MB: 94 / 48 at two tokens), two below 9 MB, three and four below 3 MB (256 x 1024 fp32 12.1 / 13.0); without them for
+// a single token, two below 200 MB (2048 x 8192 fp32 30 against 36 us; 4096 x 16384 fp16 55 against 48), three
+// and four below 12 MB (512 x 2048 fp32 13.2 / 14.5).  (Rows that the decode kernel does not take are refused in
+// either case.)
 static bool dense_cols_pays(int64_t M, int64_t d, int64_t N, int dtype, int act, bool scores) {
   if (d / vec_of(dtype) > 4096) return false;
   const double bytes = (double)(act == CI_ACT_SWIGLU ? 3 : 2) * (double)d * (double)N * (double)elem_bytes(dtype);
-  return scores || (M == 2 && bytes >= 200e6) || (M > 2 && bytes >= 8e6);
+  if (scores) return bytes >= (M == 1 ? 60e6 : (M == 2 ? 9e6 : 3e6));
+  return M > 1 && bytes >= (M == 2 ? 200e6 : 12e6);
 }
 
 int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* w_gate,

@@ -9,6 +9,9 @@
 // Measured, scores and output, before (a pass over the weights per token) and now: 4096 x 16384 fp16, 2 tokens 81 ->
 // 55 us, 4 tokens 155 -> 73; neuron-major 94 -> 48 and 173 -> 54 (the read alone 43); 5120 x 13824 gated bf16, 4 tokens
 // 249 -> 93 (67).
+// Weights that a cache holds many times over are read once per token instead, by workgroups of its own (grid.y): with
+// so few rows a call is a chain of latencies, and several tokens' reductions in one workgroup make it longer (see
+// kPerTokenBytes).
 // The row kernels: a workgroup owns a contiguous slice of groups of output rows; its threads
 // split the reduction dimension with 16-byte loads, reduce by wave shuffles and then
 // across waves through LDS (two buffers: one barrier per group).
@@ -36,7 +39,9 @@ __global__ __launch_bounds__(256) void up_rows_kernel(const void* __restrict__ X
   const int n_grp = (N + RC - 1) / RC;
   const int g0 = (int)(((int64_t)blockIdx.x * n_grp) / gridDim.x);
   const int g1 = (int)(((int64_t)(blockIdx.x + 1) * n_grp) / gridDim.x);
-  const T* x = reinterpret_cast<const T*>(X);
+  const T* x = reinterpret_cast<const T*>(X) + (size_t)blockIdx.y * MT * d;  // the tokens of this workgroup
+  if (H) H += (size_t)blockIdx.y * MT * N;
+  if (A) A += (size_t)blockIdx.y * MT * N;
   const T* wu = reinterpret_cast<const T*>(w_up);
   const T* wg = reinterpret_cast<const T*>(w_gate);
 
@@ -114,6 +119,8 @@ __global__ __launch_bounds__(256) void down_rows_kernel(const float* __restrict_
   const int g0 = (int)(((int64_t)blockIdx.x * n_grp) / gridDim.x);
   const int g1 = (int)(((int64_t)(blockIdx.x + 1) * n_grp) / gridDim.x);
   const T* w = reinterpret_cast<const T*>(w_down);
+  H += (size_t)blockIdx.y * MT * N;  // the tokens of this workgroup
+  T* y_out = reinterpret_cast<T*>(Y) + (size_t)blockIdx.y * MT * d;
 
   for (int g = g0; g < g1; ++g) {
     const int rb = g * RD;
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(256) void down_rows_kernel(const float* __restrict_
       const int m = tid / RD, r = rb + tid % RD;
       float y = red[buf][0][tid] + red[buf][1][tid] + red[buf][2][tid] + red[buf][3][tid];
       if (b_down) y += to_float<D>(reinterpret_cast<const T*>(b_down)[r]);
-      reinterpret_cast<T*>(Y)[(size_t)m * d + r] = from_float<D>(y);
+      y_out[(size_t)m * d + r] = from_float<D>(y);
     }
   }
 }
@@ -255,8 +262,8 @@ int row_grid(int64_t rows, int rc) {
 
 template <class D, int MT>
 int up_tokens(const void* X, const void* w_up, const void* w_gate, const void* b_up, int act, int d, int N, float* H,
-              float* A, hipStream_t s) {
-  dim3 grid(row_grid(N, RC)), block(256);
+              float* A, hipStream_t s, int groups = 1) {
+  dim3 grid(row_grid(N, RC), groups), block(256);
   if (act == CI_ACT_SWIGLU)
     hipLaunchKernelGGL((up_rows_kernel<D, true, MT>), grid, block, 0, s, X, w_up, w_gate, b_up, H, A, d, N);
   else
@@ -265,9 +272,16 @@ int up_tokens(const void* X, const void* w_up, const void* w_gate, const void* b
   return CI_OK;
 }
 
+// Weights of one launch up to which every token has workgroups of its own.  Tokens together / one by one (us, both
+// projections): 4 tokens, 128 x 512 gated fp32 (0.5 + 0.3 MB) 8.6 / 6.7; 256 x 1024 fp32 (1 MB each) 7.5 / 6.7; 384 x 1536
+// fp32 (2.4 MB each) 8.3 / 7.9; 512 x 2048 fp32 (4.2 MB each) the same; above, together is faster.
+constexpr double kPerTokenBytes = 2.5e6;
+
 template <class D>
 int up_typed(const void* X, int M, const void* w_up, const void* w_gate, const void* b_up, int act,
              int d, int N, float* H, float* A, hipStream_t s) {
+  if ((double)d * N * D::BYTES * (act == CI_ACT_SWIGLU ? 2 : 1) <= kPerTokenBytes)
+    return up_tokens<D, 1>(X, w_up, w_gate, b_up, act, d, N, H, A, s, M);
   switch (M) {
     case 1: return up_tokens<D, 1>(X, w_up, w_gate, b_up, act, d, N, H, A, s);
     case 2: return up_tokens<D, 2>(X, w_up, w_gate, b_up, act, d, N, H, A, s);
@@ -278,8 +292,9 @@ int up_typed(const void* X, int M, const void* w_up, const void* w_gate, const v
 }
 
 template <class D, int MT, int RD>
-int down_tokens(const float* H, const void* w_down, const void* b_down, int d, int N, void* Y, hipStream_t s) {
-  hipLaunchKernelGGL((down_rows_kernel<D, MT, RD>), dim3(row_grid(d, RD)), dim3(256), 0, s, H, w_down, b_down, Y, d, N);
+int down_tokens(const float* H, const void* w_down, const void* b_down, int d, int N, void* Y, hipStream_t s,
+                int groups = 1) {
+  hipLaunchKernelGGL((down_rows_kernel<D, MT, RD>), dim3(row_grid(d, RD), groups), dim3(256), 0, s, H, w_down, b_down, Y, d, N);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
@@ -296,6 +311,7 @@ int down_group(const float* H, const void* w_down, const void* b_down, int d, in
 template <class D>
 int down_typed(const float* H, int M, const void* w_down, const void* b_down, int d, int N, void* Y,
                hipStream_t s) {
+  if ((double)d * N * D::BYTES <= kPerTokenBytes) return down_tokens<D, 1, RC>(H, w_down, b_down, d, N, Y, s, M);
   switch (M) {
     case 1: return down_group<D, 1>(H, w_down, b_down, d, N, Y, s);
     case 2: return down_group<D, 2>(H, w_down, b_down, d, N, Y, s);
