@@ -19,10 +19,11 @@ def _reference(act, x, S, w):
 
 
 # widths around the 64-vector column chunks of the down phase and (16384 fp32 elements = 4096 vectors) rows of
-# more than one column chunk in the up phase; row counts around the blocks of 1024 neurons and, with 65537
-# and more, above the limit up to which a block counts the ones before it
+# more than one column chunk in the up phase; row counts around the blocks of 1024 neurons: eight of them, which a
+# block counts itself, 8193 neurons, the first that a launch counts ahead, and 65 blocks; slices of fewer rows than 32
 @pytest.mark.parametrize("dt,act", [(torch.float16, "relu"), (torch.bfloat16, "swiglu"), (torch.float32, "relu")])
 @pytest.mark.parametrize("d,N,K,B", [(512, 2000, 801, 4), (520, 1024, 300, 8), (1016, 1025, 1025, 2), (8, 700, 699, 3),
+                                     (64, 8192, 5000, 3), (64, 8193, 5000, 8), (24, 40, 9, 2),
                                      (64, 66000, 30000, 2), (16384, 400, 200, 2)])
 def test_gathered_through_the_union(lib, dt, act, d, N, K, B):
     print("gathered union case", dt, act, d, N, K, B, flush=True)
@@ -31,6 +32,8 @@ def test_gathered_through_the_union(lib, dt, act, d, N, K, B):
     w = rand_weights(d, N, dt, act, "neuron_major", seed=d + N + B, device=DEV)
     rng = np.random.default_rng(K + B)
     sets = np.stack([rng.permutation(N)[:K] for _ in range(B)]).astype(np.int32)   # in no order
+    if N - 1 not in sets[B - 1]:
+        sets[B - 1, 0] = N - 1      # the last neuron of the last block
     idx = torch.from_numpy(sets).to(DEV)
     x = torch.randn(B, d, generator=torch.Generator().manual_seed(N)).to(dt).to(DEV)
     desc = lib.make_weights(w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], core_idx=idx)
@@ -131,3 +134,54 @@ def test_settings_that_change_during_a_call_stay_inside_its_scratch(lib, knob, v
     for y in ys:
         for b in range(B):
             assert_close_rms(y[b], refs[b], dt, f"sentence {b}")
+
+
+@pytest.mark.parametrize("dt,act", [(torch.float16, "relu"), (torch.bfloat16, "swiglu")])
+def test_gathered_union_graph_replays_match_eager(lib, dt, act):
+    """A decode step of several sentences captured once and replayed on other inputs and other core sets (same
+    buffers), with eager work and synchronisations in between: every replay against the eager call."""
+    d, N, K, B, L = 512, 9000, 3000, 4, 2
+    ws_layers = [rand_weights(d, N, dt, act, "neuron_major", seed=70 + l, device=DEV) for l in range(L)]
+    idx = torch.zeros(L, B, K, dtype=torch.int32, device=DEV)
+    x = torch.zeros(L, B, d, dtype=dt, device=DEV)
+    y = torch.zeros_like(x)
+    ws = torch.full((lib.ffn_decode_workspace_size(B, K, d),), 0xA5, dtype=torch.uint8, device=DEV)
+    descs = [lib.make_weights(w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], core_idx=idx[l])
+             for l, w in enumerate(ws_layers)]
+
+    def step(out):
+        for l in range(L):
+            lib.ffn_decode(x[l], descs[l], act, y=out[l], ws=ws)
+
+    rng = np.random.default_rng(12)
+
+    def refill(i):
+        sets = np.stack([[np.sort(rng.permutation(N)[:K]) for _ in range(B)] for _ in range(L)]).astype(np.int32)
+        if i == 2:
+            sets[:, 1, 5:205] = sets[:, 1, 5:6]      # a neuron named 200 times, in this replay only
+        idx.copy_(torch.from_numpy(sets))
+        x.copy_(torch.randn(L, B, d, generator=torch.Generator().manual_seed(i)).to(dt))
+
+    lib.dev_set_param("gathered_union", 2)
+    try:
+        refill(0)
+        step(y)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            step(y)
+        for i in range(5):
+            refill(i)
+            y.fill_(-7.0)
+            g.replay()
+            torch.cuda.synchronize()
+            eager = torch.empty_like(y)
+            (torch.randn(256, 256, device=DEV) @ torch.randn(256, 256, device=DEV)).sum().item()
+            step(eager)
+            torch.cuda.synchronize()
+            assert torch.equal(eager, y), f"replay {i}"
+    finally:
+        lib.dev_set_param("gathered_union", 1)
+    if act == "relu":
+        S = idx[0, 0].cpu().numpy().astype(np.int64)
+        assert_close_rms(y[0, 0], _reference(act, x[0, 0], S, ws_layers[0]), dt, "last replay")
