@@ -9,6 +9,7 @@ fallback: if the library is missing, importing this module raises.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
 from typing import Optional
 
@@ -98,6 +99,10 @@ raw = _lib  # the bare C entry points, for tests of the error paths
 # development hook (csrc/coreinfer_dev.h): launch-shape parameters for sweeps, not part of the interface
 _lib.coreinfer_dev_set_param.restype = _int
 _lib.coreinfer_dev_set_param.argtypes = [ctypes.c_char_p, _int]
+_lib.coreinfer_dev_get_param.restype = _int
+_lib.coreinfer_dev_get_param.argtypes = [ctypes.c_char_p, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_param_name.restype = ctypes.c_char_p
+_lib.coreinfer_dev_param_name.argtypes = [_int]
 _lib.coreinfer_dev_fused_plan.restype = _int
 _lib.coreinfer_dev_fused_plan.argtypes = [_i64, _i64, _int, _int, ctypes.POINTER(_int)]
 _lib.coreinfer_dev_decode_slices.restype = _int
@@ -150,6 +155,18 @@ def version() -> int:
 
 def dev_set_param(name: str, value: int) -> None:
     _check(_lib.coreinfer_dev_set_param(name.encode(), int(value)), "coreinfer_dev_set_param")
+
+
+def dev_get_param(name: str) -> int:
+    out = _int(0)
+    _check(_lib.coreinfer_dev_get_param(name.encode(), ctypes.byref(out)), "coreinfer_dev_get_param")
+    return out.value
+
+
+def dev_params() -> dict:
+    """All development settings and their present values."""
+    names = iter(lambda i=itertools.count(): _lib.coreinfer_dev_param_name(next(i)), None)
+    return {n.decode(): dev_get_param(n.decode()) for n in names}
 
 
 def dev_fused_plan(K: int, d: int, dtype: torch.dtype, act: str) -> dict:

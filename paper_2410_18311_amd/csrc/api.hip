@@ -98,46 +98,71 @@ int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out) {
   return CI_OK;
 }
 
-// Development hook (coreinfer_dev.h), not part of the installed interface: launch-shape
-// parameters for tuning sweeps.  Returns CI_ERR_INVALID_ARG for unknown names.
+// Development hook (coreinfer_dev.h), not part of the installed interface: launch-shape parameters for tuning sweeps
+// and tests.
+namespace {
+struct KnobEntry {
+  const char* name;
+  Knob Params::*knob;
+  bool (*ok)(int);
+};
+const KnobEntry kKnobs[] = {
+    {"decode_wgs_per_cu", &Params::decode_wgs_per_cu, [](int v) { return v >= 1 && v <= 16; }},
+    {"decode_wgs", &Params::decode_wgs, [](int v) { return v >= 0 && v <= 1024; }},
+    {"decode_threads", &Params::decode_threads, [](int v) { return v >= 0 && v <= 1024; }},
+    {"decode_depth", &Params::decode_depth, [](int v) { return v == 4 || v == 8 || v == 16; }},
+    {"reduce_cq", &Params::reduce_cq, [](int v) { return v == 4 || v == 8 || v == 16; }},
+    {"reduce_threads", &Params::reduce_threads, [](int v) { return v == 64 || v == 128 || v == 256 || v == 512 || v == 1024; }},
+    {"decode_nt_store", &Params::decode_nt_store, [](int v) { return v == 0 || v == 1; }},
+    {"fused_depth", &Params::fused_depth, [](int v) { return v == 4 || v == 8; }},
+    {"fused_threads", &Params::fused_threads, [](int v) { return v >= 0 && v <= 1024; }},
+    {"fused_chunks", &Params::fused_chunks, [](int v) { return v >= 2 && v <= 64; }},
+    {"fused_chunk_size", &Params::fused_chunk_size, [](int v) { return v >= 0 && v <= 6144; }},
+    {"fused_wgs", &Params::fused_wgs, [](int v) { return v >= 0 && v <= 1024; }},
+    {"fused_guard_us10", &Params::fused_guard_us10, [](int v) { return v >= 0 && v <= 1000; }},
+    {"fused_chunk_cost10", &Params::fused_chunk_cost10, [](int v) { return v >= 0 && v <= 1000; }},
+    {"fused_window_slots", &Params::fused_window_slots, [](int v) { return v >= 0 && v <= 1000; }},
+    {"fused_ablate", &Params::fused_ablate, [](int v) { return v >= 0 && v <= 2; }},
+    {"fused_aux", &Params::fused_aux, [](int v) { return v == -1 || v == -2 || v == 0 || v == 16; }},
+    {"select_bytes", &Params::select_bytes, [](int v) { return v >= 0 && v <= 2; }},
+    {"select_def2_single", &Params::select_def2_single, [](int v) { return v == 0 || v == 1; }},
+    {"select_wgs_per_cu", &Params::select_wgs_per_cu, [](int v) { return v >= 1 && v <= 8; }},
+    {"gemm_tile", &Params::gemm_tile, [](int v) { return v >= -1 && v <= 4; }},
+    {"gemm_splits", &Params::gemm_splits, [](int v) { return v >= 0 && v <= 8; }},
+    {"gemv_wgs_per_cu", &Params::gemv_wgs_per_cu, [](int v) { return v >= 1 && v <= 32; }},
+    {"gemv_cols_wgs_per_cu", &Params::gemv_cols_wgs_per_cu, [](int v) { return v >= 1 && v <= 4; }},
+    {"gathered_union", &Params::gathered_union, [](int v) { return v >= 0 && v <= 2; }},
+    {"union_depth", &Params::union_depth, [](int v) { return v == 8 || v == 16; }},
+    {"union_down_threads", &Params::union_down_threads, [](int v) { return v >= 64 && v <= 512; }},
+    {"union_up_wgs_per_cu", &Params::union_up_wgs_per_cu, [](int v) { return v >= 1 && v <= 8; }},
+    {"union_down_wgs_per_cu", &Params::union_down_wgs_per_cu, [](int v) { return v >= 1 && v <= 16; }},
+    {"union_super", &Params::union_super, [](int v) { return (v == 0 || (v >= 16 && v <= 256)); }},
+};
+
+const KnobEntry* find_knob(const char* name) {
+  if (name)
+    for (const KnobEntry& e : kKnobs)
+      if (!strcmp(name, e.name)) return &e;
+  return nullptr;
+}
+}  // namespace
+
 int coreinfer_dev_set_param(const char* name, int value) {
-  if (!name) return CI_ERR_INVALID_ARG;
-  Params& p = params();
-  if (!strcmp(name, "decode_wgs_per_cu") && value >= 1 && value <= 16) p.decode_wgs_per_cu = value;
-  else if (!strcmp(name, "decode_wgs") && value >= 0 && value <= 1024) p.decode_wgs = value;
-  else if (!strcmp(name, "decode_threads") && value >= 0 && value <= 1024) p.decode_threads = value;
-  else if (!strcmp(name, "decode_depth") && (value == 4 || value == 8 || value == 16)) p.decode_depth = value;
-  else if (!strcmp(name, "reduce_cq") && (value == 4 || value == 8 || value == 16)) p.reduce_cq = value;
-  else if (!strcmp(name, "reduce_threads") && (value == 64 || value == 128 || value == 256 || value == 512 || value == 1024)) p.reduce_threads = value;
-  else if (!strcmp(name, "decode_nt_store") && (value == 0 || value == 1)) p.decode_nt_store = value;
-  else if (!strcmp(name, "fused_depth") && (value == 4 || value == 8)) p.fused_depth = value;
-  else if (!strcmp(name, "fused_threads") && value >= 0 && value <= 1024) p.fused_threads = value;
-  else if (!strcmp(name, "fused_chunks") && value >= 2 && value <= 64) p.fused_chunks = value;
-  else if (!strcmp(name, "fused_chunk_size") && value >= 0 && value <= 6144) p.fused_chunk_size = value;
-  else if (!strcmp(name, "fused_wgs") && value >= 0 && value <= 1024) p.fused_wgs = value;
-  else if (!strcmp(name, "fused_guard_us10") && value >= 0 && value <= 1000) p.fused_guard_us10 = value;
-  else if (!strcmp(name, "fused_chunk_cost10") && value >= 0 && value <= 1000) p.fused_chunk_cost10 = value;
-  else if (!strcmp(name, "fused_window_slots") && value >= 0 && value <= 1000) p.fused_window_slots = value;
-  else if (!strcmp(name, "fused_ablate") && value >= 0 && value <= 2) p.fused_ablate = value;
-  else if (!strcmp(name, "fused_aux") && (value == -1 || value == -2 || value == 0 || value == 16)) p.fused_aux = value;
-  else if (!strcmp(name, "select_bytes") && value >= 0 && value <= 2) p.select_bytes = value;
-  else if (!strcmp(name, "select_def2_single") && (value == 0 || value == 1)) p.select_def2_single = value;
-  else if (!strcmp(name, "select_wgs_per_cu") && value >= 1 && value <= 8) p.select_wgs_per_cu = value;
-  else if (!strcmp(name, "gemm_ring") && (value == 0 || value == 1)) p.gemm_ring = value;
-  else if (!strcmp(name, "gemm_direct") && (value == 0 || value == 1)) p.gemm_direct = value;
-  else if (!strcmp(name, "gemm_big") && value >= 0 && value <= 2) p.gemm_big = value;
-  else if (!strcmp(name, "gemm_tile") && value >= -1 && value <= 4) p.gemm_tile = value;
-  else if (!strcmp(name, "gemm_splits") && value >= 0 && value <= 8) p.gemm_splits = value;
-  else if (!strcmp(name, "gemv_wgs_per_cu") && value >= 1 && value <= 32) p.gemv_wgs_per_cu = value;
-  else if (!strcmp(name, "gemv_cols_wgs_per_cu") && value >= 1 && value <= 4) p.gemv_cols_wgs_per_cu = value;
-  else if (!strcmp(name, "gathered_union") && value >= 0 && value <= 2) p.gathered_union = value;
-  else if (!strcmp(name, "union_depth") && (value == 8 || value == 16)) p.union_depth = value;
-  else if (!strcmp(name, "union_down_threads") && value >= 64 && value <= 512) p.union_down_threads = value;
-  else if (!strcmp(name, "union_up_wgs_per_cu") && value >= 1 && value <= 8) p.union_up_wgs_per_cu = value;
-  else if (!strcmp(name, "union_down_wgs_per_cu") && value >= 1 && value <= 16) p.union_down_wgs_per_cu = value;
-  else if (!strcmp(name, "union_super") && (value == 0 || (value >= 16 && value <= 256))) p.union_super = value;
-  else return CI_ERR_INVALID_ARG;
+  const KnobEntry* e = find_knob(name);
+  if (!e || !e->ok(value)) return CI_ERR_INVALID_ARG;
+  params().*(e->knob) = value;
   return CI_OK;
+}
+
+int coreinfer_dev_get_param(const char* name, int* value) {
+  const KnobEntry* e = find_knob(name);
+  if (!e || !value) return CI_ERR_INVALID_ARG;
+  *value = params().*(e->knob);
+  return CI_OK;
+}
+
+const char* coreinfer_dev_param_name(int index) {
+  return index >= 0 && index < (int)(sizeof(kKnobs) / sizeof(kKnobs[0])) ? kKnobs[index].name : nullptr;
 }
 
 int coreinfer_keep_count(double frac, int64_t n, int64_t* k) {

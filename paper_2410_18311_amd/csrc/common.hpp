@@ -127,8 +127,6 @@ struct Params {
   Knob select_def2_single{0};  // Def. 2 in one workgroup even where the parallel kernel applies
   Knob gemv_wgs_per_cu{8};
   Knob gemv_cols_wgs_per_cu{1};
-  Knob gemm_ring{1}, gemm_direct{1};  // either 0: the guarded two-stage GEMM kernel instead of the planned tiles
-  Knob gemm_big{1};          // 256 x 256 tiles: 0 never, 1 where the plan takes them, 2 always
   Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256)
   Knob gemm_splits{0};       // k splits of the last round of the down projection: 0 planned
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)

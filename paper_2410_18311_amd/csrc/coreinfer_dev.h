@@ -27,9 +27,7 @@
  *   of the per-token kernel instead of a second pass over the activations),
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
- *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4), "gemm_ring", "gemm_direct" (0/1: either 0
- *   selects the guarded two-stage GEMM kernel instead of the planned tiles),
- *   "gemm_big" (0 never, 1 where the plan takes them, 2 always: 256 x 256 tiles),
+ *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4),
  *   "gemm_tile" (-1 planned, 0 .. 4: tile shape), "gemm_splits" (0 planned, 1 .. 8:
  *   k splits of the last round of tiles of the down projection);
  *   "gathered_union" (0 never, 1 by the rule, 2 wherever it can: gathered decode
@@ -52,6 +50,9 @@ extern "C" {
 #endif
 
 int coreinfer_dev_set_param(const char* name, int value);
+int coreinfer_dev_get_param(const char* name, int* value);
+/* The names, by index from 0; NULL past the last. */
+const char* coreinfer_dev_param_name(int index);
 
 /* The launch shape the single-launch decode would use for K core neurons of a
  * layer with model width d under the current settings: out[0..4] = chunks,

@@ -7,191 +7,14 @@
 //   [Kk, Nn].
 //
 // This file plans a product (which tile shape, whether the last round of tiles is
-// split along k) for the kernels of gemm_wide.hip and gemm_mid.hip, adds up split
-// sums, and holds the guarded two-stage kernel that the development settings
-// select for comparison (128x128x64 tiles, global -> register -> LDS staging with
-// two LDS buffers, every access bounds-checked).
+// split along k) for the kernels of gemm_wide.hip and gemm_mid.hip, and adds up
+// split sums.
 // The fp32 element type has its own kernels (gemm_f32.hip).
 #include "gemm_common.hpp"
 
 namespace ci {
 
 namespace {
-
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-template <class D>
-__device__ __forceinline__ f32x16 mfma32(const uint4& a, const uint4& b, f32x16 c);
-template <>
-__device__ __forceinline__ f32x16 mfma32<F16>(const uint4& a, const uint4& b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
-                                                __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ f32x16 mfma32<BF16>(const uint4& a, const uint4& b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-constexpr int BM = 128, BN = 128, BK = 64;
-constexpr int LDK = BK + 8;  // LDS row stride in elements (144 bytes)
-
-// Fused epilogue.  Accumulator element v of lane
-// l is C[row, col] with col = l % 32, row = 8 * (v / 4) + 4 * (l / 32) + v % 4
-// inside a 32x32 tile.
-template <class D, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[EPI == EPI_SWIGLU ? 2 : 1][2][2],
-                                              int m0, int n0, int wm, int wn, int lane) {
-  using T = typename D::T;
-  constexpr int NB = (EPI == EPI_SWIGLU) ? 2 : 1;
-  const T* bias = reinterpret_cast<const T*>(g.bias);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = n0 + wn * 64 + j * 32 + (lane & 31);
-    if (col >= g.Nn) continue;
-    const float bv = bias ? to_float<D>(bias[col]) : 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (row >= g.M) continue;
-        float h, score;
-        if (EPI == EPI_SWIGLU) {
-          h = silu(acc[0][i][j][v]) * acc[NB - 1][i][j][v];
-          score = fabsf(h);
-        } else if (EPI == EPI_RELU) {
-          h = fmaxf(acc[0][i][j][v] + bv, 0.f);
-          score = h;
-        } else {
-          h = acc[0][i][j][v] + bv;
-          score = h;
-        }
-        const size_t o = (size_t)row * g.ldo + col;
-        if (g.out_f) g.out_f[o] = score;
-        if (g.out_e) reinterpret_cast<T*>(g.out_e)[o] = from_float<D>(h);
-      }
-    }
-  }
-}
-
-template <class D, int EPI, bool BNN>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
-  using T = typename D::T;
-  constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  constexpr int NB = DUAL ? 2 : 1;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  T* smem = reinterpret_cast<T*>(smem_raw);
-  // per stage: A tile, then NB B tiles
-  constexpr int TILE = BM * LDK;
-  constexpr int STAGE = TILE * (1 + NB);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int tiles_m = (g.M + BM - 1) / BM;
-  const int t = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int m0 = (t % tiles_m) * BM, n0 = (t / tiles_m) * BN;
-  const T* A = reinterpret_cast<const T*>(g.A);
-  const T* Bp[2] = {reinterpret_cast<const T*>(g.B0), reinterpret_cast<const T*>(g.B1)};
-
-  uint4 ra[4], rb[NB][4];
-  auto load_global = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = tid + 256 * i;
-      {
-        const int row = v >> 3, kc = (v & 7) * 8;
-        ra[i] = make_uint4(0, 0, 0, 0);
-        if (m0 + row < g.M && k0 + kc < g.Kk) ra[i] = ld16(A + (size_t)(m0 + row) * g.lda + k0 + kc);
-      }
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        rb[q][i] = make_uint4(0, 0, 0, 0);
-        if (!BNN) {
-          const int row = v >> 3, kc = (v & 7) * 8;
-          if (n0 + row < g.Nn && k0 + kc < g.Kk)
-            rb[q][i] = ld16(Bp[q] + (size_t)(n0 + row) * g.ldb + k0 + kc);
-        } else {
-          const int krow = v >> 4, nc = (v & 15) * 8;
-          if (k0 + krow < g.Kk && n0 + nc < g.Nn)
-            rb[q][i] = ld16(Bp[q] + (size_t)(k0 + krow) * g.ldb + n0 + nc);
-        }
-      }
-    }
-  };
-  auto store_lds = [&](int stage) {
-    T* sA = smem + stage * STAGE;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = tid + 256 * i;
-      const int row = v >> 3, kc = (v & 7) * 8;
-      *reinterpret_cast<uint4*>(sA + row * LDK + kc) = ra[i];
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        T* sB = sA + TILE * (1 + q);
-        if (!BNN) {
-          *reinterpret_cast<uint4*>(sB + row * LDK + kc) = rb[q][i];
-        } else {
-          const int krow = v >> 4, nc = (v & 15) * 8;
-          const uint32_t w[4] = {rb[q][i].x, rb[q][i].y, rb[q][i].z, rb[q][i].w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const uint16_t bits = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-            reinterpret_cast<uint16_t*>(sB)[(nc + e) * LDK + krow] = bits;
-          }
-        }
-      }
-    }
-  };
-
-  f32x16 acc[NB][2][2];
-#pragma unroll
-  for (int q = 0; q < NB; ++q)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[q][i][j][v] = 0.f;
-
-  const int nk = (g.Kk + BK - 1) / BK;
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load_global((kt + 1) * BK);
-    const T* sA = smem + cur * STAGE;
-#pragma unroll
-    for (int s = 0; s < BK / 16; ++s) {
-      const int koff = s * 16 + (lane >> 5) * 8;
-      uint4 fa[2], fb[NB][2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        fa[i] = *reinterpret_cast<const uint4*>(sA + (wm * 64 + i * 32 + (lane & 31)) * LDK + koff);
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          fb[q][j] = *reinterpret_cast<const uint4*>(sA + TILE * (1 + q) +
-                                                     (wn * 64 + j * 32 + (lane & 31)) * LDK + koff);
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[q][i][j] = mfma32<D>(fa[i], fb[q][j], acc[q][i][j]);
-    }
-    if (kt + 1 < nk) {
-      store_lds(cur ^ 1);  // the other buffer: last read before the previous barrier
-      __syncthreads();
-    }
-  }
-
-  gemm_epilogue<D, EPI>(g, acc, m0, n0, wm, wn, lane);
-}
 
 // Y[m, n] = sum_s partial[s][tile][m, n] + bias[n], converted to the element type, over the `tail` tiles that were
 // split (bm x bn, from place `first` in the order of tile_of).  A workgroup takes 16 rows of a tile, a thread four
@@ -229,19 +52,6 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
   }
 }
 
-template <class D, int EPI, bool BNN>
-int launch_guarded(const GemmArgs& g, hipStream_t s) {
-  constexpr int NB = (EPI == EPI_SWIGLU) ? 2 : 1;
-  const size_t lds = (size_t)2 * BM * LDK * (1 + NB) * sizeof(typename D::T);
-  static std::atomic<uint64_t> attr_seen{0};
-  if (lds > 48 * 1024 && allow_dynamic_lds(attr_seen, reinterpret_cast<const void*>(&gemm_mfma_kernel<D, EPI, BNN>), lds) != CI_OK)
-    return CI_ERR_HIP;
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.Nn + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_mfma_kernel<D, EPI, BNN>), dim3(tiles), dim3(256), lds, s, g);
-  CI_HIP_CHECK_LAUNCH();
-  return CI_OK;
-}
-
 // ---- which tiles, and how they are spread over the chip ------------------------
 struct TileShape {
   int shape;        // kMid..., or kWide
@@ -249,6 +59,7 @@ struct TileShape {
   double rate;      // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
 };
 constexpr int kWide = 4;
+constexpr int kTileK = 64;       // k of a tile
 constexpr int kFullChip = 256;  // compute units of an MI355X
 constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12},
                                  {kMid128x256, 128, 256, 4.4e12},
@@ -266,16 +77,16 @@ constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12},
 GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, size_t room) {
   GemmPlan best{};
   double best_t = 1e30;
-  const int force = params().gemm_tile, force_splits = params().gemm_splits, big = params().gemm_big;
+  const int force = params().gemm_tile, force_splits = params().gemm_splits;
   for (const TileShape& ts : kShapes) {
-    if (force >= 0 ? ts.shape != force : ((big == 0 && ts.shape == kWide) || (big == 2 && ts.shape != kWide))) continue;
+    if (force >= 0 && ts.shape != force) continue;
     const int bn = dual ? ts.bn / 2 : ts.bn;
     const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((Nn + bn - 1) / bn);
     const double t_tile = 2.0 * ts.bm * ts.bn * (double)Kk / ts.rate;
     // first loads; results of a round, which nothing overlaps
     const double t_fixed = 3e-6 + (double)ts.bm * bn * out_bytes * kFullChip / 4.5e12;
     for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && Kk / ((int64_t)sp * BK) < 4) break;  // at least four k tiles per split
+      if (sp > 1 && Kk / ((int64_t)sp * kTileK) < 4) break;  // at least four k tiles per split
       const int64_t full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
       if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * ts.bm * bn * sizeof(float) > room)) break;
       const double t_full = (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed);
@@ -285,7 +96,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, 
       if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
         best_t = t;
         best = GemmPlan{ts.shape, ts.bm, bn, (int)full, (int)tail, sp, (int)Kk};
-        if (sp > 1) best.k_chunk = (int)(((Kk + sp - 1) / sp + BK - 1) / BK * BK);
+        if (sp > 1) best.k_chunk = (int)(((Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK);
       }
     }
     if (best_t > 1e29 && force_splits > 0) best = GemmPlan{ts.shape, ts.bm, bn, (int)tiles, 0, 1, (int)Kk};
@@ -296,7 +107,6 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, 
 
 template <class D, int EPI, bool BNN>
 int launch_mfma(GemmArgs& g, const GemmPlan& p, hipStream_t s) {
-  if (!params().gemm_ring || !params().gemm_direct) return launch_guarded<D, EPI, BNN>(g, s);
   g.full = p.full;
   g.tail = p.tail;
   g.splits = p.splits;

@@ -22,6 +22,25 @@ def lib():
     return coreinfer
 
 
+@pytest.fixture(autouse=True)
+def _development_settings_are_put_back(request):
+    """A test that changes a development setting puts it back: the tests after it run what a user gets."""
+    if "lib" not in request.fixturenames:
+        yield
+        return
+    library = request.getfixturevalue("lib")
+    before = library.dev_params()
+    assert before == _SETTINGS.setdefault("defaults", before)
+    yield
+    after = library.dev_params()
+    for name, value in before.items():
+        library.dev_set_param(name, value)
+    assert after == before, "development settings left changed"
+
+
+_SETTINGS: dict = {}
+
+
 def gpu_available() -> bool:
     import torch
     return torch.cuda.is_available()

@@ -465,16 +465,16 @@ def test_dense_matches_oracle(lib, dt, act, layout, M, d, N):
     assert torch.equal(A, A2)
 
 
-@pytest.mark.parametrize("direct", [1, 0])
-def test_dense_random_shapes(lib, direct):
+@pytest.mark.parametrize("tile", [-1, 0])
+def test_dense_random_shapes(lib, tile):
     """Seeded sweep over prompt lengths and widths around the tile edges of every GEMM variant
     (ragged and even, reduction lengths that are and are not multiples of the k tile), with the
-    128 x 128 tiles loaded straight into LDS (the default) and through the register ring."""
-    lib.dev_set_param("gemm_direct", direct)
+    planned tiles of the 16-bit kernels and with 128 x 128 ones throughout."""
+    lib.dev_set_param("gemm_tile", tile)
     try:
         _dense_random_shapes(lib)
     finally:
-        lib.dev_set_param("gemm_direct", 1)
+        lib.dev_set_param("gemm_tile", -1)
 
 
 def _dense_random_shapes(lib):
@@ -514,13 +514,13 @@ def test_dense_large_tile_kernel_matches_oracle(lib, dt, act, layout, M, d, N):
     dtype = DTYPES[dt]
     w = rand_weights(d, N, dtype, act, layout, seed=M + d + N + 9, device=DEV)
     X = torch.randn(M, d, generator=torch.Generator().manual_seed(M + 1)).to(dtype).to(DEV)
-    lib.dev_set_param("gemm_big", 2)
+    lib.dev_set_param("gemm_tile", 4)
     try:
         Y, A = lib.ffn_dense(X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], layout, act,
                              want_y=True, want_a=True)
         torch.cuda.synchronize()
     finally:
-        lib.dev_set_param("gemm_big", 1)
+        lib.dev_set_param("gemm_tile", -1)
     if act == "relu":
         A_ref = orc.score_relu(f64(X), f64(w["w_up"]), f64(w["b_up"]))
     else:
@@ -551,19 +551,23 @@ def test_dense_many_tiles_with_split_down_projection(lib, layout):
     assert_close_rms(Y[torch.from_numpy(rows).to(DEV)], Y_ref, torch.float16, "split down projection")
 
 
-@pytest.mark.parametrize("knob,value,default", [("gemm_ring", 0, 1), ("gemm_direct", 0, 1), ("gemm_big", 0, 1), ("select_wgs_per_cu", 1, 2),
-                                                ("select_def2_single", 1, 0), ("decode_depth", 8, 4), ("decode_depth", 16, 4),
-                                                ("decode_wgs_per_cu", 2, 1), ("decode_nt_store", 0, 1),
-                                                ("reduce_cq", 4, 8), ("reduce_cq", 16, 8), ("reduce_threads", 64, 256), ("reduce_threads", 1024, 256),
-                                                ("union_depth", 16, 8),
-                                                ("union_down_threads", 128, 384), ("decode_threads", 512, 0), ("decode_threads", 64, 0),
-                                                ("decode_wgs", 7, 0), ("decode_wgs", 1024, 0), ("union_up_wgs_per_cu", 3, 1),
-                                                ("union_down_wgs_per_cu", 1, 2)])
-def test_alternative_launch_shapes_give_the_same_results(lib, knob, value, default):
+@pytest.mark.parametrize("knob,value", [("gemm_tile", 0), ("gemm_tile", 1), ("gemm_tile", 2), ("gemm_tile", 3), ("gemm_tile", 4),
+                                        ("gemm_splits", 1), ("gemm_splits", 4),
+                                        ("select_wgs_per_cu", 1), ("select_bytes", 0), ("select_bytes", 2),
+                                        ("select_def2_single", 1), ("decode_depth", 8), ("decode_depth", 16),
+                                        ("decode_wgs_per_cu", 2), ("decode_nt_store", 0),
+                                        ("reduce_cq", 4), ("reduce_cq", 16), ("reduce_threads", 64), ("reduce_threads", 1024),
+                                        ("gathered_union", 0), ("gathered_union", 2), ("union_depth", 16),
+                                        ("union_down_threads", 128), ("union_down_threads", 384), ("decode_threads", 512),
+                                        ("decode_threads", 64), ("decode_wgs", 7), ("decode_wgs", 1024),
+                                        ("union_up_wgs_per_cu", 3), ("union_down_wgs_per_cu", 2)])
+def test_alternative_launch_shapes_give_the_same_results(lib, knob, value):
     """Every tuning knob selects among kernels / launch shapes that must all be correct: one prefill
     (dense FFN, selection, deployment) and decode (compacted, gathered, union-batched) pass per
     setting, against the oracle."""
     _say("knob case", knob, value)
+    default = lib.dev_get_param(knob)
+    assert value != default, "not an alternative"
     M, d, N, B = 300, 512, 2304, 3
     dt = torch.bfloat16
     w = rand_weights(d, N, dt, "swiglu", "neuron_major", seed=21, device=DEV)
