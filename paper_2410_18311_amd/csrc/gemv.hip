@@ -25,7 +25,8 @@ namespace {
 constexpr int RC = 4;  // weight rows in flight per thread; down_rows_kernel with several tokens: 8, as it
                        // reads the tokens' fp32 hidden values once per group of rows
 
-template <class D, bool SWIGLU, int MT>
+// EACH: the MT tokens of blockIdx.y (an instantiation of its own: the offsets cost the others 0.3 of 4.3 us)
+template <class D, bool SWIGLU, int MT, bool EACH>
 __global__ __launch_bounds__(256) void up_rows_kernel(const void* __restrict__ X,
                                                       const void* __restrict__ w_up,
                                                       const void* __restrict__ w_gate,
@@ -39,9 +40,12 @@ __global__ __launch_bounds__(256) void up_rows_kernel(const void* __restrict__ X
   const int n_grp = (N + RC - 1) / RC;
   const int g0 = (int)(((int64_t)blockIdx.x * n_grp) / gridDim.x);
   const int g1 = (int)(((int64_t)(blockIdx.x + 1) * n_grp) / gridDim.x);
-  const T* x = reinterpret_cast<const T*>(X) + (size_t)blockIdx.y * MT * d;  // the tokens of this workgroup
-  if (H) H += (size_t)blockIdx.y * MT * N;
-  if (A) A += (size_t)blockIdx.y * MT * N;
+  const T* x = reinterpret_cast<const T*>(X);
+  if constexpr (EACH) {
+    x += (size_t)blockIdx.y * MT * d;
+    if (H) H += (size_t)blockIdx.y * MT * N;
+    if (A) A += (size_t)blockIdx.y * MT * N;
+  }
   const T* wu = reinterpret_cast<const T*>(w_up);
   const T* wg = reinterpret_cast<const T*>(w_gate);
 
@@ -106,7 +110,7 @@ __global__ __launch_bounds__(256) void up_rows_kernel(const void* __restrict__ X
   }
 }
 
-template <class D, int MT, int RD>
+template <class D, int MT, int RD, bool EACH>
 __global__ __launch_bounds__(256) void down_rows_kernel(const float* __restrict__ H,
                                                         const void* __restrict__ w_down,
                                                         const void* __restrict__ b_down, void* Y,
@@ -119,8 +123,11 @@ __global__ __launch_bounds__(256) void down_rows_kernel(const float* __restrict_
   const int g0 = (int)(((int64_t)blockIdx.x * n_grp) / gridDim.x);
   const int g1 = (int)(((int64_t)(blockIdx.x + 1) * n_grp) / gridDim.x);
   const T* w = reinterpret_cast<const T*>(w_down);
-  H += (size_t)blockIdx.y * MT * N;  // the tokens of this workgroup
-  T* y_out = reinterpret_cast<T*>(Y) + (size_t)blockIdx.y * MT * d;
+  T* y_out = reinterpret_cast<T*>(Y);
+  if constexpr (EACH) {
+    H += (size_t)blockIdx.y * MT * N;
+    y_out += (size_t)blockIdx.y * MT * d;
+  }
 
   for (int g = g0; g < g1; ++g) {
     const int rb = g * RD;
@@ -260,28 +267,28 @@ int row_grid(int64_t rows, int rc) {
   return (int)((groups + rounds - 1) / rounds);
 }
 
-template <class D, int MT>
+template <class D, int MT, bool EACH = false>
 int up_tokens(const void* X, const void* w_up, const void* w_gate, const void* b_up, int act, int d, int N, float* H,
               float* A, hipStream_t s, int groups = 1) {
   dim3 grid(row_grid(N, RC), groups), block(256);
   if (act == CI_ACT_SWIGLU)
-    hipLaunchKernelGGL((up_rows_kernel<D, true, MT>), grid, block, 0, s, X, w_up, w_gate, b_up, H, A, d, N);
+    hipLaunchKernelGGL((up_rows_kernel<D, true, MT, EACH>), grid, block, 0, s, X, w_up, w_gate, b_up, H, A, d, N);
   else
-    hipLaunchKernelGGL((up_rows_kernel<D, false, MT>), grid, block, 0, s, X, w_up, w_gate, b_up, H, A, d, N);
+    hipLaunchKernelGGL((up_rows_kernel<D, false, MT, EACH>), grid, block, 0, s, X, w_up, w_gate, b_up, H, A, d, N);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
 
-// Weights of one launch up to which every token has workgroups of its own.  Tokens together / one by one (us, both
-// projections): 4 tokens, 128 x 512 gated fp32 (0.5 + 0.3 MB) 8.6 / 6.7; 256 x 1024 fp32 (1 MB each) 7.5 / 6.7; 384 x 1536
-// fp32 (2.4 MB each) 8.3 / 7.9; 512 x 2048 fp32 (4.2 MB each) the same; above, together is faster.
-constexpr double kPerTokenBytes = 2.5e6;
+// Weights of one launch up to which every token has workgroups of its own.  Tokens together / one by one (us): 4 tokens,
+// both projections of 128 x 512 gated fp32 (0.5 + 0.3 MB) 8.6 / 6.7, of 256 x 1024 fp32 (1 MB each) 7.5 / 6.7; the up
+// projection of 512 x 2048 fp16 (2.1 MB) 4.2 / 4.5, of 384 x 1536 fp32 (2.4 MB) 4.2 / 4.4.
+constexpr double kPerTokenBytes = 1.6e6;
 
 template <class D>
 int up_typed(const void* X, int M, const void* w_up, const void* w_gate, const void* b_up, int act,
              int d, int N, float* H, float* A, hipStream_t s) {
-  if ((double)d * N * D::BYTES * (act == CI_ACT_SWIGLU ? 2 : 1) <= kPerTokenBytes)
-    return up_tokens<D, 1>(X, w_up, w_gate, b_up, act, d, N, H, A, s, M);
+  if (M > 1 && (double)d * N * D::BYTES * (act == CI_ACT_SWIGLU ? 2 : 1) <= kPerTokenBytes)
+    return up_tokens<D, 1, true>(X, w_up, w_gate, b_up, act, d, N, H, A, s, M);
   switch (M) {
     case 1: return up_tokens<D, 1>(X, w_up, w_gate, b_up, act, d, N, H, A, s);
     case 2: return up_tokens<D, 2>(X, w_up, w_gate, b_up, act, d, N, H, A, s);
@@ -291,10 +298,10 @@ int up_typed(const void* X, int M, const void* w_up, const void* w_gate, const v
   return CI_ERR_UNSUPPORTED;
 }
 
-template <class D, int MT, int RD>
+template <class D, int MT, int RD, bool EACH = false>
 int down_tokens(const float* H, const void* w_down, const void* b_down, int d, int N, void* Y, hipStream_t s,
                 int groups = 1) {
-  hipLaunchKernelGGL((down_rows_kernel<D, MT, RD>), dim3(row_grid(d, RD), groups), dim3(256), 0, s, H, w_down, b_down, Y, d, N);
+  hipLaunchKernelGGL((down_rows_kernel<D, MT, RD, EACH>), dim3(row_grid(d, RD), groups), dim3(256), 0, s, H, w_down, b_down, Y, d, N);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
@@ -311,7 +318,7 @@ int down_group(const float* H, const void* w_down, const void* b_down, int d, in
 template <class D>
 int down_typed(const float* H, int M, const void* w_down, const void* b_down, int d, int N, void* Y,
                hipStream_t s) {
-  if ((double)d * N * D::BYTES <= kPerTokenBytes) return down_tokens<D, 1, RC>(H, w_down, b_down, d, N, Y, s, M);
+  if (M > 1 && (double)d * N * D::BYTES <= kPerTokenBytes) return down_tokens<D, 1, RC, true>(H, w_down, b_down, d, N, Y, s, M);
   switch (M) {
     case 1: return down_group<D, 1>(H, w_down, b_down, d, N, Y, s);
     case 2: return down_group<D, 2>(H, w_down, b_down, d, N, Y, s);
