@@ -1036,11 +1036,11 @@ int launch_threshold(const typename IN::T* act, int M, int N, int64_t ld, int64_
 //  - several rounds of tokens make the second pass long: one sentence from two on (1024 x 13824 39.4 / 34.2, 1024 x 11008 fp16
 //    39.8 / 36.8), more from four on (8 x 512 x 16384 96 / 73), or from two where it misses the caches (8 x 128 x 11008
 //    0.89, but 3 x 256 x 11008, 34 MB, 31.7 / 34.8);
-//  - one round of tokens, all in cache, is a matter of latency: at most 8192 neurons, or 100 tokens, 3 to 6 % faster;
-//    128 to 512 tokens of 11008 to 16384 neurons 2 to 8 % slower; above 32768 neurons (keys of nine or ten registers of
+//  - one round of tokens, all in cache, is a matter of latency: at most 8192 neurons, or 64 tokens, 3 to 6 % faster;
+//    128 to 512 tokens of 11008 to 16384 neurons 2 to 8 % slower, up to 32 MB of them (27.2 / 25.8, 512 x 16384 fp32); above 32768 neurons (keys of nine or ten registers of
 //    counts) 25.9 / 27.9 (1 x 36864), from 256 tokens on faster (512 x 36864 fp16 58.0 / 51.6).
 bool byte_counts_pay(int64_t B, int64_t M, int64_t N, size_t bytes, bool vec_ok, int rounds, int rounds_part, int cus) {
-  const bool few = B * M <= 100;
+  const bool few = B * M <= (N < 4096 ? 100 : 64);
   if (B > 2 && N < 4096) return (B <= 5 && few) || (N >= 2048 && M >= 256 && rounds >= 4);
   if (!vec_ok && (B <= 2 || M >= 32 || N > 8 * kThreads || (B <= 5 && few))) return true;
   if (B > 2 && M >= 64 && bytes >= ((size_t)40 << 20) && rounds >= 2 && (rounds_part == rounds || M >= 512)) return true;
@@ -1048,7 +1048,7 @@ bool byte_counts_pay(int64_t B, int64_t M, int64_t N, size_t bytes, bool vec_ok,
   const int64_t blocks = (N + 255) / 256 * B;  // of the counting kernel; with 64 neurons each up to half a chip full of them
   if ((blocks <= cus / 2 && 4 * blocks > cus) || rounds >= (B <= 2 ? 2 : 4)) return true;
   if (N > 32 * kThreads) return B <= 2 && B * M >= cus;
-  return B <= 2 && (N <= 8 * kThreads || few);
+  return B <= 2 && (N <= 8 * kThreads || few || bytes >= ((size_t)32 << 20));
 }
 
 // Def. 1 and Eq. 3 for an activation matrix of element type IN::T.  The fp32 path has a kernel for
