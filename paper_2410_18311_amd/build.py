@@ -8,6 +8,8 @@ import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
 
+from . import isa_check
+
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -48,6 +50,11 @@ def build_library(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    bad = isa_check.lds_load_hazards(LIB_PATH)
+    if bad:
+        os.remove(LIB_PATH)
+        raise RuntimeError("loads into LDS that read a scalar register too soon after a vector instruction wrote it:\n" +
+                           "\n".join(bad))
     if verbose:
         print("built", LIB_PATH)
     return LIB_PATH

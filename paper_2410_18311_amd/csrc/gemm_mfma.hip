@@ -27,14 +27,14 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
   const int strips = bm / 16;
   int tm, tn;
   const int tile = blockIdx.x / strips, r0 = (blockIdx.x % strips) * 16;
-  const size_t stride = (size_t)tail * bm * bn;  // a split's tiles
+  const size_t stride = (size_t)tail * sums_pitch(bm, bn);  // a split's tiles
   tile_of(first + tile, (M + bm - 1) / bm, (Nn + bn - 1) / bn, &tm, &tn);
   const int row0 = tm * bm + r0, col0 = tn * bn;
   const int quads = bn / 4;
   for (int i = threadIdx.x; i < 16 * quads; i += 256) {
     const int row = row0 + i / quads, col = col0 + (i % quads) * 4;
     if (row >= M || col >= Nn) continue;
-    const float* p = partial + ((size_t)tile * bm + r0 + i / quads) * bn + (i % quads) * 4;
+    const float* p = partial + (size_t)tile * sums_pitch(bm, bn) + (r0 + i / quads) * bn + (i % quads) * 4;
     float4 a = *reinterpret_cast<const float4*>(p);
 #pragma unroll 4
     for (int s = 1; s < splits; ++s) {
@@ -88,7 +88,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, 
     for (int sp = 1; sp <= 8; ++sp) {
       if (sp > 1 && Kk / ((int64_t)sp * kTileK) < 4) break;  // at least four k tiles per split
       const int64_t full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
-      if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * ts.bm * bn * sizeof(float) > room)) break;
+      if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
       const double t_full = (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed);
       const double t_tail = (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed);
       const double t_sum = tail == 0 ? 0.0 : 2.0 * sp * (double)tail * ts.bm * bn * 4.0 / 4.5e12 + 5e-6;
@@ -165,7 +165,7 @@ GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int dtype, size_t room)
 }
 
 size_t gemm_plan_bytes(const GemmPlan& p) {
-  return p.tail > 0 ? (size_t)p.splits * (size_t)p.tail * p.bm * p.bn * sizeof(float) : 0;
+  return p.tail > 0 ? (size_t)p.splits * (size_t)p.tail * sums_pitch(p.bm, p.bn) * sizeof(float) : 0;
 }
 
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,

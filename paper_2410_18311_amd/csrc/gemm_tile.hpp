@@ -60,13 +60,16 @@ __device__ __forceinline__ i32x4 rsrc_at(const char* p) {
 // 16 bytes per lane from `rsrc` + `off` to LDS at `lds` + 16 * lane.  Written out, because the compiler
 // orders transposing LDS reads behind every such load it knows of; nothing is returned to a register, and
 // the waits for its arrival are the kernel's own (s_waitcnt vmcnt ahead of a barrier).  The compiler does not
-// look for hazards inside: five wait states have to lie between a vector instruction that writes a scalar register
-// (a lane read that makes a descriptor uniform or fetches a spilled one) and a load that reads it, and the move to
-// m0 and four idle ones are those five, whatever stands before.
+// look for hazards inside: five wait states have to lie between a vector instruction that writes a scalar register (a
+// lane read that makes a descriptor uniform or fetches a spilled one) and a load that reads it.  The moves that make the
+// descriptors here are scalar, which need none; the build looks at every such load of the library and fails where the
+// compiler has come to something else (isa_check.py).  Waiting here instead, whatever stands before, costs the 40
+// loads that a small product starts with 0.35 us (four idle states: both products of 5 x 256 x 1024 13.2 -> 13.8 us; a copy
+// of the descriptor by scalar moves 13.6).
 __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t off, i32x4 rsrc) {
   const uint32_t m = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lds;
   uint32_t m0;  // says that m0 is written (as a clobber it is refused with a warning)
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 3\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
                : "={m0}"(m0)
                : "s"(m), "v"(off), "s"(rsrc)
                : "memory");
@@ -124,22 +127,21 @@ __device__ __forceinline__ TileWork tile_work(const GemmArgs& g, int bm, int bn)
   const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.Nn + bn - 1) / bn;
   const int id = blockIdx.x;
   TileWork w;
-  int t;
+  int t, local = 0;
   if (id < g.full) {
     t = xcd_spread(id, g.full);
     w.sums = nullptr;
     w.k_begin = 0;
     w.k_end = g.Kk;
   } else {
-    const int local = xcd_spread(id - g.full, g.tail * g.splits);
+    local = xcd_spread(id - g.full, g.tail * g.splits);
     t = g.full + local % g.tail;
     w.k_begin = local / g.tail * g.k_chunk;
     w.k_end = min(g.Kk, w.k_begin + g.k_chunk);
   }
   tile_of(t, tiles_m, tiles_n, &w.tm, &w.tn);
-  if (id >= g.full)  // sums are stored tile after tile, in the order of the workgroups' tiles and splits
-    w.sums = g.partial + ((ptrdiff_t)(w.k_begin / g.k_chunk * g.tail + (t - g.full)) * bm - (ptrdiff_t)w.tm * bm) * bn -
-             (ptrdiff_t)w.tn * bn;
+  if (id >= g.full)  // `local` is split * tail + tile: the place of this workgroup's sums
+    w.sums = g.partial + (ptrdiff_t)local * sums_pitch(bm, bn) - ((ptrdiff_t)w.tm * bm * bn + (ptrdiff_t)w.tn * bn);
   return w;
 }
 

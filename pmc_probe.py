@@ -7,9 +7,10 @@ It launches (a) a plain device-to-device copy of a known size (the calibration
 against which the FETCH_SIZE / WRITE_SIZE readings are scaled) and (b) the
 sparse decode FFN of every layer of the workload, on random compacted buffers
 of the workload's shapes, a few times.  `--what prefill` runs the prefill side
-instead: the dense FFN of one layer on the workload's prompt, the selection on
-its activations and the deployment of the selected neurons, a few times (for
-instruction-issue and LDS counters of those kernels); `--what union` runs the
+instead: the dense FFN of one layer on the prompts of all sentences of the
+workload, the selection on their activations and, for a single sentence, the
+deployment of the selected neurons, a few times (for instruction-issue, LDS and
+memory-path counters of those kernels); `--what union` runs the
 union-batched decode of the workload's sentences over resident weights after
 the calibration copy.  Nothing is timed here.
 """
@@ -45,21 +46,21 @@ def main():
 
     if args.what == "prefill":
         w = wl.layer_weights(cfg, 0, dev)
-        X = wl.prefill_hidden(cfg, 0, dev)
+        X = torch.cat([wl.prefill_hidden(cfg, 0, dev, sentence=s) for s in range(B)], dim=0).contiguous()
         M = X.shape[0]
         A = torch.empty(M, N, dtype=torch.float32, device=dev)
         Y = torch.empty(M, d, dtype=dt, device=dev)
         dws = torch.empty(ci.ffn_dense_workspace_size(M, d, N, dt), dtype=torch.uint8, device=dev)
-        sws = torch.empty(ci.select_workspace_size(M, N), dtype=torch.uint8, device=dev)
-        core = torch.empty(K, dtype=torch.int32, device=dev)
-        cnt = torch.empty(N, dtype=torch.int32, device=dev)
+        sws = torch.empty(ci.select_batch_workspace_size(B, M // B, N), dtype=torch.uint8, device=dev)
+        core = torch.empty(B, K, dtype=torch.int32, device=dev)
+        cnt = torch.empty(B, N, dtype=torch.int32, device=dev)
         bufs = None
         for _ in range(args.reps):
             ci.ffn_dense(X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], cfg.down_layout, cfg.act,
                          want_y=True, want_a=True, Y=Y, A=A, ws=dws)
-            ci.select(A, cfg.alpha, beta, core_idx=core, counts=cnt, ws=sws)
+            ci.select_batch(A, B, cfg.alpha, beta, core_idx=core, counts=cnt, ws=sws)
             if B == 1:
-                bufs = ci.compact(w["w_up"], w["w_gate"], w["b_up"], w["w_down"], cfg.down_layout, cfg.act, core,
+                bufs = ci.compact(w["w_up"], w["w_gate"], w["b_up"], w["w_down"], cfg.down_layout, cfg.act, core[0],
                                   out=bufs)
         torch.cuda.synchronize()
         print(f"workload {cfg.name}: prefill of one layer, M={M} d={d} N={N} K={K}, {args.reps} times")

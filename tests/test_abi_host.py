@@ -132,9 +132,9 @@ def test_dense_workspace_holds_the_sums_of_split_tiles_only(lib):
                     (2090, 1024, 648), (4096, 9216, 36864), (8000, 9216, 36864), (65535, 8192, 28672)]:
         assert lib.raw.coreinfer_ffn_dense_hidden_workspace_size(M, d, N, lib.CI_F16, ctypes.byref(b)) == lib.CI_OK
         sums = b.value
-        assert 256 <= sums <= 8 * 256 * 256 * 256 * 4 + 256
+        assert 256 <= sums <= 8 * 256 * (256 * 256 + 64) * 4 + 256
         if M == 4096:
-            assert sums == 64 * 4 * 256 * 256 * 4 + 256
+            assert sums == 64 * 4 * (256 * 256 + 64) * 4 + 256
         hidden = -(-M * N * 4 // 256) * 256
         assert lib.ffn_dense_workspace_size(M, d, N, torch.float16) == hidden + sums
     r, F = lib.raw.coreinfer_ffn_dense, 0x10000

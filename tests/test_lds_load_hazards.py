@@ -1,26 +1,16 @@
-"""The hand-written load into LDS of the GEMM tiles, in the assembly the compiler makes of it for gfx950: it has to be
-right whatever instruction stands in front of it, because the compiler does not look for hazards inside."""
+"""The hand-written load into LDS of the GEMM tiles: what the build looks for in the compiled library, in listings that
+have and do not have it, in the library that is built, and in the assembly of a kernel that keeps a value in m0."""
 import os
 import re
 import subprocess
 
 import pytest
 
-from paper_2410_18311_amd import build
+from paper_2410_18311_amd import build, isa_check
 
 PROBE = r"""
 #include "gemm_tile.hpp"
 namespace ci {
-// a descriptor whose words come from lane reads right in front of the load
-__global__ void probe_descriptor(const char* const* p, float* out) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[1024];
-  const uint64_t a = reinterpret_cast<uint64_t>(p[threadIdx.x]);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32));
-  load_to_lds(smem, threadIdx.x * 16u, rsrc_at(reinterpret_cast<const char*>(hi << 32 | lo)));
-  __builtin_amdgcn_s_waitcnt(0);
-  out[threadIdx.x] = reinterpret_cast<float*>(smem)[threadIdx.x];
-}
 // a value that lives in m0 across the load
 __global__ void probe_m0(const char* p, int* out) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[1024];
@@ -48,21 +38,39 @@ def assembly(tmp_path_factory):
     return bodies
 
 
-def _wait_states(ins):
-    return int(ins.split()[1], 0) + 1 if ins.startswith("s_nop") else 1
+def _listing(*lines):
+    """An objdump listing of one function: instructions four bytes apart."""
+    return "0000000000001000 <kernel>:\n" + "".join(
+        f"\t{l:<58} // {0x1000 + 4 * i:012X}: 00000000\n" for i, l in enumerate(lines))
 
 
-def test_descriptor_from_lane_reads_has_five_wait_states(assembly):
-    code = assembly["probe_descriptor"]
-    at = next(i for i, l in enumerate(code) if l.startswith("buffer_load") and l.endswith("lds"))
-    first, last = map(int, re.search(r"s\[(\d+):(\d+)\]", code[at]).groups())
-    words = {f"s{i}" for i in range(first, last + 1)}
-    states = 0
-    for l in reversed(code[:at]):
-        if re.match(r"v_read(first)?lane_b32 ", l) and l.split()[1].rstrip(",") in words:
-            break
-        states += _wait_states(l)
-    assert states >= 5, code[max(0, at - 10):at + 1]
+LOAD = ("s_mov_b32 m0, s9", "s_nop 0", "buffer_load_dwordx4 v1, s[4:7], 0 offen lds")
+
+
+@pytest.mark.parametrize("lines,hazard", [
+    (("v_readfirstlane_b32 s4, v2", *LOAD), True),
+    (("v_readlane_b32 s7, v2, 3", "v_add_u32_e32 v1, v1, v2", *LOAD), True),
+    (("v_readfirstlane_b32 s8, v2", *LOAD), False),                              # not the descriptor
+    (("v_readfirstlane_b32 s5, v2", "s_nop 2", *LOAD), False),                   # five states: three, the move, the idle one
+    (("v_readfirstlane_b32 s5, v2", "s_nop 1", *LOAD), True),                    # four
+    (("v_readfirstlane_b32 s5, v2", "v_mov_b32_e32 v3, v4", "v_mov_b32_e32 v3, v4", "s_add_u32 s2, s2, 1", *LOAD), False),
+    (("s_add_u32 s4, s4, 0x80", "s_addc_u32 s5, s5, 0", *LOAD), False),          # scalar results: the hardware waits
+    (("v_cmp_gt_i32_e64 s[6:7], s0, v1", *LOAD), True),
+    (("v_add_co_u32 v1, s[4:5], v1, v2", *LOAD), True),
+    (("v_readfirstlane_b32 s4, v2", "s_nop 0", "buffer_load_dwordx4 v[8:11], v1, s[4:7], 0 offen"), False),  # the compiler's
+    # into the load by a branch over the instructions that stand in front of it
+    (("v_readfirstlane_b32 s4, v2", "s_branch 3", "s_nop 7", "s_nop 7", "s_nop 7", *LOAD), True),
+    (("v_readfirstlane_b32 s4, v2", "s_branch 0", "s_endpgm", *LOAD), False),
+])
+def test_hazards_are_found_on_every_path(lines, hazard):
+    assert bool(isa_check.hazards_in(_listing(*lines))) == hazard
+
+
+def test_the_built_library_has_no_hazard(lib):
+    listings = [isa_check.listing(c) for c in isa_check.code_objects(build.LIB_PATH) if b"gemm_" in c]
+    loads = sum(1 for text in listings for l in text.splitlines() if "buffer_load" in l and re.search(r"\blds\b", l))
+    assert loads > 1000, "the kernels with loads into LDS are not among the code looked at"
+    assert not [h for text in listings for h in isa_check.hazards_in(text)]
 
 
 def test_a_value_in_m0_survives_the_load(assembly):
