@@ -630,8 +630,8 @@ int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtyp
 // Up to four tokens over neuron-major weights: hidden values first, then the down rows, each weight read once;
 // or the decode kernel with all neurons as the core set, which reads the weights once per token and, for the
 // scores, the up matrices once more.  The latter has shorter launches, and one fewer where no scores are asked for.
-// Where the line lies, by bytes of the weights (decode kernel / columns, us).  With scores, one token: 12 MB (512 x 2048
-// fp32, 8 MB: 10.4 / 11.9; 768 x 3072 gated fp32, 28 MB: 15.6 / 13.8), 60 MB for rows of whole 4 KB (1024 x 4096 fp32,
+// Where the line lies, by bytes of the weights (decode kernel / columns, us).  With scores, one token: 13 MB (512 x 2048
+// gated fp32, 12.6 MB: 12.5 / 14.1; 768 x 3072 gated fp32, 28 MB: 15.6 / 13.8), 60 MB for rows of whole 4 KB (1024 x 4096 fp32,
 // 34 MB: 14.8 / 20.3); two: 9 MB, gated 3 MB (384 x 1536 fp32, 4.7 MB: 12.6 / 13.5; gated 512 x 2048 fp16, 6.3 MB: 16.5 /
 // 13.6); three and four: 3 MB, gated 1.5 MB (256 x 1024 fp32, 2.1 MB: 12.1 / 13.0; gated fp16, 1.6 MB: 15.5 / 14.8).  Without
 // scores, two tokens: 200 MB (2048 x 8192 fp32 30 / 36; 4096 x 16384 fp16 55 / 48); three and four: 9 MB (512 x 2048 fp32,
@@ -643,7 +643,7 @@ static bool dense_cols_pays(int64_t M, int64_t d, int64_t N, int dtype, int act,
   const int64_t row = d * elem_bytes(dtype);
   const double bytes = (double)(gated ? 3 : 2) * (double)row * (double)N;
   if (!scores) return M > 1 && bytes >= (M == 2 ? 200e6 : 9e6);
-  if (M == 1) return bytes >= (row % 4096 == 0 ? 60e6 : 12e6);
+  if (M == 1) return bytes >= (row % 4096 == 0 ? 60e6 : 13e6);
   return bytes >= (M == 2 ? (gated ? 3e6 : 9e6) : (gated ? 1.5e6 : 3e6));
 }
 

@@ -281,13 +281,14 @@ int up_tokens(const void* X, const void* w_up, const void* w_gate, const void* b
 
 // Weights of one launch up to which every token has workgroups of its own.  Tokens together / one by one (us): 4 tokens,
 // both projections of 128 x 512 gated fp32 (0.5 + 0.3 MB) 8.6 / 6.7, of 256 x 1024 fp32 (1 MB each) 7.5 / 6.7; the up
-// projection of 512 x 2048 fp16 (2.1 MB) 4.2 / 4.5, of 384 x 1536 fp32 (2.4 MB) 4.2 / 4.4.
-constexpr double kPerTokenBytes = 1.6e6;
+// projection of 512 x 2048 fp16 (2.1 MB) 4.2 / 4.5, of 384 x 1536 fp32 (2.4 MB) 4.2 / 4.4, of 256 x 1024 gated fp32
+// (2.1 MB in two matrices) 5.4 / 5.1.
+constexpr double kPerTokenBytes = 1.6e6, kPerTokenGatedBytes = 2.2e6;
 
 template <class D>
 int up_typed(const void* X, int M, const void* w_up, const void* w_gate, const void* b_up, int act,
              int d, int N, float* H, float* A, hipStream_t s) {
-  if (M > 1 && (double)d * N * D::BYTES * (act == CI_ACT_SWIGLU ? 2 : 1) <= kPerTokenBytes)
+  if (M > 1 && (double)d * N * D::BYTES * (act == CI_ACT_SWIGLU ? 2 : 1) <= (act == CI_ACT_SWIGLU ? kPerTokenGatedBytes : kPerTokenBytes))
     return up_tokens<D, 1, true>(X, w_up, w_gate, b_up, act, d, N, H, A, s, M);
   switch (M) {
     case 1: return up_tokens<D, 1>(X, w_up, w_gate, b_up, act, d, N, H, A, s);
