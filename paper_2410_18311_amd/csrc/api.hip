@@ -127,7 +127,7 @@ const KnobEntry kKnobs[] = {
     {"select_bytes", &Params::select_bytes, [](int v) { return v >= 0 && v <= 2; }},
     {"select_def2_single", &Params::select_def2_single, [](int v) { return v == 0 || v == 1; }},
     {"select_wgs_per_cu", &Params::select_wgs_per_cu, [](int v) { return v >= 1 && v <= 8; }},
-    {"gemm_tile", &Params::gemm_tile, [](int v) { return v >= -1 && v <= 4; }},
+    {"gemm_tile", &Params::gemm_tile, [](int v) { return (v >= -1 && v <= 4) || (v >= 32 && v < 160 && v % 16 >= 2 && v % 16 <= 8); }},
     {"gemm_splits", &Params::gemm_splits, [](int v) { return v >= 0 && v <= 8; }},
     {"gemv_wgs_per_cu", &Params::gemv_wgs_per_cu, [](int v) { return v >= 1 && v <= 32; }},
     {"gemv_cols_wgs_per_cu", &Params::gemv_cols_wgs_per_cu, [](int v) { return v >= 1 && v <= 4; }},
@@ -611,19 +611,27 @@ int coreinfer_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w
                                  reinterpret_cast<float*>(ws), (hipStream_t)stream);
 }
 
+// Sums of tiles split along k, whichever layout the down matrix has.
+static size_t dense_sums_bytes(int64_t M, int64_t d, int64_t N, int dtype) {
+  return std::max(gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_OUT_MAJOR, dtype, SIZE_MAX)),
+                  gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_NEURON_MAJOR, dtype, SIZE_MAX)));
+}
+
+static bool dense_sizes_ok(int64_t M, int64_t d, int64_t N) {
+  return M >= 1 && M <= CI_MAX_TOKENS && d >= 1 && d <= CI_MAX_DMODEL && N >= 1 && N <= CI_MAX_NEURONS;
+}
+// Decode partials of up to four tokens over a neuron-major down matrix.
+static size_t dense_partial_bytes(int64_t M, int64_t d, int64_t N) {
+  return round256((size_t)M * (size_t)(N < kMaxSplits ? N : kMaxSplits) * (size_t)d * sizeof(float));
+}
+
 int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes) {
   if (!dtype_ok(dtype)) return CI_ERR_BAD_DTYPE;
-  if (!bytes || M < 1 || M > CI_MAX_TOKENS || d < 1 || d > CI_MAX_DMODEL || N < 1 || N > CI_MAX_NEURONS)
-    return CI_ERR_INVALID_ARG;
+  if (!bytes || !dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
   // hidden matrix H [M, N]: fp32 on the row-dot path (M <= 4), element type
-  // on the matrix-core path; plus the decode partials for a neuron-major down.
-  size_t b = round256((size_t)M * (size_t)N * sizeof(float));
-  if (M <= 4) {
-    b += round256((size_t)M * (size_t)(N < kMaxSplits ? N : kMaxSplits) * (size_t)d * sizeof(float));
-  } else {
-    b += round256(gemm_plan_bytes(gemm_down_plan(M, d, N, dtype, SIZE_MAX)));  // sums of tiles split along k
-  }
-  *bytes = b + 256;
+  // on the matrix-core path; plus the decode partials, or the sums of tiles split along k.
+  *bytes = round256((size_t)M * (size_t)N * sizeof(float)) +
+           (M <= 4 ? dense_partial_bytes(M, d, N) : round256(dense_sums_bytes(M, d, N, dtype))) + 256;
   return CI_OK;
 }
 
@@ -653,10 +661,10 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
                         size_t ws_bytes, void* stream) {
   if (!dtype_ok(dtype) || !act_ok(act)) return CI_ERR_BAD_DTYPE;
   if (!layout_ok(down_layout)) return CI_ERR_BAD_LAYOUT;
-  size_t need = 0;
-  if (coreinfer_ffn_dense_workspace_size(M, d, N, dtype, &need) != CI_OK) return CI_ERR_INVALID_ARG;
+  if (!dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
   const size_t hidden = round256((size_t)M * (size_t)N * sizeof(float));
-  if (M > 4) need = hidden + 256;  // without room for the sums of split tiles none is split
+  // without room for the sums of split tiles none is split
+  const size_t need = hidden + (M <= 4 ? dense_partial_bytes(M, d, N) : 0) + 256;
   if (!X || !w_up || (!Y && !A) || (Y && !w_down)) return CI_ERR_INVALID_ARG;
   if ((act == CI_ACT_SWIGLU) != (w_gate != nullptr)) return CI_ERR_INVALID_ARG;
   if (act == CI_ACT_SWIGLU && b_up) return CI_ERR_INVALID_ARG;
@@ -691,7 +699,7 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
     if (rc != CI_OK || !Y) return rc;
     return launch_down_rows(H, M, w_down, b_down, dtype, d, N, Y, s);
   }
-  const GemmPlan plan = gemm_down_plan(M, d, N, dtype, ws_bytes - hidden);
+  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, ws_bytes - hidden);
   void* H = Y ? ws : nullptr;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, A, s);
   if (rc != CI_OK || !Y) return rc;
@@ -701,9 +709,8 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
 
 int coreinfer_ffn_dense_hidden_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes) {
   if (!dtype_ok(dtype)) return CI_ERR_BAD_DTYPE;
-  if (!bytes || M < 1 || M > CI_MAX_TOKENS || d < 1 || d > CI_MAX_DMODEL || N < 1 || N > CI_MAX_NEURONS)
-    return CI_ERR_INVALID_ARG;
-  *bytes = round256(gemm_plan_bytes(gemm_down_plan(M, d, N, dtype, SIZE_MAX))) + 256;  // sums of tiles split along k
+  if (!bytes || !dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
+  *bytes = round256(dense_sums_bytes(M, d, N, dtype)) + 256;  // sums of tiles split along k
   return CI_OK;
 }
 
@@ -723,7 +730,7 @@ int coreinfer_ffn_dense_hidden(const void* X, int64_t M, const void* w_up, const
     return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < 256) return CI_ERR_WORKSPACE;  // without room for the sums of split tiles none is split
   if (!aligned16(ws)) return CI_ERR_BAD_LAYOUT;
-  const GemmPlan plan = gemm_down_plan(M, d, N, dtype, ws_bytes);
+  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, ws_bytes);
   hipStream_t s = (hipStream_t)stream;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, nullptr, s);
   if (rc != CI_OK || !Y) return rc;

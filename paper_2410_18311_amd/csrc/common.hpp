@@ -127,7 +127,7 @@ struct Params {
   Knob select_def2_single{0};  // Def. 2 in one workgroup even where the parallel kernel applies
   Knob gemv_wgs_per_cu{8};
   Knob gemv_cols_wgs_per_cu{1};
-  Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256)
+  Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256; 16 + 16 tm + tn = tiles of 16 tm x 16 tn)
   Knob gemm_splits{0};       // k splits of the last round of the down projection: 0 planned
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)
   Knob reduce_cq{8};         // column quads per reduce workgroup (4, 8, 16)
@@ -258,7 +258,7 @@ struct GemmPlan {
   int full, tail, splits, k_chunk;  // tiles computed whole, tiles split along k, by how many workgroups, k of each
 };
 // Plan of the down projection whose sums of split tiles take at most `room` bytes, and what they take.
-GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int dtype, size_t room);
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, size_t room);
 size_t gemm_plan_bytes(const GemmPlan& p);
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,
                      int down_layout, int dtype, int64_t d, int64_t N, void* Y, float* partial,

@@ -57,6 +57,10 @@ int launch_gemm_wide(int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipSt
 // Smaller tiles for 16-bit types (gemm_mid.hip): rows of A x rows of B per workgroup.
 enum { kMid128x128 = 0, kMid128x256 = 1, kMid256x64 = 2, kMid128x64 = 3 };
 int launch_gemm_mid(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
+// Tiles of 16 tm rows of A x 16 tn rows of B (gemm_slim.hpp), B k-contiguous; tm 1 .. 8, tn 2 .. 8.
+constexpr int kSlim = 16;  // a tile shape's number: kSlim + 16 tm + tn
+int launch_gemm_slim_f16(int tm, int tn, int epi, const GemmArgs& g, hipStream_t s);
+int launch_gemm_slim_bf16(int tm, int tn, int epi, const GemmArgs& g, hipStream_t s);
 // fp32 kernels (gemm_f32.hip); epi: EPI_*, b_kmajor: B given as [Kk, Nn].
 int launch_gemm_f32(int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
 

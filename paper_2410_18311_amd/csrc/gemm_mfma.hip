@@ -17,23 +17,24 @@ namespace ci {
 namespace {
 
 // Y[m, n] = sum_s partial[s][tile][m, n] + bias[n], converted to the element type, over the `tail` tiles that were
-// split (bm x bn, from place `first` in the order of tile_of).  A workgroup takes the rows of a tile that give each
-// thread four columns of one row; all splits' loads of it are in flight together.  (16 rows, several turns a thread, left
-// half of the compute units without work where one row of tiles is split: 256 tokens, 4096 x 16384, both products 105.8 -> 105.0 us.)
-constexpr int reduce_rows(int bn) { return 1024 / bn; }
+// split (bm x bn, from place `first` in the order of tile_of).  A thread has four columns of one row; all splits' loads
+// of it are in flight together.  (16 rows a workgroup, several turns a thread, left half of the compute units without work
+// where one row of tiles is split: 256 tokens, 4096 x 16384, both products 105.8 -> 105.0 us.)
+constexpr int kReduceQuads = 256;
 template <class D>
-__global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ partial, const void* __restrict__ bias,
+__global__ __launch_bounds__(kReduceQuads) void split_reduce_kernel(const float* __restrict__ partial, const void* __restrict__ bias,
                                                            void* __restrict__ out, int splits, int M, int Nn, int bm,
                                                            int bn, int first, int tail) {
   using T = typename D::T;
-  const int strips = bm * bn / 1024;
+  const int strips = (bm * bn / 4 + kReduceQuads - 1) / kReduceQuads;
   int tm, tn;
   const int tile = blockIdx.x / strips, quads = bn / 4;
-  const int r = blockIdx.x % strips * reduce_rows(bn) + threadIdx.x / quads, c = threadIdx.x % quads * 4;
+  const int quad = blockIdx.x % strips * kReduceQuads + threadIdx.x;
+  const int r = quad / quads, c = quad % quads * 4;
   const size_t stride = (size_t)tail * sums_pitch(bm, bn);  // a split's tiles
   tile_of(first + tile, (M + bm - 1) / bm, (Nn + bn - 1) / bn, &tm, &tn);
   const int row = tm * bm + r, col = tn * bn + c;
-  if (row >= M || col >= Nn) return;
+  if (r >= bm || row >= M || col >= Nn) return;
   const float* p = partial + (size_t)tile * sums_pitch(bm, bn) + r * bn + c;
   float4 a = *reinterpret_cast<const float4*>(p);
 #pragma unroll 4
@@ -53,55 +54,124 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
 
 // ---- which tiles, and how they are spread over the chip ------------------------
 struct TileShape {
-  int shape;        // kMid..., or kWide
-  int bm, bn;       // rows of A, rows of B (SwiGLU: half of them gate, half up)
-  double rate;      // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
+  int shape;    // kMid..., kWide, or kSlim + ...
+  int bm, bn;   // rows of A, rows of B (SwiGLU: half of them gate, half up)
+  double rate;  // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
+  // few_rows_time: bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a fill takes when
+  // every 128 bytes of a row lie in two lines
+  double fill, flops, fixed, two_lines;
 };
 constexpr int kWide = 4;
-constexpr int kTileK = 64;       // k of a tile
+constexpr int kTileK = 64;      // k of a tile
 constexpr int kFullChip = 256;  // compute units of an MI355X
-constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12},
-                                 {kMid128x256, 128, 256, 4.4e12},
-                                 {kMid256x64, 256, 64, 3.2e12},
-                                 {kMid128x64, 128, 64, 2.7e12},
-                                 {kWide, 256, 256, 5.5e12}};
+constexpr int kSlimRows = 128;
+constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12, 144e9, 10.1e12, 4.3e-6, 0.85},
+                                 {kMid128x256, 128, 256, 4.4e12, 114e9, 16.6e12, 4.0e-6, 1.0},
+                                 {kMid256x64, 256, 64, 3.2e12, 0, 0, 0, 0},
+                                 {kMid128x64, 128, 64, 2.7e12, 212e9, 6.5e12, 4.5e-6, 1.8},
+                                 {kWide, 256, 256, 5.5e12, 1e15, 8.1e12, 4.2e-6, 0}};
+constexpr TileShape slim_shape(int tm, int tn) {
+  return TileShape{kSlim + 16 * tm + tn, 16 * tm, 16 * tn, 2.7e12, 165e9, 7.3e12, 5.3e-6, 2.6};
+}
 
-// Every workgroup takes all of a compute unit's LDS, so tiles run in rounds of 256.  Tiles of the last, partly
-// filled round can be split along k into `splits` parts each, whose fp32 sums are written, read back and
-// added by another launch (about 4.5 TB/s and 5 us).  The shape and split of the least estimated time whose sums fit
-// `room` bytes are taken; out_bytes: written per output.  Examples (both projections, former kernels -> these): 77 tokens, 4096 x 11008
-// gated 97 -> 71 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000 tokens, 7168 x 28672,
-// neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
+struct Product {
+  int M, Nn, Kk;
+  bool dual;
+  int out_bytes;  // written per output
+};
+
+// A product of `full` tiles computed whole and `tail` tiles split along k, tiles in rounds of 256: every workgroup takes all of a
+// compute unit's LDS.  The sums of split tiles are written, read back and added by another launch (about 4.5 TB/s and 5 us).
+double many_rows_time(const TileShape& ts, const Product& p, int full, int tail, int sp) {
+  const int bn = p.dual ? ts.bn / 2 : ts.bn;
+  const double t_tile = 2.0 * ts.bm * ts.bn * (double)p.Kk / ts.rate;
+  // first loads; results of a round, which nothing overlaps
+  const double t_fixed = 3e-6 + (double)ts.bm * bn * p.out_bytes * kFullChip / 4.5e12;
+  return (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed) +
+         (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed) +
+         (tail == 0 ? 0.0 : 2.0 * sp * (double)tail * ts.bm * bn * 4.0 / 4.5e12 + 5e-6);
+}
+
+// The same for up to 128 rows: what an L1 is filled with, the multiplications, and the weights that a round reads from memory
+// add up rather than hide one another (a maximum, or a power mean of any higher order, fits worse).  The rates are fitted to
+// 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to 36864, odd lengths among them, all shapes and splits.
+double few_rows_time(const TileShape& ts, const Product& p, int full, int tail, int sp) {
+  const int bn = p.dual ? ts.bn / 2 : ts.bn, rows = p.M < ts.bm ? p.M : ts.bm, tiles_m = (p.M + ts.bm - 1) / ts.bm;
+  const int odd = p.Kk * 2 % 128;  // 16-bit elements; pieces of 128 bytes of a row that lie in two cache lines:
+  const double two_lines = odd == 0 ? 0.0 : odd % 64 == 0 ? 0.5 : odd % 32 == 0 ? 0.75 : 0.875;
+  const double per_k = (rows + ts.bn) * (1.0 + ts.two_lines * two_lines) / ts.fill + (double)ts.bm * ts.bn / ts.flops;
+  auto rounds = [&](int wgs, double k, int out_bytes) {
+    auto round = [&](int n) {
+      const double columns = n > tiles_m ? (double)n / tiles_m : 1.0;  // tiles whose weights differ
+      return 2.0 * k * (per_k + columns * ts.bn / 9.9e12) + ts.fixed + (double)n * rows * bn * out_bytes / 4.5e12;
+    };
+    const int whole = wgs / kFullChip, rest = wgs % kFullChip;
+    return (whole > 0 ? whole * round(kFullChip) : 0.0) + (rest > 0 ? round(rest) : 0.0);
+  };
+  return rounds(full, p.Kk, p.out_bytes) + rounds(tail * sp, (double)p.Kk / sp, 4) +
+         (tail == 0 ? 0.0 : (double)sp * tail * rows * bn * 4.0 / 7.9e12 + 2.5e-6);
+}
+
+// Adds a shape, whole and with its last round in 2 .. 8 parts, to the best plan so far by `time`.
+template <class F>
+void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPlan& best, double& best_t) {
+  const int force_splits = params().gemm_splits;
+  const int bn = p.dual ? ts.bn / 2 : ts.bn;
+  const int tiles = ((p.M + ts.bm - 1) / ts.bm) * ((p.Nn + bn - 1) / bn);
+  for (int sp = 1; sp <= 8; ++sp) {
+    if (sp > 1 && p.Kk < 4 * kTileK * sp) break;  // at least four k tiles per split
+    const int full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
+    if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
+    const double t = time(ts, p, full, tail, sp);
+    if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
+      best_t = t;
+      best = GemmPlan{ts.shape, ts.bm, bn, full, tail, sp, p.Kk};
+      if (sp > 1) best.k_chunk = ((p.Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK;
+    }
+  }
+  if (best_t > 1e29 && force_splits > 0) best = GemmPlan{ts.shape, ts.bm, bn, tiles, 0, 1, p.Kk};
+}
+
+// The shape and split of the least estimated time whose sums fit `room` bytes.  Examples (both projections, former
+// kernels -> these): 77 tokens, 4096 x 11008 gated 97 -> 66 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000
+// tokens, 7168 x 28672, neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
-GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, int out_bytes, size_t room) {
+// Up to 128 rows the plan is made again by few_rows_time, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
+// that estimate promises 6 % or more: over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
+// most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  From 129 rows on the slim tiles are 3 to
+// 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
+// to 256 bytes, ran on them from 23 % faster to 25 % slower.
+GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, int out_bytes, size_t room) {
+  const Product p{(int)M, (int)Nn, (int)Kk, dual, out_bytes};
   GemmPlan best{};
   double best_t = 1e30;
-  const int force = params().gemm_tile, force_splits = params().gemm_splits;
-  for (const TileShape& ts : kShapes) {
-    if (force >= 0 && ts.shape != force) continue;
-    const int bn = dual ? ts.bn / 2 : ts.bn;
-    const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((Nn + bn - 1) / bn);
-    const double t_tile = 2.0 * ts.bm * ts.bn * (double)Kk / ts.rate;
-    // first loads; results of a round, which nothing overlaps
-    const double t_fixed = 3e-6 + (double)ts.bm * bn * out_bytes * kFullChip / 4.5e12;
-    for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && Kk / ((int64_t)sp * kTileK) < 4) break;  // at least four k tiles per split
-      const int64_t full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
-      if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
-      const double t_full = (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed);
-      const double t_tail = (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed);
-      const double t_sum = tail == 0 ? 0.0 : 2.0 * sp * (double)tail * ts.bm * bn * 4.0 / 4.5e12 + 5e-6;
-      const double t = t_full + t_tail + t_sum;
-      if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
-        best_t = t;
-        best = GemmPlan{ts.shape, ts.bm, bn, (int)full, (int)tail, sp, (int)Kk};
-        if (sp > 1) best.k_chunk = (int)(((Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK);
-      }
+  const int force = params().gemm_tile;
+  if (force >= kSlim && !b_kmajor) {
+    consider(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, many_rows_time, best, best_t);
+  } else {
+    for (const TileShape& ts : kShapes)
+      if (force < 0 || force >= kSlim || ts.shape == force) consider(ts, p, room, many_rows_time, best, best_t);
+    if (force < 0 && params().gemm_splits == 0 && M <= kSlimRows) {
+      double few_t = 1e30;
+      for (const TileShape& ts : kShapes)
+        if (ts.shape == best.shape && ts.fill > 0) few_t = 0.94 * few_rows_time(ts, p, best.full, best.tail, best.splits);
+      for (const TileShape& ts : kShapes)
+        if (ts.fill > 0) consider(ts, p, room, few_rows_time, best, few_t);
+      if (!b_kmajor)
+        for (int tn = 2; tn <= 8; ++tn) consider(slim_shape((p.M + 15) / 16, tn), p, room, few_rows_time, best, few_t);
     }
-    if (best_t > 1e29 && force_splits > 0) best = GemmPlan{ts.shape, ts.bm, bn, (int)tiles, 0, 1, (int)Kk};
   }
-  if (best.splits > 1) best.splits = (int)((Kk + best.k_chunk - 1) / best.k_chunk);  // rounding the chunk up can empty the last one
+  if (best.splits > 1) best.splits = ((int)Kk + best.k_chunk - 1) / best.k_chunk;  // rounding the chunk up can empty the last one
   return best;
+}
+
+template <class D>
+int launch_sums(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
+  const int strips = (p.bm * p.bn / 4 + kReduceQuads - 1) / kReduceQuads;
+  hipLaunchKernelGGL((split_reduce_kernel<D>), dim3((unsigned)(p.tail * strips)), dim3(kReduceQuads), 0, s, g.partial, g.bias,
+                     g.out_e, p.splits, g.M, g.Nn, p.bm, p.bn, p.full, p.tail);
+  CI_HIP_CHECK_LAUNCH();
+  return CI_OK;
 }
 
 template <class D, int EPI, bool BNN>
@@ -111,12 +181,15 @@ int launch_mfma(GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   g.splits = p.splits;
   g.k_chunk = p.k_chunk;
   constexpr int dtype = __is_same(D, F16) ? CI_F16 : CI_BF16;
-  const int rc = p.shape == kWide ? launch_gemm_wide(dtype, EPI, BNN, g, s) : launch_gemm_mid(p.shape, dtype, EPI, BNN, g, s);
+  int rc = CI_ERR_UNSUPPORTED;
+  if (p.shape >= kSlim) {
+    const int tm = (p.shape - kSlim) / 16, tn = (p.shape - kSlim) % 16;
+    if (!BNN) rc = __is_same(D, F16) ? launch_gemm_slim_f16(tm, tn, EPI, g, s) : launch_gemm_slim_bf16(tm, tn, EPI, g, s);
+  } else {
+    rc = p.shape == kWide ? launch_gemm_wide(dtype, EPI, BNN, g, s) : launch_gemm_mid(p.shape, dtype, EPI, BNN, g, s);
+  }
   if (rc != CI_OK || p.tail == 0) return rc;
-  hipLaunchKernelGGL((split_reduce_kernel<D>), dim3((unsigned)(p.tail * (p.bm / reduce_rows(p.bn)))), dim3(256), 0, s, g.partial, g.bias,
-                     g.out_e, p.splits, g.M, g.Nn, p.bm, p.bn, p.full, p.tail);
-  CI_HIP_CHECK_LAUNCH();
-  return CI_OK;
+  return launch_sums<D>(g, p, s);
 }
 
 template <int EPI, bool BNN>
@@ -145,7 +218,7 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
   g.out_f = A;
   g.k_chunk = (int)d;
   g.partial = nullptr;
-  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, 6, 0);
+  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, (H ? 2 : 0) + (A ? 4 : 0), 0);
   if (act == CI_ACT_SWIGLU) {
     g.B0 = w_gate;
     g.B1 = w_up;
@@ -159,8 +232,8 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
 }
 
 // The down projection's plan, made once per call: the size check, the place of the sums and the launches all go by it.
-GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int dtype, size_t room) {
-  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, d, N, false, 2, room);
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, size_t room) {
+  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, d, N, false, down_layout == CI_DOWN_NEURON_MAJOR, 2, room);
 }
 
 size_t gemm_plan_bytes(const GemmPlan& p) {

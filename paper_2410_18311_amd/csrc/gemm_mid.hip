@@ -13,8 +13,8 @@ namespace ci {
 
 namespace {
 
-// WM x WN waves of TI x TJ blocks of 32x32.
-template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ>
+// WM x WN waves of TI x TJ blocks of 32x32.  ONCE: see read_once.
+template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_mid_kernel(GemmArgs g) {
   using T = typename D::T;
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
@@ -93,7 +93,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       }
       base = ((DUAL && q >= PB / 2) ? Ub : Bb) + (size_t)t * stepB;
     }
-    load_to_lds(st + (p < PA ? 4 * p + wave : BM / 8 + 4 * (p - PA) + wave) * 1024, off, rsrc_at(base));
+    if (p < PA) load_to_lds(st + (4 * p + wave) * 1024, off, rsrc_at(base));
+    else load_to_lds<ONCE>(st + (BM / 8 + 4 * (p - PA) + wave) * 1024, off, rsrc_at(base));
   };
 
   f32x16 acc[TI][TJ];
@@ -196,8 +197,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ>
 int launch_shape(const GemmArgs& g, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_mid_kernel<D, EPI, BNN, WM, WN, TI, TJ>), dim3((unsigned)(g.full + g.tail * g.splits)),
-                     dim3(256), 0, s, g);
+  const dim3 grid((unsigned)(g.full + g.tail * g.splits));
+  if (!BNN && read_once(g, EPI == EPI_SWIGLU))
+    hipLaunchKernelGGL((gemm_mid_kernel<D, EPI, BNN, WM, WN, TI, TJ, !BNN>), grid, dim3(256), 0, s, g);
+  else
+    hipLaunchKernelGGL((gemm_mid_kernel<D, EPI, BNN, WM, WN, TI, TJ, false>), grid, dim3(256), 0, s, g);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }

@@ -65,14 +65,33 @@ __device__ __forceinline__ i32x4 rsrc_at(const char* p) {
 // descriptors here are scalar, which need none; the build looks at every such load of the library and fails where the
 // compiler has come to something else (isa_check.py).  Waiting here instead, whatever stands before, costs the 40
 // loads that a small product starts with 0.35 us (four idle states: both products of 5 x 256 x 1024 13.2 -> 13.8 us; a copy
-// of the descriptor by scalar moves 13.6).
+// of the descriptor by scalar moves 13.6).  ONCE: the lines are the first to leave the caches.
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t off, i32x4 rsrc) {
   const uint32_t m = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lds;
   uint32_t m0;  // says that m0 is written (as a clobber it is refused with a warning)
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
-               : "={m0}"(m0)
-               : "s"(m), "v"(off), "s"(rsrc)
-               : "memory");
+  if constexpr (ONCE)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen nt lds"
+                 : "={m0}"(m0)
+                 : "s"(m), "v"(off), "s"(rsrc)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+                 : "={m0}"(m0)
+                 : "s"(m), "v"(off), "s"(rsrc)
+                 : "memory");
+}
+
+// Whether the rows of B go through the caches as data that is not read again: products of one row of tiles whose weights
+// are so large that the memory-side cache (256 MB) keeps nothing of them from one call to the next.  They then leave the caches
+// to the rows of A: 77 x 4096 x 11008 gated 72.5 -> 69.3, 5 x 5824 x 22656 gated 145 -> 126 us
+// (both projections).  Smaller weights may still be cached in part (two layers in turn: 74 x 2944 x 9152, 54 MB a product,
+// 36 us, 45 this way; 10 x 1792 x 4800 gated 17.0 and 20.8), and pieces that lie in two lines each need
+// both lines to stay for the next k-tile (9 x 5912 x 21232 gated 165 us, 192 this way).  Two rows of tiles read
+// B twice: 256 x 4096 x 16384 104.7 -> 102.8, but 145 x 2816 x 9728 gated 71 -> 77.6.
+inline bool read_once(const GemmArgs& g, bool dual) {
+  const double bytes = (dual ? 2.0 : 1.0) * g.Nn * g.Kk * 2.0;
+  return g.M <= 128 && bytes >= 80e6 && g.ldb % 64 == 0;
 }
 
 // Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,

@@ -78,6 +78,41 @@ def test_dense_tile_shapes(lib, tile, act, layout, dtype, splits):
         lib.dev_set_param("gemm_splits", 0)
 
 
+# Tiles of 16 tm x 16 tn (16 + 16 tm + tn), whole and with k split over 3 workgroups per tile: one row past a tile and one
+# short of it, columns that end inside a tile, k of one k-tile (three waves without any), k that ends inside one, k that
+# does not divide by the four waves.
+@pytest.mark.parametrize("tm", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tn", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("act,dtype", [("relu", torch.float16), ("swiglu", torch.bfloat16)])
+def test_dense_slim_tiles(lib, tm, tn, act, dtype):
+    try:
+        lib.dev_set_param("gemm_tile", 16 + 16 * tm + tn)
+        for splits in (1, 3):
+            lib.dev_set_param("gemm_splits", splits)
+            for M, d, N in [(max(5, 16 * tm - 3), 8, 24), (16 * tm + 1, 16 * tn + 8, 840), (16 * tm, 456, 16 * tn * 3)]:
+                _check_dense(lib, dtype, act, "out_major", M, d, N, hidden=tm % 2 == 0)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+
+
+# As planned: token counts on both sides of the slim tiles' range, with a workspace for sums and with the least there is
+@pytest.mark.parametrize("M", [5, 16, 17, 64, 77, 128, 129, 256, 257])
+@pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
+def test_dense_planned_few_rows(lib, M, layout):
+    _check_dense(lib, torch.float16, "relu", layout, M, 1032, 3080)
+    _check_dense(lib, torch.bfloat16, "swiglu", layout, M, 520, 1400, hidden=True)
+    d, N = 1032, 3080
+    w = rand_weights(d, N, torch.float16, "relu", layout, seed=M, device=DEV)
+    X = torch.randn(M, d, generator=torch.Generator().manual_seed(M)).half().to(DEV)
+    args = (X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], layout, "relu")
+    least = (M * N * 4 + 255) // 256 * 256 + 256
+    assert lib.ffn_dense_workspace_size(M, d, N, torch.float16) >= least
+    Y0, _ = lib.ffn_dense(*args)
+    Y1, _ = lib.ffn_dense(*args, ws=torch.empty(least, dtype=torch.uint8, device=DEV))
+    assert_close_rms(Y1, f64(Y0), torch.float16, "Y without room for sums")
+
+
 @pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
 def test_dense_split_last_round_only(lib, layout):
     """A down projection of more than 256 tiles whose last round is split along k: 17 x 16 tiles of
