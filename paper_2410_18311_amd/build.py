@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libcoreinfer.so")
 
-SOURCES = ["api.hip", "ffn_decode.hip", "ffn_decode_fused.hip", "ffn_union.hip", "select.hip", "compact.hip", "centroid.hip", "gemv.hip", "gemm_mfma.hip", "gemm_f32.hip", "gemm_wide.hip", "gemm_mid.hip", "gemm_slim_f16.hip", "gemm_slim_bf16.hip", "stream_probe.hip"]
+SOURCES = ["api.hip", "ffn_decode.hip", "ffn_decode_small.hip", "ffn_decode_fused.hip", "ffn_union.hip", "select.hip", "compact.hip", "centroid.hip", "gemv.hip", "gemm_mfma.hip", "gemm_f32.hip", "gemm_wide.hip", "gemm_mid.hip", "gemm_slim_f16.hip", "gemm_slim_bf16.hip", "stream_probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -487,6 +487,7 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   GatheredUnion plan;
   if (w->core_idx && gathered_union_pays(B, w->K, w->N, w->d, dtype, act, &plan))
     return launch_gathered_union(x, B, w, dtype, act, y, partial, plan, s);
+  if (!w->core_idx && decode_small_pays(B, w->K, w->d, dtype, act)) return launch_ffn_decode_small(x, B, w, dtype, act, y, s);
   DecodeArgs a;
   a.x = x;
   a.w_up = w->w_up;

@@ -1,0 +1,88 @@
+"""The one-launch decode of small layers (every workgroup computes all hidden values) against the oracle and, by its rule,
+against the two launches."""
+import pytest
+import torch
+
+from oracle import coreinfer_oracle as orc
+from tests._util import assert_close_rms, f64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _layer(dt, act, d, K, seed):
+    g = torch.Generator().manual_seed(seed)
+    mat = lambda *s: (torch.randn(*s, generator=g) * 0.05).to(dt).to(DEV)  # noqa: E731
+    return dict(up=mat(K, d), gate=mat(K, d) if act == "swiglu" else None, b_up=mat(K) if act == "relu" else None,
+                down=mat(K, d), b_down=mat(d))
+
+
+def _reference(w, act, x):
+    down = f64(w["down"]).T
+    if act == "relu":
+        return orc.ffn_relu(f64(x), None, f64(w["up"]), f64(w["b_up"]), down, f64(w["b_down"]))
+    return orc.ffn_swiglu(f64(x), None, f64(w["gate"]), f64(w["up"]), down, f64(w["b_down"]))
+
+
+# rows of one vector, of the lanes of a quarter, half and whole wave, one vector more than each, and of two loads; one
+# neuron, one short of and one past a batch of rows, more than the down rows a thread holds (512), the most there can be
+@pytest.mark.parametrize("act", ["relu", "swiglu"])
+@pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
+def test_small_decode_shapes(lib, act, dt):
+    vec = 4 if dt == torch.float32 else 8
+    lib.dev_set_param("decode_small", 2)
+    try:
+        for vecs in (1, 15, 16, 17, 32, 33, 64, 65, 128):
+            d = vecs * vec
+            for K, B in ((1, 1), (63, 2), (65, 1), (257, 4), (513, 1), (4096, 1)):
+                print("small decode case", dt, act, d, K, B, flush=True)
+                w = _layer(dt, act, d, K, d + K)
+                x = torch.randn(B, d, generator=torch.Generator().manual_seed(K)).to(dt).to(DEV)
+                y = torch.full((B * d + 64,), -7.0, dtype=dt, device=DEV)
+                desc = lib.make_weights(w["up"], w["gate"], w["b_up"], w["down"], w["b_down"])
+                # a workspace of anything: this path uses none
+                ws = torch.full((lib.ffn_decode_workspace_size(B, K, d),), 255, dtype=torch.uint8, device=DEV)
+                lib.ffn_decode(x, desc, act, y=y[:B * d].view(B, d), ws=ws)
+                torch.cuda.synchronize()
+                assert bool((y[B * d:] == -7.0).all()), "stored past the end"
+                assert_close_rms(y[:B * d].view(B, d), _reference(w, act, x), dt, "y")
+    finally:
+        lib.dev_set_param("decode_small", 1)
+
+
+# both sides of the rule's lines, with the setting that every program has: elements, vectors of a row, neurons, tokens
+@pytest.mark.parametrize("d,K,B", [(256, 512, 1), (256, 513, 1), (512, 256, 4), (512, 256, 5), (516, 8, 1), (4, 2048, 1), (8, 4097, 1)])
+def test_small_decode_rule(lib, d, K, B):
+    w = _layer(torch.float32, "relu", d, K, d + K)
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(1)).to(DEV)
+    desc = lib.make_weights(w["up"], None, w["b_up"], w["down"], w["b_down"])
+    got = lib.ffn_decode(x, desc, "relu")
+    assert_close_rms(got, _reference(w, "relu", x), torch.float32, "y")
+    static = lib.ffn_decode_static(x, desc, "relu")
+    assert torch.equal(static, got)
+    # inputs that are not finite reach the output as they do through two launches
+    x[0, 0] = float("inf")
+    lib.dev_set_param("decode_small", 0)
+    try:
+        two = lib.ffn_decode(x, desc, "relu")
+    finally:
+        lib.dev_set_param("decode_small", 1)
+    one = lib.ffn_decode(x, desc, "relu")
+    assert torch.equal(torch.isnan(one), torch.isnan(two)) and torch.equal(torch.isinf(one), torch.isinf(two))
+
+
+def test_small_decode_graph(lib):
+    w = _layer(torch.float32, "swiglu", 128, 300, 9)
+    desc = lib.make_weights(w["up"], w["gate"], None, w["down"], w["b_down"])
+    x, y = torch.zeros(1, 128, device=DEV), torch.empty(1, 128, device=DEV)
+    ws = lib.decode_workspace(1, 300, 128, DEV)
+    lib.ffn_decode(x, desc, "swiglu", y=y, ws=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        lib.ffn_decode(x, desc, "swiglu", y=y, ws=ws)
+    for i in range(4):
+        x.copy_(torch.randn(1, 128, generator=torch.Generator().manual_seed(i)))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, lib.ffn_decode(x, desc, "swiglu"))
