@@ -1,0 +1,38 @@
+"""The per-token selection kernel at the ends of rows: what lies behind a row is never a key."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import coreinfer_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# rows that end inside, at and one past an item of 1024 keys, one item and an odd number of them, the last of each build
+# (4, 8, 16, 24, 40 items); longer strides with larger values, infinities and NaN behind the row
+@pytest.mark.parametrize("N", [1, 1023, 1024, 1025, 3072, 4097, 13824, 16384, 16385, 23552, 36865, 40960])
+@pytest.mark.parametrize("M", [3, 300])
+@pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
+def test_select_ends_of_rows(lib, N, M, dt):
+    if M > 3 and N > 17000:
+        M = 20
+    print("row end case", N, M, dt, flush=True)
+    g = torch.Generator().manual_seed(N + M)
+    wide = torch.randn(M, N + 40, generator=g)
+    wide[:, N:] = torch.tensor([float("inf"), 60000.0, float("nan"), 9.0]).repeat(10)
+    if N > 8:
+        wide[0, :4] = torch.tensor([float("inf"), float("nan"), -float("inf"), 0.0])
+        wide[1, :] = -wide[1, :].abs()      # nothing positive
+        wide[1, N:] = 7.0
+        wide[2, :] = 1.5                    # one value
+    wide = wide.to(dt)
+    act = wide.to(DEV)[:, :N]
+    alpha, beta = 0.2, 0.4
+    if dt == torch.float32:
+        S, counts = lib.select(act, alpha, beta)
+    else:
+        S, counts = lib.select_hidden(act, "relu", alpha, beta)
+    S_ref, c_ref = orc.select(wide[:, :N].float().numpy(), alpha, beta)
+    assert np.array_equal(counts.cpu().numpy(), c_ref)
+    assert np.array_equal(S.cpu().numpy(), S_ref)
