@@ -749,19 +749,32 @@ __global__ __launch_bounds__(1024) void count_kernel(const typename IN::T* __res
 __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __restrict__ counts,
                                                              const uint32_t* __restrict__ ghist, int N, int K,
                                                              int32_t* __restrict__ core_idx, int vec_ok,
-                                                             int64_t counts_stride) {
+                                                             int64_t counts_stride, int max_count) {
   counts += (size_t)blockIdx.y * counts_stride;  // blockIdx.y: the sentence of a batch
   ghist += (size_t)blockIdx.y * kCountBins * kHistCopies;
   core_idx += (size_t)blockIdx.y * K;
   __shared__ __attribute__((aligned(16))) uint32_t wtot[4], wg[kMaxWaves], we[kMaxWaves];
   __shared__ uint32_t T_s, need_s;
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  // (0) the counts that are compared with T further down, requested before the histogram is waited for: this block's own
+  // and the first eight vectors a thread of those before it
+  const int before = blockIdx.x * 256;
+  const int4* cv = reinterpret_cast<const int4*>(counts);
+  const int nv = vec_ok ? before / 4 : 0;
+  int4 v[8];
+  if (nv > 0) {  // uniform
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = cv[min(tid + u * nt, nv - 1)];
+  }
+  const int n = before + tid;
+  const bool valid = tid < 256 && n < N;
+  const uint32_t c = valid ? (uint32_t)counts[n] : 0u;
   // (1) T: the count value with #(count > T) < K <= #(count >= T).  Thread t < 256 owns the eight
   // bins 2047 - 8t - j, highest first, so the keys above a bin are a prefix sum over threads.
   uint32_t bins[8], mine = 0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) bins[j] = 0;
-  if (tid < kCountBins / 8) {
+  if (tid < kCountBins / 8 && kCountBins - 8 - tid * 8 <= max_count) {  // no count is above max_count
 #pragma unroll
     for (int r = 0; r < kHistCopies; ++r) {
       const uint4* hp = reinterpret_cast<const uint4*>(ghist + r * kCountBins + (kCountBins - 8 - tid * 8));
@@ -797,15 +810,13 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
   const uint32_t T = T_s, need = need_s;
   // (2) neurons before this block that are above / at T: all threads, eight loads in flight each
   // (the loop is nothing but latency)
-  const int before = blockIdx.x * 256;
   uint32_t g = 0, e = 0;
   if (vec_ok) {
-    const int4* cv = reinterpret_cast<const int4*>(counts);
-    const int nv = before / 4;
     for (int i0 = tid; i0 < nv; i0 += nt * 8) {
-      int4 v[8];
+      if (i0 != tid) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = cv[min(i0 + u * nt, nv - 1)];
+        for (int u = 0; u < 8; ++u) v[u] = cv[min(i0 + u * nt, nv - 1)];
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (i0 + u * nt < nv) {
@@ -816,14 +827,14 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
     }
   } else {
     for (int i0 = tid; i0 < before; i0 += nt * 8) {
-      uint32_t v[8];
+      uint32_t w[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = (uint32_t)counts[min(i0 + u * nt, before - 1)];
+      for (int u = 0; u < 8; ++u) w[u] = (uint32_t)counts[min(i0 + u * nt, before - 1)];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (i0 + u * nt < before) {
-          g += v[u] > T;
-          e += v[u] == T;
+          g += w[u] > T;
+          e += w[u] == T;
         }
       }
     }
@@ -832,9 +843,6 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
   g = wave_prefix_incl(g);
   e = wave_prefix_incl(e);
   // (3) this block's neurons (threads 0..255), in index order = wave, then lane
-  const int n = before + tid;
-  const bool valid = tid < 256 && n < N;
-  const uint32_t c = valid ? (uint32_t)counts[n] : 0u;
   const bool isg = valid && c > T, ise = valid && c == T;
   const uint64_t bg = __ballot(isg), be = __ballot(ise);
   if (lane == 63) {
@@ -1292,7 +1300,7 @@ int launch_select(const void* act, int act_dtype, int take_abs, int64_t M64, int
     if (parallel_final) {
       const int cvec = (reinterpret_cast<uintptr_t>(counts) & 15u) == 0 ? 1 : 0;
       hipLaunchKernelGGL(def2_parallel_kernel, dim3(nblocks, B), dim3(1024), 0, s, counts, ghist, N, K, core_idx,
-                         cvec && counts_stride % 4 == 0, counts_stride);
+                         cvec && counts_stride % 4 == 0, counts_stride, (int)max_count);
       CI_HIP_CHECK_LAUNCH();
       return CI_OK;
     }
