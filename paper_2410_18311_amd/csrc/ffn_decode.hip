@@ -487,7 +487,12 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   GatheredUnion plan;
   if (w->core_idx && gathered_union_pays(B, w->K, w->N, w->d, dtype, act, &plan))
     return launch_gathered_union(x, B, w, dtype, act, y, partial, plan, s);
-  if (!w->core_idx && decode_small_pays(B, w->K, w->d, dtype, act)) return launch_ffn_decode_small(x, B, w, dtype, act, y, s);
+  // in place, the one launch would store outputs that other workgroups still read as inputs
+  const size_t bytes = (size_t)B * (size_t)w->d * (dtype == CI_F32 ? 4 : 2);
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+  const bool apart = x0 + bytes <= y0 || y0 + bytes <= x0;
+  if (!w->core_idx && apart && decode_small_pays(B, w->K, w->d, dtype, act))
+    return launch_ffn_decode_small(x, B, w, dtype, act, y, s);
   DecodeArgs a;
   a.x = x;
   a.w_up = w->w_up;

@@ -86,3 +86,25 @@ def test_small_decode_graph(lib):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, lib.ffn_decode(x, desc, "swiglu"))
+
+
+# y over x, whole or in part: as two launches leave it, to the bit
+@pytest.mark.parametrize("shift", [0, 1, -1])
+def test_small_decode_in_place(lib, shift):
+    d, K, B = 256, 200, 4
+    w = _layer(torch.float32, "relu", d, K, 5)
+    desc = lib.make_weights(w["up"], None, w["b_up"], w["down"], w["b_down"])
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(2)).to(DEV)
+
+    def run(mode):
+        buf = torch.zeros(3 * B * d, device=DEV)
+        xin = buf[B * d:2 * B * d].view(B, d)
+        xin.copy_(x)
+        o = B * d + shift * d
+        lib.dev_set_param("decode_small", mode)
+        try:
+            lib.ffn_decode(xin, desc, "relu", y=buf[o:o + B * d].view(B, d))
+        finally:
+            lib.dev_set_param("decode_small", 1)
+        return buf
+    assert torch.equal(run(1), run(0))
