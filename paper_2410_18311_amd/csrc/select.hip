@@ -370,14 +370,18 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
     asm volatile("" : "+v"(lane_id));
     if constexpr (ITEMS > 0) {
       // One descriptor for the row: a lane offset that is the same for every item, the item as a scalar offset, and zero,
-      // which is no key, from past the end of the row.
-      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TI*>(row), 0, (int)(N * sizeof(TI)), 0x00020000);
+      // which is no key, from past the end of the row.  The range check subtracts the scalar offset from the row's length, so
+      // it goes no further than that; the length is opaque so that the offsets are not all made ahead of the token loop.
+      int row_bytes = (int)(N * sizeof(TI));
+      asm volatile("" : "+s"(row_bytes));
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TI*>(row), 0, row_bytes, 0x00020000);
       const int lane_off = (int)(lane_id * sizeof(TI));
       TI av[ITEMS];
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i) {
-        if constexpr (kNarrow) av[i] = __builtin_bit_cast(TI, __builtin_amdgcn_raw_buffer_load_b16(rsrc, lane_off, i * nt * (int)sizeof(TI), 0));
-        else av[i] = __builtin_bit_cast(TI, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_off, i * nt * (int)sizeof(TI), 0));
+        const int item = min(i * nt * (int)sizeof(TI), row_bytes);
+        if constexpr (kNarrow) av[i] = __builtin_bit_cast(TI, __builtin_amdgcn_raw_buffer_load_b16(rsrc, lane_off, item, 0));
+        else av[i] = __builtin_bit_cast(TI, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_off, item, 0));
       }
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i) kc[i] = act_key(IN::bits(av[i]), sign_mask, kNoKey);
