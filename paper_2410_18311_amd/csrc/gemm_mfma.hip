@@ -141,6 +141,11 @@ void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPl
 // most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  From 129 rows on the slim tiles are 3 to
 // 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
 // to 256 bytes, ran on them from 23 % faster to 25 % slower.
+// The up projection's plan of more rows is made again too, without them, and taken where the estimate promises 24 % or more:
+// these are row lengths that are no multiple of 64 bytes, whose pieces lie in two cache lines and which tiles of 256 x 256 read
+// least often.  Of 630 measured products of 129 to 4096 rows 21 change, 3 to 16 % faster but one (0.7 % slower), e.g. 577 x 6256 x 16328 gated
+// 376 -> 316 us, 444 x 5624 x 16448 344 -> 289; promises of 17 to 22 % gave from 13 % less to 9 % more time, and the down projection's plans
+// by this estimate one in fifteen more than 3 % slower.
 GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, int out_bytes, size_t room) {
   const Product p{(int)M, (int)Nn, (int)Kk, dual, out_bytes};
   GemmPlan best{};
@@ -151,13 +156,14 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
   } else {
     for (const TileShape& ts : kShapes)
       if (force < 0 || force >= kSlim || ts.shape == force) consider(ts, p, room, many_rows_time, best, best_t);
-    if (force < 0 && params().gemm_splits == 0 && M <= kSlimRows) {
-      double few_t = 1e30;
+    const bool few = M <= kSlimRows;
+    if (force < 0 && params().gemm_splits == 0 && (few || room == 0)) {
+      double few_t = few ? 1e30 : 0.0;
       for (const TileShape& ts : kShapes)
-        if (ts.shape == best.shape && ts.fill > 0) few_t = 0.94 * few_rows_time(ts, p, best.full, best.tail, best.splits);
+        if (ts.shape == best.shape && ts.fill > 0) few_t = (few ? 0.94 : 0.76) * few_rows_time(ts, p, best.full, best.tail, best.splits);
       for (const TileShape& ts : kShapes)
         if (ts.fill > 0) consider(ts, p, room, few_rows_time, best, few_t);
-      if (!b_kmajor)
+      if (few && !b_kmajor)
         for (int tn = 2; tn <= 8; ++tn) consider(slim_shape((p.M + 15) / 16, tn), p, room, few_rows_time, best, few_t);
     }
   }

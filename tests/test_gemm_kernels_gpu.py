@@ -207,3 +207,10 @@ def test_settings_that_change_during_a_call_stay_inside_its_workspace(lib):
     assert bool((ws[size:] == 0xA5).all()), "stored past the workspace"
     for y in ys:
         assert_close_rms(y, y_ref, torch.float16, "while settings change")
+
+
+# up projections that the second estimate gives to 256 x 256 tiles: rows of no multiple of 64 bytes, last tiles of few
+# rows and columns
+@pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 2400, 1288, 4440), ("relu", torch.float16, 3166, 1832, 5616)])
+def test_dense_odd_rows_wide_tiles(lib, act, dtype, M, d, N):
+    _check_dense(lib, dtype, act, "out_major", M, d, N)
