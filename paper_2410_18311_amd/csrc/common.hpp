@@ -220,9 +220,10 @@ int decode_splits_bound(int64_t B, int64_t K);  // at least decode_splits; what 
 // max_slices: how many slices per sentence the partial sums have room for
 int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
                       void* y, float* partial, int max_slices, hipStream_t s);
-// Small layers in one launch (ffn_decode_small.hip): every workgroup computes all hidden values.
-bool decode_small_pays(int64_t B, int64_t K, int64_t d, int dtype, int act);
-int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, hipStream_t s);
+// Small layers in one launch (ffn_decode_small.hip), with the outputs of n_wg slices to the bit.
+bool decode_small_pays(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s);
+int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg,
+                            hipStream_t s);
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
                          int dtype, hipStream_t s);
 size_t fused_decode_ws_bytes(int64_t K);

@@ -487,12 +487,14 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   GatheredUnion plan;
   if (w->core_idx && gathered_union_pays(B, w->K, w->N, w->d, dtype, act, &plan))
     return launch_gathered_union(x, B, w, dtype, act, y, partial, plan, s);
+  int n_wg = decode_splits(B, w->K, w->d * (dtype == CI_F32 ? 4 : 2), w->core_idx != nullptr);
+  if (n_wg > max_slices) n_wg = max_slices;
   // in place, the one launch would store outputs that other workgroups still read as inputs
   const size_t bytes = (size_t)B * (size_t)w->d * (dtype == CI_F32 ? 4 : 2);
   const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
   const bool apart = x0 + bytes <= y0 || y0 + bytes <= x0;
-  if (!w->core_idx && apart && decode_small_pays(B, w->K, w->d, dtype, act))
-    return launch_ffn_decode_small(x, B, w, dtype, act, y, s);
+  if (!w->core_idx && apart && decode_small_pays(B, w->K, w->d, dtype, act, n_wg, s))
+    return launch_ffn_decode_small(x, B, w, dtype, act, y, n_wg, s);
   DecodeArgs a;
   a.x = x;
   a.w_up = w->w_up;
@@ -504,8 +506,7 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   a.K = (int)w->K;
   a.d = (int)w->d;
   a.N = (int)w->N;
-  a.n_wg = decode_splits(B, w->K, w->d * (dtype == CI_F32 ? 4 : 2), w->core_idx != nullptr);
-  if (a.n_wg > max_slices) a.n_wg = max_slices;
+  a.n_wg = n_wg;
   a.nt_store = params().decode_nt_store;
   switch (dtype) {
     case CI_F32: return launch_dtype<F32>(a, (int)B, act, w->b_down, y, s);

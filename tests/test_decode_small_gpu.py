@@ -1,5 +1,5 @@
-"""The one-launch decode of small layers (every workgroup computes all hidden values) against the oracle and, by its rule,
-against the two launches."""
+"""The one-launch decode of small layers (every workgroup computes all hidden values): against the oracle, the same bits as
+the two launches in every form of the call, and which of the two a call takes."""
 import pytest
 import torch
 
@@ -45,18 +45,32 @@ def test_small_decode_shapes(lib, act, dt):
                 lib.ffn_decode(x, desc, act, y=y[:B * d].view(B, d), ws=ws)
                 torch.cuda.synchronize()
                 assert bool((y[B * d:] == -7.0).all()), "stored past the end"
+                assert bool((ws == 255).all()), "two launches"
+                lib.dev_set_param("decode_small", 0)
+                two = lib.ffn_decode(x, desc, act)
+                lib.dev_set_param("decode_small", 2)
+                assert torch.equal(y[:B * d].view(B, d), two), "other bits than two launches"
                 assert_close_rms(y[:B * d].view(B, d), _reference(w, act, x), dt, "y")
     finally:
         lib.dev_set_param("decode_small", 1)
 
 
+def _one_launch(lib, x, desc, act, y=None):
+    """The output of a call and whether it took one launch: two leave partial sums in the workspace."""
+    ws = torch.full((lib.ffn_decode_workspace_size(x.shape[0], desc.K, x.shape[1]),), 255, dtype=torch.uint8, device=DEV)
+    y = lib.ffn_decode(x, desc, act, y=y, ws=ws)
+    return y, bool((ws == 255).all())
+
+
 # both sides of the rule's lines, with the setting that every program has: elements, vectors of a row, neurons, tokens
-@pytest.mark.parametrize("d,K,B", [(256, 512, 1), (256, 513, 1), (512, 256, 4), (512, 256, 5), (516, 8, 1), (4, 2048, 1), (8, 4097, 1)])
-def test_small_decode_rule(lib, d, K, B):
+@pytest.mark.parametrize("d,K,B,one", [(256, 512, 1, True), (256, 513, 1, False), (512, 256, 4, True), (512, 256, 5, False),
+                                       (516, 8, 1, False), (4, 2048, 1, True), (4, 2049, 1, False), (8, 4097, 1, False)])
+def test_small_decode_rule(lib, d, K, B, one):
     w = _layer(torch.float32, "relu", d, K, d + K)
     x = torch.randn(B, d, generator=torch.Generator().manual_seed(1)).to(DEV)
     desc = lib.make_weights(w["up"], None, w["b_up"], w["down"], w["b_down"])
-    got = lib.ffn_decode(x, desc, "relu")
+    got, took_one = _one_launch(lib, x, desc, "relu")
+    assert took_one == one
     assert_close_rms(got, _reference(w, "relu", x), torch.float32, "y")
     static = lib.ffn_decode_static(x, desc, "relu")
     assert torch.equal(static, got)
@@ -71,40 +85,42 @@ def test_small_decode_rule(lib, d, K, B):
     assert torch.equal(torch.isnan(one), torch.isnan(two)) and torch.equal(torch.isinf(one), torch.isinf(two))
 
 
-def test_small_decode_graph(lib):
-    w = _layer(torch.float32, "swiglu", 128, 300, 9)
-    desc = lib.make_weights(w["up"], w["gate"], None, w["down"], w["b_down"])
-    x, y = torch.zeros(1, 128, device=DEV), torch.empty(1, 128, device=DEV)
-    ws = lib.decode_workspace(1, 300, 128, DEV)
-    lib.ffn_decode(x, desc, "swiglu", y=y, ws=ws)
+# layers on both sides of the line for captured calls (64 K elements): the same bits as launched, whichever way either goes
+@pytest.mark.parametrize("act,d,K,one", [("swiglu", 128, 256, True), ("swiglu", 128, 300, False), ("relu", 256, 256, True),
+                                         ("relu", 256, 257, False)])
+def test_small_decode_graph(lib, act, d, K, one):
+    w = _layer(torch.float32, act, d, K, 9)
+    desc = lib.make_weights(w["up"], w["gate"], w["b_up"], w["down"], w["b_down"])
+    x, y = torch.zeros(1, d, device=DEV), torch.empty(1, d, device=DEV)
+    ws = lib.decode_workspace(1, K, d, DEV)
+    lib.ffn_decode(x, desc, act, y=y, ws=ws)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        lib.ffn_decode(x, desc, "swiglu", y=y, ws=ws)
+        lib.ffn_decode(x, desc, act, y=y, ws=ws)
     for i in range(4):
-        x.copy_(torch.randn(1, 128, generator=torch.Generator().manual_seed(i)))
+        x.copy_(torch.randn(1, d, generator=torch.Generator().manual_seed(i)))
+        ws.fill_(255)
         g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(y, lib.ffn_decode(x, desc, "swiglu"))
+        assert bool((ws == 255).all()) == one
+        got, took_one = _one_launch(lib, x, desc, act)
+        assert took_one
+        assert torch.equal(y, got)
 
 
-# y over x, whole or in part: as two launches leave it, to the bit
-@pytest.mark.parametrize("shift", [0, 1, -1])
+# y over x, whole or in part: two launches, and where they do not lie over one another the same bits from one
+@pytest.mark.parametrize("shift", [0, 1, -1, 4, -4])
 def test_small_decode_in_place(lib, shift):
     d, K, B = 256, 200, 4
     w = _layer(torch.float32, "relu", d, K, 5)
     desc = lib.make_weights(w["up"], None, w["b_up"], w["down"], w["b_down"])
     x = torch.randn(B, d, generator=torch.Generator().manual_seed(2)).to(DEV)
-
-    def run(mode):
-        buf = torch.zeros(3 * B * d, device=DEV)
-        xin = buf[B * d:2 * B * d].view(B, d)
-        xin.copy_(x)
-        o = B * d + shift * d
-        lib.dev_set_param("decode_small", mode)
-        try:
-            lib.ffn_decode(xin, desc, "relu", y=buf[o:o + B * d].view(B, d))
-        finally:
-            lib.dev_set_param("decode_small", 1)
-        return buf
-    assert torch.equal(run(1), run(0))
+    apart, took_one = _one_launch(lib, x, desc, "relu")
+    assert took_one
+    buf = torch.zeros(9 * B * d, device=DEV)
+    buf[4 * B * d:5 * B * d].view(B, d).copy_(x)
+    o = (4 * B + shift) * d
+    got, took_one = _one_launch(lib, buf[4 * B * d:5 * B * d].view(B, d), desc, "relu", y=buf[o:o + B * d].view(B, d))
+    assert took_one == (abs(shift) == B)
+    assert torch.equal(got, apart)
