@@ -224,7 +224,8 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
   g.out_f = A;
   g.k_chunk = (int)d;
   g.partial = nullptr;
-  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, (H ? 2 : 0) + (A ? 4 : 0), 0);
+  // one plan whichever outputs are asked for: another tile adds up in another order, and their bits are the same in every call
+  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, 6, 0);
   if (act == CI_ACT_SWIGLU) {
     g.B0 = w_gate;
     g.B1 = w_up;

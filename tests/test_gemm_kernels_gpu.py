@@ -214,3 +214,21 @@ def test_settings_that_change_during_a_call_stay_inside_its_workspace(lib):
 @pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 2400, 1288, 4440), ("relu", torch.float16, 3166, 1832, 5616)])
 def test_dense_odd_rows_wide_tiles(lib, act, dtype, M, d, N):
     _check_dense(lib, dtype, act, "out_major", M, d, N)
+
+
+# Sizes whose up projection has two tile shapes of nearly the same estimated time, up to 128 tokens and above: scores, hidden
+# values and outputs are the same bits whichever of them a call asks for.
+@pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 13, 496, 2624), ("relu", torch.float16, 53, 1000, 2224),
+                                             ("relu", torch.bfloat16, 21, 568, 2816), ("swiglu", torch.float16, 21, 560, 2048),
+                                             ("relu", torch.float16, 57, 6856, 18768)])
+def test_outputs_asked_for_change_no_bits(lib, act, dtype, M, d, N):
+    w = rand_weights(d, N, dtype, act, "out_major", seed=M, device=DEV)
+    X = torch.randn(M, d, generator=torch.Generator().manual_seed(M)).to(dtype).to(DEV)
+    args = (X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], "out_major", act)
+    Y, A = lib.ffn_dense(*args, want_y=True, want_a=True)
+    _, A_only = lib.ffn_dense(*args, want_y=False, want_a=True)
+    Y_only, _ = lib.ffn_dense(*args, want_y=True, want_a=False)
+    Y_hidden, H = lib.ffn_dense_hidden(*args)
+    assert torch.equal(A_only, A)
+    assert torch.equal(Y_only, Y) and torch.equal(Y_hidden, Y)
+    assert torch.equal(H.abs(), A.to(dtype))   # one rounding of the same fp32 values
