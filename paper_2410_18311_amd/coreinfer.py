@@ -107,6 +107,8 @@ _lib.coreinfer_dev_fused_plan.restype = _int
 _lib.coreinfer_dev_fused_plan.argtypes = [_i64, _i64, _int, _int, ctypes.POINTER(_int)]
 _lib.coreinfer_dev_decode_slices.restype = _int
 _lib.coreinfer_dev_decode_slices.argtypes = [_i64, _i64, _i64, _int, _int, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_dense_plan.restype = _int
+_lib.coreinfer_dev_dense_plan.argtypes = [_i64, _i64, _i64, _int, _int, _int, _i64, ctypes.POINTER(_i64)]
 _lib.coreinfer_dev_select_layout.restype = _int
 _lib.coreinfer_dev_select_layout.argtypes = [_i64, _i64, _i64, ctypes.POINTER(_i64)]
 _lib.coreinfer_dev_stream_probe.restype = _int
@@ -182,6 +184,14 @@ def dev_decode_slices(B: int, K: int, d: int, dtype: torch.dtype, gathered: bool
     _check(_lib.coreinfer_dev_decode_slices(B, K, d, DTYPE_CODE[dtype], int(bool(gathered)), ctypes.byref(out)),
            "coreinfer_dev_decode_slices")
     return out.value
+
+
+def dev_dense_plan(M: int, d: int, N: int, dtype: torch.dtype, act: str, down_layout: str, room: int = 1 << 62) -> dict:
+    """How coreinfer_ffn_dense would tile both projections of more than four tokens with `room` bytes for split sums."""
+    out = (_i64 * 7)()
+    _check(_lib.coreinfer_dev_dense_plan(M, d, N, DTYPE_CODE[dtype], ACT_CODE[act], LAYOUT_CODE[down_layout], room, out),
+           "coreinfer_dev_dense_plan")
+    return dict(zip(("up", "up_tiles", "down", "full", "tail", "splits", "bytes"), out))
 
 
 def dev_select_layout(B: int, M: int, N: int) -> dict:

@@ -626,6 +626,19 @@ static size_t dense_partial_bytes(int64_t M, int64_t d, int64_t N) {
   return round256((size_t)M * (size_t)(N < kMaxSplits ? N : kMaxSplits) * (size_t)d * sizeof(float));
 }
 
+int coreinfer_dev_dense_plan(int64_t M, int64_t d, int64_t N, int dtype, int act, int down_layout, int64_t room,
+                             int64_t* out) {
+  if (!dtype_ok(dtype) || !act_ok(act)) return CI_ERR_BAD_DTYPE;
+  if (!layout_ok(down_layout)) return CI_ERR_BAD_LAYOUT;
+  if (!out || room < 0 || !dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
+  if (M <= 4 || dtype == CI_F32) return CI_ERR_UNSUPPORTED;
+  const GemmPlan up = gemm_up_plan(M, d, N, dtype, act);
+  const GemmPlan down = gemm_down_plan(M, d, N, down_layout, dtype, (size_t)room);
+  const int64_t values[] = {up.shape, up.full, down.shape, down.full, down.tail, down.splits, (int64_t)gemm_plan_bytes(down)};
+  std::copy(std::begin(values), std::end(values), out);
+  return CI_OK;
+}
+
 int coreinfer_ffn_dense_workspace_size(int64_t M, int64_t d, int64_t N, int dtype, size_t* bytes) {
   if (!dtype_ok(dtype)) return CI_ERR_BAD_DTYPE;
   if (!bytes || !dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;

@@ -262,6 +262,7 @@ struct GemmPlan {
   int shape, bm, bn;                // tile shape; bn: output columns
   int full, tail, splits, k_chunk;  // tiles computed whole, tiles split along k, by how many workgroups, k of each
 };
+GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act);
 // Plan of the down projection whose sums of split tiles take at most `room` bytes, and what they take.
 GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, size_t room);
 size_t gemm_plan_bytes(const GemmPlan& p);

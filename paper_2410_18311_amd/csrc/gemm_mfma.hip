@@ -121,12 +121,15 @@ void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPl
   for (int sp = 1; sp <= 8; ++sp) {
     if (sp > 1 && p.Kk < 4 * kTileK * sp) break;  // at least four k tiles per split
     const int full = sp == 1 ? tiles : tiles / kFullChip * kFullChip, tail = tiles - full;
-    if (sp > 1 && (tail == 0 || (size_t)sp * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
+    // rounding the chunk up can leave the last split without work: it then needs no room either (or a workspace of just what
+    // the plan needs would lead to another plan than a larger one)
+    const int k_chunk = sp == 1 ? p.Kk : ((p.Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK;
+    const int parts = (p.Kk + k_chunk - 1) / k_chunk;
+    if (sp > 1 && (tail == 0 || (size_t)parts * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
     const double t = time(ts, p, full, tail, sp);
     if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
       best_t = t;
-      best = GemmPlan{ts.shape, ts.bm, bn, full, tail, sp, p.Kk};
-      if (sp > 1) best.k_chunk = ((p.Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK;
+      best = GemmPlan{ts.shape, ts.bm, bn, full, tail, sp, k_chunk};
     }
   }
   if (best_t > 1e29 && force_splits > 0) best = GemmPlan{ts.shape, ts.bm, bn, tiles, 0, 1, p.Kk};
@@ -167,7 +170,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
         for (int tn = 2; tn <= 8; ++tn) consider(slim_shape((p.M + 15) / 16, tn), p, room, few_rows_time, best, few_t);
     }
   }
-  if (best.splits > 1) best.splits = ((int)Kk + best.k_chunk - 1) / best.k_chunk;  // rounding the chunk up can empty the last one
+  if (best.splits > 1) best.splits = ((int)Kk + best.k_chunk - 1) / best.k_chunk;
   return best;
 }
 
@@ -224,8 +227,7 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
   g.out_f = A;
   g.k_chunk = (int)d;
   g.partial = nullptr;
-  // one plan whichever outputs are asked for: another tile adds up in another order, and their bits are the same in every call
-  const GemmPlan p = dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, 6, 0);
+  const GemmPlan p = gemm_up_plan(M, d, N, dtype, act);
   if (act == CI_ACT_SWIGLU) {
     g.B0 = w_gate;
     g.B1 = w_up;
@@ -236,6 +238,11 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
   g.B1 = nullptr;
   g.bias = b_up;
   return launch_any<EPI_RELU, false>(dtype, g, p, s);
+}
+
+GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act) {
+  // one plan whichever outputs are asked for: another tile adds up in another order, and their bits are the same in every call
+  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, 6, 0);
 }
 
 // The down projection's plan, made once per call: the size check, the place of the sums and the launches all go by it.

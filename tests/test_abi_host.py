@@ -101,6 +101,27 @@ def test_select_refuses_a_workspace_that_ends_before_its_counters(lib, B, M, N):
         assert r.coreinfer_group_select(F, M, 1, N, 0.2, F, F, F, least - 1, None) == lib.CI_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
+def test_dense_plan_is_the_same_in_any_workspace_of_the_stated_size(lib, layout):
+    """A workspace of just the size that the query states gives the plan, and so the bits, that a larger one gives."""
+    import ctypes
+    import torch
+    sizes = [(17, 896, 3136), (39, 512, 1920), (26, 768, 2688), (50, 448, 1600), (7, 416, 1552), (24, 840, 2688)]
+    sizes += [(M, d, N) for M in (5, 16, 33, 61, 77, 100, 128, 129, 200, 577) for d in range(256, 2305, 152)
+              for N in (2 * d + 8, 3 * d, 4 * d)]
+    for M, d, N in sizes:
+        best = lib.dev_dense_plan(M, d, N, torch.float16, "relu", layout)
+        hidden = (M * N * 4 + 255) // 256 * 256
+        beside = lib.ffn_dense_workspace_size(M, d, N, torch.float16) - hidden
+        b = ctypes.c_size_t()
+        assert lib.raw.coreinfer_ffn_dense_hidden_workspace_size(M, d, N, lib.CI_F16, ctypes.byref(b)) == 0
+        assert best["bytes"] <= min(beside, b.value)
+        for room in (beside, b.value, 3 * beside):
+            assert lib.dev_dense_plan(M, d, N, torch.float16, "relu", layout, room) == best, (M, d, N, room)
+        least = lib.dev_dense_plan(M, d, N, torch.float16, "relu", layout, 256)
+        assert least["tail"] == 0 and least["bytes"] == 0   # without room none is split
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 def test_decode_slices_leave_few_compute_units_idle(lib, gathered):
     """On 256 compute units: narrow rows keep every slice (two workgroups on a compute unit cost them nothing) but a
