@@ -733,8 +733,7 @@ int coreinfer_ffn_dense_hidden(const void* X, int64_t M, const void* w_up, const
                                int64_t d, int64_t N, void* Y, void* H, void* ws, size_t ws_bytes, void* stream) {
   if (!dtype_ok(dtype) || !act_ok(act)) return CI_ERR_BAD_DTYPE;
   if (!layout_ok(down_layout)) return CI_ERR_BAD_LAYOUT;
-  size_t need = 0;
-  if (coreinfer_ffn_dense_hidden_workspace_size(M, d, N, dtype, &need) != CI_OK) return CI_ERR_INVALID_ARG;
+  if (!dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
   if (!X || !w_up || !H || (Y && !w_down)) return CI_ERR_INVALID_ARG;
   if ((act == CI_ACT_SWIGLU) != (w_gate != nullptr)) return CI_ERR_INVALID_ARG;
   if (act == CI_ACT_SWIGLU && b_up) return CI_ERR_INVALID_ARG;

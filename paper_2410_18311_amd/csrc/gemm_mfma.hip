@@ -57,7 +57,7 @@ struct TileShape {
   int shape;    // kMid..., kWide, or kSlim + ...
   int bm, bn;   // rows of A, rows of B (SwiGLU: half of them gate, half up)
   double rate;  // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
-  // few_rows_time: bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a fill takes when
+  // FewRowsTime: bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a fill takes when
   // every 128 bytes of a row lie in two lines
   double fill, flops, fixed, two_lines;
 };
@@ -82,39 +82,61 @@ struct Product {
 
 // A product of `full` tiles computed whole and `tail` tiles split along k, tiles in rounds of 256: every workgroup takes all of a
 // compute unit's LDS.  The sums of split tiles are written, read back and added by another launch (about 4.5 TB/s and 5 us).
-double many_rows_time(const TileShape& ts, const Product& p, int full, int tail, int sp) {
-  const int bn = p.dual ? ts.bn / 2 : ts.bn;
-  const double t_tile = 2.0 * ts.bm * ts.bn * (double)p.Kk / ts.rate;
-  // first loads; results of a round, which nothing overlaps
-  const double t_fixed = 3e-6 + (double)ts.bm * bn * p.out_bytes * kFullChip / 4.5e12;
-  return (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed) +
-         (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed) +
-         (tail == 0 ? 0.0 : 2.0 * sp * (double)tail * ts.bm * bn * 4.0 / 4.5e12 + 5e-6);
-}
+struct ManyRowsTime {
+  double t_tile, t_fixed, t_sums;
+  ManyRowsTime(const TileShape& ts, const Product& p) {
+    const int bn = p.dual ? ts.bn / 2 : ts.bn;
+    t_tile = 2.0 * ts.bm * ts.bn * (double)p.Kk / ts.rate;
+    // first loads; results of a round, which nothing overlaps
+    t_fixed = 3e-6 + (double)ts.bm * bn * p.out_bytes * kFullChip / 4.5e12;
+    t_sums = 2.0 * ts.bm * bn * 4.0 / 4.5e12;
+  }
+  double operator()(int full, int tail, int sp) const {
+    return (double)((full + kFullChip - 1) / kFullChip) * (t_tile + t_fixed) +
+           (double)((tail * sp + kFullChip - 1) / kFullChip) * (t_tile / sp + t_fixed) +
+           (tail == 0 ? 0.0 : (double)sp * tail * t_sums + 5e-6);
+  }
+};
 
-// The same for up to 128 rows: what an L1 is filled with, the multiplications, and the weights that a round reads from memory
-// add up rather than hide one another (a maximum, or a power mean of any higher order, fits worse).  The rates are fitted to
-// 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to 36864, odd lengths among them, all shapes and splits.
-double few_rows_time(const TileShape& ts, const Product& p, int full, int tail, int sp) {
-  const int bn = p.dual ? ts.bn / 2 : ts.bn, rows = p.M < ts.bm ? p.M : ts.bm, tiles_m = (p.M + ts.bm - 1) / ts.bm;
-  const int odd = p.Kk * 2 % 128;  // 16-bit elements; pieces of 128 bytes of a row that lie in two cache lines:
-  const double two_lines = odd == 0 ? 0.0 : odd % 64 == 0 ? 0.5 : odd % 32 == 0 ? 0.75 : 0.875;
-  const double per_k = (rows + ts.bn) * (1.0 + ts.two_lines * two_lines) / ts.fill + (double)ts.bm * ts.bn / ts.flops;
-  auto rounds = [&](int wgs, double k, int out_bytes) {
-    auto round = [&](int n) {
-      const double columns = n > tiles_m ? (double)n / tiles_m : 1.0;  // tiles whose weights differ
-      return 2.0 * k * (per_k + columns * ts.bn / 9.9e12) + ts.fixed + (double)n * rows * bn * out_bytes / 4.5e12;
-    };
+// The same as a sum rather than a maximum of three parts: what an L1 is filled with, the multiplications, and the weights that a
+// round reads from memory (a maximum, or a power mean of any higher order, fits worse).  It is a fit, not a model of the chip: the
+// constants of kShapes are those that come closest to 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to
+// 36864, odd lengths among them, all shapes and splits.  (For tiles of 256 x 256 a fill that costs nothing came closest, with
+// fewer flop/s; 256 x 64 was not fitted and takes no part.)
+struct FewRowsTime {
+  int tiles_m, out_bytes;
+  double k, fill, columns_fill, inv_tiles_m, fixed, store, t_sums;
+  FewRowsTime(const TileShape& ts, const Product& p) {
+    const int bn = p.dual ? ts.bn / 2 : ts.bn, rows = p.M < ts.bm ? p.M : ts.bm;
+    tiles_m = (p.M + ts.bm - 1) / ts.bm;
+    out_bytes = p.out_bytes;
+    const int odd = p.Kk * 2 % 128;  // 16-bit elements; pieces of 128 bytes of a row that lie in two cache lines:
+    const double two_lines = odd == 0 ? 0.0 : odd % 64 == 0 ? 0.5 : odd % 32 == 0 ? 0.75 : 0.875;
+    k = p.Kk;
+    fill = 2.0 * ((rows + ts.bn) * (1.0 + ts.two_lines * two_lines) / ts.fill + (double)ts.bm * ts.bn / ts.flops);
+    columns_fill = 2.0 * ts.bn / 9.9e12;
+    inv_tiles_m = 1.0 / tiles_m;
+    fixed = ts.fixed;
+    store = (double)rows * bn / 4.5e12;
+    t_sums = (double)rows * bn * 4.0 / 7.9e12;
+  }
+  double round(int n, double k_n, int bytes) const {
+    const double columns = n > tiles_m ? n * inv_tiles_m : 1.0;  // tiles whose weights differ
+    return k_n * (fill + columns * columns_fill) + fixed + n * store * bytes;
+  }
+  double rounds(int wgs, double k_n, int bytes) const {
     const int whole = wgs / kFullChip, rest = wgs % kFullChip;
-    return (whole > 0 ? whole * round(kFullChip) : 0.0) + (rest > 0 ? round(rest) : 0.0);
-  };
-  return rounds(full, p.Kk, p.out_bytes) + rounds(tail * sp, (double)p.Kk / sp, 4) +
-         (tail == 0 ? 0.0 : (double)sp * tail * rows * bn * 4.0 / 7.9e12 + 2.5e-6);
-}
+    return (whole > 0 ? whole * round(kFullChip, k_n, bytes) : 0.0) + (rest > 0 ? round(rest, k_n, bytes) : 0.0);
+  }
+  double operator()(int full, int tail, int sp) const {
+    return rounds(full, k, out_bytes) + (tail == 0 ? 0.0 : rounds(tail * sp, k / sp, 4) + (double)sp * tail * t_sums + 2.5e-6);
+  }
+};
 
-// Adds a shape, whole and with its last round in 2 .. 8 parts, to the best plan so far by `time`.
-template <class F>
-void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPlan& best, double& best_t) {
+// Adds a shape, whole and with its last round in 2 .. 8 parts, to the best plan so far by the estimate Time.
+template <class Time>
+void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best, double& best_t) {
+  const Time time(ts, p);
   const int force_splits = params().gemm_splits;
   const int bn = p.dual ? ts.bn / 2 : ts.bn;
   const int tiles = ((p.M + ts.bm - 1) / ts.bm) * ((p.Nn + bn - 1) / bn);
@@ -126,7 +148,7 @@ void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPl
     const int k_chunk = sp == 1 ? p.Kk : ((p.Kk + sp - 1) / sp + kTileK - 1) / kTileK * kTileK;
     const int parts = (p.Kk + k_chunk - 1) / k_chunk;
     if (sp > 1 && (tail == 0 || (size_t)parts * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
-    const double t = time(ts, p, full, tail, sp);
+    const double t = time(full, tail, sp);
     if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
       best_t = t;
       best = GemmPlan{ts.shape, ts.bm, bn, full, tail, sp, k_chunk};
@@ -139,7 +161,7 @@ void consider(const TileShape& ts, const Product& p, size_t room, F time, GemmPl
 // kernels -> these): 77 tokens, 4096 x 11008 gated 97 -> 66 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000
 // tokens, 7168 x 28672, neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
-// Up to 128 rows the plan is made again by few_rows_time, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
+// Up to 128 rows the plan is made again by FewRowsTime, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
 // that estimate promises 6 % or more: over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
 // most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  From 129 rows on the slim tiles are 3 to
 // 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
@@ -155,19 +177,19 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
   double best_t = 1e30;
   const int force = params().gemm_tile;
   if (force >= kSlim && !b_kmajor) {
-    consider(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, many_rows_time, best, best_t);
+    consider<ManyRowsTime>(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, best, best_t);
   } else {
     for (const TileShape& ts : kShapes)
-      if (force < 0 || force >= kSlim || ts.shape == force) consider(ts, p, room, many_rows_time, best, best_t);
+      if (force < 0 || force >= kSlim || ts.shape == force) consider<ManyRowsTime>(ts, p, room, best, best_t);
     const bool few = M <= kSlimRows;
     if (force < 0 && params().gemm_splits == 0 && (few || room == 0)) {
       double few_t = few ? 1e30 : 0.0;
       for (const TileShape& ts : kShapes)
-        if (ts.shape == best.shape && ts.fill > 0) few_t = (few ? 0.94 : 0.76) * few_rows_time(ts, p, best.full, best.tail, best.splits);
+        if (ts.shape == best.shape && ts.fill > 0) few_t = (few ? 0.94 : 0.76) * FewRowsTime(ts, p)(best.full, best.tail, best.splits);
       for (const TileShape& ts : kShapes)
-        if (ts.fill > 0) consider(ts, p, room, few_rows_time, best, few_t);
+        if (ts.fill > 0) consider<FewRowsTime>(ts, p, room, best, few_t);
       if (few && !b_kmajor)
-        for (int tn = 2; tn <= 8; ++tn) consider(slim_shape((p.M + 15) / 16, tn), p, room, few_rows_time, best, few_t);
+        for (int tn = 2; tn <= 8; ++tn) consider<FewRowsTime>(slim_shape((p.M + 15) / 16, tn), p, room, best, few_t);
     }
   }
   if (best.splits > 1) best.splits = ((int)Kk + best.k_chunk - 1) / best.k_chunk;

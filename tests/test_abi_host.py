@@ -122,6 +122,27 @@ def test_dense_plan_is_the_same_in_any_workspace_of_the_stated_size(lib, layout)
         assert least["tail"] == 0 and least["bytes"] == 0   # without room none is split
 
 
+def test_hidden_call_makes_no_plans_to_check_its_arguments(lib):
+    """A call that is refused for want of a workspace has cost what the same refusal of coreinfer_ffn_dense does, far less
+    than the size query, which plans both layouts (fastest of many rounds of each)."""
+    import ctypes
+    import time
+    F, M, d, N = 0x10000, 77, 4096, 11008
+    b = ctypes.c_size_t()
+    dense = lambda: lib.raw.coreinfer_ffn_dense(F, M, F, None, None, F, None, 0, lib.CI_F16, 0, d, N, F, None, None, 0, None)  # noqa: E731
+    hidden = lambda: lib.raw.coreinfer_ffn_dense_hidden(F, M, F, None, None, F, None, 0, lib.CI_F16, 0, d, N, F, F, None, 0, None)  # noqa: E731
+    query = lambda: lib.raw.coreinfer_ffn_dense_hidden_workspace_size(M, d, N, lib.CI_F16, ctypes.byref(b))  # noqa: E731
+    assert dense() == lib.CI_ERR_WORKSPACE and hidden() == lib.CI_ERR_WORKSPACE and query() == 0
+    best = {}
+    for _ in range(60):
+        for name, f in (("dense", dense), ("hidden", hidden), ("query", query)):
+            t = time.perf_counter()
+            for _ in range(50):
+                f()
+            best[name] = min(best.get(name, 1.0), (time.perf_counter() - t) / 50)
+    assert best["hidden"] < best["dense"] + 0.4 * best["query"], best
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 def test_decode_slices_leave_few_compute_units_idle(lib, gathered):
     """On 256 compute units: narrow rows keep every slice (two workgroups on a compute unit cost them nothing) but a
