@@ -57,8 +57,14 @@ int launch_gemm_wide(int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipSt
 // Smaller tiles for 16-bit types (gemm_mid.hip): rows of A x rows of B per workgroup.
 enum { kMid128x128 = 0, kMid128x256 = 1, kMid256x64 = 2, kMid128x64 = 3 };
 int launch_gemm_mid(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
-// Tiles of 16 tm rows of A x 16 tn rows of B (gemm_slim.hpp), B k-contiguous; tm 1 .. 8, tn 2 .. 8.
+// Tiles of 16 tm rows of A x 16 tn rows of B (gemm_slim.hpp), B k-contiguous.
 constexpr int kSlim = 16;  // a tile shape's number: kSlim + 16 tm + tn
+// Three shapes are not built: of 24 million plans (d up to 32768, N up to 200000, workspaces of any size) three took one of them.
+// The other large ones are rare too (one plan in 1700 to 500000, and only where d is far from a third of N or the workspace small),
+// but the next best shape is 6 % slower there and more.
+constexpr bool slim_built(int tm, int tn) {
+  return tm >= 1 && tm <= 8 && tn >= 2 && tn <= 8 && !(tm == 8 && (tn == 4 || tn == 7 || tn == 8));
+}
 int launch_gemm_slim_f16(int tm, int tn, int epi, const GemmArgs& g, hipStream_t s);
 int launch_gemm_slim_bf16(int tm, int tn, int epi, const GemmArgs& g, hipStream_t s);
 // fp32 kernels (gemm_f32.hip); epi: EPI_*, b_kmajor: B given as [Kk, Nn].

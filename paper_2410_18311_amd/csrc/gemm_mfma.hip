@@ -189,7 +189,8 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
       for (const TileShape& ts : kShapes)
         if (ts.fill > 0) consider<FewRowsTime>(ts, p, room, best, few_t);
       if (few && !b_kmajor)
-        for (int tn = 2; tn <= 8; ++tn) consider<FewRowsTime>(slim_shape((p.M + 15) / 16, tn), p, room, best, few_t);
+        for (int tn = 2; tn <= 8; ++tn)
+          if (slim_built((p.M + 15) / 16, tn)) consider<FewRowsTime>(slim_shape((p.M + 15) / 16, tn), p, room, best, few_t);
     }
   }
   if (best.splits > 1) best.splits = ((int)Kk + best.k_chunk - 1) / best.k_chunk;

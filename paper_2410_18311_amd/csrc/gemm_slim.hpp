@@ -213,16 +213,22 @@ int launch_shape(int epi, const GemmArgs& g, hipStream_t s) {
   return CI_OK;
 }
 
+template <class D, int TM, int TN>
+int launch_built(int epi, const GemmArgs& g, hipStream_t s) {
+  if constexpr (slim_built(TM, TN)) return launch_shape<D, TM, TN>(epi, g, s);
+  else return CI_ERR_UNSUPPORTED;
+}
+
 template <class D, int TM>
 int launch_tn(int tn, int epi, const GemmArgs& g, hipStream_t s) {
   switch (tn) {
-    case 2: return launch_shape<D, TM, 2>(epi, g, s);
-    case 3: return launch_shape<D, TM, 3>(epi, g, s);
-    case 4: return launch_shape<D, TM, 4>(epi, g, s);
-    case 5: return launch_shape<D, TM, 5>(epi, g, s);
-    case 6: return launch_shape<D, TM, 6>(epi, g, s);
-    case 7: return launch_shape<D, TM, 7>(epi, g, s);
-    case 8: return launch_shape<D, TM, 8>(epi, g, s);
+    case 2: return launch_built<D, TM, 2>(epi, g, s);
+    case 3: return launch_built<D, TM, 3>(epi, g, s);
+    case 4: return launch_built<D, TM, 4>(epi, g, s);
+    case 5: return launch_built<D, TM, 5>(epi, g, s);
+    case 6: return launch_built<D, TM, 6>(epi, g, s);
+    case 7: return launch_built<D, TM, 7>(epi, g, s);
+    case 8: return launch_built<D, TM, 8>(epi, g, s);
   }
   return CI_ERR_UNSUPPORTED;
 }

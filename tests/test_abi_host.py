@@ -122,6 +122,28 @@ def test_dense_plan_is_the_same_in_any_workspace_of_the_stated_size(lib, layout)
         assert least["tail"] == 0 and least["bytes"] == 0   # without room none is split
 
 
+def test_dense_plans_take_shapes_that_are_built(lib):
+    """Every tile shape of a plan is one that the setting for tests accepts, and so has a kernel; those that no size takes have none."""
+    import torch
+    taken = set()
+    for M in (5, 17, 33, 48, 64, 77, 90, 112, 113, 128):
+        for d in (8, 64, 256, 456, 1024, 4096, 9216, 32768):
+            for N in (8, 136, 1024, 2816, 11008, 16384, 36864, 131072):
+                for act in ("relu", "swiglu"):
+                    for room in (256, 1 << 20, 1 << 62):
+                        plan = lib.dev_dense_plan(M, d, N, torch.bfloat16, act, "out_major", room)
+                        taken |= {plan["up"], plan["down"]}
+    assert len(taken) > 40
+    try:
+        for tile in taken:
+            lib.dev_set_param("gemm_tile", tile)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+    for tm, tn in ((8, 4), (8, 7), (8, 8), (0, 2), (9, 2), (1, 1), (1, 9)):
+        assert lib.raw.coreinfer_dev_set_param(b"gemm_tile", 16 + 16 * tm + tn) == lib.CI_ERR_INVALID_ARG
+    assert lib.raw.coreinfer_dev_set_param(b"gemm_tile", 15) == lib.CI_ERR_INVALID_ARG
+
+
 def test_hidden_call_makes_no_plans_to_check_its_arguments(lib):
     """A call that is refused for want of a workspace has cost what the same refusal of coreinfer_ffn_dense does, far less
     than the size query, which plans both layouts (fastest of many rounds of each)."""
