@@ -128,6 +128,7 @@ struct Params {
   Knob gemv_wgs_per_cu{8};
   Knob gemv_cols_wgs_per_cu{1};
   Knob gemm_tile{-1};        // tile shape: -1 planned, else its number (gemm_common.hpp; 4 = 256 x 256; 16 + 16 tm + tn = tiles of 16 tm x 16 tn)
+  Knob gemm_once{1};         // weights loaded as data that is not read again: 0 never, 1 by the rule, 2 wherever they can be
   Knob gemm_splits{0};       // k splits of the last round of the down projection: 0 planned
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)
   Knob reduce_cq{8};         // column quads per reduce workgroup (4, 8, 16)

@@ -10,7 +10,8 @@
  *   derive from d, else a multiple of 64 up to 1024), "decode_depth" (4, 8 or 16
  *   weight rows in flight per thread), "reduce_cq" (4, 8, 16 column quads per
  *   reduction workgroup), "reduce_threads" (64 .. 1024, a power of two: threads per reduction
- *   workgroup), "decode_nt_store" (0/1): two-launch decode;
+ *   workgroup), "decode_nt_store" (0/1): two-launch decode; "decode_small" (0
+ *   never, 1 by the rule, 2 wherever it can): small layers in one launch;
  *   "fused_depth" (4, 8), "fused_threads" (0 or a multiple of 64 up to 896),
  *   "fused_chunks" (least number of neuron chunks, 2..64),
  *   "fused_chunk_size" (0 = cost model, else neurons per chunk, a multiple of the
@@ -28,7 +29,10 @@
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
  *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4),
- *   "gemm_tile" (-1 planned, 0 .. 4: tile shape), "gemm_splits" (0 planned, 1 .. 8:
+ *   "gemm_tile" (-1 planned, 0 .. 4: tile shape, 16 + 16 tm + tn: tiles of 16 tm x
+ *   16 tn where they are built and the weights k-contiguous), "gemm_once" (0 never, 1 by
+ *   the rule, 2 wherever they can be: weights loaded as data that is not read
+ *   again), "gemm_splits" (0 planned, 1 .. 8:
  *   k splits of the last round of tiles of the down projection);
  *   "gathered_union" (0 never, 1 by the rule, 2 wherever it can: gathered decode
  *   through the union of its lists);

@@ -95,6 +95,60 @@ def test_dense_slim_tiles(lib, tm, tn, act, dtype):
         lib.dev_set_param("gemm_splits", 0)
 
 
+# Weights loaded as data that is not read again, in every tile shape that can: the bits of the ordinary loads (which the
+# tests above hold to the oracle), whole and split, with k that ends inside a k-tile and more k-tiles than a ring holds
+@pytest.mark.parametrize("tile", [0, 1, 2, 3] + [16 + 16 * tm + tn for tn in range(2, 9) for tm in range(1, 9)
+                                                 if (tm, tn) not in ((8, 4), (8, 7), (8, 8))])
+@pytest.mark.parametrize("act,dtype", [("relu", torch.float16), ("relu", torch.bfloat16), ("swiglu", torch.bfloat16)])
+def test_dense_read_once_loads(lib, tile, act, dtype):
+    M, d, N = 100, 776, 1736
+    w = rand_weights(d, N, dtype, act, "out_major", seed=tile, device=DEV)
+    X = torch.randn(M, d, generator=torch.Generator().manual_seed(tile)).to(dtype).to(DEV)
+    args = (X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], "out_major", act)
+    lib.dev_set_param("gemm_tile", tile)
+    try:
+        for splits in (1, 3):
+            lib.dev_set_param("gemm_splits", splits)
+            out = {}
+            for once in (0, 2):
+                lib.dev_set_param("gemm_once", once)
+                out[once] = lib.ffn_dense(*args, want_y=True, want_a=True)
+            assert torch.equal(out[0][0], out[2][0]) and torch.equal(out[0][1], out[2][1])
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+        lib.dev_set_param("gemm_once", 1)
+
+
+# Short prompts over weights of more than 80 MB a product, where the rule takes those loads: slim tiles for both
+# projections, for one and for none, a down projection below the line, and rows of no multiple of 128 bytes, which keep
+# the ordinary loads
+@pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 77, 4096, 11008), ("relu", torch.float16, 16, 4096, 16384),
+                                             ("relu", torch.bfloat16, 128, 5120, 13824), ("swiglu", torch.float16, 33, 3072, 8192),
+                                             ("relu", torch.float16, 45, 4104, 12008)])
+def test_dense_short_prompts_of_large_layers(lib, act, dtype, M, d, N):
+    print("large layer case", act, dtype, M, d, N, lib.dev_dense_plan(M, d, N, dtype, act, "out_major"), flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M)
+    mat = lambda *s: (torch.randn(*s, generator=g, device=DEV) * 0.02).to(dtype)  # noqa: E731
+    up, gate, down = mat(N, d), mat(N, d) if act == "swiglu" else None, mat(d, N)
+    X = torch.randn(M, d, generator=g, device=DEV).to(dtype)
+    args = (X, up, gate, None, down, None, "out_major", act)
+    Y, A = lib.ffn_dense(*args, want_y=True, want_a=True)
+    _, H = lib.ffn_dense_hidden(*args)
+    cols = torch.randperm(N, generator=torch.Generator().manual_seed(M))[:500].to(DEV)  # sampled neurons, in 64 bits
+    z = X.double() @ up[cols].double().t()
+    h = torch.nn.functional.silu(X.double() @ gate[cols].double().t()) * z if act == "swiglu" else z.clamp(min=0)
+    A_ref = f64(h.abs())
+    assert np.abs(f64(A[:, cols]) - A_ref).max() <= score_bound(dtype, act, A_ref), "A"
+    assert_close_rms(Y, f64(H.double() @ down.double().t()), dtype, "Y")  # from the rounded hidden matrix itself
+    lib.dev_set_param("gemm_once", 0)
+    try:
+        Y0, A0 = lib.ffn_dense(*args, want_y=True, want_a=True)
+    finally:
+        lib.dev_set_param("gemm_once", 1)
+    assert torch.equal(Y, Y0) and torch.equal(A, A0)
+
+
 # As planned: token counts on both sides of the slim tiles' range, with a workspace for sums and with the least there is
 @pytest.mark.parametrize("M", [5, 16, 17, 64, 77, 128, 129, 256, 257])
 @pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
