@@ -285,3 +285,92 @@ def test_outputs_asked_for_change_no_bits(lib, act, dtype, M, d, N):
     assert torch.equal(A_only, A)
     assert torch.equal(Y_only, Y) and torch.equal(Y_hidden, Y)
     assert torch.equal(H.abs(), A.to(dtype))   # one rounding of the same fp32 values
+
+
+# Slim tiles, as planned, for both projections (the second with k split)
+SLIM = [("swiglu", torch.bfloat16, 15, 1280, 4864), ("relu", torch.float16, 32, 2512, 9888)]
+
+
+def _slim_call(lib, act, dtype, M, d, N):
+    plan = lib.dev_dense_plan(M, d, N, dtype, act, "out_major")
+    assert plan["up"] >= 32 and plan["down"] >= 32 and plan["splits"] > 1, plan
+    w = rand_weights(d, N, dtype, act, "out_major", seed=M, device=DEV)
+    X = torch.randn(M, d, generator=torch.Generator().manual_seed(d)).to(dtype).to(DEV)
+    ws = torch.empty(lib.ffn_dense_workspace_size(M, d, N, dtype), dtype=torch.uint8, device=DEV)
+    Y, A = torch.empty(M, d, dtype=dtype, device=DEV), torch.empty(M, N, device=DEV)
+
+    def call():
+        lib.ffn_dense(X, w["w_up"], w["w_gate"], w["b_up"], w["w_down"], w["b_down"], "out_major", act, want_y=True, want_a=True,
+                      Y=Y, A=A, ws=ws)
+    return X, Y, A, ws, call
+
+
+@pytest.mark.parametrize("act,dtype,M,d,N", SLIM)
+def test_dense_planned_slim(lib, act, dtype, M, d, N):
+    _check_dense(lib, dtype, act, "out_major", M, d, N)
+    _check_dense(lib, dtype, act, "out_major", M, d, N, hidden=True)
+
+
+@pytest.mark.parametrize("act,dtype,M,d,N", SLIM)
+def test_dense_slim_on_another_stream_and_captured(lib, act, dtype, M, d, N):
+    X, Y, A, ws, call = _slim_call(lib, act, dtype, M, d, N)
+    call()
+    torch.cuda.synchronize()
+    first = Y.clone(), A.clone()
+    for _ in range(4):   # the same bits whatever the workspace held
+        ws.fill_(255)
+        call()
+        assert torch.equal(Y, first[0]) and torch.equal(A, first[1])
+    side = torch.cuda.Stream()
+    Y.zero_(), A.zero_(), ws.fill_(255)
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    assert torch.equal(Y, first[0]) and torch.equal(A, first[1])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for i in range(4):
+        X.copy_(torch.randn(M, d, generator=torch.Generator().manual_seed(100 + i)))
+        Y.zero_(), A.zero_(), ws.fill_(255)
+        g.replay()
+        torch.cuda.synchronize()
+        replayed = Y.clone(), A.clone()
+        call()
+        assert torch.equal(replayed[0], Y) and torch.equal(replayed[1], A)
+
+
+# Infinities and NaN at the last k and at the first of the last, ragged k-tile, which is what chunks past the end are
+# loaded from: they reach the rows (or columns) that have them and no others, as sums without those chunks give
+@pytest.mark.parametrize("tile", [0, 3, 34, 51, 86, 120])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_dense_values_that_are_not_finite_in_a_ragged_k_tile(lib, tile, splits):
+    M, d, N, dt = 20, 1032, 1096, torch.float16    # 16 k-tiles and 8, 17 and 8
+    g = torch.Generator().manual_seed(tile)
+    pos = lambda *s: (torch.rand(*s, generator=g) * 0.02 + 0.001).to(dt).to(DEV)  # noqa: E731
+    w_up, w_down, X = pos(N, d), pos(d, N), pos(M, d)
+    X[3, d - 1], X[5, d - 8], X[7, d - 8] = float("inf"), float("inf"), float("nan")
+    w_up[N - 1, d - 1] = float("inf")
+    lib.dev_set_param("gemm_tile", tile)
+    lib.dev_set_param("gemm_splits", splits)
+    try:
+        Y, A = lib.ffn_dense(X, w_up, None, None, w_down, None, "out_major", "relu", want_y=True, want_a=True)
+        X[3, d - 1], X[5, d - 8], X[7, d - 8], w_up[N - 1, d - 1] = 0.5, 0.5, 0.5, 0.01
+        w_down[2, N - 1], w_down[4, N - 8] = float("inf"), float("nan")
+        Y2, A2 = lib.ffn_dense(X, w_up, None, None, w_down, None, "out_major", "relu", want_y=True, want_a=True)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+    inf_A = torch.zeros(M, N, dtype=torch.bool, device=DEV)
+    inf_A[3], inf_A[5], inf_A[:, N - 1] = True, True, True
+    inf_A[7] = False                      # max(NaN, 0) is 0
+    assert torch.equal(torch.isinf(A), inf_A)
+    assert bool((A[7] == 0).all()) and not bool(torch.isnan(A).any())
+    inf_Y = torch.ones(M, d, dtype=torch.bool, device=DEV)
+    inf_Y[7] = False
+    assert torch.equal(torch.isinf(Y), inf_Y) and bool((Y[7] == 0).all())
+    assert bool(torch.isfinite(A2).all())
+    assert bool(torch.isinf(Y2[:, 2]).all()) and bool(torch.isnan(Y2[:, 4]).all())
+    rest = [c for c in range(d) if c not in (2, 4)]
+    assert bool(torch.isfinite(Y2[:, rest]).all())
