@@ -188,10 +188,10 @@ def dev_decode_slices(B: int, K: int, d: int, dtype: torch.dtype, gathered: bool
 
 def dev_dense_plan(M: int, d: int, N: int, dtype: torch.dtype, act: str, down_layout: str, room: int = 1 << 62) -> dict:
     """How coreinfer_ffn_dense would tile both projections of more than four tokens with `room` bytes for split sums."""
-    out = (_i64 * 7)()
+    out = (_i64 * 9)()
     _check(_lib.coreinfer_dev_dense_plan(M, d, N, DTYPE_CODE[dtype], ACT_CODE[act], LAYOUT_CODE[down_layout], room, out),
            "coreinfer_dev_dense_plan")
-    return dict(zip(("up", "up_tiles", "down", "full", "tail", "splits", "bytes"), out))
+    return dict(zip(("up", "up_tiles", "down", "full", "tail", "splits", "bytes", "up_once", "down_once"), out))
 
 
 def dev_select_layout(B: int, M: int, N: int) -> dict:

@@ -616,8 +616,8 @@ int coreinfer_ffn_decode_union(const void* x, int64_t B, const ci_ffn_weights* w
 
 // Sums of tiles split along k, whichever layout the down matrix has.
 static size_t dense_sums_bytes(int64_t M, int64_t d, int64_t N, int dtype) {
-  return std::max(gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_OUT_MAJOR, dtype, SIZE_MAX)),
-                  gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_NEURON_MAJOR, dtype, SIZE_MAX)));
+  return std::max(gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_OUT_MAJOR, dtype, false, SIZE_MAX)),
+                  gemm_plan_bytes(gemm_down_plan(M, d, N, CI_DOWN_NEURON_MAJOR, dtype, false, SIZE_MAX)));
 }
 
 static bool dense_sizes_ok(int64_t M, int64_t d, int64_t N) {
@@ -635,8 +635,9 @@ int coreinfer_dev_dense_plan(int64_t M, int64_t d, int64_t N, int dtype, int act
   if (!out || room < 0 || !dense_sizes_ok(M, d, N)) return CI_ERR_INVALID_ARG;
   if (M <= 4 || dtype == CI_F32) return CI_ERR_UNSUPPORTED;
   const GemmPlan up = gemm_up_plan(M, d, N, dtype, act);
-  const GemmPlan down = gemm_down_plan(M, d, N, down_layout, dtype, (size_t)room);
-  const int64_t values[] = {up.shape, up.full, down.shape, down.full, down.tail, down.splits, (int64_t)gemm_plan_bytes(down)};
+  const GemmPlan down = gemm_down_plan(M, d, N, down_layout, dtype, act == CI_ACT_SWIGLU, (size_t)room);
+  const int64_t values[] = {up.shape, up.full, down.shape, down.full, down.tail, down.splits,
+                            (int64_t)gemm_plan_bytes(down), up.once, down.once};
   std::copy(std::begin(values), std::end(values), out);
   return CI_OK;
 }
@@ -715,7 +716,7 @@ int coreinfer_ffn_dense(const void* X, int64_t M, const void* w_up, const void* 
     if (rc != CI_OK || !Y) return rc;
     return launch_down_rows(H, M, w_down, b_down, dtype, d, N, Y, s);
   }
-  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, ws_bytes - hidden);
+  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, w_gate != nullptr, ws_bytes - hidden);
   void* H = Y ? ws : nullptr;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, A, s);
   if (rc != CI_OK || !Y) return rc;
@@ -745,7 +746,7 @@ int coreinfer_ffn_dense_hidden(const void* X, int64_t M, const void* w_up, const
     return CI_ERR_BAD_LAYOUT;
   if (!ws || ws_bytes < 256) return CI_ERR_WORKSPACE;  // without room for the sums of split tiles none is split
   if (!aligned16(ws)) return CI_ERR_BAD_LAYOUT;
-  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, ws_bytes);
+  const GemmPlan plan = gemm_down_plan(M, d, N, down_layout, dtype, w_gate != nullptr, ws_bytes);
   hipStream_t s = (hipStream_t)stream;
   int rc = launch_gemm_up(X, M, w_up, w_gate, b_up, dtype, act, d, N, H, nullptr, s);
   if (rc != CI_OK || !Y) return rc;

@@ -262,10 +262,11 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
 struct GemmPlan {
   int shape, bm, bn;                // tile shape; bn: output columns
   int full, tail, splits, k_chunk;  // tiles computed whole, tiles split along k, by how many workgroups, k of each
+  bool once;                        // weights loaded as data that is not read again
 };
 GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act);
 // Plan of the down projection whose sums of split tiles take at most `room` bytes, and what they take.
-GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, size_t room);
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, bool gated, size_t room);
 size_t gemm_plan_bytes(const GemmPlan& p);
 int launch_gemm_down(const void* H, int64_t M, const void* w_down, const void* b_down,
                      int down_layout, int dtype, int64_t d, int64_t N, void* Y, float* partial,

@@ -71,10 +71,11 @@ int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int 
 
 /* The plans of coreinfer_ffn_dense for more than four tokens of a 16-bit type
  * under the current settings, the down projection's with room for `room` bytes
- * of split sums: out[0..6] = tile shape (0 .. 4, or 16 + 16 tm + tn for tiles
+ * of split sums: out[0..8] = tile shape (0 .. 4, or 16 + 16 tm + tn for tiles
  * of 16 tm x 16 tn) and tiles of the up projection; tile shape, tiles computed
  * whole, tiles split along k, splits and bytes of their sums of the down
- * projection.  Host array; CI_ERR_UNSUPPORTED for calls without such plans. */
+ * projection; whether the weights of the up and of the down projection are
+ * loaded as data that is not read again.  Host array; CI_ERR_UNSUPPORTED for calls without such plans. */
 int coreinfer_dev_dense_plan(int64_t M, int64_t d, int64_t N, int dtype, int act, int down_layout, int64_t room,
                              int64_t* out);
 

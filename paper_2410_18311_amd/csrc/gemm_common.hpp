@@ -19,6 +19,7 @@ struct GemmArgs {
   float* partial;  // where the k of a product is split: [splits][tail] tiles of fp32 partial products, sums_pitch apart
   // tiles computed whole, tiles computed by `splits` workgroups of k_chunk each (a multiple of the k tile)
   int full, tail, splits, k_chunk;
+  bool once;  // B is loaded as data that is not read again
 };
 
 // Floats from one tile of sums to the next.  The tiles are powers of two and their workgroups store in step: 256 bytes in

@@ -197,6 +197,25 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
   return best;
 }
 
+// Whether the rows of B go through the caches as data that is not read again, which leaves the caches to the rows of A: products
+// of one row of tiles over 80 MB of weights and more, whose layer does not fit the memory-side cache (256 MB), or of up to 32
+// rows.  us, ordinary loads -> these, both projections, for one layer again and again / layers in turn that fit no cache:
+//   larger than it   67 x 4288 x 15616 (268 MB) 60.1 -> 61.1 / 68.5 -> 67.4; 91 x 4928 x 15424 (304 MB) 81.5 -> 70.3 / 83.6 -> 79.4;
+//                    7 x 4928 x 16640 (328 MB) 63.3 -> 57.8 / 64.7 -> 59.5; 81 x 4096 x 14720 gated (362 MB) 85.5 -> 78.4 / 85.6 -> 79.2
+//   smaller          16 x 3264 x 10304 gated (202 MB) 37.2 -> 40.3 / 44.7 -> 43.4; 5 x 4224 x 13632 (230 MB) 42.1 -> 43.6 / 48.6 -> 45.3;
+//                    54 x 3968 x 13504 (214 MB) 46.6 -> 54.4 / 56.1 -> 55.3; 120 x 3584 x 11456 (164 MB) 44.7 -> 60.4 / 59.2 -> 60.3
+// (of 190 such layers).  Of the smaller ones a single layer is slower with them, in a model of several it is 2 to 8 % faster
+// up to 32 rows and 0 to 3 % above.  Two layers of 81 MB in turn: 74 x 2944 x 9152 36 -> 45.  Pieces that lie in two lines each need both
+// lines to stay for the next k-tile (9 x 5912 x 21232 gated 165 -> 192).  Two rows of tiles read B twice: 256 x 4096 x 16384
+// 104.7 -> 102.8, but 145 x 2816 x 9728 gated 71 -> 77.6.
+bool read_once(const GemmPlan& p, int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, bool gated) {
+  const int mode = params().gemm_once;
+  if (mode == 0 || b_kmajor || p.shape == kWide) return false;
+  const int64_t one = Nn * Kk * 2;  // bytes of a matrix of the layer
+  return mode == 2 || (M <= 128 && (dual ? 2 : 1) * one >= 80000000 && Kk % 64 == 0 &&
+                       (M <= 32 || (gated ? 3 : 2) * one > (int64_t)256 << 20));
+}
+
 template <class D>
 int launch_sums(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   const int strips = (p.bm * p.bn / 4 + kReduceQuads - 1) / kReduceQuads;
@@ -212,6 +231,7 @@ int launch_mfma(GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   g.tail = p.tail;
   g.splits = p.splits;
   g.k_chunk = p.k_chunk;
+  g.once = p.once;
   constexpr int dtype = __is_same(D, F16) ? CI_F16 : CI_BF16;
   int rc = CI_ERR_UNSUPPORTED;
   if (p.shape >= kSlim) {
@@ -265,12 +285,20 @@ int launch_gemm_up(const void* X, int64_t M, const void* w_up, const void* w_gat
 
 GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act) {
   // one plan whichever outputs are asked for: another tile adds up in another order, and their bits are the same in every call
-  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, N, d, act == CI_ACT_SWIGLU, false, 6, 0);
+  if (dtype == CI_F32) return GemmPlan{};
+  const bool gated = act == CI_ACT_SWIGLU;
+  GemmPlan p = plan_gemm(M, N, d, gated, false, 6, 0);
+  p.once = read_once(p, M, N, d, gated, false, gated);
+  return p;
 }
 
 // The down projection's plan, made once per call: the size check, the place of the sums and the launches all go by it.
-GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, size_t room) {
-  return dtype == CI_F32 ? GemmPlan{} : plan_gemm(M, d, N, false, down_layout == CI_DOWN_NEURON_MAJOR, 2, room);
+GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, bool gated, size_t room) {
+  if (dtype == CI_F32) return GemmPlan{};
+  const bool b_kmajor = down_layout == CI_DOWN_NEURON_MAJOR;
+  GemmPlan p = plan_gemm(M, d, N, false, b_kmajor, 2, room);
+  p.once = read_once(p, M, d, N, false, b_kmajor, gated);
+  return p;
 }
 
 size_t gemm_plan_bytes(const GemmPlan& p) {

@@ -13,7 +13,7 @@ namespace ci {
 
 namespace {
 
-// WM x WN waves of TI x TJ blocks of 32x32.  ONCE: see read_once.
+// WM x WN waves of TI x TJ blocks of 32x32.  ONCE: B's lines are the first to leave the caches.
 template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_mid_kernel(GemmArgs g) {
   using T = typename D::T;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 template <class D, int EPI, bool BNN, int WM, int WN, int TI, int TJ>
 int launch_shape(const GemmArgs& g, hipStream_t s) {
   const dim3 grid((unsigned)(g.full + g.tail * g.splits));
-  if (!BNN && read_once(g, EPI == EPI_SWIGLU))
+  if (!BNN && g.once)
     hipLaunchKernelGGL((gemm_mid_kernel<D, EPI, BNN, WM, WN, TI, TJ, !BNN>), grid, dim3(256), 0, s, g);
   else
     hipLaunchKernelGGL((gemm_mid_kernel<D, EPI, BNN, WM, WN, TI, TJ, false>), grid, dim3(256), 0, s, g);

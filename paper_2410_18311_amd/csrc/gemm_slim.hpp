@@ -32,7 +32,7 @@ __device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, f32x4 c)
 constexpr int kLds = 163840;
 
 // TM x TN blocks of 16x16: 16 TM rows of A, 16 TN rows of B.  SwiGLU: a block of B rows is eight gate and eight up rows of
-// the same columns.  epi: EPI_*.  ONCE: see read_once.
+// the same columns.  epi: EPI_*.  ONCE: B's lines are the first to leave the caches.
 template <class D, int TM, int TN, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_slim_kernel(GemmArgs g, int epi) {
   using T = typename D::T;
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 template <class D, int TM, int TN>
 int launch_shape(int epi, const GemmArgs& g, hipStream_t s) {
   const dim3 grid((unsigned)(g.full + g.tail * g.splits));
-  if (read_once(g, epi == EPI_SWIGLU)) hipLaunchKernelGGL((gemm_slim_kernel<D, TM, TN, true>), grid, dim3(256), 0, s, g, epi);
+  if (g.once) hipLaunchKernelGGL((gemm_slim_kernel<D, TM, TN, true>), grid, dim3(256), 0, s, g, epi);
   else hipLaunchKernelGGL((gemm_slim_kernel<D, TM, TN, false>), grid, dim3(256), 0, s, g, epi);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;

@@ -82,18 +82,6 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t o
                  : "memory");
 }
 
-// Whether the rows of B go through the caches as data that is not read again, which leaves the caches to the rows of A: products
-// of one row of tiles over large weights.  The line at 80 MB is where it began to pay, between 54 MB (two layers in turn: 74 x 2944 x 9152,
-// 36 us, 45 this way; 10 x 1792 x 4800 gated 17.0 and 20.8) and 90 MB (77 x 4096 x 11008 gated, 180 and 90 MB, 72.5 -> 69.3 us; 5 x 5824 x
-// 22656 gated 145 -> 126, both projections).  Pieces that lie in two lines each need both lines to stay for the next k-tile (9 x 5912 x
-// 21232 gated 165 us, 192 this way).  Two rows of tiles read B twice: 256 x 4096 x 16384 104.7 -> 102.8, but 145 x 2816 x 9728
-// gated 71 -> 77.6.
-inline bool read_once(const GemmArgs& g, bool dual) {
-  const int mode = params().gemm_once;
-  const double bytes = (dual ? 2.0 : 1.0) * g.Nn * g.Kk * 2.0;
-  return mode == 2 || (mode == 1 && g.M <= 128 && bytes >= 80e6 && g.ldb % 64 == 0);
-}
-
 // Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
 // column l % 32 of a 32x32 block) -> LDS -> rows, four columns per lane, so that a row's columns are whole
 // cache lines.  PITCH (words) is 8 modulo 16: the two half-waves of a store, four rows apart, then lie in

@@ -144,6 +144,26 @@ def test_dense_plans_take_shapes_that_are_built(lib):
     assert lib.raw.coreinfer_dev_set_param(b"gemm_tile", 15) == lib.CI_ERR_INVALID_ARG
 
 
+def test_dense_plan_reads_large_weights_once(lib):
+    """Where the weights are loaded as data that is not read again: at most 128 tokens, k-contiguous rows of whole cache lines, 80 MB
+    of a product, and up to 32 tokens or a layer that the memory-side cache does not hold."""
+    import torch
+    for M, d, N, act, layout, up, down in [
+            (32, 3776, 12736, "relu", "out_major", 1, 1),       # 96 MB a product, 192 MB a layer
+            (33, 3776, 12736, "relu", "out_major", 0, 0),
+            (32, 3072, 12736, "relu", "out_major", 0, 0),       # 78 MB
+            (32, 3008, 10048, "swiglu", "out_major", 1, 0),     # 121 and 60 MB
+            (77, 4096, 11008, "swiglu", "out_major", 1, 1),     # 180 and 90 MB: 270 of the cache's 268
+            (77, 4096, 10880, "swiglu", "out_major", 0, 0),     # 267 MB
+            (77, 4096, 11008, "swiglu", "neuron_major", 1, 0),
+            (128, 4096, 16384, "relu", "out_major", 0, 0),      # just the cache's size
+            (128, 4096, 16448, "relu", "out_major", 1, 1),
+            (129, 5120, 20480, "relu", "out_major", 0, 0),
+            (32, 5128, 20488, "relu", "out_major", 0, 0)]:
+        plan = lib.dev_dense_plan(M, d, N, torch.float16, act, layout)
+        assert (plan["up_once"], plan["down_once"]) == (up, down), (M, d, N, act, layout, plan)
+
+
 def test_hidden_call_makes_no_plans_to_check_its_arguments(lib):
     """A call that is refused for want of a workspace has cost what the same refusal of coreinfer_ffn_dense does, far less
     than the size query, which plans both layouts (fastest of many rounds of each)."""

@@ -120,13 +120,14 @@ def test_dense_read_once_loads(lib, tile, act, dtype):
         lib.dev_set_param("gemm_once", 1)
 
 
-# Short prompts over weights of more than 80 MB a product, where the rule takes those loads: slim tiles for both
-# projections, for one and for none, a down projection below the line, and rows of no multiple of 128 bytes, which keep
-# the ordinary loads
-@pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 77, 4096, 11008), ("relu", torch.float16, 16, 4096, 16384),
-                                             ("relu", torch.bfloat16, 128, 5120, 13824), ("swiglu", torch.float16, 33, 3072, 8192),
-                                             ("relu", torch.float16, 45, 4104, 12008)])
-def test_dense_short_prompts_of_large_layers(lib, act, dtype, M, d, N):
+# Short prompts over weights of more than 80 MB a product, where the rule takes those loads, and two that keep the ordinary
+# ones: a layer that the memory-side cache holds, and rows of no multiple of 128 bytes
+@pytest.mark.parametrize("act,dtype,M,d,N,once", [("swiglu", torch.bfloat16, 77, 4096, 11008, (1, 1)), ("relu", torch.float16, 16, 4096, 16384, (1, 1)),
+                                                  ("relu", torch.bfloat16, 128, 5120, 13824, (1, 1)), ("swiglu", torch.float16, 31, 3072, 8192, (1, 0)),
+                                                  ("swiglu", torch.float16, 33, 3072, 8192, (0, 0)), ("relu", torch.float16, 45, 4104, 12008, (0, 0))])
+def test_dense_short_prompts_of_large_layers(lib, act, dtype, M, d, N, once):
+    plan = lib.dev_dense_plan(M, d, N, dtype, act, "out_major")
+    assert (plan["up_once"], plan["down_once"]) == once
     print("large layer case", act, dtype, M, d, N, lib.dev_dense_plan(M, d, N, dtype, act, "out_major"), flush=True)
     g = torch.Generator(device=DEV).manual_seed(M)
     mat = lambda *s: (torch.randn(*s, generator=g, device=DEV) * 0.02).to(dtype)  # noqa: E731
