@@ -750,7 +750,9 @@ __global__ __launch_bounds__(1024) void count_kernel(const typename IN::T* __res
 // before its own that are above / at T, and places its own: position = #greater before +
 // min(#equal before, need).  The tally re-reads the counts before the block (cache resident;
 // N <= 65536 keeps that to a few MB in all).
-__global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __restrict__ counts,
+// EARLY: one workgroup per compute unit; else two.
+template <bool EARLY>
+__global__ __launch_bounds__(1024, EARLY ? 4 : 8) void def2_parallel_kernel(const int32_t* __restrict__ counts,
                                                              const uint32_t* __restrict__ ghist, int N, int K,
                                                              int32_t* __restrict__ core_idx, int vec_ok,
                                                              int64_t counts_stride, int max_count) {
@@ -760,19 +762,19 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
   __shared__ __attribute__((aligned(16))) uint32_t wtot[4], wg[kMaxWaves], we[kMaxWaves];
   __shared__ uint32_t T_s, need_s;
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
-  // (0) the counts that are compared with T further down, requested before the histogram is waited for: this block's own
-  // and the first eight vectors a thread of those before it
+  // (0) EARLY: the counts that are compared with T further down, requested before the histogram is waited for: this block's
+  // own and the first eight vectors a thread of those before it
   const int before = blockIdx.x * 256;
   const int4* cv = reinterpret_cast<const int4*>(counts);
   const int nv = vec_ok ? before / 4 : 0;
   int4 v[8];
-  if (nv > 0) {  // uniform
+  if (EARLY && nv > 0) {  // uniform
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = cv[min(tid + u * nt, nv - 1)];
   }
   const int n = before + tid;
   const bool valid = tid < 256 && n < N;
-  const uint32_t c = valid ? (uint32_t)counts[n] : 0u;
+  uint32_t c = EARLY && valid ? (uint32_t)counts[n] : 0u;
   // (1) T: the count value with #(count > T) < K <= #(count >= T).  Thread t < 256 owns the eight
   // bins 2047 - 8t - j, highest first, so the keys above a bin are a prefix sum over threads.
   uint32_t bins[8], mine = 0;
@@ -817,7 +819,7 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
   uint32_t g = 0, e = 0;
   if (vec_ok) {
     for (int i0 = tid; i0 < nv; i0 += nt * 8) {
-      if (i0 != tid) {
+      if (!EARLY || i0 != tid) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = cv[min(i0 + u * nt, nv - 1)];
       }
@@ -847,6 +849,7 @@ __global__ __launch_bounds__(1024) void def2_parallel_kernel(const int32_t* __re
   g = wave_prefix_incl(g);
   e = wave_prefix_incl(e);
   // (3) this block's neurons (threads 0..255), in index order = wave, then lane
+  if (!EARLY) c = valid ? (uint32_t)counts[n] : 0u;
   const bool isg = valid && c > T, ise = valid && c == T;
   const uint64_t bg = __ballot(isg), be = __ballot(ise);
   if (lane == 63) {
@@ -1303,8 +1306,16 @@ int launch_select(const void* act, int act_dtype, int take_abs, int64_t M64, int
     if (rc != CI_OK) return rc;
     if (parallel_final) {
       const int cvec = (reinterpret_cast<uintptr_t>(counts) & 15u) == 0 ? 1 : 0;
-      hipLaunchKernelGGL(def2_parallel_kernel, dim3(nblocks, B), dim3(1024), 0, s, counts, ghist, N, K, core_idx,
-                         cvec && counts_stride % 4 == 0, counts_stride, (int)max_count);
+      // Early requests keep 32 registers a thread in use: two workgroups no longer share a compute unit.  Where each has one of its
+      // own they save a wait (1024 x 13824, all launches 28.7 -> 28.2 us), else they cost (8 sentences, this kernel alone: of 16384
+      // neurons 6.2 us without and 8.0 with them, of 43008 18.1 and 24.7, of 64960 28.4 and 40.0).
+      const int vec = cvec && counts_stride % 4 == 0;
+      if (nblocks * B <= di.cus)
+        hipLaunchKernelGGL(def2_parallel_kernel<true>, dim3(nblocks, B), dim3(1024), 0, s, counts, ghist, N, K, core_idx, vec,
+                           counts_stride, (int)max_count);
+      else
+        hipLaunchKernelGGL(def2_parallel_kernel<false>, dim3(nblocks, B), dim3(1024), 0, s, counts, ghist, N, K, core_idx, vec,
+                           counts_stride, (int)max_count);
       CI_HIP_CHECK_LAUNCH();
       return CI_OK;
     }

@@ -36,3 +36,16 @@ def test_select_ends_of_rows(lib, N, M, dt):
     S_ref, c_ref = orc.select(wide[:, :N].float().numpy(), alpha, beta)
     assert np.array_equal(counts.cpu().numpy(), c_ref)
     assert np.array_equal(S.cpu().numpy(), S_ref)
+
+
+# Def. 2 in parallel with as many workgroups as there are compute units (256) and with more, where its counts are requested
+# later; fewer and more than 8192 vectors of counts before a workgroup; counts that do and do not start on 16 bytes
+@pytest.mark.parametrize("B,M,N", [(4, 3, 16384), (4, 3, 16385), (5, 2, 13824), (3, 2, 40001), (2, 2, 65536)])
+def test_select_batch_workgroups(lib, B, M, N):
+    print("batch case", B, M, N, flush=True)
+    act = torch.randn(B * M, N, generator=torch.Generator().manual_seed(N)).abs()
+    S, counts = lib.select_batch(act.to(DEV), B, 0.2, 0.4)
+    for b in range(B):
+        S_ref, c_ref = orc.select(act[b * M:(b + 1) * M].numpy(), 0.2, 0.4)
+        assert np.array_equal(counts[b].cpu().numpy(), c_ref)
+        assert np.array_equal(S[b].cpu().numpy(), S_ref)
