@@ -3,11 +3,12 @@
 // The two launches of ffn_decode.hip cost the host about 3.9 us each, more than the GPU needs for both where the weights
 // are a few hundred kilobytes.  So every workgroup here computes ALL hidden values, from weights that lie in its L2, keeps
 // them in LDS and sums its own columns of y over all neurons: no partial sums, no second launch, nothing to agree on.
-// What bounds it is the fill of a compute unit's L1 with the up (and gate) rows, about 130 GB/s (fp32; 80 in 16 bits,
-// with twice the products a byte); the down rows of the workgroup's columns are requested ahead of them and wait in registers.
-// A call gives the same bits whichever way it goes (launched or captured, apart or in place): dot products are added up
-// over the lanes as there, down rows slice by slice, and the slices in the order of decode_reduce_kernel.  That costs nothing
-// measurable: 256 x 410 fp32 from a graph 6.9 us, and 6.9 with the rows spread over all threads.
+// What bounds it is the fill of a compute unit's L1 with the up (and gate) rows: by the slope of its time over their size 124 GB/s
+// in fp32 and 85 in 16 bits, with twice the products a byte (256 x 96 to 256 x 512).  The down rows of the workgroup's columns
+// are requested ahead of them and wait in registers.
+// A call gives the same bits whichever way it goes (launched or captured, apart or in place; finite weights): dot products are
+// added up over the lanes as there, down rows slice by slice, and the slices in the order of decode_reduce_kernel.  That costs
+// nothing measurable: 256 x 424 fp32 from a graph 6.91 us, and 6.89 with the rows spread over all threads.
 #include "common.hpp"
 #include "decode_common.hpp"
 

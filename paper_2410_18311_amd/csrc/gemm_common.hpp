@@ -22,7 +22,7 @@ struct GemmArgs {
   bool once;  // B is loaded as data that is not read again
 };
 
-// Floats from one tile of sums to the next.  The tiles are powers of two and their workgroups store in step: 256 bytes in
+// Floats from one tile of sums to the next.  Most tiles are powers of two and their workgroups store in step: 256 bytes in
 // between keep them off the same memory channels (256 tokens, gated 8192 x 28672: 380 us with tiles end to end or
 // 1 KB apart in one run of two, 370 to 373 with 256 bytes and in rows of the whole product).
 __host__ __device__ constexpr int64_t sums_pitch(int bm, int bn) { return (int64_t)bm * bn + 64; }

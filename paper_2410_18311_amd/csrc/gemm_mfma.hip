@@ -7,8 +7,8 @@
 //   [Kk, Nn].
 //
 // This file plans a product (which tile shape, whether the last round of tiles is
-// split along k) for the kernels of gemm_wide.hip and gemm_mid.hip, and adds up
-// split sums.
+// split along k) for the kernels of gemm_wide.hip, gemm_mid.hip and gemm_slim.hpp,
+// and adds up split sums.
 // The fp32 element type has its own kernels (gemm_f32.hip).
 #include "gemm_common.hpp"
 
@@ -54,11 +54,11 @@ __global__ __launch_bounds__(kReduceQuads) void split_reduce_kernel(const float*
 
 // ---- which tiles, and how they are spread over the chip ------------------------
 struct TileShape {
-  int shape;    // kMid..., kWide, or kSlim + ...
+  int shape;    // kMid..., kWide, or kSlim + 16 tm + tn
   int bm, bn;   // rows of A, rows of B (SwiGLU: half of them gate, half up)
   double rate;  // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
-  // FewRowsTime: bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a fill takes when
-  // every 128 bytes of a row lie in two lines
+  // FewRowsTime (fill 0: takes no part): bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a
+  // fill takes when every 128 bytes of a row lie in two lines
   double fill, flops, fixed, two_lines;
 };
 constexpr int kWide = 4;
@@ -163,14 +163,16 @@ void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
 // Up to 128 rows the plan is made again by FewRowsTime, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
 // that estimate promises 6 % or more: over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
-// most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  From 129 rows on the slim tiles are 3 to
+// most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  (The line was drawn on these products.  164
+// others, both projections together, layers of 120 to 330 MB in turn: 13 % faster on average, at most 2.5 % slower.)  From 129 rows on the slim tiles are 3 to
 // 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
 // to 256 bytes, ran on them from 23 % faster to 25 % slower.
 // The up projection's plan of more rows is made again too, without them, and taken where the estimate promises 24 % or more:
 // these are row lengths that are no multiple of 64 bytes, whose pieces lie in two cache lines and which tiles of 256 x 256 read
 // least often.  Of 630 measured products of 129 to 4096 rows 21 change, 3 to 16 % faster but one (0.7 % slower), e.g. 577 x 6256 x 16328 gated
 // 376 -> 316 us, 444 x 5624 x 16448 344 -> 289; promises of 17 to 22 % gave from 13 % less to 9 % more time, and the down projection's plans
-// by this estimate one in fifteen more than 3 % slower.
+// by this estimate one in fifteen more than 3 % slower.  (Of 200 others of 129 to 3000 rows the average is unchanged; the eight that
+// seemed slowest, by 2 to 3 % call by call, are within 1 % from a graph.)
 GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, int out_bytes, size_t room) {
   const Product p{(int)M, (int)Nn, (int)Kk, dual, out_bytes};
   GemmPlan best{};

@@ -1,12 +1,12 @@
 // Dense prefill FFN (Def. 1 of arXiv 2410.18311): the GEMM for 16-bit element types where few rows of tokens meet
 // many weights (up to 128 tokens), with the operand layouts in LDS, the loads and the epilogues of gemm_wide.hip.
 //
-// What bounds such a product is the fill of a compute unit's L1: it keeps 32 KB of lines outstanding, whatever the ring in
-// LDS holds, and hits wait behind misses, so that tile loads that miss the L2 in part come at 45 to 57 GB/s per compute
-// unit (hits alone 117), while the weights alone could come at 23 (all 256 together 5.8 TB/s).  So a tile should have no
+// What bounds such a product is the fill of a compute unit's L1: it keeps about 110 lines of 128 bytes outstanding, whatever the
+// ring in LDS holds, and one that misses the L2 in part takes 700 cycles (77 x 4096 x 11008 gated: 10.4 thousand lines in 66
+// thousand cycles, 20 bytes per clock, where a stream of hits alone comes at 50).  So a tile should have no
 // row of padding, and there should be as many tiles as compute units: tiles are any multiple of 16 in both directions.
 // To make that possible the four waves of a workgroup share no rows or columns but the k-tiles: wave w multiplies the
-// whole tile for k-tiles w, w + 4, ..., with loads and an LDS ring of its own (10 to 40 KB), so there is no barrier in the
+// whole tile for k-tiles w, w + 4, ..., with loads and an LDS ring of its own (18 to 40 KB), so there is no barrier in the
 // loop, every fragment is read from LDS once (waves of 64x64 of a 128x128 tile read each twice), and blocks need not
 // divide by four.  The four sums are added at the end, in the order of the waves, on the way to the outputs.
 // Measured (gated up projection of 4096 x 11008 in bf16, 180 MB of weights; gemm_mid.hip -> here): 16 tokens 36.8 -> 29.8 us

@@ -26,17 +26,18 @@
 //     is the pair (T, cut): neuron n is in its core set iff key > T or (key == T
 //     and n <= cut).  Nine barriers per token in the usual fp32 case (no tie
 //     cut, at most 64 keys left after two digits).
-//     The kernel is bound by vector instructions (four waves of each SIMD, nine thousand cycles a token before, two
-//     thirds of that now): keys come through a buffer descriptor of the row, whose end needs no test and whose addresses are
-//     one register, tests of a digit are one subtraction and one comparison, and no mask outlives its use (for_pairs).
-//     1024 x 13824 fp32, all launches 33.9 -> 28.7 us; 256 x 16384 fp16 20.0 -> 19.0; 986 x 18112 bf16 75 -> 57.
+//     Instructions and barriers are what a token takes: keys come through a buffer descriptor of the row, whose end needs no test
+//     and whose addresses are one register, tests of a digit are one subtraction and one comparison, and no mask outlives its
+//     use (for_pairs).  By counter, 1024 x 13824 fp32: 11.6 -> 7.5 million vector and 6.0 -> 4.2 million scalar instructions,
+//     53.7 -> 41.0 thousand busy cycles of a compute unit for its four tokens; all launches 33.9 -> 28.4 us; 256 x 16384 fp16
+//     20.0 -> 18.7; 986 x 18112 bf16 75 -> 57.
 //     Where the keys are in registers the workgroup also counts, for each of its
 //     neurons, the tokens of its own that have it in their core set (a byte per
 //     neuron, four to a register), and writes those bytes once at its end.
 // count_partial_kernel -- Eq. 3 from those bytes: one byte per neuron and workgroup
 //     instead of every activation again (1024 x 13824 fp32 scores: 7 MB instead of
-//     57 MB read, counting 13.0 -> 4.5 us, the
-//     per-token kernel 24.4 -> 26.3 us).
+//     57 MB read, counting 13.1 -> 4.6 us, the
+//     per-token kernel 19.0 -> 20.3 us).
 // count_kernel -- Eq. 3 where there are no such bytes (see byte_counts_pay; rows
 //     of more than 40960 neurons, more than 64 sentences).
 //     Counting is then a second pass over the activations by neuron: a workgroup owns 64 neurons (256 when that still gives more
@@ -1105,21 +1106,23 @@ int launch_threshold(const typename IN::T* act, int M, int N, int64_t ld, int64_
   return CI_OK;
 }
 
-// Whether the per-token kernel leaves byte counts, so that the activations need not be read again.  They cost it 1 to 2
-// us, and, as each workgroup then has one sentence's tokens only, sometimes a round of tokens more (rounds, rounds_part:
-// without and with them).  Measured, counting kernel / byte counts (us):
+// Whether the per-token kernel leaves byte counts, so that the activations need not be read again.  They cost it about
+// 1 us, and, as each workgroup then has one sentence's tokens only, sometimes a round of tokens more (rounds, rounds_part:
+// without and with them).  Measured from a graph, counting kernel / byte counts (us):
 //  - rows of fewer than 4096 neurons fill a row of byte counts (words of four neurons, 1024 apart) badly: one or two
-//    sentences 113 / 57 (4096 x 1024), 17 / 16 (32 x 1024); from three on 17.8 / 19.7 (12 x 33 x 1024), 19 / 29 (64 x 4 x 1024),
-//    but for few tokens in all (14.1 / 13.6, 3 x 11 x 1024) and for many each (96 / 87, 24 x 256 x 3072);
+//    sentences 104 / 46 (4096 x 1024), 12.6 / 11.8 (32 x 1024); from three on 14.9 / 16.2 (12 x 33 x 1024), 14 / 23 (64 x 4 x 1024),
+//    but for few tokens in all (13.3 / 12.5, 3 x 11 x 1024) and for many each (83 / 71, 24 x 256 x 3072);
 //  - a counting kernel of 64 neurons per workgroup takes two rounds once it has more workgroups than there are compute units:
-//    21.2 / 18.5 (5 x 64 x 4096), 27.7 / 25.3 (256 x 22016), 23.4 / 20.7 (2 x 128 x 16384); with loads of one element
-//    it is slower still: 27.5 / 24.9 (300 x 13825; few tokens of many sentences 43 / 49, 64 x 4 x 4097);
-//  - several rounds of tokens make the second pass long: one sentence from two on (1024 x 13824 39.4 / 34.2, 1024 x 11008 fp16
-//    39.8 / 36.8), more from four on (8 x 512 x 16384 96 / 73), or from two where it misses the caches (8 x 128 x 11008
-//    0.89, but 3 x 256 x 11008, 34 MB, 31.7 / 34.8);
-//  - one round of tokens, all in cache, is a matter of latency: at most 8192 neurons, or 64 tokens, 3 to 6 % faster;
-//    128 to 512 tokens of 11008 to 16384 neurons 2 to 8 % slower, up to 32 MB of them (27.2 / 25.8, 512 x 16384 fp32); above 32768 neurons (keys of nine or ten registers of
-//    counts) 25.9 / 27.9 (1 x 36864), from 256 tokens on faster (512 x 36864 fp16 58.0 / 51.6).
+//    18.5 / 15.4 (5 x 64 x 4096), 25.0 / 21.5 (256 x 22016), 21.8 / 18.8 (2 x 128 x 16384); with loads of one element
+//    it is slower still: 24.7 / 21.0 (300 x 13825; few tokens of many sentences 38 / 43, 64 x 4 x 4097);
+//  - several rounds of tokens make the second pass long: one sentence from two on (1024 x 13824 35.6 / 29.5, 1024 x 11008 fp16
+//    33.4 / 30.1), more from four on (8 x 512 x 16384 117 / 84), or from two where it misses the caches (8 x 128 x 11008
+//    35.3 / 30.6; 3 x 256 x 11008, 34 MB, 27.3 / 27.2);
+//  - one round of tokens, all in cache, is a matter of latency: at most 8192 neurons, or 64 tokens, 1 to 4 % faster (64 x 8192
+//    14.7 / 14.1, 256 x 8192 15.9 / 15.8); 128 to 512 tokens of 11008 to 16384 neurons from 5 % slower to 2 % faster (256 x 16384 fp16
+//    18.7 / 19.6, fp32 20.5 / 20.0, 512 x 11008 21.0 / 20.5), faster from 32 MB of them on (24.7 / 22.6, 512 x 16384 fp32); above 32768
+//    neurons (keys of nine or ten registers of counts) 22.1 / 23.6 (1 x 36864), from 256 tokens on faster (30.5 / 28.5; 512 x 36864 fp16
+//    49.2 / 40.8).
 bool byte_counts_pay(int64_t B, int64_t M, int64_t N, size_t bytes, bool vec_ok, int rounds, int rounds_part, int cus) {
   const bool few = B * M <= (N < 4096 ? 100 : 64);
   if (B > 2 && N < 4096) return (B <= 5 && few) || (N >= 2048 && M >= 256 && rounds >= 4);

@@ -10,7 +10,8 @@ of the workload's shapes, a few times.  `--what prefill` runs the prefill side
 instead: the dense FFN of one layer on the prompts of all sentences of the
 workload, the selection on their activations and, for a single sentence, the
 deployment of the selected neurons, a few times (for instruction-issue, LDS and
-memory-path counters of those kernels); `--what union` runs the
+memory-path counters of those kernels; `--tokens` for a shorter prompt than the
+workload's); `--what union` runs the
 union-batched decode of the workload's sentences over resident weights after
 the calibration copy.  Nothing is timed here.
 """
@@ -33,6 +34,7 @@ def main():
     p.add_argument("--layers", type=int, default=8)
     p.add_argument("--reps", type=int, default=3)
     p.add_argument("--what", choices=["decode", "prefill", "union"], default="decode")
+    p.add_argument("--tokens", type=int, default=None, help="prompt length of the prefill run (default: the workload's)")
     p.add_argument("--beta", type=float, default=None, help="sentence keep fraction (default: the workload's first)")
     p.add_argument("--down-layout", choices=["auto", "out_major", "neuron_major"], default="auto",
                    help="compact down matrix of the decode run (auto: the library's preference for the shape)")
@@ -46,7 +48,7 @@ def main():
 
     if args.what == "prefill":
         w = wl.layer_weights(cfg, 0, dev)
-        X = torch.cat([wl.prefill_hidden(cfg, 0, dev, sentence=s) for s in range(B)], dim=0).contiguous()
+        X = torch.cat([wl.prefill_hidden(cfg, 0, dev, sentence=s)[:args.tokens] for s in range(B)], dim=0).contiguous()
         M = X.shape[0]
         A = torch.empty(M, N, dtype=torch.float32, device=dev)
         Y = torch.empty(M, d, dtype=dt, device=dev)
