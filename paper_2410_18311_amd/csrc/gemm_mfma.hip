@@ -76,7 +76,7 @@ constexpr TileShape slim_shape(int tm, int tn) {
 
 struct Product {
   int M, Nn, Kk;
-  bool dual;
+  bool up, dual;  // the up projection, whose k is not split; with a gate matrix
   int out_bytes;  // written per output
 };
 
@@ -149,7 +149,7 @@ void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best
     const int parts = (p.Kk + k_chunk - 1) / k_chunk;
     if (sp > 1 && (tail == 0 || (size_t)parts * (size_t)tail * sums_pitch(ts.bm, bn) * sizeof(float) > room)) break;
     const double t = time(full, tail, sp);
-    if (force_splits > 0 && room > 0 ? sp == force_splits : t < best_t) {
+    if (force_splits > 0 && !p.up ? sp == force_splits : t < best_t) {
       best_t = t;
       best = GemmPlan{ts.shape, ts.bm, bn, full, tail, sp, k_chunk};
     }
@@ -173,8 +173,8 @@ void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best
 // 376 -> 316 us, 444 x 5624 x 16448 344 -> 289; promises of 17 to 22 % gave from 13 % less to 9 % more time, and the down projection's plans
 // by this estimate one in fifteen more than 3 % slower.  (Of 200 others of 129 to 3000 rows the average is unchanged; the eight that
 // seemed slowest, by 2 to 3 % call by call, are within 1 % from a graph.)
-GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, int out_bytes, size_t room) {
-  const Product p{(int)M, (int)Nn, (int)Kk, dual, out_bytes};
+GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool up, bool dual, bool b_kmajor, int out_bytes, size_t room) {
+  const Product p{(int)M, (int)Nn, (int)Kk, up, dual, out_bytes};
   GemmPlan best{};
   double best_t = 1e30;
   const int force = params().gemm_tile;
@@ -184,7 +184,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, 
     for (const TileShape& ts : kShapes)
       if (force < 0 || force >= kSlim || ts.shape == force) consider<ManyRowsTime>(ts, p, room, best, best_t);
     const bool few = M <= kSlimRows;
-    if (force < 0 && params().gemm_splits == 0 && (few || room == 0)) {
+    if (force < 0 && params().gemm_splits == 0 && (few || up)) {
       double few_t = few ? 1e30 : 0.0;
       for (const TileShape& ts : kShapes)
         if (ts.shape == best.shape && ts.fill > 0) few_t = (few ? 0.94 : 0.76) * FewRowsTime(ts, p)(best.full, best.tail, best.splits);
@@ -289,7 +289,7 @@ GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act) {
   // one plan whichever outputs are asked for: another tile adds up in another order, and their bits are the same in every call
   if (dtype == CI_F32) return GemmPlan{};
   const bool gated = act == CI_ACT_SWIGLU;
-  GemmPlan p = plan_gemm(M, N, d, gated, false, 6, 0);
+  GemmPlan p = plan_gemm(M, N, d, true, gated, false, 6, 0);
   p.once = read_once(p, M, N, d, gated, false, gated);
   return p;
 }
@@ -298,7 +298,7 @@ GemmPlan gemm_up_plan(int64_t M, int64_t d, int64_t N, int dtype, int act) {
 GemmPlan gemm_down_plan(int64_t M, int64_t d, int64_t N, int down_layout, int dtype, bool gated, size_t room) {
   if (dtype == CI_F32) return GemmPlan{};
   const bool b_kmajor = down_layout == CI_DOWN_NEURON_MAJOR;
-  GemmPlan p = plan_gemm(M, d, N, false, b_kmajor, 2, room);
+  GemmPlan p = plan_gemm(M, d, N, false, false, b_kmajor, 2, room);
   p.once = read_once(p, M, d, N, false, b_kmajor, gated);
   return p;
 }
