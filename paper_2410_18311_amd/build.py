@@ -50,10 +50,10 @@ def build_library(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
-    bad = isa_check.lds_load_hazards(LIB_PATH)
+    bad = isa_check.hazards(LIB_PATH)
     if bad:
         os.remove(LIB_PATH)
-        raise RuntimeError("loads into LDS that read a scalar register too soon after a vector instruction wrote it:\n" +
+        raise RuntimeError("loads into LDS or matrix products that read a register too soon after it was written, or a product's result read too soon:\n" +
                            "\n".join(bad))
     if verbose:
         print("built", LIB_PATH)

@@ -53,10 +53,11 @@ __device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n, int* tm
   *tn = in / rows;
 }
 
-// 256x256-tile kernel for 16-bit types (gemm_wide.hip).
-int launch_gemm_wide(int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
-// Smaller tiles for 16-bit types (gemm_mid.hip): rows of A x rows of B per workgroup.
-enum { kMid128x128 = 0, kMid128x256 = 1, kMid256x64 = 2, kMid128x64 = 3 };
+// Tile shapes for 16-bit types, rows of A x rows of B per workgroup: 128 x 64 .. 256 (gemm_mid.hip), 256 x 160 .. 256
+// (gemm_wide.hip).
+enum { kMid128x128 = 0, kMid128x256 = 1, kWide192 = 2, kMid128x64 = 3, kWide = 4, kWide224 = 5, kWide160 = 6 };
+constexpr bool is_wide(int shape) { return shape == kWide || shape == kWide224 || shape == kWide192 || shape == kWide160; }
+int launch_gemm_wide(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
 int launch_gemm_mid(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s);
 // Tiles of 16 tm rows of A x 16 tn rows of B (gemm_slim.hpp), B k-contiguous.
 constexpr int kSlim = 16;  // a tile shape's number: kSlim + 16 tm + tn

@@ -53,38 +53,82 @@ __global__ __launch_bounds__(kReduceQuads) void split_reduce_kernel(const float*
 }
 
 // ---- which tiles, and how they are spread over the chip ------------------------
-struct TileShape {
-  int shape;    // kMid..., kWide, or kSlim + 16 tm + tn
-  int bm, bn;   // rows of A, rows of B (SwiGLU: half of them gate, half up)
-  double rate;  // flop/s of one compute unit inside a tile (measured: rounds of full tiles at 512 to 4096 rows)
-  // FewRowsTime (fill 0: takes no part): bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a
-  // fill takes when every 128 bytes of a row lie in two lines
-  double fill, flops, fixed, two_lines;
-};
-constexpr int kWide = 4;
+// Every workgroup takes all of a compute unit's LDS, so tiles run in rounds of 256.  Three estimates, each for the products it was
+// fitted to.
 constexpr int kTileK = 64;      // k of a tile
 constexpr int kFullChip = 256;  // compute units of an MI355X
 constexpr int kSlimRows = 128;
-constexpr TileShape kShapes[] = {{kMid128x128, 128, 128, 3.6e12, 144e9, 10.1e12, 4.3e-6, 0.85},
-                                 {kMid128x256, 128, 256, 4.4e12, 114e9, 16.6e12, 4.0e-6, 1.0},
-                                 {kMid256x64, 256, 64, 3.2e12, 0, 0, 0, 0},
-                                 {kMid128x64, 128, 64, 2.7e12, 212e9, 6.5e12, 4.5e-6, 1.8},
-                                 {kWide, 256, 256, 5.5e12, 1e15, 8.1e12, 4.2e-6, 0}};
-constexpr TileShape slim_shape(int tm, int tn) {
-  return TileShape{kSlim + 16 * tm + tn, 16 * tm, 16 * tn, 2.7e12, 165e9, 7.3e12, 5.3e-6, 2.6};
-}
 
 struct Product {
   int M, Nn, Kk;
   bool up, dual;  // the up projection, whose k is not split; with a gate matrix
+  bool b_kmajor;
   int out_bytes;  // written per output
+  // 16-bit elements: what share of the 128-byte pieces of a row lie in two cache lines
+  double two_lines() const {
+    const int odd = Kk * 2 % 128;
+    return odd == 0 ? 0.0 : odd % 64 == 0 ? 0.5 : odd % 32 == 0 ? 0.75 : 0.875;
+  }
 };
 
-// A product of `full` tiles computed whole and `tail` tiles split along k, tiles in rounds of 256: every workgroup takes all of a
-// compute unit's LDS.  The sums of split tiles are written, read back and added by another launch (about 4.5 TB/s and 5 us).
+// More than 128 rows.  A round of n tiles takes their multiplications, faster the fewer run side by side (they share the chip's
+// power and caches), a fixed part (first loads, results) and the stores; the sums of split tiles are written, read back
+// and added by another launch.  The constants are those that come closest to 4900 measured products of 129 to 4096 rows, d
+// 1024 to 9216 and N 2048 to 36864, odd lengths among them, all shapes and splits (7.6 % off on average).  Of 271 pairs of products the plans by
+// it are on average 0.2 % (up) and 2.2 % (down) behind the fastest of all; those by the former estimate of whole rounds were 1.0 and 5.3 %.
+struct ManyShape {
+  int shape;
+  int bm, bn;        // rows of A, rows of B (SwiGLU: half of them gate, half up)
+  double rate;       // flop/s of one compute unit inside a tile, all of them busy
+  double fixed;      // s of a round
+  double alone;      // a tile's time with nothing beside it, as a share of that
+  double two_lines;  // what share more it takes when every 128 bytes of a row lie in two lines
+};
+constexpr ManyShape kManyShapes[] = {{kMid128x128, 128, 128, 3.54e12, 2.8e-6, 0.58, 0.37}, {kMid128x256, 128, 256, 4.41e12, 3.9e-6, 0.61, 0.41},
+                                     {kMid128x64, 128, 64, 2.72e12, 2.1e-6, 0.70, 0.42},   {kWide, 256, 256, 6.12e12, 8.0e-6, 0.72, 0.13},
+                                     {kWide224, 256, 224, 5.85e12, 6.3e-6, 0.73, 0.16},    {kWide192, 256, 192, 5.51e12, 4.9e-6, 0.71, 0.19},
+                                     {kWide160, 256, 160, 4.94e12, 3.0e-6, 0.69, 0.24}};
 struct ManyRowsTime {
+  double t_k, alone, fixed, store, t_sums;
+  int out_bytes;
+  ManyRowsTime(const ManyShape& ts, const Product& p) {
+    const int bn = p.dual ? ts.bn / 2 : ts.bn;
+    t_k = 2.0 * ts.bm * ts.bn * (double)p.Kk / ts.rate * (1.0 + ts.two_lines * p.two_lines() * (p.b_kmajor ? 0.5 : 1.0));
+    alone = ts.alone;
+    fixed = ts.fixed;
+    store = (double)ts.bm * bn / 16e12;
+    t_sums = (double)ts.bm * bn / 5e12;
+    out_bytes = p.out_bytes;
+  }
+  double round(int n, double t, int bytes) const { return t * (alone + (1.0 - alone) / kFullChip * n) + fixed + n * store * bytes; }
+  double rounds(int wgs, double t, int bytes) const {
+    const int whole = wgs / kFullChip, rest = wgs % kFullChip;
+    return (whole > 0 ? whole * round(kFullChip, t, bytes) : 0.0) + (rest > 0 ? round(rest, t, bytes) : 0.0);
+  }
+  double operator()(int full, int tail, int sp) const {
+    return rounds(full, t_k, out_bytes) + (tail == 0 ? 0.0 : rounds(tail * sp, t_k / sp, 4) + (double)tail * (4 * sp + 2) * t_sums + 3e-6);
+  }
+};
+
+// Up to 128 rows.  The first estimate counts whole rounds of the larger tiles (about 4.5 TB/s and 5 us for split sums).
+struct FewShape {
+  int shape;
+  int bm, bn;
+  double rate;  // flop/s of one compute unit inside a tile
+  // FewRowsTime: bytes/s and flop/s of one compute unit, s of a round, and what share more of its time a
+  // fill takes when every 128 bytes of a row lie in two lines
+  double fill, flops, fixed, two_lines;
+};
+constexpr FewShape kFewShapes[] = {{kMid128x128, 128, 128, 3.6e12, 144e9, 10.1e12, 4.3e-6, 0.85},
+                                   {kMid128x256, 128, 256, 4.4e12, 114e9, 16.6e12, 4.0e-6, 1.0},
+                                   {kMid128x64, 128, 64, 2.7e12, 212e9, 6.5e12, 4.5e-6, 1.8},
+                                   {kWide, 256, 256, 5.5e12, 1e15, 8.1e12, 4.2e-6, 0}};
+constexpr FewShape slim_shape(int tm, int tn) {
+  return FewShape{kSlim + 16 * tm + tn, 16 * tm, 16 * tn, 2.7e12, 165e9, 7.3e12, 5.3e-6, 2.6};
+}
+struct WholeRoundsTime {
   double t_tile, t_fixed, t_sums;
-  ManyRowsTime(const TileShape& ts, const Product& p) {
+  WholeRoundsTime(const FewShape& ts, const Product& p) {
     const int bn = p.dual ? ts.bn / 2 : ts.bn;
     t_tile = 2.0 * ts.bm * ts.bn * (double)p.Kk / ts.rate;
     // first loads; results of a round, which nothing overlaps
@@ -98,22 +142,20 @@ struct ManyRowsTime {
   }
 };
 
-// The same as a sum rather than a maximum of three parts: what an L1 is filled with, the multiplications, and the weights that a
+// The second is a sum rather than a maximum of three parts: what an L1 is filled with, the multiplications, and the weights that a
 // round reads from memory (a maximum, or a power mean of any higher order, fits worse).  It is a fit, not a model of the chip: the
-// constants of kShapes are those that come closest to 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to
+// constants of kFewShapes are those that come closest to 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to
 // 36864, odd lengths among them, all shapes and splits.  (For tiles of 256 x 256 a fill that costs nothing came closest, with
-// fewer flop/s; 256 x 64 was not fitted and takes no part.)
+// fewer flop/s.)
 struct FewRowsTime {
   int tiles_m, out_bytes;
   double k, fill, columns_fill, inv_tiles_m, fixed, store, t_sums;
-  FewRowsTime(const TileShape& ts, const Product& p) {
+  FewRowsTime(const FewShape& ts, const Product& p) {
     const int bn = p.dual ? ts.bn / 2 : ts.bn, rows = p.M < ts.bm ? p.M : ts.bm;
     tiles_m = (p.M + ts.bm - 1) / ts.bm;
     out_bytes = p.out_bytes;
-    const int odd = p.Kk * 2 % 128;  // 16-bit elements; pieces of 128 bytes of a row that lie in two cache lines:
-    const double two_lines = odd == 0 ? 0.0 : odd % 64 == 0 ? 0.5 : odd % 32 == 0 ? 0.75 : 0.875;
     k = p.Kk;
-    fill = 2.0 * ((rows + ts.bn) * (1.0 + ts.two_lines * two_lines) / ts.fill + (double)ts.bm * ts.bn / ts.flops);
+    fill = 2.0 * ((rows + ts.bn) * (1.0 + ts.two_lines * p.two_lines()) / ts.fill + (double)ts.bm * ts.bn / ts.flops);
     columns_fill = 2.0 * ts.bn / 9.9e12;
     inv_tiles_m = 1.0 / tiles_m;
     fixed = ts.fixed;
@@ -134,8 +176,8 @@ struct FewRowsTime {
 };
 
 // Adds a shape, whole and with its last round in 2 .. 8 parts, to the best plan so far by the estimate Time.
-template <class Time>
-void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best, double& best_t) {
+template <class Time, class Shape>
+void consider(const Shape& ts, const Product& p, size_t room, GemmPlan& best, double& best_t) {
   const Time time(ts, p);
   const int force_splits = params().gemm_splits;
   const int bn = p.dual ? ts.bn / 2 : ts.bn;
@@ -159,7 +201,7 @@ void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best
 
 // The shape and split of the least estimated time whose sums fit `room` bytes.  Examples (both projections, former
 // kernels -> these): 77 tokens, 4096 x 11008 gated 97 -> 66 us; 700 tokens, 4096 x 16384, neuron-major down 708 -> 207 us; 1000
-// tokens, 7168 x 28672, neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.2 ms (its down projection: 576 tiles =
+// tokens, 7168 x 28672, neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.0 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
 // Up to 128 rows the plan is made again by FewRowsTime, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
 // that estimate promises 6 % or more: over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
@@ -167,30 +209,24 @@ void consider(const TileShape& ts, const Product& p, size_t room, GemmPlan& best
 // others, both projections together, layers of 120 to 330 MB in turn: 13 % faster on average, at most 2.5 % slower.)  From 129 rows on the slim tiles are 3 to
 // 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
 // to 256 bytes, ran on them from 23 % faster to 25 % slower.
-// The up projection's plan of more rows is made again too, without them, and taken where the estimate promises 24 % or more:
-// these are row lengths that are no multiple of 64 bytes, whose pieces lie in two cache lines and which tiles of 256 x 256 read
-// least often.  Of 630 measured products of 129 to 4096 rows 21 change, 3 to 16 % faster but one (0.7 % slower), e.g. 577 x 6256 x 16328 gated
-// 376 -> 316 us, 444 x 5624 x 16448 344 -> 289; promises of 17 to 22 % gave from 13 % less to 9 % more time, and the down projection's plans
-// by this estimate one in fifteen more than 3 % slower.  (Of 200 others of 129 to 3000 rows the average is unchanged; the eight that
-// seemed slowest, by 2 to 3 % call by call, are within 1 % from a graph.)
 GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool up, bool dual, bool b_kmajor, int out_bytes, size_t room) {
-  const Product p{(int)M, (int)Nn, (int)Kk, up, dual, out_bytes};
+  const Product p{(int)M, (int)Nn, (int)Kk, up, dual, b_kmajor, out_bytes};
   GemmPlan best{};
   double best_t = 1e30;
   const int force = params().gemm_tile;
   if (force >= kSlim && !b_kmajor) {
-    consider<ManyRowsTime>(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, best, best_t);
-  } else {
-    for (const TileShape& ts : kShapes)
+    consider<WholeRoundsTime>(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, best, best_t);
+  } else if (M > kSlimRows || (force >= 0 && force < kSlim)) {
+    for (const ManyShape& ts : kManyShapes)
       if (force < 0 || force >= kSlim || ts.shape == force) consider<ManyRowsTime>(ts, p, room, best, best_t);
-    const bool few = M <= kSlimRows;
-    if (force < 0 && params().gemm_splits == 0 && (few || up)) {
-      double few_t = few ? 1e30 : 0.0;
-      for (const TileShape& ts : kShapes)
-        if (ts.shape == best.shape && ts.fill > 0) few_t = (few ? 0.94 : 0.76) * FewRowsTime(ts, p)(best.full, best.tail, best.splits);
-      for (const TileShape& ts : kShapes)
-        if (ts.fill > 0) consider<FewRowsTime>(ts, p, room, best, few_t);
-      if (few && !b_kmajor)
+  } else {
+    for (const FewShape& ts : kFewShapes) consider<WholeRoundsTime>(ts, p, room, best, best_t);
+    if (force < 0 && params().gemm_splits == 0) {
+      double few_t = 0.0;
+      for (const FewShape& ts : kFewShapes)
+        if (ts.shape == best.shape) few_t = 0.94 * FewRowsTime(ts, p)(best.full, best.tail, best.splits);
+      for (const FewShape& ts : kFewShapes) consider<FewRowsTime>(ts, p, room, best, few_t);
+      if (!b_kmajor)
         for (int tn = 2; tn <= 8; ++tn)
           if (slim_built((p.M + 15) / 16, tn)) consider<FewRowsTime>(slim_shape((p.M + 15) / 16, tn), p, room, best, few_t);
     }
@@ -212,7 +248,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool up, bool dual, bool b
 // 104.7 -> 102.8, but 145 x 2816 x 9728 gated 71 -> 77.6.
 bool read_once(const GemmPlan& p, int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, bool gated) {
   const int mode = params().gemm_once;
-  if (mode == 0 || b_kmajor || p.shape == kWide) return false;
+  if (mode == 0 || b_kmajor || is_wide(p.shape)) return false;
   const int64_t one = Nn * Kk * 2;  // bytes of a matrix of the layer
   return mode == 2 || (M <= 128 && (dual ? 2 : 1) * one >= 80000000 && Kk % 64 == 0 &&
                        (M <= 32 || (gated ? 3 : 2) * one > (int64_t)256 << 20));
@@ -240,7 +276,7 @@ int launch_mfma(GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     const int tm = (p.shape - kSlim) / 16, tn = (p.shape - kSlim) % 16;
     if (!BNN) rc = __is_same(D, F16) ? launch_gemm_slim_f16(tm, tn, EPI, g, s) : launch_gemm_slim_bf16(tm, tn, EPI, g, s);
   } else {
-    rc = p.shape == kWide ? launch_gemm_wide(dtype, EPI, BNN, g, s) : launch_gemm_mid(p.shape, dtype, EPI, BNN, g, s);
+    rc = is_wide(p.shape) ? launch_gemm_wide(p.shape, dtype, EPI, BNN, g, s) : launch_gemm_mid(p.shape, dtype, EPI, BNN, g, s);
   }
   if (rc != CI_OK || p.tail == 0) return rc;
   return launch_sums<D>(g, p, s);

@@ -211,7 +211,6 @@ int launch_typed(int shape, const GemmArgs& g, hipStream_t s) {
   switch (shape) {
     case kMid128x128: return launch_shape<D, EPI, BNN, 2, 2, 2, 2>(g, s);
     case kMid128x256: return launch_shape<D, EPI, BNN, 2, 2, 2, 4>(g, s);
-    case kMid256x64: return launch_shape<D, EPI, BNN, 4, 1, 2, 2>(g, s);
     case kMid128x64: return launch_shape<D, EPI, BNN, 4, 1, 1, 2>(g, s);
   }
   return CI_ERR_UNSUPPORTED;

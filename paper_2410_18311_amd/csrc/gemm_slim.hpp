@@ -19,16 +19,6 @@ namespace ci {
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <class D>
-__device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, f32x4 c) {
-  if constexpr (__is_same(D, F16))
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 constexpr int kLds = 163840;
 
 // TM x TN blocks of 16x16: 16 TM rows of A, 16 TN rows of B.  SwiGLU: a block of B rows is eight gate and eight up rows of

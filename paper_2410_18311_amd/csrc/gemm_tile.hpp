@@ -10,11 +10,17 @@ namespace {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int WK = 64;             // k per tile
+
+template <int V>
+struct Const {
+  static constexpr int value = V;
+};
 
 template <class D>
 __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c) {
@@ -22,6 +28,24 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+template <class D>
+__device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, f32x4 c) {
+  if constexpr (__is_same(D, F16))
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The same, c = a * b + c, written out: the sum stays where it is.  The compiler does not see a matrix product in it: two wait
+// states after a vector instruction that writes an operand, and 18 before anything else touches the sum, are the caller's.
+template <class D>
+__device__ __forceinline__ void mfma16_in_place(const uint4& a, const uint4& b, f32x4& c) {
+  if constexpr (__is_same(D, F16))
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(f16x8, a)), "v"(__builtin_bit_cast(f16x8, b)));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
 }
 
 // Four consecutive columns of one output row: epilogue, then one 16-byte and / or one 8-byte store.
@@ -80,6 +104,28 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* lds, uint32_t o
                  : "={m0}"(m0)
                  : "s"(m), "v"(off), "s"(rsrc)
                  : "memory");
+}
+
+// The same from an address up to an end: reads at or past it return zero.
+__device__ __forceinline__ i32x4 rsrc_until(const char* p, const char* end) {
+  i32x4 r = rsrc_at(p);
+  const size_t n = (size_t)(end - p);
+  r[2] = n < 0xffffffffu ? (int)n : -1;
+  return r;
+}
+
+// A load into LDS in two instructions: the place, written at least one instruction ahead (at_once: a load may follow immediately),
+// and loads that go by it, to 1 KB `piece` behind the place, from as far behind `off` + `scalar_off`.
+__device__ __forceinline__ uint32_t lds_place(uint32_t place, bool at_once = false) {
+  uint32_t m0;
+  if (at_once) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0" : "={m0}"(m0) : "s"(place));
+  else asm volatile("s_mov_b32 m0, %1" : "={m0}"(m0) : "s"(place));
+  return m0;
+}
+__device__ __forceinline__ void load_to_lds_at(int piece, uint32_t place, uint32_t off, i32x4 rsrc, uint32_t scalar_off) {
+  asm volatile("buffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+               :: "{m0}"(place), "v"(off), "s"(rsrc), "s"(scalar_off), "n"(piece * 1024)
+               : "memory");
 }
 
 // Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,

@@ -1,38 +1,38 @@
-// Dense prefill FFN (Def. 1 of arXiv 2410.18311): the 256x256-tile GEMM for
-// 16-bit element types, C[M, Nn] = A[M, Kk] * B^T with the fused epilogues of
-// gemm_mfma.hip.
+// Dense prefill FFN (Def. 1 of arXiv 2410.18311): the GEMM for 16-bit element types
+// with tiles of 256 rows, C[M, Nn] = A[M, Kk] * B^T with the fused epilogues of gemm_mfma.hip.
 //
-// What bounds a tiled MFMA kernel here is LDS traffic next to the matrix cores:
+// What bounds a tiled MFMA kernel here is LDS traffic next to the matrix cores, and the power of both:
 // per 64-k tile the fragments of 2x2 waves of 128x128 outputs take 131 KB of
 // LDS reads and the two operand tiles 64 KB of writes, 1536 clocks at 128 bytes
 // per clock against 2048 clocks of MFMAs (eight waves of 128x64 would read half
 // as much again and come out level).  So four waves, one per SIMD, with the
 // accumulators in 256 registers each; and since a wave then has nobody to hide
 // its waits behind, nothing in its instruction stream may wait:
+//   - products of 16x16x32: per multiplication they read and write half as many sums as those of 32x32x16, and the chip then
+//     holds 1.5 to 1.7 GHz at 4096 x 9216 x 36864 where it held 1.3 to 1.5 (all of that layer 4210 -> 3955 us, 1024 x 5120 x 13824
+//     gated 383 -> 365; with shapes of 160 to 224 columns for its rounds 352);
+//   - they are written out, sums in place: the compiler gives a product's result other registers than its
+//     sum has and moves them back, up to one move a product (the build looks for what it then no longer does, isa_check.py);
 //   - the operand tiles go from global memory straight into LDS, as buffer loads
 //     with a 32-bit offset per lane (with 64-bit addresses an issuing wave stood
 //     still for longer: 1325 against 1374 TFLOP/s at 4096 x 36864 x 9216), in rows
 //     of 128 bytes (rows of 64 bytes cost twice the tag look-ups of the L1:
-//     1156 TFLOP/s);
-//   - fragments are read TWO k-steps (of 16) before they are multiplied, so that
-//     the last fragment of a k-tile is read in its second step, and the one
-//     barrier per k-tile sits there;
+//     1156 TFLOP/s), a constant offset apart for one place in LDS;
+//   - fragments are read half a k-tile before they are multiplied, and the one barrier per k-tile sits in its middle;
 //   - LDS holds five operand tiles of 32 KB: A and B of the k-tile that is
-//     multiplied and of the next one, and room for A of the one after, so that
-//     four loads go out in every k-step and have a k-tile's time to arrive;
-//   - between two MFMAs at most one LDS read and one load are issued, in the order
-//     written.
-// Measured at 4096 x 9216 x 36864 in bf16: 1559 TFLOP/s without the stores of the
-// results (torch's library: 1341 to 1532 for the same two products); in fp16 the
-// matrix pipes are busy 81 % (up) and 89 % (down) of the cycles in which a compute unit
-// has work, at 1.5 and 1.3 GHz under the profiler: the clock is the limit then.
+//     multiplied and of the next one, and room for B of the one after;
+//   - loads go out evenly, eight in half a k-tile: in bursts of one to two products, for more time to arrive, 1970 -> 2100 us for the
+//     larger layer's up projection, and at places of its own for each wave, by branches, 2310.
+// What is left of a k-tile of 256 x 256 at 4096 x 9216 x 36864, 1.37 us: 1.0 us the products with nothing beside them, 0.14 the
+// LDS reads, 0.25 the loads, mostly as lower clock (the same k-tile again and again takes as long, one of zeros 0.95).
+// A tile of fewer columns takes its share of the time: 256, 224, 192 and 160 columns 126, 112, 98 and 84 us in one round of 5120 k.
 //
 // LDS layout: the destination of such a load cannot be padded, so the 16-byte
 // chunks are permuted instead, on the global side.  k-contiguous operand: rows of
 // 128 bytes, chunk j of row r at j ^ ((r / 2) & 7) (any 16 rows of one chunk then
 // touch every bank once).  k-major B (a neuron-major down matrix): rows of 512
-// bytes (one k, 256 columns), chunk j of row k at j ^ 4 (k & 3), read through
-// ds_read_b64_tr_b16, whose 32 lanes then cover four rows x 64 bytes in 256
+// bytes (one k, 256 columns or fewer), chunk j of row k at j ^ 4 (k & 3) ^ 2 (k / 8 & 1), read through
+// ds_read_b64_tr_b16, whose 32 lanes then cover eight rows x 32 bytes in 256
 // different bytes of the banks.
 #include "gemm_tile.hpp"
 
@@ -40,190 +40,316 @@ namespace ci {
 
 namespace {
 
-constexpr int WT = 256;                // output rows and B rows (k-major: columns) of a workgroup
-constexpr int kOperand = WT * WK * 2;  // bytes of one operand tile
+constexpr int WT = 256;                // output rows of a workgroup
+constexpr int kOperand = WT * WK * 2;  // bytes of LDS for one operand tile
 constexpr int kUnits = 5;              // operand tiles in LDS: all of its 160 KB
 
-// TAIL: the last k-tile is not full; chunks past the end of k are read from the start of the row instead and
-// zeroed, in both operands, before they are multiplied.
-template <class D, int EPI, bool BNN, bool TAIL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_wide_kernel(GemmArgs g) {
+// k-major B: chunk j of row k lies at j ^ this.
+__device__ __forceinline__ int kmajor_swizzle(int k) { return (k & 3) << 2 | (k >> 3 & 1) << 1; }
+
+// What goes out behind which of a step's MF products: at most one LDS read (of a fragment) and one load, and mostly not both; the
+// scalar register that a load takes its place in LDS from is written one product ahead.
+template <int MF, int READS, int LOADS>
+struct Places {
+  int read[MF] = {}, load[MF] = {}, place[MF] = {};  // number, -1: none
+  constexpr Places() {
+    for (int m = 0; m < MF; ++m) read[m] = load[m] = place[m] = -1;
+    for (int r = 0; r < READS; ++r) read[r * MF * 3 / (4 * READS)] = r;  // in the first three quarters
+    for (int p = 0; p < LOADS; ++p) {
+      int m = (2 * p + 1) * MF / (2 * LOADS);
+      if (read[m] >= 0 && read[m + 1] < 0) ++m;
+      load[m] = p;
+      if (p % 4 == 0) place[m - 1] = p / 4;
+    }
+  }
+};
+
+// 2 x 2 waves of 8 x TJ blocks of 16x16: 256 rows of A, 32 TJ rows of B.  SwiGLU: a block of B rows is eight gate and eight up
+// rows of the same columns.
+template <class D, bool BNN, int TJ>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_wide_kernel(GemmArgs g, int epi) {
   using T = typename D::T;
-  constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  static_assert(!(BNN && DUAL), "k-major B is only needed for the down projection");
-  constexpr int BNO = DUAL ? WT / 2 : WT;  // output columns of a workgroup
+  constexpr int TI = 8;
+  constexpr int BN = 32 * TJ;
+  constexpr int PB = BNN ? 8 : TJ;  // 1 KB pieces of B per wave and k-tile (k-major: rows of 512 bytes, whatever BN)
+  const bool dual = !BNN && epi == EPI_SWIGLU;
+  const int bno = dual ? BN / 2 : BN;  // output columns of a workgroup
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kUnits * kOperand];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const TileWork w = tile_work(g, WT, BNO);
-  const int m0 = w.tm * WT, n0 = w.tn * BNO;
-  const int k_begin = w.k_begin, k_end = w.k_end;
-  const int nk = (k_end - k_begin + WK - 1) / WK;
-  const int tail_chunks = TAIL ? ((k_end - k_begin) - (nk - 1) * WK) / 8 : 8;  // valid 16-byte chunks of the last k-tile
-  (void)tail_chunks;
+  const TileWork w = tile_work(g, WT, bno);
+  const int m0 = w.tm * WT, n0 = w.tn * bno;
+  const int nk = (w.k_end - w.k_begin + WK - 1) / WK;
+  const int tail_chunks = ((w.k_end - w.k_begin) - (nk - 1) * WK) / 8;  // valid 16-byte chunks of the last k-tile
 
-  // Loads: piece p of a k-contiguous operand is rows 32 p + 8 wave + lane / 8 (rows past the edge are
-  // clamped: they only feed outputs that are not stored); of a k-major B it is k rows 8 p + 2 wave +
-  // lane / 32.  Uniform bases plus 32-bit byte offsets (256 rows of an operand span less than 4 GB).
-  const char* Ab = reinterpret_cast<const char*>(g.A) + ((size_t)m0 * g.lda + k_begin) * sizeof(T);
-  const char* Bb = BNN ? reinterpret_cast<const char*>(g.B0) + ((size_t)k_begin * g.ldb + n0) * sizeof(T)
-                       : reinterpret_cast<const char*>(g.B0) + ((size_t)n0 * g.ldb + k_begin) * sizeof(T);
-  const char* Ub = DUAL ? reinterpret_cast<const char*>(g.B1) + ((size_t)n0 * g.ldb + k_begin) * sizeof(T) : Bb;
-  uint32_t offA[8], offB[8];
-  const int lrow = 8 * wave + (lane >> 3);
-  const int chunk = (lane & 7) ^ ((lrow >> 1) & 7);  // the same in all pieces: 32 p does not reach bits 1 .. 3
-  const int bchunk = (lane & 31) ^ ((2 * (wave & 1) + (lane >> 5)) << 2);  // k-major: k & 3 of row 8 p + 2 wave + lane / 32
+  // Loads: piece p of a k-contiguous operand is eight rows, 8 (8 wave + p) + lane / 8 of A and 8 (TJ wave + p) + lane / 8 of B
+  // (rows past the edge are clamped: they only feed outputs that are not stored); of a k-major B it is k rows 16 wave + 2 p +
+  // lane / 32.  A load adds its constant offset, 1 KB for a piece, to both of its addresses, so that four pieces go by one place
+  // in LDS; the lanes' offsets take it back, and 3 KB that the bases lie ahead keep them positive (256 rows of an operand span less
+  // than 4 GB).  Chunks past the end of k are whatever follows the row, zero behind the matrix, and are zeroed before
+  // they are multiplied.
+  const char* Ab = reinterpret_cast<const char*>(g.A) + ((size_t)m0 * g.lda + w.k_begin) * sizeof(T) - 3072;
+  const size_t b0 = (BNN ? (size_t)w.k_begin * g.ldb + n0 : (size_t)n0 * g.ldb + w.k_begin) * sizeof(T);
+  // SwiGLU: pieces of even rows of eight are the gate's, of odd ones the up matrix's
+  const bool swap = dual && (TJ * wave & 1);
+  const char* B[2] = {reinterpret_cast<const char*>(swap ? g.B1 : g.B0) + b0 - 3072,
+                      reinterpret_cast<const char*>(dual && !swap ? g.B1 : g.B0) + b0 - 3072};
+  uint32_t offA[8], offB[PB];
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
-    offA[p] = (uint32_t)(((size_t)min(32 * p + lrow, g.M - 1 - m0) * g.lda + chunk * 8) * sizeof(T));
+    const int r = 64 * wave + 8 * p + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+    offA[p] = (uint32_t)(((size_t)min(r, g.M - 1 - m0) * g.lda + chunk * 8) * sizeof(T)) + (3 - (p & 3)) * 1024;
+  }
+#pragma unroll
+  for (int p = 0; p < PB; ++p) {
     if (BNN) {
-      const int col = min(n0 + bchunk * 8, g.Nn - 8) - n0;  // Nn is a multiple of 8
-      offB[p] = (uint32_t)(((size_t)(8 * p + 2 * wave + (lane >> 5)) * g.ldb + col) * sizeof(T));
+      const int kr = 16 * wave + 2 * p + (lane >> 5);
+      int c = (lane & 31) ^ kmajor_swizzle(kr);
+      if (c >= BN / 8) c = 0;                        // no such columns: a chunk that is loaded anyway
+      const int col = min(n0 + c * 8, g.Nn - 8) - n0;  // Nn is a multiple of 8
+      offB[p] = (uint32_t)(((size_t)kr * g.ldb + col) * sizeof(T)) + (3 - (p & 3)) * 1024;
     } else {
-      const int r = DUAL ? 32 * (p & 3) + lrow : 32 * p + lrow;
-      offB[p] = (uint32_t)(((size_t)min(r, g.Nn - 1 - n0) * g.ldb + chunk * 8) * sizeof(T));
+      const int r = 8 * (TJ * wave + p) + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+      const int row = dual ? 8 * ((TJ * wave + p) >> 1) + (lane >> 3) : r;
+      offB[p] = (uint32_t)(((size_t)min(row, g.Nn - 1 - n0) * g.ldb + chunk * 8) * sizeof(T)) + (3 - (p & 3)) * 1024;
     }
   }
-  const size_t stepB = BNN ? (size_t)WK * g.ldb * sizeof(T) : (size_t)WK * sizeof(T);
+  const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)smem;
+  const uint32_t myA = lds + wave * 8192, myB = lds + wave * (PB * 1024);
+  const char* endA = reinterpret_cast<const char*>(g.A) + (size_t)g.M * g.lda * sizeof(T);
+  const size_t bytesB = (size_t)(BNN ? g.Kk : g.Nn) * g.ldb * sizeof(T);
+  const i32x4 rsrcA = rsrc_until(Ab, endA);
+  // k-major: bytes from the last k-tile's first row to the end of the matrix
+  const int last_rows = BNN ? (int)((size_t)tail_chunks * 8 * g.ldb * sizeof(T) - (size_t)n0 * sizeof(T)) + 3072 : 0;
+  const i32x4 rsrcB[2] = {rsrc_until(B[0], reinterpret_cast<const char*>(swap ? g.B1 : g.B0) + bytesB),
+                    rsrc_until(B[1], reinterpret_cast<const char*>(dual && !swap ? g.B1 : g.B0) + bytesB)};
+  int rangeA = rsrcA[2], rangeB[2] = {rsrcB[0][2], rsrcB[1][2]};
+  const uint32_t stepB = (uint32_t)g.ldb * (WK * sizeof(T));  // k-major: from one k-tile to the next
+  uint32_t kofs = 0;                                          // of the k-tile that is loaded
 
-  // piece p of operand A / B of k-tile kt into LDS unit `unit`: 1 KB per wave, 8 rows of 128 bytes, k-major 2
-  // rows of 512
-  auto load_a = [&](int unit, int kt, int p) {
-    const int t = min(kt, nk - 1);
-    uint32_t off = offA[p];
-    if (TAIL && t == nk - 1 && chunk >= tail_chunks) off -= (uint32_t)(chunk * 8 * sizeof(T));
-    load_to_lds(smem + unit * kOperand + (4 * p + wave) * 1024, off, rsrc_at(Ab + (size_t)t * (WK * sizeof(T))));
+  uint64_t atB = reinterpret_cast<uint64_t>(B[0]);           // k-major: of the k-tile that is loaded
+  auto with_range = [](i32x4 rsrc, int bytes) { return i32x4{rsrc[0], rsrc[1], bytes, rsrc[3]}; };
+  auto load_a = [&](uint32_t place, int p) { load_to_lds_at(p & 3, place, offA[p], with_range(rsrcA, rangeA), kofs); };
+  auto load_b = [&](uint32_t place, int p) {
+    const i32x4 r = BNN ? i32x4{(int)(uint32_t)atB, (int)(uint32_t)(atB >> 32), rangeB[0], rsrcB[0][3]} : with_range(rsrcB[p & 1], rangeB[p & 1]);
+    load_to_lds_at(p & 3, place, offB[p], r, BNN ? 0u : kofs);
   };
-  auto load_b = [&](int unit, int kt, int p) {
-    const int t = min(kt, nk - 1);
-    uint32_t off = offB[p];
-    if (TAIL && t == nk - 1) {
-      if (BNN) {
-        const int kr = 8 * p + 2 * wave + (lane >> 5);
-        if (kr >= tail_chunks * 8) off -= (uint32_t)((size_t)kr * g.ldb * sizeof(T));
-      } else if (chunk >= tail_chunks) {
-        off -= (uint32_t)(chunk * 8 * sizeof(T));
-      }
-    }
-    load_to_lds(smem + unit * kOperand + (4 * p + wave) * 1024, off,
-                rsrc_at(((DUAL && p >= 4) ? Ub : Bb) + (size_t)t * stepB));
-  };
-
-  f32x16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  // Fragments of k-step s: A rows 128 wm + 32 i + l31; B rows 128 wn + 32 j + l31, SwiGLU: gate rows
-  // 64 wn + 32 j (j < 2) and up rows 128 + 64 wn + 32 (j - 2); chunk 2 s + lane / 32.
-  const int l31 = lane & 31, hi = lane >> 5;
-  const int trow = 8 * hi + ((lane & 15) >> 2);  // k-major: k row of this lane's transposing read, upper half + 4
-  uint4 fa[4][4], fb[4][4];
-  auto read_frag = [&](const unsigned char* sa, const unsigned char* sb, int s, int f) {  // f: 0 .. 3 A, 4 .. 7 B
-    const int sw = ((2 * s + hi) ^ ((l31 >> 1) & 7)) << 4;
-    const int j = f & 3;
-    if (f < 4) {
-      fa[s][j] = *reinterpret_cast<const uint4*>(sa + (wm * 128 + l31) * 128 + sw + j * 4096);
-    } else if (!BNN) {
-      const int r = DUAL ? (j >> 1) * 128 + wn * 64 + (j & 1) * 32 : wn * 128 + j * 32;
-      fb[s][j] = *reinterpret_cast<const uint4*>(sb + l31 * 128 + sw + r * 128);
+  // On to the next k-tile, behind which there are `behind` more; past the last one nothing is in range and loads read nothing.
+  // (Written out, so that the loop is not taken apart at its last turns: every copy of it would have its own sums' registers.)
+  auto step = [&](int behind) {
+    asm volatile("s_add_u32 %0, %0, %3\n\ts_cmp_lt_i32 %4, 0\n\ts_cselect_b32 %0, 0, %0\n\ts_cselect_b32 %1, 0, %1\n\ts_cselect_b32 %2, 0, %2"
+                 : "+s"(kofs), "+s"(rangeA), "+s"(rangeB[1])
+                 : "n"(WK * sizeof(T)), "s"(behind)
+                 : "scc");
+    if (BNN) {
+      atB += stepB;
+      asm volatile("s_cmp_eq_u32 %1, 0\n\ts_cselect_b32 %0, %2, -1\n\ts_cmp_lt_i32 %1, 0\n\ts_cselect_b32 %0, 0, %0"
+                   : "=&s"(rangeB[0])
+                   : "s"(behind), "s"(last_rows)
+                   : "scc");
     } else {
-      const int c = (wn * 16 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + ((j ^ ((lane & 15) >> 2)) << 2);
-      const unsigned char* p = sb + (16 * s + trow) * 512 + c * 16 + (lane & 1) * 8;
+      asm volatile("s_cmp_lt_i32 %1, 0\n\ts_cselect_b32 %0, 0, %0" : "+s"(rangeB[0]) : "s"(behind) : "scc");
+    }
+  };
+
+  f32x4 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // Fragments of half s of a k-tile (32 k): A rows 128 wm + 16 i + lane % 16, B rows 16 (TJ wn + j) + lane % 16, chunk
+  // 4 s + lane / 16.
+  const int l15 = lane & 15, quarter = lane >> 4;
+  const uint32_t in_row = (uint32_t)((quarter ^ (l15 >> 1)) << 4);
+  const uint32_t laneA = (uint32_t)(wm * 128 + l15) * 128 + in_row;
+  uint32_t laneB[BNN ? TJ : 1];
+  if constexpr (BNN) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      laneB[j] = (uint32_t)((8 * quarter + (l15 >> 2)) * 512 + (((2 * (wn * TJ + j) + ((lane & 3) >> 1)) ^ kmajor_swizzle(8 * quarter + (l15 >> 2))) << 4) + (lane & 1) * 8);
+  } else {
+    laneB[0] = (uint32_t)(wn * TJ * 16 + l15) * 128 + in_row;
+  }
+  uint4 fa[2][TI], fb[2][TJ];
+  auto read_frag = [&](uint32_t ua, uint32_t ub, int s, int f) {  // f < TJ: B, else A
+    if (f >= TJ) {
+      fa[s][f - TJ] = *reinterpret_cast<const uint4*>(smem + ((laneA ^ (s << 6)) + ua) + (f - TJ) * 2048);
+    } else if (!BNN) {
+      fb[s][f] = *reinterpret_cast<const uint4*>(smem + ((laneB[0] ^ (s << 6)) + ub) + f * 2048);
+    } else {
+      const unsigned char* p = smem + (laneB[BNN ? f : 0] + ub) + 32 * s * 512;
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
       const s16x4 h4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * 512));
-      fb[s][j] = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, h4, 0, 1, 2, 3, 4, 5, 6, 7));
+      fb[s][f] = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, h4, 0, 1, 2, 3, 4, 5, 6, 7));
     }
   };
 
-  // prologue: k-tiles 0 and 1 on their way, the first two k-steps' fragments read
+  // K-tile kt lies in units ua and ub, k-tile kt + 1 in na and nb, `spare` is free.  The first half reads the fragments of the
+  // second and sends B of k-tile kt + 2, weights that come from memory, into the spare unit; then everybody has read all of
+  // k-tile kt and k-tile kt + 1 has landed (all but the newest B), so the second half reads from k-tile kt + 1 and sends A of
+  // k-tile kt + 2 into unit ua.
+  uint32_t ua = 0, ub = kOperand, na = 2 * kOperand, nb = 3 * kOperand, spare = 4 * kOperand;
+  constexpr int MF = TI * TJ;
+  auto half = [&](auto s_, bool ragged) {
+    constexpr int s = s_.value;
+    constexpr Places<MF, TI + TJ, s == 0 ? PB : 8> places;
+    if (ragged) {
+      if (4 * s + quarter >= tail_chunks) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) fa[s][i] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) fb[s][j] = make_uint4(0, 0, 0, 0);
+      }
+      asm volatile("s_nop 1");  // between such a zero and its product
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t place = 0;
+#pragma unroll
+    for (int m = 0; m < MF; ++m) {
+      mfma16_in_place<D>(fb[s][m % TJ], fa[s][m / TJ], acc[m / TJ][m % TJ]);
+      if (places.read[m] >= 0) read_frag(s == 0 ? ua : na, s == 0 ? ub : nb, s ^ 1, places.read[m]);
+      if (places.place[m] >= 0) place = lds_place((s == 0 ? spare + myB : ua + myA) + places.place[m] * 4096);
+      if (places.load[m] >= 0) {
+        if (s == 0) load_b(place, places.load[m]);
+        else load_a(place, places.load[m]);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // this order
+    }
+  };
+
+  // prologue: k-tiles 0 and 1 on their way, the first half's fragments read
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
+    uint32_t place = 0;
 #pragma unroll
-    for (int p = 0; p < 8; ++p) load_a(2 * t, t, p);
+    for (int p = 0; p < 8; ++p) {
+      if (p % 4 == 0) place = lds_place(myA + 2 * t * kOperand + p * 1024, true);
+      load_a(place, p);
+    }
 #pragma unroll
-    for (int p = 0; p < 8; ++p) load_b(2 * t + 1, t, p);
+    for (int p = 0; p < PB; ++p) {
+      if (p % 4 == 0) place = lds_place(myB + (2 * t + 1) * kOperand + p * 1024, true);
+      load_b(place, p);
+    }
+    step(nk - t - 2);
   }
-  __builtin_amdgcn_s_waitcnt(0x4F70);  // vmcnt(16): k-tile 0 has landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + PB) : "memory");  // k-tile 0 has landed
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int f = 0; f < 16; ++f) read_frag(smem, smem + kOperand, f >> 3, f & 7);
-
-  // K-tile kt lies in units ua, ua + 1 (modulo 5), k-tile kt + 1 in the two after them, the fifth is free.
-  // Steps 0 and 1 read the fragments of steps 2 and 3 and send A of k-tile kt + 2 into the free unit; then
-  // everybody has read all of k-tile kt and k-tile kt + 1 has landed (all but the 8 newest loads), so steps 2
-  // and 3 read from k-tile kt + 1 and send B of k-tile kt + 2 into unit ua.
-  int ua = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int ub = ua + 1 >= kUnits ? ua + 1 - kUnits : ua + 1;
-    const int na = ua + 2 >= kUnits ? ua + 2 - kUnits : ua + 2;
-    const int nb = ua + 3 >= kUnits ? ua + 3 - kUnits : ua + 3;
-    const int uf = ua + 4 >= kUnits ? ua + 4 - kUnits : ua + 4;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const unsigned char* sa = smem + (s < 2 ? ua : na) * kOperand;
-      const unsigned char* sb = smem + (s < 2 ? ub : nb) * kOperand;
-      if (TAIL && kt == nk - 1 && 2 * s + hi >= tail_chunks) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fa[s][i] = fb[s][i] = make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        acc[m >> 2][m & 3] = mfma<D>(fa[s][m >> 2], fb[s][m & 3], acc[m >> 2][m & 3]);
-        if ((m & 1) == 0) read_frag(sa, sb, (s + 2) & 3, m >> 1);
-        if ((m & 3) == 1) {
-          if (s < 2) load_a(uf, kt + 2, 4 * s + (m >> 2));
-          else load_b(ua, kt + 2, 4 * (s - 2) + (m >> 2));
-        }
-        __builtin_amdgcn_sched_barrier(0);  // this order: one LDS read or one load between two MFMAs
-      }
-      if (s == 1) {
-        __builtin_amdgcn_s_waitcnt(0x0078);  // vmcnt(8), lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    ua = na;
+  for (int f = 0; f < TI + TJ; ++f) read_frag(ua, ub, 0, f);
+  const int ragged_at = tail_chunks < 8 ? 1 : 0;
+  for (int left = nk; left > 0; --left) {
+    const bool ragged = left == ragged_at;
+    half(Const<0>{}, ragged);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PB) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    half(Const<1>{}, ragged);
+    step(left - 4);
+    const uint32_t a = ua, b = ub;
+    ua = na; ub = nb; na = a; nb = spare; spare = b;
   }
   __builtin_amdgcn_s_waitcnt(0x0070);  // nothing of mine is still on its way into LDS
-  __syncthreads();  // the units are free: each wave turns its outputs to rows in one of its own
-  store_wave<D, EPI, 4, 4>(g, acc, reinterpret_cast<float*>(smem + wave * kOperand), m0 + wm * 128,
-                           n0 + wn * (DUAL ? 64 : 128), w.sums, BNO, lane);
+  // the last products' sums are in their registers 18 wait states later
+  asm volatile("s_nop 15\n\ts_nop 3");
+  auto settled = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+  };
+
+  // Element v of lane l is row l % 16, column 4 (l / 16) + v of a block: four neighbouring columns go out as they are.
+  const int row0 = m0 + wm * 128 + l15;
+  if (dual) {
+    // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
+    const int col0 = n0 + wn * 8 * TJ + 4 * (quarter & 1) + 8 * (quarter >> 1);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int row = row0 + 16 * i;
+      settled(i);
+#pragma unroll
+      for (int j = 0; j < TJ; j += 2) {
+        const int j1 = j + 1 < TJ ? j + 1 : j;
+        float z[4], u[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[i][j][v]), f2u(acc[i][j1][v]), false, false);
+          z[v] = u2f(sw[0]);
+          u[v] = u2f(sw[1]);
+        }
+        const int col = col0 + 8 * j;
+        const float none[4] = {0.f, 0.f, 0.f, 0.f};
+        if (row < g.M && col < g.Nn && (j + 1 < TJ || quarter < 2))
+          store_quad<D, EPI_SWIGLU>(g, make_float4(z[0], z[1], z[2], z[3]), make_float4(u[0], u[1], u[2], u[3]), none, (size_t)row * g.ldo + col);
+      }
+    }
+    return;
+  }
+  const int col0 = n0 + wn * 16 * TJ + 4 * quarter;
+  if (w.sums) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int row = row0 + 16 * i;
+      settled(i);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const int col = col0 + 16 * j;
+        if (row < g.M && col < g.Nn) *reinterpret_cast<f32x4*>(w.sums + (ptrdiff_t)row * bno + col) = acc[i][j];
+      }
+    }
+    return;
+  }
+  float bv[TJ][4];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int col = col0 + 16 * j;
+      bv[j][k] = g.bias && col < g.Nn ? to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]) : 0.f;
+    }
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    const int row = row0 + 16 * i;
+    settled(i);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int col = col0 + 16 * j;
+      const float4 c = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
+        if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, c, c, bv[j], (size_t)row * g.ldo + col);
+        else store_quad<D, EPI_LINEAR>(g, c, c, bv[j], (size_t)row * g.ldo + col);
+      }
+    }
+  }
 }
 
-template <class D, int EPI, bool BNN>
-int launch_typed(const GemmArgs& g, hipStream_t s) {
+template <class D, bool BNN, int TJ>
+int launch_width(int epi, const GemmArgs& g, hipStream_t s) {
   const dim3 grid((unsigned)(g.full + g.tail * g.splits));
-  if (g.Kk % WK == 0) hipLaunchKernelGGL((gemm_wide_kernel<D, EPI, BNN, false>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm_wide_kernel<D, EPI, BNN, true>), grid, dim3(256), 0, s, g);
+  hipLaunchKernelGGL((gemm_wide_kernel<D, BNN, TJ>), grid, dim3(256), 0, s, g, epi);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
 
-template <class D>
-int launch_epi(int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s) {
-  switch (epi) {
-    case EPI_RELU: return launch_typed<D, EPI_RELU, false>(g, s);
-    case EPI_SWIGLU: return launch_typed<D, EPI_SWIGLU, false>(g, s);
-    case EPI_LINEAR:
-      return b_kmajor ? launch_typed<D, EPI_LINEAR, true>(g, s) : launch_typed<D, EPI_LINEAR, false>(g, s);
+template <class D, bool BNN>
+int launch_typed(int shape, int epi, const GemmArgs& g, hipStream_t s) {
+  switch (shape) {
+    case kWide: return launch_width<D, BNN, 8>(epi, g, s);
+    case kWide224: return launch_width<D, BNN, 7>(epi, g, s);
+    case kWide192: return launch_width<D, BNN, 6>(epi, g, s);
+    case kWide160: return launch_width<D, BNN, 5>(epi, g, s);
   }
-  return CI_ERR_INVALID_ARG;
+  return CI_ERR_UNSUPPORTED;
 }
 
 }  // namespace
 
-int launch_gemm_wide(int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s) {
-  switch (dtype) {
-    case CI_F16: return launch_epi<F16>(epi, b_kmajor, g, s);
-    case CI_BF16: return launch_epi<BF16>(epi, b_kmajor, g, s);
-  }
+int launch_gemm_wide(int shape, int dtype, int epi, bool b_kmajor, const GemmArgs& g, hipStream_t s) {
+  if (dtype == CI_F16) return b_kmajor ? launch_typed<F16, true>(shape, epi, g, s) : launch_typed<F16, false>(shape, epi, g, s);
+  if (dtype == CI_BF16) return b_kmajor ? launch_typed<BF16, true>(shape, epi, g, s) : launch_typed<BF16, false>(shape, epi, g, s);
   return CI_ERR_BAD_DTYPE;
 }
 

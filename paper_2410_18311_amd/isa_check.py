@@ -1,10 +1,13 @@
-"""What the compiler does not check of the hand-written loads into LDS (csrc/gemm_tile.hpp: load_to_lds), looked up in the
-gfx950 code of a built library.
+"""What the compiler does not check of the hand-written loads into LDS and matrix products (csrc/gemm_tile.hpp), looked up in
+the gfx950 code of a built library.
 
-Hazards inside inline assembly are the author's: a buffer load must not read a scalar register within five wait states
-after a vector instruction wrote it (a lane read, a compare, a carry).  The kernels' descriptors are made by scalar
-instructions, which the hardware waits for; whether they all still are depends on what the compiler does with the code
-around, so every build looks.
+Hazards inside inline assembly are the author's.  A buffer load must not read a scalar register within five wait states
+after a vector instruction wrote it (a lane read, a compare, a carry), nor go by m0 in the instruction after the one that
+writes it.  The kernels' descriptors are made by scalar
+instructions, which the hardware waits for.  A matrix product must not read a register within two wait states after a vector
+instruction wrote it, and its result is read by others 18 wait states later at the earliest (more than the largest product
+takes).  Whether all that holds depends on what the compiler does with the code
+around, copies of a sum among it, so every build looks.
 """
 
 from __future__ import annotations
@@ -18,6 +21,7 @@ import tempfile
 OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"))), "llvm", "bin",
                        "llvm-objdump")
 WAIT_STATES = 5
+TO_PRODUCT, FROM_PRODUCT = 2, 18
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -63,10 +67,10 @@ def _vector_writes(op: str, args: list) -> set:
     return set()
 
 
-def hazards_in(text: str) -> list:
-    """Loads into LDS in an objdump listing that a vector instruction's scalar result reaches too soon, on any path."""
-    found = []
-    for body in re.split(r"^[0-9a-f]+ <[^>]+>:\n", text, flags=re.M)[1:]:
+def _functions(text: str):
+    """Name, instructions (mnemonic, operands, line) and, for each, those that can run right before it, of a listing's functions."""
+    parts = re.split(r"^[0-9a-f]+ <([^>]+)>:\n", text, flags=re.M)
+    for name, body in zip(parts[1::2], parts[2::2]):
         ins, where = [], {}
         for line in body.splitlines():
             m = re.match(r"\s+(\S+)\s*(.*?)\s*//\s*([0-9A-F]+):", line)
@@ -81,28 +85,68 @@ def hazards_in(text: str) -> list:
                 target = addresses[i] + 4 + 4 * (offset - 65536 if offset >= 32768 else offset)
                 if target in where:
                     before[where[target]].append(i)
+        yield name, ins, before
+
+
+def _within(ins, before, i, limit, hit):
+    """Instructions that hit() accepts less than `limit` wait states ahead of instruction i, on any path, with the states between."""
+    todo, seen = [(j, 0) for j in before[i]], {}
+    while todo:
+        j, states = todo.pop()
+        if states >= limit or seen.get(j, limit) <= states:
+            continue
+        seen[j] = states
+        if hit(j):
+            yield f"{ins[j][2].strip()}  ->  {ins[i][2].strip()}  ({states} wait states)"
+            continue
+        states += int(ins[j][1][0], 0) + 1 if ins[j][0] == "s_nop" else 1
+        todo += [(k, states) for k in before[j]]
+
+
+def hazards_in(text: str) -> list:
+    """Loads into LDS in an objdump listing that a vector instruction's scalar result, or m0, reaches too soon, on any path."""
+    found = []
+    for _, ins, before in _functions(text):
         for i, (op, args, line) in enumerate(ins):
             if not (op.startswith("buffer_load") and re.search(r"\blds\b", line)):
                 continue
             wanted = set().union(*(_registers(a.split()[0]) for a in args if a))
-            todo, seen = [(j, 0) for j in before[i]], {}
-            while todo:
-                j, states = todo.pop()
-                if states >= WAIT_STATES or seen.get(j, WAIT_STATES) <= states:
-                    continue
-                seen[j] = states
-                o, a, text_j = ins[j]
-                if _vector_writes(o, a) & wanted:
-                    found.append(f"{text_j.strip()}  ->  {line.strip()}  ({states} wait states)")
-                    continue
-                states += int(a[0], 0) + 1 if o == "s_nop" else 1
-                todo += [(k, states) for k in before[j]]
+            found += _within(ins, before, i, WAIT_STATES, lambda j: _vector_writes(ins[j][0], ins[j][1]) & wanted)
+            found += _within(ins, before, i, 1, lambda j: ins[j][0].startswith("s_") and ins[j][1][0] == "m0")
     return found
 
 
-def lds_load_hazards(path: str) -> list:
+def _lanes(operand: str) -> set:
+    m = re.match(r"([av])(\d+)$", operand) or re.match(r"([av])\[(\d+):(\d+)\]", operand)
+    return {(m[1], r) for r in range(int(m[2]), int(m[m.lastindex]) + 1)} if m else set()
+
+
+def product_hazards_in(text: str, names: str = "") -> list:
+    """Matrix products in an objdump listing (functions whose name contains `names`) that read a vector instruction's result, or whose
+    own result another instruction reads or overwrites, too soon, on any path."""
+    found = []
+    for name, ins, before in _functions(text):
+        if names not in name:
+            continue
+        regs = [[_lanes(a) for a in args] for _, args, _ in ins]
+        product = [op.startswith("v_mfma") for op, _, _ in ins]
+        # a swap writes both its operands
+        writes = [r[0] | (r[1] if "swap" in ins[i][0] and len(r) > 1 else set()) if r and ins[i][0].startswith("v_") else set()
+                  for i, r in enumerate(regs)]
+        for i in range(len(ins)):
+            touched = set().union(*regs[i])
+            if product[i]:
+                found += _within(ins, before, i, TO_PRODUCT, lambda j: not product[j] and writes[j] & touched)
+            elif touched:
+                found += _within(ins, before, i, FROM_PRODUCT, lambda j: product[j] and writes[j] & touched)
+    return found
+
+
+def hazards(path: str) -> list:
+    """Both kinds in a built library: loads in the kernels that have them, products in those that write them out."""
     out = []
     for code in code_objects(path):
-        if b"gemm_" in code:                      # the kernels with such loads
-            out += hazards_in(listing(code))
+        if b"gemm_" in code:
+            text = listing(code)
+            out += hazards_in(text) + product_hazards_in(text, "gemm_wide")
     return out

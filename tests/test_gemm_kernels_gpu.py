@@ -55,8 +55,8 @@ def test_dense_f32_tiles(lib, act, layout, M, d, N):
     _check_dense(lib, torch.float32, act, layout, M, d, N)
 
 
-# The LDS-tiled kernels for 16-bit types, every tile shape forced (0 .. 3: 128x128, 128x256, 256x64, 128x64
-# rows of A x rows of B; 4: 256x256), whole and with k split over 3 workgroups per tile: one row and column
+# The LDS-tiled kernels for 16-bit types, tile shapes forced (0 .. 4: 128x128, 128x256, 256x192, 128x64, 256x256
+# rows of A x rows of B), whole and with k split over 3 workgroups per tile: one row and column
 # past a tile, k shorter than the ring, k that ends inside a 64-k tile, an odd number of k-tiles, several
 # tiles per XCD.
 TILE_CASES = [(5, 8, 8), (129, 264, 136), (257, 328, 520), (64, 1608, 776), (300, 1152, 1032)]
@@ -76,6 +76,55 @@ def test_dense_tile_shapes(lib, tile, act, layout, dtype, splits):
     finally:
         lib.dev_set_param("gemm_tile", -1)
         lib.dev_set_param("gemm_splits", 0)
+
+
+# 256 rows of A x 192, 256, 224 and 160 of B: blocks that two waves share by halves (224 and 160), one to four k-tiles and a bit (fewer than
+# are loaded ahead), columns that end inside a tile and one tile further, a row past a tile
+@pytest.mark.parametrize("tile,bn", [(2, 192), (4, 256), (5, 224), (6, 160)])
+@pytest.mark.parametrize("act,layout,dtype", [("relu", "out_major", torch.bfloat16), ("swiglu", "out_major", torch.float16),
+                                              ("relu", "neuron_major", torch.float16)])
+def test_dense_wide_tiles(lib, tile, bn, act, layout, dtype):
+    cols = bn // 2 if act == "swiglu" else bn
+    try:
+        lib.dev_set_param("gemm_tile", tile)
+        for splits, M, d, N in [(1, 5, 64, 72), (1, 256, 72, cols), (1, 257, 128, cols + 8), (1, 130, 136, 2 * cols - 8),
+                                (2, 300, bn, 520), (3, 257, bn + 8, 840), (1, 513, 192, 200)]:
+            lib.dev_set_param("gemm_splits", splits)
+            _check_dense(lib, dtype, act, layout, M, d, N, hidden=splits == 2)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+
+
+# What lies behind the end of k in memory, the start of the next row (of a k-major B: nothing), is loaded and takes no part,
+# whatever it is; values that are not finite at the last k reach their own row or column
+@pytest.mark.parametrize("tile", [2, 4, 5, 6])
+@pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_dense_wide_tiles_beside_values_that_are_not_finite(lib, tile, layout, splits):
+    M, d, N, dt = 20, 520, 584, torch.float16    # 8 k-tiles and 8, 9 and 8
+    g = torch.Generator().manual_seed(tile)
+    pos = lambda *s: (torch.rand(*s, generator=g) * 0.02 + 0.001).to(dt).to(DEV)  # noqa: E731
+    w_up, down, X = pos(N, d), pos(d, N), pos(M, d)
+    X[4, 0], X[9, d - 1], w_up[7, 0], w_up[N - 1, d - 1] = float("inf"), float("inf"), float("inf"), float("inf")
+    lib.dev_set_param("gemm_tile", tile)
+    lib.dev_set_param("gemm_splits", splits)
+    try:
+        A = lib.ffn_dense(X, w_up, None, None, down if layout == "out_major" else down.t().contiguous(), None, layout, "relu",
+                          want_y=False, want_a=True)[1]
+        X, w_up = pos(M, d), pos(N, d)
+        down[3, 0], down[d - 1, N - 1], down[11, N - 8] = float("nan"), float("inf"), float("nan")
+        Y = lib.ffn_dense(X, w_up, None, None, down if layout == "out_major" else down.t().contiguous(), None, layout, "relu",
+                          want_y=True, want_a=False)[0]
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+    inf_A = torch.zeros(M, N, dtype=torch.bool, device=DEV)
+    inf_A[4], inf_A[9], inf_A[:, 7], inf_A[:, N - 1] = True, True, True, True
+    assert torch.equal(torch.isinf(A), inf_A) and not bool(torch.isnan(A).any())
+    bad = torch.zeros(M, d, dtype=torch.bool, device=DEV)
+    bad[:, 3], bad[:, 11], bad[:, d - 1] = True, True, True
+    assert torch.equal(~torch.isfinite(Y), bad) and bool(torch.isinf(Y[:, d - 1]).all())
 
 
 # Tiles of 16 tm x 16 tn (16 + 16 tm + tn), whole and with k split over 3 workgroups per tile: one row past a tile and one

@@ -66,11 +66,43 @@ def test_hazards_are_found_on_every_path(lines, hazard):
     assert bool(isa_check.hazards_in(_listing(*lines))) == hazard
 
 
+PRODUCT = "v_mfma_f32_16x16x32_f16 a[4:7], v[0:3], v[8:11], a[4:7]"
+
+
+@pytest.mark.parametrize("lines,hazard", [
+    (("v_mov_b32_e32 v9, 0", PRODUCT), True),
+    (("v_mov_b32_e32 v9, 0", "s_nop 0", PRODUCT), True),
+    (("v_mov_b32_e32 v9, 0", "s_nop 1", PRODUCT), False),
+    (("v_mov_b64_e32 v[12:13], v[4:5]", PRODUCT), False),                        # not its operands
+    (("v_accvgpr_write_b32 a7, v20", PRODUCT), True),
+    (("v_permlane32_swap_b32_e32 v20, v3", PRODUCT), True),                      # writes both
+    (("ds_read_b128 v[0:3], v40", PRODUCT), False),                              # waited for by its counter
+    ((PRODUCT, PRODUCT), False),
+    ((PRODUCT, "v_accvgpr_read_b32 v20, a6"), True),
+    ((PRODUCT, "s_nop 15", "s_nop 0", "v_accvgpr_read_b32 v20, a6"), True),      # 17
+    ((PRODUCT, "s_nop 15", "s_nop 1", "v_accvgpr_read_b32 v20, a6"), False),
+    ((PRODUCT, "global_store_dwordx4 v[30:31], a[4:7], off"), True),
+    ((PRODUCT, "v_accvgpr_read_b32 v20, a8"), False),
+    ((PRODUCT, "s_cbranch_scc1 1", "s_nop 15", "s_nop 1", "v_accvgpr_mov_b32 a12, a4"), True),   # past the first idle states
+])
+def test_product_hazards_are_found_on_every_path(lines, hazard):
+    assert bool(isa_check.product_hazards_in(_listing(*lines))) == hazard
+
+
+@pytest.mark.parametrize("lines,hazard", [(("s_mov_b32 m0, s9", LOAD[2]), True), (("s_add_i32 m0, s9, s2", "s_nop 0", LOAD[2]), False),
+                                          (("s_mov_b32 m0, s9", PRODUCT, LOAD[2]), False)])
+def test_a_load_does_not_go_by_m0_at_once(lines, hazard):
+    assert bool(isa_check.hazards_in(_listing(*lines))) == hazard
+
+
 def test_the_built_library_has_no_hazard(lib):
     listings = [isa_check.listing(c) for c in isa_check.code_objects(build.LIB_PATH) if b"gemm_" in c]
     loads = sum(1 for text in listings for l in text.splitlines() if "buffer_load" in l and re.search(r"\blds\b", l))
     assert loads > 1000, "the kernels with loads into LDS are not among the code looked at"
     assert not [h for text in listings for h in isa_check.hazards_in(text)]
+    products = sum(text.count("v_mfma") for text in listings if "gemm_wide" in text)
+    assert products > 1000, "the kernels that write out their products are not among the code looked at"
+    assert not isa_check.hazards(build.LIB_PATH)
 
 
 def test_a_value_in_m0_survives_the_load(assembly):
