@@ -122,10 +122,16 @@ __device__ __forceinline__ uint32_t lds_place(uint32_t place, bool at_once = fal
   else asm volatile("s_mov_b32 m0, %1" : "={m0}"(m0) : "s"(place));
   return m0;
 }
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds_at(int piece, uint32_t place, uint32_t off, i32x4 rsrc, uint32_t scalar_off) {
-  asm volatile("buffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
-               :: "{m0}"(place), "v"(off), "s"(rsrc), "s"(scalar_off), "n"(piece * 1024)
-               : "memory");
+  if constexpr (ONCE)
+    asm volatile("buffer_load_dwordx4 %1, %2, %3 offen offset:%4 nt lds"
+                 :: "{m0}"(place), "v"(off), "s"(rsrc), "s"(scalar_off), "n"(piece * 1024)
+                 : "memory");
+  else
+    asm volatile("buffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+                 :: "{m0}"(place), "v"(off), "s"(rsrc), "s"(scalar_off), "n"(piece * 1024)
+                 : "memory");
 }
 
 // Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
@@ -164,6 +170,112 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc
       if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
         if (sums) *reinterpret_cast<float4*>(sums + (ptrdiff_t)row * sums_ld + col) = c0;
         else store_quad<D, EPI>(g, c0, c1, bv, (size_t)row * g.ldo + col);
+      }
+    }
+  }
+}
+
+// k-major B in LDS, rows of BN columns (of one k): chunk j of row k lies at j ^ this.  Transposing reads of 32 lanes cover eight rows
+// (k % 4 and k / 8 % 2) x 32 bytes in 256 different bytes of the banks.
+template <int BN>
+__device__ __forceinline__ int kmajor_swizzle(int k) {
+  return BN >= 128 ? (k & 3) << 2 | (k >> 3 & 1) << 1 : (k >> 1 & 1) << 2 | (k >> 3 & 1) << 1;
+}
+
+// What goes out behind which of MF products: at most one LDS read (of a fragment) and one load, and mostly not both; the
+// scalar register that a load takes its place in LDS from is written one product ahead, for every four pieces of an operand (the first
+// FIRST loads are one operand's, the others another's).
+template <int MF, int READS, int LOADS, int FIRST = LOADS>
+struct Places {
+  int read[MF] = {}, load[MF] = {}, place[MF] = {};  // number, -1: none; place: of the load it is for
+  constexpr Places() {
+    for (int m = 0; m < MF; ++m) read[m] = load[m] = place[m] = -1;
+    for (int r = 0; r < READS; ++r) read[r * MF * 3 / (4 * READS)] = r;  // in the first three quarters
+    for (int p = 0; p < LOADS; ++p) {
+      int m = (2 * p + 1) * MF / (2 * LOADS);
+      if (m + 1 < MF && read[m] >= 0 && read[m + 1] < 0) ++m;
+      load[m] = p;
+      if (p < FIRST ? p % 4 == 0 : (p - FIRST) % 4 == 0) place[m - 1] = p;
+    }
+  }
+};
+
+// Results of 2 x 2 waves of TI x TJ blocks of 16x16, sums of mfma16_in_place with B's fragment first: element v of lane l is row
+// l % 16, column 4 (l / 16) + v of a block, so that four neighbouring columns go out as they are.  SwiGLU (dual): a block is eight
+// gate and eight up columns.  row0: the wave's first row, n0: the tile's first output column, wn: the wave's half of its columns; sums:
+// not null where raw sums are stored instead of outputs, by row and column of the product `bno` apart.
+template <class D, int TI, int TJ>
+__device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool dual, f32x4 (&acc)[TI][TJ], int row0, int n0, int wn,
+                                             float* sums, int bno, int lane) {
+  using T = typename D::T;
+  // the last products' sums are in their registers 18 wait states later
+  asm volatile("s_nop 15\n\ts_nop 3");
+  auto settled = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+  };
+
+  // Element v of lane l is row l % 16, column 4 (l / 16) + v of a block: four neighbouring columns go out as they are.
+  const int l15 = lane & 15, quarter = lane >> 4;
+  row0 += l15;
+  if (dual) {
+    // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
+    const int col0 = n0 + wn * 8 * TJ + 4 * (quarter & 1) + 8 * (quarter >> 1);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int row = row0 + 16 * i;
+      settled(i);
+#pragma unroll
+      for (int j = 0; j < TJ; j += 2) {
+        const int j1 = j + 1 < TJ ? j + 1 : j;
+        float z[4], u[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[i][j][v]), f2u(acc[i][j1][v]), false, false);
+          z[v] = u2f(sw[0]);
+          u[v] = u2f(sw[1]);
+        }
+        const int col = col0 + 8 * j;
+        const float none[4] = {0.f, 0.f, 0.f, 0.f};
+        if (row < g.M && col < g.Nn && (j + 1 < TJ || quarter < 2))
+          store_quad<D, EPI_SWIGLU>(g, make_float4(z[0], z[1], z[2], z[3]), make_float4(u[0], u[1], u[2], u[3]), none, (size_t)row * g.ldo + col);
+      }
+    }
+    return;
+  }
+  const int col0 = n0 + wn * 16 * TJ + 4 * quarter;
+  if (sums) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int row = row0 + 16 * i;
+      settled(i);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const int col = col0 + 16 * j;
+        if (row < g.M && col < g.Nn) *reinterpret_cast<f32x4*>(sums + (ptrdiff_t)row * bno + col) = acc[i][j];
+      }
+    }
+    return;
+  }
+  float bv[TJ][4];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int col = col0 + 16 * j;
+      bv[j][k] = g.bias && col < g.Nn ? to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]) : 0.f;
+    }
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    const int row = row0 + 16 * i;
+    settled(i);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int col = col0 + 16 * j;
+      const float4 c = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
+        if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, c, c, bv[j], (size_t)row * g.ldo + col);
+        else store_quad<D, EPI_LINEAR>(g, c, c, bv[j], (size_t)row * g.ldo + col);
       }
     }
   }

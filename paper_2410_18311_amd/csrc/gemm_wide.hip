@@ -44,26 +44,6 @@ constexpr int WT = 256;                // output rows of a workgroup
 constexpr int kOperand = WT * WK * 2;  // bytes of LDS for one operand tile
 constexpr int kUnits = 5;              // operand tiles in LDS: all of its 160 KB
 
-// k-major B: chunk j of row k lies at j ^ this.
-__device__ __forceinline__ int kmajor_swizzle(int k) { return (k & 3) << 2 | (k >> 3 & 1) << 1; }
-
-// What goes out behind which of a step's MF products: at most one LDS read (of a fragment) and one load, and mostly not both; the
-// scalar register that a load takes its place in LDS from is written one product ahead.
-template <int MF, int READS, int LOADS>
-struct Places {
-  int read[MF] = {}, load[MF] = {}, place[MF] = {};  // number, -1: none
-  constexpr Places() {
-    for (int m = 0; m < MF; ++m) read[m] = load[m] = place[m] = -1;
-    for (int r = 0; r < READS; ++r) read[r * MF * 3 / (4 * READS)] = r;  // in the first three quarters
-    for (int p = 0; p < LOADS; ++p) {
-      int m = (2 * p + 1) * MF / (2 * LOADS);
-      if (read[m] >= 0 && read[m + 1] < 0) ++m;
-      load[m] = p;
-      if (p % 4 == 0) place[m - 1] = p / 4;
-    }
-  }
-};
-
 // 2 x 2 waves of 8 x TJ blocks of 16x16: 256 rows of A, 32 TJ rows of B.  SwiGLU: a block of B rows is eight gate and eight up
 // rows of the same columns.
 template <class D, bool BNN, int TJ>
@@ -106,7 +86,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int p = 0; p < PB; ++p) {
     if (BNN) {
       const int kr = 16 * wave + 2 * p + (lane >> 5);
-      int c = (lane & 31) ^ kmajor_swizzle(kr);
+      int c = (lane & 31) ^ kmajor_swizzle<256>(kr);
       if (c >= BN / 8) c = 0;                        // no such columns: a chunk that is loaded anyway
       const int col = min(n0 + c * 8, g.Nn - 8) - n0;  // Nn is a multiple of 8
       offB[p] = (uint32_t)(((size_t)kr * g.ldb + col) * sizeof(T)) + (3 - (p & 3)) * 1024;
@@ -169,7 +149,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if constexpr (BNN) {
 #pragma unroll
     for (int j = 0; j < TJ; ++j)
-      laneB[j] = (uint32_t)((8 * quarter + (l15 >> 2)) * 512 + (((2 * (wn * TJ + j) + ((lane & 3) >> 1)) ^ kmajor_swizzle(8 * quarter + (l15 >> 2))) << 4) + (lane & 1) * 8);
+      laneB[j] = (uint32_t)((8 * quarter + (l15 >> 2)) * 512 + (((2 * (wn * TJ + j) + ((lane & 3) >> 1)) ^ kmajor_swizzle<256>(8 * quarter + (l15 >> 2))) << 4) + (lane & 1) * 8);
   } else {
     laneB[0] = (uint32_t)(wn * TJ * 16 + l15) * 128 + in_row;
   }
@@ -211,7 +191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int m = 0; m < MF; ++m) {
       mfma16_in_place<D>(fb[s][m % TJ], fa[s][m / TJ], acc[m / TJ][m % TJ]);
       if (places.read[m] >= 0) read_frag(s == 0 ? ua : na, s == 0 ? ub : nb, s ^ 1, places.read[m]);
-      if (places.place[m] >= 0) place = lds_place((s == 0 ? spare + myB : ua + myA) + places.place[m] * 4096);
+      if (places.place[m] >= 0) place = lds_place((s == 0 ? spare + myB : ua + myA) + places.place[m] * 1024);
       if (places.load[m] >= 0) {
         if (s == 0) load_b(place, places.load[m]);
         else load_a(place, places.load[m]);
@@ -254,76 +234,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     ua = na; ub = nb; na = a; nb = spare; spare = b;
   }
   __builtin_amdgcn_s_waitcnt(0x0070);  // nothing of mine is still on its way into LDS
-  // the last products' sums are in their registers 18 wait states later
-  asm volatile("s_nop 15\n\ts_nop 3");
-  auto settled = [&](int i) {
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) asm volatile("" : "+a"(acc[i][j]));
-  };
-
-  // Element v of lane l is row l % 16, column 4 (l / 16) + v of a block: four neighbouring columns go out as they are.
-  const int row0 = m0 + wm * 128 + l15;
-  if (dual) {
-    // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
-    const int col0 = n0 + wn * 8 * TJ + 4 * (quarter & 1) + 8 * (quarter >> 1);
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      const int row = row0 + 16 * i;
-      settled(i);
-#pragma unroll
-      for (int j = 0; j < TJ; j += 2) {
-        const int j1 = j + 1 < TJ ? j + 1 : j;
-        float z[4], u[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[i][j][v]), f2u(acc[i][j1][v]), false, false);
-          z[v] = u2f(sw[0]);
-          u[v] = u2f(sw[1]);
-        }
-        const int col = col0 + 8 * j;
-        const float none[4] = {0.f, 0.f, 0.f, 0.f};
-        if (row < g.M && col < g.Nn && (j + 1 < TJ || quarter < 2))
-          store_quad<D, EPI_SWIGLU>(g, make_float4(z[0], z[1], z[2], z[3]), make_float4(u[0], u[1], u[2], u[3]), none, (size_t)row * g.ldo + col);
-      }
-    }
-    return;
-  }
-  const int col0 = n0 + wn * 16 * TJ + 4 * quarter;
-  if (w.sums) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      const int row = row0 + 16 * i;
-      settled(i);
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) {
-        const int col = col0 + 16 * j;
-        if (row < g.M && col < g.Nn) *reinterpret_cast<f32x4*>(w.sums + (ptrdiff_t)row * bno + col) = acc[i][j];
-      }
-    }
-    return;
-  }
-  float bv[TJ][4];
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int col = col0 + 16 * j;
-      bv[j][k] = g.bias && col < g.Nn ? to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]) : 0.f;
-    }
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    const int row = row0 + 16 * i;
-    settled(i);
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const int col = col0 + 16 * j;
-      const float4 c = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
-        if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, c, c, bv[j], (size_t)row * g.ldo + col);
-        else store_quad<D, EPI_LINEAR>(g, c, c, bv[j], (size_t)row * g.ldo + col);
-      }
-    }
-  }
+  store_blocks<D, TI, TJ>(g, epi, dual, acc, m0 + wm * 16 * TI, n0, wn, w.sums, bno, lane);
 }
 
 template <class D, bool BNN, int TJ>
