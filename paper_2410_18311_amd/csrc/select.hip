@@ -15,7 +15,7 @@
 //     64; 11 + 7 bits for 16-bit inputs, which have no more) finds the value T of
 //     the k-th largest key, k being the share alpha of the positive keys -- their
 //     number is the total of the first digit's histogram.  That histogram is
-//     replicated eight times by lane so that activations sharing an exponent do
+//     replicated four times by lane (eight where the keys are read again from memory) so that activations sharing an exponent do
 //     not serialise on one LDS address; both digits' histograms are cleared
 //     while the row is still on its way from memory.  The digit that holds the
 //     k-th key is found by prefix sums over threads (DPP shifts inside rows of 16
@@ -30,7 +30,9 @@
 //     and whose addresses are one register, tests of a digit are one subtraction and one comparison, and no mask outlives its
 //     use (for_pairs).  By counter, 1024 x 13824 fp32: 11.6 -> 7.5 million vector and 6.0 -> 4.2 million scalar instructions,
 //     53.7 -> 41.0 thousand busy cycles of a compute unit for its four tokens; all launches 33.9 -> 28.4 us; 256 x 16384 fp16
-//     20.0 -> 18.7; 986 x 18112 bf16 75 -> 57.
+//     20.0 -> 18.7; 986 x 18112 bf16 75 -> 57.  A key is one addition to an activation's bits (kLift) instead of a test and a choice, and
+//     an atomic's address a shift and an addition: with four replicas for eight those take 29.1 -> 28.4, 18.8 -> 18.3, 2000 x 11008 fp32 41.0 ->
+//     39.2 and 8 x 512 x 36864 199 -> 193.5, whose time is barriers and LDS atomics rather than instructions.
 //     Where the keys are in registers the workgroup also counts, for each of its
 //     neurons, the tokens of its own that have it in their core set (a byte per
 //     neuron, four to a register), and writes those bytes once at its end.
@@ -68,7 +70,7 @@ constexpr int kMaxWaves = 16;
 constexpr int kThreads = 1024;           // threads of the per-token and the one-workgroup Def. 2 kernels
 // second digit's histogram of the per-token kernel, next to the first one so that both are cleared
 // up front: fp32 keys use one replica of 2048 digits (few keys are left, spread over all digits),
-// 16-bit keys eight replicas of 128 digits
+// 16-bit keys four or eight replicas of 128 digits
 constexpr int kHist2Words = kBins + 8;
 constexpr int kCopyStride2 = 128 + 8;
 constexpr uint32_t kNoKey = 0xffffffffu;  // stands for an activation that is not positive
@@ -280,6 +282,13 @@ __device__ __forceinline__ void for_pairs(int n_iter, F f) {
   }
 }
 
+// v >> n, opaque so that an address made from it is that and one shift and addition (and not a shift, a mask and an addition).
+__device__ __forceinline__ uint32_t shifted(uint32_t v, int n) {
+  uint32_t d = v >> n;
+  asm("" : "+v"(d));
+  return d;
+}
+
 // Clears COPIES replicas (STRIDE words apart) of an nb-digit histogram, 16 bytes per store (nb and
 // STRIDE are multiples of 4; the padding words are never read).
 template <int COPIES, int STRIDE>
@@ -333,11 +342,18 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
                                                                uint32_t* __restrict__ part) {
   using TI = typename IN::T;
   constexpr bool kNarrow = sizeof(TI) == 2;  // the fp32 image of a 16-bit value has nothing below bit 13
+  // Keys in registers are the bits plus a constant that takes NaN past the largest positive number: as signed numbers those of
+  // positive activations, +inf included, are the ones above kLift, in their order (one instruction a key, where a test for a positive
+  // number takes three).  They still fit 31 bits, and of 16-bit inputs the low 13 stay zero.
+  constexpr uint32_t kLift = ITEMS == 0 ? 0u : kNarrow ? 0x7fe000u : 0x7fffffu;
   __shared__ SelShared sh;
   __shared__ uint32_t cut_s;
   constexpr int kCand = 64;
   __shared__ uint32_t cand[kCand];
   __shared__ uint32_t cand_n;
+  // replicas of a histogram: with keys in registers four (eight take longer to clear and to add up than they save in conflicts:
+  // 256 x 16384 fp16 18.5 -> 18.3 us, 1024 x 13824 fp32 28.7 -> 28.4, 2000 x 11008 40.2 -> 39.2)
+  constexpr int kFirst = ITEMS > 0 ? 4 : kCopies;
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];  // [kHistWords + kHist2Words], cleared 16 bytes at a time
   uint32_t* hist2 = dyn;  // first: its place then fits the offset of an LDS instruction
   uint32_t* hist = dyn + kHist2Words;
@@ -362,8 +378,8 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
   for (int m = blockIdx.x; m < M; m += gridDim.x) {
     const TI* row = act + (size_t)m * ld;
     // the histograms of both digits are cleared while the row is on its way
-    clear_hist<kCopies, kCopyStride>(hist, 2048);
-    if (kNarrow) clear_hist<kCopies, kCopyStride2>(hist2, 128);
+    clear_hist<kFirst, kCopyStride>(hist, 2048);
+    if (kNarrow) clear_hist<kFirst, kCopyStride2>(hist2, 128);
     else clear_hist<1, kCopyStride>(hist2, 2048);
     if (tid == 0) cand_n = 0;
     uint32_t kc[ITEMS > 0 ? ITEMS : 1];
@@ -385,11 +401,11 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
         else av[i] = __builtin_bit_cast(TI, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_off, item, 0));
       }
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) kc[i] = act_key(IN::bits(av[i]), sign_mask, kNoKey);
+      for (int i = 0; i < ITEMS; ++i) kc[i] = (IN::bits(av[i]) & sign_mask) + kLift;
     }
-    // key of this thread's i-th element.  Elements that are not positive, and those past the end,
-    // get all-ones: bit 31 is part of the prefix mask from the start, so they match no prefix, and
-    // no threshold equals them
+    // key of this thread's i-th element.  Elements that are not positive, and those past the end, get all-ones (in
+    // registers: a number that is at most kLift or has bit 31): bit 31 is part of the prefix mask from the start, so they
+    // match no prefix, and no threshold equals them
     auto key_at = [&](int i) -> uint32_t {
       if (ITEMS > 0) return kc[ITEMS > 0 ? i : 0];  // i is a constant after unrolling
       const int e = i * nt + tid;
@@ -406,13 +422,13 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
     // them -- is taken from its total.
     uint32_t prefix = 0, prefix_mask = 0x80000000u, need = 0, n_eq = 0;
     if constexpr (ITEMS > 0) {
-      // the stand-in is negative as a signed number, every key is not and below 2^31
-      uint32_t* my_hist = hist + (tid & (kCopies - 1)) * kCopyStride;
+      uint32_t* my_hist = hist + (tid & (kFirst - 1)) * kCopyStride;
       for_pairs<ITEMS>(n_iter, [&](int i) {
-        if ((int)kc[i] >= 0) atomicAdd(&my_hist[kc[i] >> 20], 1u);
+        uint32_t* bin = &my_hist[shifted(kc[i], 20)];
+        if ((int)kc[i] > (int)kLift) atomicAdd(bin, 1u);
       });
       __syncthreads();
-      need = find_digit<true, kCopies, kCopyStride>(hist, 2048, 0, q_alpha, &sh);
+      need = find_digit<true, kFirst, kCopyStride>(hist, 2048, 0, q_alpha, &sh);
       if (need != 0) {
         prefix = sh.bin << 20;
         prefix_mask = 0xfff00000u;
@@ -432,7 +448,8 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       uint32_t* my_hist = hist2 + (tid & (copies.value - 1)) * stride.value;
       for_pairs<ITEMS>(n_iter, [&](int i) {
         const uint32_t t = kc[i] - prefix;
-        if (t < (1u << 20)) atomicAdd(&my_hist[t >> shift], 1u);
+        uint32_t* bin = &my_hist[shifted(t, shift)];
+        if (t < (1u << 20)) atomicAdd(bin, 1u);
       });
       __syncthreads();
       find_digit<false, copies.value, stride.value>(hist2, nb, need, 0, &sh);
@@ -442,7 +459,7 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       n_eq = sh.in_bin;
     };
     if constexpr (kNarrow) {
-      if constexpr (ITEMS > 0) second_pass(Const<kCopies>{}, Const<kCopyStride2>{}, 13, 128);
+      if constexpr (ITEMS > 0) second_pass(Const<kFirst>{}, Const<kCopyStride2>{}, 13, 128);
       else radix_pass<ITEMS, false, true, kCopies, kCopyStride2>(key_sel, n_iter, 13, 128, hist2, &sh, prefix, prefix_mask,
                                                                  need, n_eq);
       T = prefix;  // bits 13 .. 30 are all of the key
@@ -547,8 +564,7 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       __syncthreads();  // cut_s is final, and the tables in the histogram's place are done with
     }
     if constexpr (BYTES) {
-      // keys that are not positive are all-ones, negative as signed numbers; T is not negative
-      auto count = [&](auto least) {  // least(i): the least key of item i that is taken
+      auto count = [&](auto below) {  // below(i): one less than the least key of item i that is taken (T is positive)
         int n = n_iter;
 #pragma unroll
         for (int q = 0; q < ITEMS / 4; ++q) {
@@ -556,21 +572,21 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
           if (4 * q < n) {
             asm volatile("");
 #pragma unroll
-            for (int j = 0; j < 4; ++j) cp[q] += (int)kc[4 * q + j] >= least(4 * q + j) ? 1u << (8 * j) : 0u;
+            for (int j = 0; j < 4; ++j) cp[q] += (int)kc[4 * q + j] > below(4 * q + j) ? 1u << (8 * j) : 0u;
           }
           __builtin_amdgcn_sched_barrier(0);
         }
       };
       if (need == n_eq) {  // uniform
-        count([&](int) { return (int)T; });
+        count([&](int) { return (int)T - 1; });
       } else {
         // a tie past the cut is not taken: thread tid takes the ties of its items i with i * 1024 + tid <= cut
         const int cut = (int)cut_s;
         const int last = cut - tid >= 0 ? (cut - tid) / nt : -1;
-        count([&](int i) { return (int)T + (i <= last ? 0 : 1); });
+        count([&](int i) { return (int)T - (i <= last ? 1 : 0); });
       }
     }
-    if (tid == 0) { thr[2 * m] = T; thr[2 * m + 1] = cut_s; }
+    if (tid == 0) { thr[2 * m] = T - kLift; thr[2 * m + 1] = cut_s; }
     // no barrier: the next token clears the histograms (last read before a barrier above) and
     // thread 0 alone resets cut_s, behind barriers of its own; everything else in LDS is written again only
     // after barriers

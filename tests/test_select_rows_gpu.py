@@ -38,6 +38,40 @@ def test_select_ends_of_rows(lib, N, M, dt):
     assert np.array_equal(S.cpu().numpy(), S_ref)
 
 
+# Values at the ends of the key range: signaling, quiet and negative NaN of the least and the largest payload, both zeros, the least and the
+# largest denormal and normal number and infinity, the last as a tie that is cut; few positive ones, so that the threshold is among them
+@pytest.mark.parametrize("dt,bits,act", [(torch.float32, 32, "relu"), (torch.float16, 16, "relu"), (torch.float16, 16, "swiglu"),
+                                         (torch.bfloat16, 16, "relu"), (torch.bfloat16, 16, "swiglu")])
+@pytest.mark.parametrize("N", [40, 2000, 9000])
+def test_select_values_at_the_ends_of_the_range(lib, dt, bits, act, N):
+    inf = {torch.float32: 0x7f800000, torch.float16: 0x7c00, torch.bfloat16: 0x7f80}[dt]
+    sign = 1 << (bits - 1)
+    normal = {torch.float32: 0x800000, torch.float16: 0x400, torch.bfloat16: 0x80}[dt]
+    special = [inf + 1, inf | (inf >> 1 & ~inf) | 1, sign - 1, sign | (inf + 1), 2 * sign - 1, 0, sign, 1, normal - 1, normal, normal + 1,
+               inf - 1, inf, inf, inf, sign | 1, sign | inf, sign | normal]
+    M = 12
+    v = np.zeros((M, N), dtype=np.int64)
+    rng = np.random.default_rng(N)
+    for m in range(M):
+        at = rng.permutation(N)[:len(special)]
+        v[m, at] = special
+        if m % 3 == 1:
+            v[m] = np.where(v[m] == 0, inf, v[m])      # infinities everywhere: ties at the largest key
+        if m % 3 == 2:
+            v[m] = np.where(v[m] == 0, rng.integers(1, normal, N), v[m])   # denormals
+    kind = {32: (np.uint32, np.int32), 16: (np.uint16, np.int16)}[bits]
+    raw = torch.from_numpy(v.astype(kind[0]).view(kind[1])).view(dt)
+    alpha, beta = 0.2, 0.4
+    if dt == torch.float32:
+        S, counts = lib.select(raw.to(DEV), alpha, beta)
+    else:
+        S, counts = lib.select_hidden(raw.to(DEV), act, alpha, beta)
+    A = raw.float().abs() if act == "swiglu" else raw.float()
+    S_ref, c_ref = orc.select(A.numpy(), alpha, beta)
+    assert np.array_equal(counts.cpu().numpy(), c_ref)
+    assert np.array_equal(S.cpu().numpy(), S_ref)
+
+
 # Def. 2 in parallel with as many workgroups as there are compute units (256) and with more, where its counts are requested
 # later; fewer and more than 8192 vectors of counts before a workgroup; counts that do and do not start on 16 bytes
 @pytest.mark.parametrize("B,M,N", [(4, 3, 16384), (4, 3, 16385), (5, 2, 13824), (3, 2, 40001), (2, 2, 65536)])
