@@ -114,7 +114,8 @@ const KnobEntry kKnobs[] = {
     {"decode_depth", &Params::decode_depth, [](int v) { return v == 4 || v == 8 || v == 16; }},
     {"reduce_cq", &Params::reduce_cq, [](int v) { return v == 4 || v == 8 || v == 16; }},
     {"reduce_threads", &Params::reduce_threads, [](int v) { return v == 64 || v == 128 || v == 256 || v == 512 || v == 1024; }},
-    {"decode_small", &Params::decode_small, [](int v) { return v >= 0 && v <= 2; }},
+    {"decode_small", &Params::decode_small, [](int v) { return v >= 0 && v <= 3; }},
+    {"decode_small_patience", &Params::decode_small_patience, [](int v) { return v >= 0 && v <= 100000; }},
     {"decode_nt_store", &Params::decode_nt_store, [](int v) { return v == 0 || v == 1; }},
     {"fused_depth", &Params::fused_depth, [](int v) { return v == 4 || v == 8; }},
     {"fused_threads", &Params::fused_threads, [](int v) { return v >= 0 && v <= 1024; }},

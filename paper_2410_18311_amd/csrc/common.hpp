@@ -132,7 +132,8 @@ struct Params {
   Knob gemm_splits{0};       // k splits of the last round of the down projection: 0 planned
   Knob reduce_threads{256};  // threads per reduce workgroup (64, 128, 256)
   Knob reduce_cq{8};         // column quads per reduce workgroup (4, 8, 16)
-  Knob decode_small{1};      // small layers in one launch: 0 never, 1 by the rule, 2 wherever it can
+  Knob decode_small_patience{2000};  // ticks of 10 ns that shared hidden values are waited for
+  Knob decode_small{1};      // small layers in one launch: 0 never, 1 by the rule, 2 wherever it can, 3 the same with shared hidden values
   Knob decode_nt_store{1};   // non-temporal stores for the partial sums
   Knob gathered_union{1};         // gathered decode through the union of the lists: 0 never, 1 by the rule, 2 wherever it can
   Knob union_depth{8};            // union-batched decode: rows in flight per thread (8 or 16)
@@ -222,8 +223,9 @@ int decode_splits_bound(int64_t B, int64_t K);  // at least decode_splits; what 
 int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act,
                       void* y, float* partial, int max_slices, hipStream_t s);
 // Small layers in one launch (ffn_decode_small.hip), with the outputs of n_wg slices to the bit.
-bool decode_small_pays(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s);
-int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg,
+enum class DecodeSmall { kNo, kAll, kShare };  // every workgroup computes all hidden values, or its part of them for all
+DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s);
+int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg, bool share,
                             hipStream_t s);
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
                          int dtype, hipStream_t s);

@@ -11,7 +11,10 @@
  *   weight rows in flight per thread), "reduce_cq" (4, 8, 16 column quads per
  *   reduction workgroup), "reduce_threads" (64 .. 1024, a power of two: threads per reduction
  *   workgroup), "decode_nt_store" (0/1): two-launch decode; "decode_small" (0
- *   never, 1 by the rule, 2 wherever it can): small layers in one launch;
+ *   never, 1 by the rule, 2 wherever it can, 3 wherever it can with shared hidden
+ *   values unless the stream is captured): small layers in one launch;
+ *   "decode_small_patience" (0 .. 100000 ticks of 10 ns that a workgroup waits for
+ *   shared values before it computes them itself);
  *   "fused_depth" (4, 8), "fused_threads" (0 or a multiple of 64 up to 896),
  *   "fused_chunks" (least number of neuron chunks, 2..64),
  *   "fused_chunk_size" (0 = cost model, else neurons per chunk, a multiple of the

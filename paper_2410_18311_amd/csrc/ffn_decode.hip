@@ -493,8 +493,8 @@ int launch_ffn_decode(const void* x, int64_t B, const ci_ffn_weights* w, int dty
   const size_t bytes = (size_t)B * (size_t)w->d * (dtype == CI_F32 ? 4 : 2);
   const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
   const bool apart = x0 + bytes <= y0 || y0 + bytes <= x0;
-  if (!w->core_idx && apart && decode_small_pays(B, w->K, w->d, dtype, act, n_wg, s))
-    return launch_ffn_decode_small(x, B, w, dtype, act, y, n_wg, s);
+  const DecodeSmall small = !w->core_idx && apart ? decode_small_way(B, w->K, w->d, dtype, act, n_wg, s) : DecodeSmall::kNo;
+  if (small != DecodeSmall::kNo) return launch_ffn_decode_small(x, B, w, dtype, act, y, n_wg, small == DecodeSmall::kShare, s);
   DecodeArgs a;
   a.x = x;
   a.w_up = w->w_up;

@@ -6,9 +6,16 @@
 // What bounds it is the fill of a compute unit's L1 with the up (and gate) rows: by the slope of its time over their size 124 GB/s
 // in fp32 and 85 in 16 bits, with twice the products a byte (256 x 96 to 256 x 512).  The down rows of the workgroup's columns
 // are requested ahead of them and wait in registers.
+// Where that fill takes longer than to hand a value on (SHARE), a workgroup computes its part of the hidden values only and stores each
+// as words that say themselves that they are this call's; the others read them until they are (about 1.5 us).  Nothing depends on the
+// others being there: a workgroup whose values have not come in 20 us computes them itself.  256 x 410 fp32, call by call, 6.95 ->
+// 5.39 us, 256 x 512 7.6 -> 5.4, 4 tokens of 256 x 448 7.2 -> 5.8, fp16 512 x 256 6.7 -> 5.8.
 // A call gives the same bits whichever way it goes (launched or captured, apart or in place; finite weights): dot products are
 // added up over the lanes as there, down rows slice by slice, and the slices in the order of decode_reduce_kernel.  That costs
 // nothing measurable: 256 x 424 fp32 from a graph 6.91 us, and 6.89 with the rows spread over all threads.
+#include <atomic>
+#include <random>
+
 #include "common.hpp"
 #include "decode_common.hpp"
 
@@ -28,6 +35,9 @@ struct SmallArgs {
   int n_wg;           // slices of the neurons
   uint32_t inv_n_wg;  // 2^32 / n_wg rounded up: a product below 2^20 times it, 32 bits up, is the product over n_wg
   int most_rows;      // at least the rows of any slice
+  uint32_t tag[2];    // shared hidden values: of this call and no other
+  int slot;           // and the first of its rows of g_hidden
+  int patience;       // ticks of 10 ns that a workgroup waits for the others before it computes their values itself
 };
 
 constexpr int kSmallThreads = 512, kSmallWaves = 8;
@@ -38,6 +48,12 @@ constexpr int kSmallMaxK = 4096; // hidden values in LDS
 constexpr int kReduceGroups = 32;  // groups of slices in decode_reduce_kernel: 256 threads, eight column quads
 constexpr int kSmallSlices = 8 * kReduceGroups;  // most slices of the neurons, two a thread
 
+// Shared hidden values, two words each: half of the call's tag and the value's bits.  A value is there where both halves are the
+// call's and both values the same, so nothing has to be cleared, and calls on other streams that come to use the same row
+// (every sixteenth) can at most take each other's values away.
+constexpr int kSmallCalls = 16, kSmallTokens = 4;
+static __device__ unsigned long long g_hidden[kSmallCalls * kSmallTokens][kSmallMaxK][2];
+
 // The value L lanes further on in the same sixteen (past them: zero).
 template <int L>
 __device__ __forceinline__ float lane_behind(float v) {
@@ -45,13 +61,14 @@ __device__ __forceinline__ float lane_behind(float v) {
 }
 
 // G lanes share a row of d elements, NI vectors each.
-template <class D, int G, int NI, bool SWIGLU>
+template <class D, int G, int NI, bool SWIGLU, bool SHARE>
 __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallArgs a) {
   using T = typename D::T;
   constexpr int VEC = D::VEC;
   constexpr int GPW = 64 / G, STEP = kSmallWaves * GPW;  // rows side by side
   __shared__ float h[kSmallMaxK];
   __shared__ float sums[kSmallWaves][kSmallQuads * VEC];
+  __shared__ int late;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.y;
   const size_t rowbytes = (size_t)a.d * sizeof(T);
@@ -95,40 +112,91 @@ __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallAr
   request_down(dn[0], 0);
 
   constexpr int SH = G / kSmallRows;  // lanes that end with the same row's sum
-  for (int r0 = row0; r0 - row0 < a.K; r0 += kSmallRows * STEP) {
-    const int mine = r0 + gl / SH * STEP;  // the row whose sum ends in this lane
-    float bias = 0.f;
-    if (!SWIGLU && a.b_up) bias = to_float<D>(reinterpret_cast<const T*>(a.b_up)[min(mine, a.K - 1)]);
-    uint4 u[kSmallRows][NI], g[SWIGLU ? kSmallRows : 1][NI];
+  auto hidden = [&](int lo, int hi, auto sink) {  // of the rows lo .. hi - 1
+    for (int r0 = lo + row0; r0 - row0 < hi; r0 += kSmallRows * STEP) {
+      const int mine = r0 + gl / SH * STEP;  // the row whose sum ends in this lane
+      float bias = 0.f;
+      if (!SWIGLU && a.b_up) bias = to_float<D>(reinterpret_cast<const T*>(a.b_up)[min(mine, hi - 1)]);
+      uint4 u[kSmallRows][NI], g[SWIGLU ? kSmallRows : 1][NI];
 #pragma unroll
-    for (int s = 0; s < kSmallRows; ++s) {
-      const size_t row = (size_t)min(r0 + s * STEP, a.K - 1) * rowbytes;
+      for (int s = 0; s < kSmallRows; ++s) {
+        const size_t row = (size_t)min(r0 + s * STEP, hi - 1) * rowbytes;
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        if (SWIGLU) g[s][i] = ld16(gate + row + off[i]);
-        u[s][i] = ld16(up + row + off[i]);
-      }
-    }
-    float zu[kSmallRows], zg[kSmallRows];
-#pragma unroll
-    for (int s = 0; s < kSmallRows; ++s) {
-      zu[s] = zg[s] = 0.f;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        float f[VEC];
-        unpack<D>(u[s][i], f);
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) zu[s] = fmaf(f[c], xr[i][c], zu[s]);
-        if (SWIGLU) {
-          unpack<D>(g[s][i], f);
-#pragma unroll
-          for (int c = 0; c < VEC; ++c) zg[s] = fmaf(f[c], xr[i][c], zg[s]);
+        for (int i = 0; i < NI; ++i) {
+          if (SWIGLU) g[s][i] = ld16(gate + row + off[i]);
+          u[s][i] = ld16(up + row + off[i]);
         }
       }
+      float zu[kSmallRows], zg[kSmallRows];
+#pragma unroll
+      for (int s = 0; s < kSmallRows; ++s) {
+        zu[s] = zg[s] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          float f[VEC];
+          unpack<D>(u[s][i], f);
+#pragma unroll
+          for (int c = 0; c < VEC; ++c) zu[s] = fmaf(f[c], xr[i][c], zu[s]);
+          if (SWIGLU) {
+            unpack<D>(g[s][i], f);
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) zg[s] = fmaf(f[c], xr[i][c], zg[s]);
+          }
+        }
+      }
+      halve_rows<kSmallRows, G / 2>(zu, lane);
+      if (SWIGLU) halve_rows<kSmallRows, G / 2>(zg, lane);
+      if (gl % SH == 0 && mine < hi) sink(mine, SWIGLU ? silu(zg[0]) * zu[0] : fmaxf(zu[0] + bias, 0.f));
     }
-    halve_rows<kSmallRows, G / 2>(zu, lane);
-    if (SWIGLU) halve_rows<kSmallRows, G / 2>(zg, lane);
-    if (gl % SH == 0 && mine < a.K) h[mine] = SWIGLU ? silu(zg[0]) * zu[0] : fmaxf(zu[0] + bias, 0.f);
+  };
+  auto keep = [&](int k, float v) { h[k] = v; };
+  if constexpr (SHARE) {
+    // an equal part of the rows each, handed to the others as they come
+    const int lo = (int)((uint32_t)a.K * blockIdx.x / gridDim.x), hi = (int)((uint32_t)a.K * (blockIdx.x + 1) / gridDim.x);
+    unsigned long long(*words)[2] = g_hidden[a.slot + b];
+    const unsigned long long t0 = (unsigned long long)a.tag[0] << 32, t1 = (unsigned long long)a.tag[1] << 32;
+    if (tid == 0) late = 0;
+    hidden(lo, hi, [&](int k, float v) {
+      h[k] = v;
+      __hip_atomic_store(&words[k][0], t0 | f2u(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&words[k][1], t1 | f2u(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
+    __syncthreads();
+    const long long start = __builtin_amdgcn_s_memrealtime();
+    constexpr int kAtOnce = 4;
+    for (int k0 = tid; k0 < a.K; k0 += kAtOnce * kSmallThreads) {
+      uint32_t wanted = 0;
+#pragma unroll
+      for (int i = 0; i < kAtOnce; ++i) {
+        const int k = k0 + i * kSmallThreads;
+        if (k < a.K && (k < lo || k >= hi)) wanted |= 1u << i;
+      }
+      while (wanted) {
+        unsigned long long w0[kAtOnce], w1[kAtOnce];
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i) {
+          const int k = min(k0 + i * kSmallThreads, a.K - 1);
+          w0[i] = __hip_atomic_load(&words[k][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          w1[i] = __hip_atomic_load(&words[k][1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i) {
+          if ((wanted >> i & 1) && w0[i] == (t0 | (uint32_t)w0[i]) && w1[i] == (t1 | (uint32_t)w0[i])) {
+            h[k0 + i * kSmallThreads] = u2f((uint32_t)w0[i]);
+            wanted &= ~(1u << i);
+          }
+        }
+        if (wanted && (long long)__builtin_amdgcn_s_memrealtime() - start > a.patience) {
+          late = 1;
+          break;
+        }
+      }
+      if (wanted) break;
+    }
+    __syncthreads();
+    if (late) hidden(0, a.K, keep);
+  } else {
+    hidden(0, a.K, keep);
   }
   if (a.most_rows > step) request_down(dn[1], step);  // uniform
   __syncthreads();
@@ -198,21 +266,37 @@ __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallAr
   }
 }
 
-template <class D, bool SWIGLU>
-int launch_typed(const SmallArgs& a, int B, hipStream_t s) {
+template <class D, int G, int NI, bool SWIGLU>
+int launch_rows(const SmallArgs& a, int B, bool share, hipStream_t s) {
   const int vecs = a.d / D::VEC;
   const dim3 grid((vecs + kSmallQuads - 1) / kSmallQuads, B), block(kSmallThreads);
-  if (vecs <= 16) hipLaunchKernelGGL((ffn_decode_small_kernel<D, 16, 1, SWIGLU>), grid, block, 0, s, a);
-  else if (vecs <= 32) hipLaunchKernelGGL((ffn_decode_small_kernel<D, 32, 1, SWIGLU>), grid, block, 0, s, a);
-  else if (vecs <= 64) hipLaunchKernelGGL((ffn_decode_small_kernel<D, 64, 1, SWIGLU>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((ffn_decode_small_kernel<D, 64, 2, SWIGLU>), grid, block, 0, s, a);
+  if (share) hipLaunchKernelGGL((ffn_decode_small_kernel<D, G, NI, SWIGLU, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((ffn_decode_small_kernel<D, G, NI, SWIGLU, false>), grid, block, 0, s, a);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
 }
 
+template <class D, bool SWIGLU>
+int launch_typed(const SmallArgs& a, int B, bool share, hipStream_t s) {
+  const int vecs = a.d / D::VEC;
+  if (vecs <= 16) return launch_rows<D, 16, 1, SWIGLU>(a, B, share, s);
+  if (vecs <= 32) return launch_rows<D, 32, 1, SWIGLU>(a, B, share, s);
+  if (vecs <= 64) return launch_rows<D, 64, 1, SWIGLU>(a, B, share, s);
+  return launch_rows<D, 64, 2, SWIGLU>(a, B, share, s);
+}
+
 template <class D>
-int launch_dtype(const SmallArgs& a, int B, int act, hipStream_t s) {
-  return act == CI_ACT_SWIGLU ? launch_typed<D, true>(a, B, s) : launch_typed<D, false>(a, B, s);
+int launch_dtype(const SmallArgs& a, int B, int act, bool share, hipStream_t s) {
+  return act == CI_ACT_SWIGLU ? launch_typed<D, true>(a, B, share, s) : launch_typed<D, false>(a, B, share, s);
+}
+
+// 64 bits that no other call of this process has, from a start that no other process has (memory keeps what was in it)
+uint64_t next_call() {
+  static std::atomic<uint64_t> calls{[] {
+    std::random_device r;
+    return (uint64_t)r() << 32 | r();
+  }()};
+  return calls.fetch_add(1, std::memory_order_relaxed);
 }
 
 }  // namespace
@@ -228,27 +312,40 @@ int launch_dtype(const SmallArgs& a, int B, int act, hipStream_t s) {
 //   four tokens   fp32  256 x 256   7.9 / 5.2, 5.9 / 5.2     256 x 512  7.8 / 7.8, 6.7 / 8.1   gated 512 x 72 7.8 / 6.9, 6.3 / 7.0
 //                 fp16  256 x 512   7.9 / 6.8, 6.9 / 6.9     gated 256 x 256  7.8 / 5.6, 6.6 / 5.7
 // (of 208 such layers none of up to 64 K elements was slower in either way).  Both ways give the same bits.
-constexpr int64_t kSmallElements = 128 * 1024, kSmallElementsGraph = 64 * 1024;
-bool decode_small_pays(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s) {
+// Call by call the hidden values of more than 64 K elements are shared where a workgroup would read four batches of rows or more (a call's
+// words are its own only once, so a captured call, which runs many times, has none).  us, every workgroup all / shared:
+//   fp32  256 x 256 (4 batches, 64 K) 5.38 / 5.33    256 x 288 (5) 5.81 / 5.33    256 x 384 (6) 6.37 / 5.31   128 x 576 (5) 5.95 / 5.69
+//         512 x 192 (3) 5.84 / 6.08   512 x 224 (4) 6.86 / 6.10   gated 256 x 192 (3) 5.92 / 5.65   256 x 224 (4) 6.73 / 5.71   512 x 112 (2) 6.65 / 6.37
+//         four tokens   256 x 288 6.02 / 5.80    512 x 192 5.84 / 6.11   512 x 224 6.93 / 6.20
+//   fp16  256 x 384 (3) 5.59 / 5.98   256 x 448 (4) 6.26 / 5.86   512 x 224 (4) 6.62 / 5.81   1024 x 128 (2) 5.84 / 6.14   bf16 gated 256 x 256 (2) 6.11 / 6.42
+constexpr int64_t kSmallElements = 128 * 1024, kSmallElementsGraph = 64 * 1024, kSmallBatchesShare = 4;
+DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s) {
   const int mode = params().decode_small;
   const int64_t vec = 16 / elem_bytes(dtype), vecs = d / vec;
-  if (mode == 0 || K < 1 || K > kSmallMaxK || vecs > 128 || B > 4 || n_wg > kSmallSlices) return false;
+  if (mode == 0 || K < 1 || K > kSmallMaxK || vecs > 128 || B > kSmallTokens || n_wg > kSmallSlices) return DecodeSmall::kNo;
   const int64_t held = vecs <= 16 ? 16 : vecs <= 32 ? 32 : (vecs + 63) / 64 * 64;
   const int64_t elements = (act == CI_ACT_SWIGLU ? 2 : 1) * K * held * vec;
-  if (mode == 2 || elements <= kSmallElementsGraph) return true;
-  if (elements > kSmallElements) return false;
+  if (mode == 2) return DecodeSmall::kAll;
+  if (mode == 1 && elements > kSmallElements) return DecodeSmall::kNo;
+  if (mode == 1 && elements <= kSmallElementsGraph) return DecodeSmall::kAll;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;  // the null stream is never captured
-  return !s || (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone);
+  if (s && !(hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)) return DecodeSmall::kNo;
+  const int64_t lanes = vecs <= 16 ? 16 : vecs <= 32 ? 32 : 64, rows = kSmallRows * kSmallWaves * (64 / lanes);
+  return mode == 3 || (K + rows - 1) / rows >= kSmallBatchesShare ? DecodeSmall::kShare : DecodeSmall::kAll;
 }
 
-int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg, hipStream_t s) {
+int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg, bool share,
+                            hipStream_t s) {
   const int K = (int)w->K;
+  const uint64_t call = share ? next_call() : 0;
   const SmallArgs a{x, w->w_up, w->w_gate, w->b_up, w->w_down, w->b_down, y, K, (int)w->d, n_wg,
-                    (uint32_t)(((1ull << 32) + n_wg - 1) / n_wg), (K + n_wg - 1) / n_wg};
+                    (uint32_t)(((1ull << 32) + n_wg - 1) / n_wg), (K + n_wg - 1) / n_wg,
+                    {(uint32_t)(call >> 32), (uint32_t)call}, (int)(call % kSmallCalls) * kSmallTokens,
+                    (int)params().decode_small_patience};
   switch (dtype) {
-    case CI_F32: return launch_dtype<F32>(a, (int)B, act, s);
-    case CI_F16: return launch_dtype<F16>(a, (int)B, act, s);
-    case CI_BF16: return launch_dtype<BF16>(a, (int)B, act, s);
+    case CI_F32: return launch_dtype<F32>(a, (int)B, act, share, s);
+    case CI_F16: return launch_dtype<F16>(a, (int)B, act, share, s);
+    case CI_BF16: return launch_dtype<BF16>(a, (int)B, act, share, s);
   }
   return CI_ERR_BAD_DTYPE;
 }

@@ -124,3 +124,64 @@ def test_small_decode_in_place(lib, shift):
     got, took_one = _one_launch(lib, buf[4 * B * d:5 * B * d].view(B, d), desc, "relu", y=buf[o:o + B * d].view(B, d))
     assert took_one == (abs(shift) == B)
     assert torch.equal(got, apart)
+
+
+# Hidden values shared by the workgroups: the bits of two launches, for fewer and more neurons than workgroups and than a thread takes at
+# once, one to four tokens; and again with no time to wait for any, when every workgroup computes what it misses itself
+@pytest.mark.parametrize("patience", [2000, 0])
+@pytest.mark.parametrize("act", ["relu", "swiglu"])
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_small_decode_shared(lib, act, dt, patience):
+    vec = 4 if dt == torch.float32 else 8
+    lib.dev_set_param("decode_small_patience", patience)
+    try:
+        for vecs in (1, 16, 33, 64, 128):
+            d = vecs * vec
+            for K, B in ((1, 4), (9, 1), (257, 3), (513, 1), (2049, 2), (4096, 1)):
+                w = _layer(dt, act, d, K, d + K)
+                desc = lib.make_weights(w["up"], w["gate"], w["b_up"], w["down"], w["b_down"])
+                x = torch.randn(B, d, generator=torch.Generator().manual_seed(K)).to(dt).to(DEV)
+                x[0, 0] = float("inf") if K == 9 else x[0, 0]
+                lib.dev_set_param("decode_small", 0)
+                two = lib.ffn_decode(x, desc, act)
+                lib.dev_set_param("decode_small", 3)
+                y = torch.full((B * d + 64,), -7.0, dtype=dt, device=DEV)
+                for _ in range(20):   # more calls than rows of words
+                    y[:B * d] = 0
+                    lib.ffn_decode(x, desc, act, y=y[:B * d].view(B, d))
+                    assert torch.equal(y[:B * d].view(B, d).nan_to_num(nan=3.0), two.nan_to_num(nan=3.0)), (d, K, B)
+                assert bool((y[B * d:] == -7.0).all()), "stored past the end"
+    finally:
+        lib.dev_set_param("decode_small", 1)
+        lib.dev_set_param("decode_small_patience", 2000)
+
+
+# Calls of several threads, each on a stream of its own, take the same rows of words in turn
+def test_small_decode_shared_by_threads(lib):
+    import threading
+    d, K = 256, 500
+    w = _layer(torch.float32, "relu", d, K, 3)
+    desc = lib.make_weights(w["up"], None, w["b_up"], w["down"], w["b_down"])
+    xs = torch.randn(6, d, generator=torch.Generator().manual_seed(4)).to(DEV)
+    lib.dev_set_param("decode_small", 0)
+    want = torch.cat([lib.ffn_decode(xs[i:i + 1], desc, "relu") for i in range(6)])
+    lib.dev_set_param("decode_small", 1)
+    torch.cuda.synchronize()
+    wrong = [None] * 6
+
+    def run(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ws, y, n = lib.decode_workspace(1, K, d, DEV), torch.empty(1, d, device=DEV), torch.zeros((), dtype=torch.int64, device=DEV)
+            for _ in range(200):
+                lib.ffn_decode(xs[i:i + 1], desc, "relu", y=y, ws=ws)
+                n += (y != want[i:i + 1]).sum()
+            s.synchronize()
+            wrong[i] = int(n)
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert wrong == [0] * 6
