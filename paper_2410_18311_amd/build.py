@@ -6,6 +6,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 from . import isa_check
@@ -16,6 +17,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libcoreinfer.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")   # a Python module, linked against the library beside it
 
 SOURCES = ["api.hip", "ffn_decode.hip", "ffn_decode_small.hip", "ffn_decode_fused.hip", "ffn_union.hip", "select.hip", "compact.hip", "centroid.hip", "gemv.hip", "gemm_mfma.hip", "gemm_f32.hip", "gemm_wide.hip", "gemm_mid.hip", "gemm_slim_f16.hip", "gemm_slim_bf16.hip", "stream_probe.hip"]
 
@@ -55,6 +57,11 @@ def build_library(verbose: bool = False) -> str:
         os.remove(LIB_PATH)
         raise RuntimeError("loads into LDS or matrix products that read a register too soon after it was written, or a product's result read too soon:\n" +
                            "\n".join(bad))
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+           os.path.join(CSRC, "binding.c"), "-o", BINDING_PATH, "-L", PKG_DIR, "-lcoreinfer", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("binding failed:\n" + r.stderr)
     if verbose:
         print("built", LIB_PATH)
     return LIB_PATH

@@ -1,4 +1,4 @@
-"""ctypes binding over libcoreinfer.so -- argument marshalling only.
+"""Binding over libcoreinfer.so -- argument marshalling only: ctypes, and for the per-token call csrc/binding.c.
 
 Function names mirror the C ABI (include/coreinfer.h).  Tensors are torch
 tensors on the GPU; torch supplies device memory and the current stream,
@@ -15,7 +15,7 @@ from typing import Optional
 
 import torch  # imported first so that the HIP runtime torch ships is the one the library binds to
 
-from .build import LIB_PATH
+from .build import BINDING_PATH, LIB_PATH
 
 CI_OK = 0
 CI_ERR_INVALID_ARG = -1
@@ -33,12 +33,14 @@ DTYPE_CODE = {torch.float32: CI_F32, torch.float16: CI_F16, torch.bfloat16: CI_B
 ACT_CODE = {"relu": CI_ACT_RELU, "swiglu": CI_ACT_SWIGLU}
 LAYOUT_CODE = {"out_major": CI_DOWN_OUT_MAJOR, "neuron_major": CI_DOWN_NEURON_MAJOR}
 
-if not os.path.exists(LIB_PATH):
+if not (os.path.exists(LIB_PATH) and os.path.exists(BINDING_PATH)):
     raise ImportError(
-        f"{LIB_PATH} is not built; run `python -m paper_2410_18311_amd.build` "
+        f"{LIB_PATH} or {BINDING_PATH} is not built; run `python -m paper_2410_18311_amd.build` "
         "(there is no CPU or PyTorch fallback for the CoreInfer kernels)")
 
 _lib = ctypes.CDLL(LIB_PATH)
+
+from . import _binding  # noqa: E402  (linked against the library that is now loaded)
 
 _vp, _i64, _int, _dbl, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_double, ctypes.c_size_t
 
@@ -493,10 +495,13 @@ def ffn_decode(x: torch.Tensor, weights: ci_ffn_weights, act: str, y: Optional[t
         y = torch.empty_like(x2)
     if ws is None:
         ws = decode_workspace(B, weights.K, d, x.device)
-    _check(_lib.coreinfer_ffn_decode(_ptr(x2), B, ctypes.byref(weights), DTYPE_CODE[x.dtype],
-                                     ACT_CODE[act], _ptr(y), _ptr(ws), ws.numel(), _stream(x)),
-           "coreinfer_ffn_decode")
-    return y if x.dim() == 2 else y.squeeze(0)
+    if not isinstance(weights, ci_ffn_weights):
+        raise TypeError("weights: a descriptor of make_weights")
+    status = _binding.ffn_decode(x2.data_ptr(), B, ctypes.addressof(weights), DTYPE_CODE[x.dtype], ACT_CODE[act],
+                                 y.data_ptr(), ws.data_ptr(), ws.numel(), _stream(x))
+    if status != CI_OK:
+        raise CoreInferError(status, "coreinfer_ffn_decode")
+    return y if x2 is x else y.squeeze(0)
 
 
 def ffn_decode_static(x: torch.Tensor, weights: ci_ffn_weights, act: str, y: Optional[torch.Tensor] = None,

@@ -648,3 +648,32 @@ def test_bench_prints_one_short_line_with_every_field_of_its_contract():
     assert got["value"] == x and got["ms_per_step"] == x and len(got["workloads"]) == len(bench.OTHER_WORKLOADS)
     alone = bench.printed_line({**record(bench.TOP_WORKLOAD, 0.2), "parity": None, "cpu_baseline": None}, None)
     assert "workloads" not in alone and "parity" not in alone
+
+
+def test_per_token_call_of_the_binding_returns_the_status_of_the_c_call(lib):
+    """csrc/binding.c hands its arguments on as they are: the same status for every argument that is refused, and no call for arguments
+    that are not numbers."""
+    import ctypes
+    import torch
+    w = torch.zeros(4, 8)
+    desc = lib.make_weights(w, None, None, w, None)
+    good = [w.data_ptr(), 1, ctypes.addressof(desc), lib.CI_F32, lib.CI_ACT_RELU, w.data_ptr(), None, 0, None]
+    wrong = {0: (None, 3), 1: (0, -1, 1 << 40), 2: (None,), 3: (7, -1), 4: (9, -1), 5: (None, w.data_ptr() + 2), 6: (None,), 7: (8,)}
+    seen = set()
+    for at, values in wrong.items():
+        for v in values:
+            args = good[:at] + [v] + good[at + 1:]
+            c_args = list(args)
+            c_args[2] = ctypes.cast(args[2], ctypes.POINTER(lib.ci_ffn_weights)) if args[2] else None
+            status = lib._binding.ffn_decode(*args)
+            assert status == lib.raw.coreinfer_ffn_decode(*c_args) != lib.CI_OK, (at, v)
+            seen.add(status)
+    assert len(seen) >= 3
+    with pytest.raises(TypeError):
+        lib._binding.ffn_decode(*good[:-1])
+    with pytest.raises(TypeError):
+        lib._binding.ffn_decode("x", *good[1:])
+    with pytest.raises(OverflowError):
+        lib._binding.ffn_decode(good[0], 1 << 70, *good[2:])
+    with pytest.raises(TypeError):
+        lib.ffn_decode(w, None, "relu", y=w, ws=w)
