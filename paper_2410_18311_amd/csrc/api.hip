@@ -130,7 +130,7 @@ const KnobEntry kKnobs[] = {
     {"select_bytes", &Params::select_bytes, [](int v) { return v >= 0 && v <= 2; }},
     {"select_def2_single", &Params::select_def2_single, [](int v) { return v == 0 || v == 1; }},
     {"select_wgs_per_cu", &Params::select_wgs_per_cu, [](int v) { return v >= 1 && v <= 8; }},
-    {"gemm_tile", &Params::gemm_tile, [](int v) { return (v >= -1 && v <= kWide160) || (v >= kSlim && slim_built((v - kSlim) / 16, v % 16)); }},
+    {"gemm_tile", &Params::gemm_tile, [](int v) { return (v >= -1 && v < kShapes) || (v >= kSlim && slim_built((v - kSlim) / 16, v % 16)); }},
     {"gemm_once", &Params::gemm_once, [](int v) { return v >= 0 && v <= 2; }},
     {"gemm_splits", &Params::gemm_splits, [](int v) { return v >= 0 && v <= 8; }},
     {"gemv_wgs_per_cu", &Params::gemv_wgs_per_cu, [](int v) { return v >= 1 && v <= 32; }},

@@ -32,7 +32,7 @@
  *   "select_def2_single" (0/1: 1 runs Def. 2 in one workgroup even where the
  *   parallel kernel applies);
  *   "gemv_wgs_per_cu" (1..32), "gemv_cols_wgs_per_cu" (1..4),
- *   "gemm_tile" (-1 planned, 0 .. 6: tile shape, 16 + 16 tm + tn: tiles of 16 tm x
+ *   "gemm_tile" (-1 planned, 0 .. 10: tile shape, 16 + 16 tm + tn: tiles of 16 tm x
  *   16 tn where they are built and the weights k-contiguous), "gemm_once" (0 never, 1 by
  *   the rule, 2 wherever they can be: weights loaded as data that is not read
  *   again), "gemm_splits" (0 planned, 1 .. 8:
@@ -74,7 +74,7 @@ int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int 
 
 /* The plans of coreinfer_ffn_dense for more than four tokens of a 16-bit type
  * under the current settings, the down projection's with room for `room` bytes
- * of split sums: out[0..8] = tile shape (0 .. 6, or 16 + 16 tm + tn for tiles
+ * of split sums: out[0..8] = tile shape (0 .. 10, or 16 + 16 tm + tn for tiles
  * of 16 tm x 16 tn) and tiles of the up projection; tile shape, tiles computed
  * whole, tiles split along k, splits and bytes of their sums of the down
  * projection; whether the weights of the up and of the down projection are

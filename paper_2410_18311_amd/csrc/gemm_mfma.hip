@@ -76,6 +76,10 @@ struct Product {
 // and added by another launch.  The constants are those that come closest to 4900 measured products of 129 to 4096 rows, d
 // 1024 to 9216 and N 2048 to 36864, odd lengths among them, all shapes and splits (7.6 % off on average).  Of 271 pairs of products the plans by
 // it are on average 0.2 % (up) and 2.2 % (down) behind the fastest of all; those by the former estimate of whole rounds were 1.0 and 5.3 %.
+// The last four shapes came later, with 394 more up projections of 129 to 1536 rows, layers in turn; their constants are 2 % on the slow
+// side, so that they are taken where they promise that much.  24 % of 5800 other up projections of 129 to 2048 rows take them: layers in
+// turn 13 % faster on average, one in a hundred by more than 3 % slower (small ones, 17 % at most), one layer again and again 12 %
+// and 6 % at most.
 struct ManyShape {
   int shape;
   int bm, bn;        // rows of A, rows of B (SwiGLU: half of them gate, half up)
@@ -87,7 +91,9 @@ struct ManyShape {
 constexpr ManyShape kManyShapes[] = {{kMid128x128, 128, 128, 3.54e12, 2.8e-6, 0.58, 0.37}, {kMid128x256, 128, 256, 4.41e12, 3.9e-6, 0.61, 0.41},
                                      {kMid128x64, 128, 64, 2.72e12, 2.1e-6, 0.70, 0.42},   {kWide, 256, 256, 6.12e12, 8.0e-6, 0.72, 0.13},
                                      {kWide224, 256, 224, 5.85e12, 6.3e-6, 0.73, 0.16},    {kWide192, 256, 192, 5.51e12, 4.9e-6, 0.71, 0.19},
-                                     {kWide160, 256, 160, 4.94e12, 3.0e-6, 0.69, 0.24}};
+                                     {kWide160, 256, 160, 4.94e12, 3.0e-6, 0.69, 0.24},    {kMid192x128, 192, 128, 4.35e12, 2.3e-6, 0.90, 0.25},
+                                     {kMid128x96, 128, 96, 3.17e12, 2.5e-6, 0.56, 0.30},   {kMid128x160, 128, 160, 3.83e12, 3.7e-6, 0.61, 0.36},
+                                     {kMid128x192, 128, 192, 4.08e12, 3.5e-6, 0.69, 0.38}};
 struct ManyRowsTime {
   double t_k, alone, fixed, store, t_sums;
   int out_bytes;
@@ -218,7 +224,9 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool up, bool dual, bool b
     consider<WholeRoundsTime>(slim_shape((force - kSlim) / 16, (force - kSlim) % 16), p, room, best, best_t);
   } else if (M > kSlimRows || (force >= 0 && force < kSlim)) {
     for (const ManyShape& ts : kManyShapes)
-      if (force < 0 || force >= kSlim || ts.shape == force) consider<ManyRowsTime>(ts, p, room, best, best_t);
+      if ((force < 0 || force >= kSlim || ts.shape == force) && (up || !only_up(ts.shape)))
+        consider<ManyRowsTime>(ts, p, room, best, best_t);
+    if (best.bm == 0) consider<ManyRowsTime>(kManyShapes[0], p, room, best, best_t);  // a forced shape that is not for down projections
   } else {
     for (const FewShape& ts : kFewShapes) consider<WholeRoundsTime>(ts, p, room, best, best_t);
     if (force < 0 && params().gemm_splits == 0) {

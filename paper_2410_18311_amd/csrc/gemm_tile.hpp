@@ -9,7 +9,6 @@ namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -21,14 +20,6 @@ template <int V>
 struct Const {
   static constexpr int value = V;
 };
-
-template <class D>
-__device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c) {
-  if constexpr (D::VEC == 8 && __is_same(D, F16))
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 template <class D>
 __device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, f32x4 c) {
@@ -132,47 +123,6 @@ __device__ __forceinline__ void load_to_lds_at(int piece, uint32_t place, uint32
     asm volatile("buffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
                  :: "{m0}"(place), "v"(off), "s"(rsrc), "s"(scalar_off), "n"(piece * 1024)
                  : "memory");
-}
-
-// Epilogue of one wave: 32 rows at a time, accumulators (element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
-// column l % 32 of a 32x32 block) -> LDS -> rows, four columns per lane, so that a row's columns are whole
-// cache lines.  PITCH (words) is 8 modulo 16: the two half-waves of a store, four rows apart, then lie in
-// different halves of the banks.  acc: TI x TJ blocks; SwiGLU: the second half of the column blocks holds the
-// up values of the first half's columns.  part: 32 * PITCH floats of LDS of this wave's own; row0, col0: the
-// wave's first output row and column; sums: not null where raw sums are stored instead of outputs, by row and column of
-// the product `sums_ld` apart.
-template <class D, int EPI, int TI, int TJ>
-__device__ __forceinline__ void store_wave(const GemmArgs& g, const f32x16 (&acc)[TI][TJ], float* part, int row0, int col0,
-                                           float* sums, int sums_ld, int lane) {
-  using T = typename D::T;
-  constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  constexpr int PITCH = TJ * 32 + 8;
-  constexpr int CW = DUAL ? TJ * 16 : TJ * 32;  // output columns of this wave
-  constexpr int LPR = CW / 4;                   // lanes per row
-  const int l31 = lane & 31, hi = lane >> 5;
-  const int col = col0 + 4 * (lane % LPR);
-  float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (g.bias && !sums && col < g.Nn) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) bv[k] = to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]);
-  }
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) part[(8 * (v >> 2) + 4 * hi + (v & 3)) * PITCH + 32 * j + l31] = acc[i][j][v];
-#pragma unroll 4
-    for (int r = lane / LPR; r < 32; r += 64 / LPR) {
-      const int row = row0 + 32 * i + r;
-      const float4 c0 = *reinterpret_cast<const float4*>(part + r * PITCH + 4 * (lane % LPR));
-      const float4 c1 = DUAL ? *reinterpret_cast<const float4*>(part + r * PITCH + CW + 4 * (lane % LPR)) : c0;
-      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
-        if (sums) *reinterpret_cast<float4*>(sums + (ptrdiff_t)row * sums_ld + col) = c0;
-        else store_quad<D, EPI>(g, c0, c1, bv, (size_t)row * g.ldo + col);
-      }
-    }
-  }
 }
 
 // k-major B in LDS, rows of BN columns (of one k): chunk j of row k lies at j ^ this.  Transposing reads of 32 lanes cover eight rows
@@ -286,7 +236,7 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
 struct TileWork {
   int tm, tn;
   int k_begin, k_end;
-  float* sums;  // null, or where store_wave finds row 0, column 0 of the product for this workgroup's tile of sums
+  float* sums;  // null, or where store_blocks finds row 0, column 0 of the product for this workgroup's tile of sums
 };
 __device__ __forceinline__ TileWork tile_work(const GemmArgs& g, int bm, int bn) {
   const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.Nn + bn - 1) / bn;

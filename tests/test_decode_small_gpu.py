@@ -1,4 +1,4 @@
-"""The one-launch decode of small layers (every workgroup computes all hidden values): against the oracle, the same bits as
+"""The one-launch decode of small layers (every workgroup computes all hidden values, or a part of them that the others read): against the oracle, the same bits as
 the two launches in every form of the call, and which of the two a call takes."""
 import pytest
 import torch

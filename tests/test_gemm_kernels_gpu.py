@@ -96,9 +96,27 @@ def test_dense_wide_tiles(lib, tile, bn, act, layout, dtype):
         lib.dev_set_param("gemm_splits", 0)
 
 
+# The shapes for up projections, 192 x 128 and 128 x 96, 160 and 192 (7 .. 10; the down projection behind them falls back to 128 x 128):
+# the same edges
+@pytest.mark.parametrize("tile,bm,bn", [(7, 192, 128), (8, 128, 96), (9, 128, 160), (10, 128, 192)])
+@pytest.mark.parametrize("act,layout,dtype", [("relu", "out_major", torch.bfloat16), ("swiglu", "out_major", torch.float16),
+                                              ("relu", "neuron_major", torch.float16)])
+def test_dense_mid_tiles(lib, tile, bm, bn, act, layout, dtype):
+    cols = bn // 2 if act == "swiglu" else bn
+    try:
+        lib.dev_set_param("gemm_tile", tile)
+        for splits, M, d, N in [(1, 5, 64, 72), (1, bm, 72, cols), (1, bm + 1, 128, cols + 8), (1, bm - 62, 136, 2 * cols - 8),
+                                (2, 300, bn, 520), (3, bm + 1, bn + 8, 840), (1, 513, 448, 200)]:
+            lib.dev_set_param("gemm_splits", splits)
+            _check_dense(lib, dtype, act, layout, M, d, N, hidden=splits == 2)
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_splits", 0)
+
+
 # What lies behind the end of k in memory, the start of the next row (of a k-major B: nothing), is loaded and takes no part,
 # whatever it is; values that are not finite at the last k reach their own row or column
-@pytest.mark.parametrize("tile", [2, 4, 5, 6])
+@pytest.mark.parametrize("tile", [2, 4, 5, 6, 7, 8, 9, 10])
 @pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
 @pytest.mark.parametrize("splits", [1, 2])
 def test_dense_wide_tiles_beside_values_that_are_not_finite(lib, tile, layout, splits):
