@@ -15,8 +15,10 @@
 //     64; 11 + 7 bits for 16-bit inputs, which have no more) finds the value T of
 //     the k-th largest key, k being the share alpha of the positive keys -- their
 //     number is the total of the first digit's histogram.  That histogram is
-//     replicated four times by lane (eight where the keys are read again from memory) so that activations sharing an exponent do
-//     not serialise on one LDS address; both digits' histograms are cleared
+//     replicated eight times by lane so that activations sharing an exponent do
+//     not serialise on one LDS address (four take 1 to 2 % less where the keys are spread, 256 x 16384 fp16 18.3 -> 18.1 us, 1024 x
+//     13824 fp32 27.6 -> 27.1, and up to 30 % more where they are not: rows of one value, 512 x 36864 fp16 48.9 -> 63.8; of values
+//     between 1 and 1.12, 2000 x 11008 fp32 46.9 -> 54.4); both digits' histograms are cleared
 //     while the row is still on its way from memory.  The digit that holds the
 //     k-th key is found by prefix sums over threads (DPP shifts inside rows of 16
 //     lanes, scalar lane reads across rows and waves).  Keys > T are token-wise
@@ -31,8 +33,8 @@
 //     use (for_pairs).  By counter, 1024 x 13824 fp32: 11.6 -> 7.5 million vector and 6.0 -> 4.2 million scalar instructions,
 //     53.7 -> 41.0 thousand busy cycles of a compute unit for its four tokens; all launches 33.9 -> 28.4 us; 256 x 16384 fp16
 //     20.0 -> 18.7; 986 x 18112 bf16 75 -> 57.  A key is one addition to an activation's bits (kLift) instead of a test and a choice, and
-//     an atomic's address a shift and an addition: with four replicas for eight those take 29.1 -> 28.4, 18.8 -> 18.3, 2000 x 11008 fp32 41.0 ->
-//     39.2 and 8 x 512 x 36864 199 -> 193.5, whose time is barriers and LDS atomics rather than instructions.
+//     an atomic's address a shift and an addition: 1024 x 13824 fp32 28.2 -> 27.6, 256 x 16384 fp16 18.6 -> 18.3, 2000 x 11008 fp32
+//     40.4 -> 39.4 and 8 x 512 x 36864 199 -> 193, whose time is barriers and LDS atomics rather than instructions.
 //     Where the keys are in registers the workgroup also counts, for each of its
 //     neurons, the tokens of its own that have it in their core set (a byte per
 //     neuron, four to a register), and writes those bytes once at its end.
@@ -70,7 +72,7 @@ constexpr int kMaxWaves = 16;
 constexpr int kThreads = 1024;           // threads of the per-token and the one-workgroup Def. 2 kernels
 // second digit's histogram of the per-token kernel, next to the first one so that both are cleared
 // up front: fp32 keys use one replica of 2048 digits (few keys are left, spread over all digits),
-// 16-bit keys four or eight replicas of 128 digits
+// 16-bit keys eight replicas of 128 digits
 constexpr int kHist2Words = kBins + 8;
 constexpr int kCopyStride2 = 128 + 8;
 constexpr uint32_t kNoKey = 0xffffffffu;  // stands for an activation that is not positive
@@ -351,9 +353,6 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
   constexpr int kCand = 64;
   __shared__ uint32_t cand[kCand];
   __shared__ uint32_t cand_n;
-  // replicas of a histogram: with keys in registers four (eight take longer to clear and to add up than they save in conflicts:
-  // 256 x 16384 fp16 18.5 -> 18.3 us, 1024 x 13824 fp32 28.7 -> 28.4, 2000 x 11008 40.2 -> 39.2)
-  constexpr int kFirst = ITEMS > 0 ? 4 : kCopies;
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];  // [kHistWords + kHist2Words], cleared 16 bytes at a time
   uint32_t* hist2 = dyn;  // first: its place then fits the offset of an LDS instruction
   uint32_t* hist = dyn + kHist2Words;
@@ -378,8 +377,8 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
   for (int m = blockIdx.x; m < M; m += gridDim.x) {
     const TI* row = act + (size_t)m * ld;
     // the histograms of both digits are cleared while the row is on its way
-    clear_hist<kFirst, kCopyStride>(hist, 2048);
-    if (kNarrow) clear_hist<kFirst, kCopyStride2>(hist2, 128);
+    clear_hist<kCopies, kCopyStride>(hist, 2048);
+    if (kNarrow) clear_hist<kCopies, kCopyStride2>(hist2, 128);
     else clear_hist<1, kCopyStride>(hist2, 2048);
     if (tid == 0) cand_n = 0;
     uint32_t kc[ITEMS > 0 ? ITEMS : 1];
@@ -422,13 +421,13 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
     // them -- is taken from its total.
     uint32_t prefix = 0, prefix_mask = 0x80000000u, need = 0, n_eq = 0;
     if constexpr (ITEMS > 0) {
-      uint32_t* my_hist = hist + (tid & (kFirst - 1)) * kCopyStride;
+      uint32_t* my_hist = hist + (tid & (kCopies - 1)) * kCopyStride;
       for_pairs<ITEMS>(n_iter, [&](int i) {
         uint32_t* bin = &my_hist[shifted(kc[i], 20)];
         if ((int)kc[i] > (int)kLift) atomicAdd(bin, 1u);
       });
       __syncthreads();
-      need = find_digit<true, kFirst, kCopyStride>(hist, 2048, 0, q_alpha, &sh);
+      need = find_digit<true, kCopies, kCopyStride>(hist, 2048, 0, q_alpha, &sh);
       if (need != 0) {
         prefix = sh.bin << 20;
         prefix_mask = 0xfff00000u;
@@ -459,7 +458,7 @@ __global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void token_threshold_kernel(
       n_eq = sh.in_bin;
     };
     if constexpr (kNarrow) {
-      if constexpr (ITEMS > 0) second_pass(Const<kFirst>{}, Const<kCopyStride2>{}, 13, 128);
+      if constexpr (ITEMS > 0) second_pass(Const<kCopies>{}, Const<kCopyStride2>{}, 13, 128);
       else radix_pass<ITEMS, false, true, kCopies, kCopyStride2>(key_sel, n_iter, 13, 128, hist2, &sh, prefix, prefix_mask,
                                                                  need, n_eq);
       T = prefix;  // bits 13 .. 30 are all of the key
