@@ -22,6 +22,7 @@ OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "
                        "llvm-objdump")
 WAIT_STATES = 5
 TO_PRODUCT, FROM_PRODUCT = 2, 18
+BY_COMPILER = ("gemm_slim_kernel", "gemm_f32_")   # kernels whose products are builtins: the compiler keeps the hardware's own, shorter, states
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -67,10 +68,12 @@ def _vector_writes(op: str, args: list) -> set:
     return set()
 
 
-def _functions(text: str):
+def _functions(text: str, wanted=lambda name, body: True):
     """Name, instructions (mnemonic, operands, line) and, for each, those that can run right before it, of a listing's functions."""
     parts = re.split(r"^[0-9a-f]+ <([^>]+)>:\n", text, flags=re.M)
     for name, body in zip(parts[1::2], parts[2::2]):
+        if not wanted(name, body):
+            continue
         ins, where = [], {}
         for line in body.splitlines():
             m = re.match(r"\s+(\S+)\s*(.*?)\s*//\s*([0-9A-F]+):", line)
@@ -106,7 +109,7 @@ def _within(ins, before, i, limit, hit):
 def hazards_in(text: str) -> list:
     """Loads into LDS in an objdump listing that a vector instruction's scalar result, or m0, reaches too soon, on any path."""
     found = []
-    for _, ins, before in _functions(text):
+    for _, ins, before in _functions(text, lambda name, body: re.search(r"\blds\b", body)):
         for i, (op, args, line) in enumerate(ins):
             if not (op.startswith("buffer_load") and re.search(r"\blds\b", line)):
                 continue
@@ -121,13 +124,11 @@ def _lanes(operand: str) -> set:
     return {(m[1], r) for r in range(int(m[2]), int(m[m.lastindex]) + 1)} if m else set()
 
 
-def product_hazards_in(text: str, names: str = "") -> list:
-    """Matrix products in an objdump listing (functions whose name contains `names`) that read a vector instruction's result, or whose
-    own result another instruction reads or overwrites, too soon, on any path."""
+def product_hazards_in(text: str, but: tuple = ()) -> list:
+    """Matrix products in an objdump listing (functions whose name contains none of `but`) that read a vector instruction's result, or
+    whose own result another instruction reads or overwrites, too soon, on any path."""
     found = []
-    for name, ins, before in _functions(text):
-        if names not in name:
-            continue
+    for _, ins, before in _functions(text, lambda name, body: "v_mfma" in body and not any(family in name for family in but)):
         regs = [[_lanes(a) for a in args] for _, args, _ in ins]
         product = [op.startswith("v_mfma") for op, _, _ in ins]
         # a swap writes both its operands
@@ -143,10 +144,10 @@ def product_hazards_in(text: str, names: str = "") -> list:
 
 
 def hazards(path: str) -> list:
-    """Both kinds in a built library: loads in the kernels that have them, products in those that write them out."""
+    """Both kinds in a built library.  Products are looked at in every kernel but those that leave them to the compiler, so that no kernel
+    that comes to write them out can be forgotten."""
     out = []
     for code in code_objects(path):
-        if b"gemm_" in code:
-            text = listing(code)
-            out += hazards_in(text) + product_hazards_in(text, "gemm_wide")
+        text = listing(code)
+        out += hazards_in(text) + product_hazards_in(text, BY_COMPILER)
     return out

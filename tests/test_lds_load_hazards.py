@@ -95,6 +95,39 @@ def test_a_load_does_not_go_by_m0_at_once(lines, hazard):
     assert bool(isa_check.hazards_in(_listing(*lines))) == hazard
 
 
+@pytest.mark.parametrize("kernel,looked_at", [("gemm_wide_kernel", True), ("gemm_mid_kernel", True), ("some_kernel", True),
+                                              ("gemm_slim_kernel", False)])
+def test_the_build_looks_at_every_kernel_that_writes_out_its_products(monkeypatch, kernel, looked_at):
+    text = _listing(PRODUCT, "v_accvgpr_read_b32 v20, a6").replace("<kernel>", f"<_ZN2ci{len(kernel)}{kernel}Ev>")
+    monkeypatch.setattr(isa_check, "code_objects", lambda path: [kernel.encode()])
+    monkeypatch.setattr(isa_check, "listing", lambda code: text)
+    assert bool(isa_check.hazards("library")) == looked_at
+
+
+def test_products_that_are_left_to_the_compiler_are_builtins():
+    """The kernels that the build leaves out use no written-out product, and the others are there under the names that it goes by."""
+    csrc = {f: open(os.path.join(build.CSRC, f)).read() for f in os.listdir(build.CSRC) if f.endswith((".hip", ".hpp"))}
+    assert sorted(f for f, s in csrc.items() if "mfma16_in_place<" in s) == ["gemm_mid.hip", "gemm_wide.hip"]
+    names = set(re.findall(r"\b(gemm_\w+_kernel)\(", "".join(s for s in csrc.values() if "mfma" in s)))
+    assert {"gemm_mid_kernel", "gemm_wide_kernel"} <= names
+    out = {n for n in names if any(f in n for f in isa_check.BY_COMPILER)}
+    assert not out & {"gemm_mid_kernel", "gemm_wide_kernel"} and all(any(f in n for n in out) for f in isa_check.BY_COMPILER)
+
+
+def test_both_families_of_written_out_products_are_in_the_built_library(lib):
+    kernels, products = {}, {}
+    for code in isa_check.code_objects(build.LIB_PATH):
+        if b"gemm_" not in code:
+            continue
+        for name, ins, _ in isa_check._functions(isa_check.listing(code)):
+            m = re.search(r"gemm_(wide|mid)_kernel", name)
+            if m and not any(family in name for family in isa_check.BY_COMPILER):
+                kernels[m[1]] = kernels.get(m[1], 0) + 1
+                products[m[1]] = products.get(m[1], 0) + sum(op.startswith("v_mfma") for op, _, _ in ins)
+    # both types of B's four widths, k-major ones too; seven shapes and three of them k-major, some built twice
+    assert kernels["wide"] >= 16 and kernels["mid"] >= 20 and min(products.values()) > 1000
+
+
 def test_the_built_library_has_no_hazard(lib):
     listings = [isa_check.listing(c) for c in isa_check.code_objects(build.LIB_PATH) if b"gemm_" in c]
     loads = sum(1 for text in listings for l in text.splitlines() if "buffer_load" in l and re.search(r"\blds\b", l))
