@@ -13,8 +13,11 @@
 // A call gives the same bits whichever way it goes (launched or captured, apart or in place; finite weights): dot products are
 // added up over the lanes as there, down rows slice by slice, and the slices in the order of decode_reduce_kernel.  That costs
 // nothing measurable: 256 x 424 fp32 from a graph 6.91 us, and 6.89 with the rows spread over all threads.
+#include <sys/random.h>
+#include <time.h>
+#include <unistd.h>
+
 #include <atomic>
-#include <random>
 
 #include "common.hpp"
 #include "decode_common.hpp"
@@ -290,12 +293,17 @@ int launch_dtype(const SmallArgs& a, int B, int act, bool share, hipStream_t s) 
   return act == CI_ACT_SWIGLU ? launch_typed<D, true>(a, B, share, s) : launch_typed<D, false>(a, B, share, s);
 }
 
-// 64 bits that no other call of this process has, from a start that no other process has (memory keeps what was in it)
-uint64_t next_call() {
-  static std::atomic<uint64_t> calls{[] {
-    std::random_device r;
-    return (uint64_t)r() << 32 | r();
-  }()};
+// 64 bits that no other call of this process has, from a start that no other process has (memory keeps what was in it).  Nothing in
+// it throws; where the system has no random numbers ready, process and time take their place.
+uint64_t first_call() noexcept {
+  uint64_t v = 0;
+  if (getrandom(&v, sizeof(v), GRND_NONBLOCK) == (ssize_t)sizeof(v)) return v;
+  timespec t{};
+  clock_gettime(CLOCK_REALTIME, &t);
+  return ((uint64_t)getpid() << 32 ^ (uint64_t)t.tv_sec * 1000000000u ^ (uint64_t)t.tv_nsec) * 0x9e3779b97f4a7c15u;
+}
+uint64_t next_call() noexcept {
+  static std::atomic<uint64_t> calls{first_call()};
   return calls.fetch_add(1, std::memory_order_relaxed);
 }
 

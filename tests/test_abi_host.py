@@ -677,3 +677,14 @@ def test_per_token_call_of_the_binding_returns_the_status_of_the_c_call(lib):
         lib._binding.ffn_decode(good[0], 1 << 70, *good[2:])
     with pytest.raises(TypeError):
         lib.ffn_decode(w, None, "relu", y=w, ws=w)
+
+
+def test_nothing_in_the_library_throws(lib):
+    """No exception crosses the C boundary: the library neither throws nor allocates, and takes no part of the C++ runtime that does
+    (random_device throws where the system refuses it)."""
+    import subprocess
+    from paper_2410_18311_amd import build, isa_check
+    out = subprocess.run([isa_check.OBJDUMP, "-T", build.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    wanted = [line.split()[-1] for line in out.splitlines() if "*UND*" in line]
+    assert any(s.startswith("hip") for s in wanted), "no symbols were read"
+    assert not [s for s in wanted if s.startswith(("__cxa_throw", "__cxa_rethrow", "_Znw", "_Zna")) or "random_device" in s]
