@@ -109,6 +109,10 @@ _lib.coreinfer_dev_fused_plan.restype = _int
 _lib.coreinfer_dev_fused_plan.argtypes = [_i64, _i64, _int, _int, ctypes.POINTER(_int)]
 _lib.coreinfer_dev_decode_slices.restype = _int
 _lib.coreinfer_dev_decode_slices.argtypes = [_i64, _i64, _i64, _int, _int, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_decode_small.restype = _int
+_lib.coreinfer_dev_decode_small.argtypes = [_i64, _i64, _i64, _int, _int, _vp, ctypes.POINTER(_int)]
+_lib.coreinfer_dev_decode_small_gave_up.restype = _int
+_lib.coreinfer_dev_decode_small_gave_up.argtypes = [ctypes.POINTER(ctypes.c_uint32)]
 _lib.coreinfer_dev_dense_plan.restype = _int
 _lib.coreinfer_dev_dense_plan.argtypes = [_i64, _i64, _i64, _int, _int, _int, _i64, ctypes.POINTER(_i64)]
 _lib.coreinfer_dev_select_layout.restype = _int
@@ -185,6 +189,21 @@ def dev_decode_slices(B: int, K: int, d: int, dtype: torch.dtype, gathered: bool
     out = _int(0)
     _check(_lib.coreinfer_dev_decode_slices(B, K, d, DTYPE_CODE[dtype], int(bool(gathered)), ctypes.byref(out)),
            "coreinfer_dev_decode_slices")
+    return out.value
+
+
+def dev_decode_small(B: int, K: int, d: int, dtype: torch.dtype, act: str, stream=None) -> str:
+    """Which way ffn_decode takes on a stream (a handle; the null stream by default) for neuron-major compact weights."""
+    out = _int(0)
+    _check(_lib.coreinfer_dev_decode_small(B, K, d, DTYPE_CODE[dtype], ACT_CODE[act], stream, ctypes.byref(out)),
+           "coreinfer_dev_decode_small")
+    return ("two launches", "all", "shared")[out.value]
+
+
+def dev_decode_small_gave_up() -> int:
+    """Workgroups that computed shared hidden values after all, on the current device so far."""
+    out = ctypes.c_uint32(0)
+    _check(_lib.coreinfer_dev_decode_small_gave_up(ctypes.byref(out)), "coreinfer_dev_decode_small_gave_up")
     return out.value
 
 

@@ -88,6 +88,18 @@ int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int 
   return CI_OK;
 }
 
+int coreinfer_dev_decode_small(int64_t B, int64_t K, int64_t d, int dtype, int act, void* stream, int* way) {
+  if (!way || B < 1 || B > 65535 || K < 1 || K > CI_MAX_NEURONS || d < 1 || d > CI_MAX_DMODEL || !dtype_ok(dtype) ||
+      (act != CI_ACT_RELU && act != CI_ACT_SWIGLU))
+    return CI_ERR_INVALID_ARG;
+  *way = (int)decode_small_way(B, K, d, dtype, act, decode_splits(B, K, d * elem_bytes(dtype), false), (hipStream_t)stream);
+  return CI_OK;
+}
+
+int coreinfer_dev_decode_small_gave_up(uint32_t* workgroups) {
+  return workgroups ? decode_small_gave_up(workgroups) : CI_ERR_INVALID_ARG;
+}
+
 int coreinfer_dev_select_layout(int64_t B, int64_t M, int64_t N, int64_t* out) {
   size_t need = 0;
   if (!out || coreinfer_select_batch_workspace_size(B, M, N, &need) != CI_OK) return CI_ERR_INVALID_ARG;

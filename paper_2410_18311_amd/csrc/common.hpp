@@ -227,6 +227,7 @@ enum class DecodeSmall { kNo, kAll, kShare };  // every workgroup computes all h
 DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s);
 int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg, bool share,
                             hipStream_t s);
+int decode_small_gave_up(uint32_t* out);  // on this device so far; waits for its work
 int launch_decode_reduce(const float* partial, const void* b_down, void* y, int n_wg, int d, int B,
                          int dtype, hipStream_t s);
 size_t fused_decode_ws_bytes(int64_t K);

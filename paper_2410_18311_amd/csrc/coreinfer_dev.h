@@ -14,7 +14,7 @@
  *   never, 1 by the rule, 2 wherever it can, 3 wherever it can with shared hidden
  *   values unless the stream is captured): small layers in one launch;
  *   "decode_small_patience" (0 .. 100000 ticks of 10 ns that a workgroup waits for
- *   shared values before it computes them itself);
+ *   shared values before it computes them itself; 0: without a look at them);
  *   "fused_depth" (4, 8), "fused_threads" (0 or a multiple of 64 up to 896),
  *   "fused_chunks" (least number of neuron chunks, 2..64),
  *   "fused_chunk_size" (0 = cost model, else neurons per chunk, a multiple of the
@@ -71,6 +71,15 @@ int coreinfer_dev_fused_plan(int64_t K, int64_t d, int dtype, int act, int* out)
 /* Neuron slices per sentence of the two-launch decode under the current
  * settings: *slices (host). */
 int coreinfer_dev_decode_slices(int64_t B, int64_t K, int64_t d, int dtype, int gathered, int* slices);
+
+/* Which way coreinfer_ffn_decode takes on this stream for neuron-major compact
+ * weights, x and y apart: *way (host) = 0 two launches, 1 one launch whose
+ * workgroups compute all hidden values each, 2 one whose workgroups share them. */
+int coreinfer_dev_decode_small(int64_t B, int64_t K, int64_t d, int dtype, int act, void* stream, int* way);
+/* Workgroups of such shared launches on the current device so far that did not
+ * get the others' values in time and computed them: *workgroups (host).  Waits
+ * for the device. */
+int coreinfer_dev_decode_small_gave_up(uint32_t* workgroups);
 
 /* The plans of coreinfer_ffn_dense for more than four tokens of a 16-bit type
  * under the current settings, the down projection's with room for `room` bytes

@@ -40,7 +40,7 @@ struct SmallArgs {
   int most_rows;      // at least the rows of any slice
   uint32_t tag[2];    // shared hidden values: of this call and no other
   int slot;           // and the first of its rows of g_hidden
-  int patience;       // ticks of 10 ns that a workgroup waits for the others before it computes their values itself
+  int patience;       // ticks of 10 ns that a workgroup waits for the others before it computes their values itself; 0: does not look for them
 };
 
 constexpr int kSmallThreads = 512, kSmallWaves = 8;
@@ -56,6 +56,7 @@ constexpr int kSmallSlices = 8 * kReduceGroups;  // most slices of the neurons, 
 // (every sixteenth) can at most take each other's values away.
 constexpr int kSmallCalls = 16, kSmallTokens = 4;
 static __device__ unsigned long long g_hidden[kSmallCalls * kSmallTokens][kSmallMaxK][2];
+static __device__ unsigned int g_gave_up;  // workgroups so far that computed all hidden values after all
 
 // The value L lanes further on in the same sixteen (past them: zero).
 template <int L>
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallAr
     const int lo = (int)((uint32_t)a.K * blockIdx.x / gridDim.x), hi = (int)((uint32_t)a.K * (blockIdx.x + 1) / gridDim.x);
     unsigned long long(*words)[2] = g_hidden[a.slot + b];
     const unsigned long long t0 = (unsigned long long)a.tag[0] << 32, t1 = (unsigned long long)a.tag[1] << 32;
-    if (tid == 0) late = 0;
+    if (tid == 0) late = a.patience == 0 && hi - lo < a.K;
     hidden(lo, hi, [&](int k, float v) {
       h[k] = v;
       __hip_atomic_store(&words[k][0], t0 | f2u(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallAr
     __syncthreads();
     const long long start = __builtin_amdgcn_s_memrealtime();
     constexpr int kAtOnce = 4;
-    for (int k0 = tid; k0 < a.K; k0 += kAtOnce * kSmallThreads) {
+    for (int k0 = a.patience == 0 ? a.K : tid; k0 < a.K; k0 += kAtOnce * kSmallThreads) {
       uint32_t wanted = 0;
 #pragma unroll
       for (int i = 0; i < kAtOnce; ++i) {
@@ -197,7 +198,10 @@ __global__ __launch_bounds__(kSmallThreads) void ffn_decode_small_kernel(SmallAr
       if (wanted) break;
     }
     __syncthreads();
-    if (late) hidden(0, a.K, keep);
+    if (late) {
+      if (tid == 0) atomicAdd(&g_gave_up, 1u);
+      hidden(0, a.K, keep);
+    }
   } else {
     hidden(0, a.K, keep);
   }
@@ -340,6 +344,10 @@ DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act
   if (s && !(hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)) return DecodeSmall::kNo;
   const int64_t lanes = vecs <= 16 ? 16 : vecs <= 32 ? 32 : 64, rows = kSmallRows * kSmallWaves * (64 / lanes);
   return mode == 3 || (K + rows - 1) / rows >= kSmallBatchesShare ? DecodeSmall::kShare : DecodeSmall::kAll;
+}
+
+int decode_small_gave_up(uint32_t* out) {
+  return hipMemcpyFromSymbol(out, HIP_SYMBOL(g_gave_up), sizeof(*out)) == hipSuccess ? CI_OK : CI_ERR_HIP;
 }
 
 int launch_ffn_decode_small(const void* x, int64_t B, const ci_ffn_weights* w, int dtype, int act, void* y, int n_wg, bool share,

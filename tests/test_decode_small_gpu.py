@@ -127,12 +127,13 @@ def test_small_decode_in_place(lib, shift):
 
 
 # Hidden values shared by the workgroups: the bits of two launches, for fewer and more neurons than workgroups and than a thread takes at
-# once, one to four tokens; and again with no time to wait for any, when every workgroup computes what it misses itself
+# once, one to four tokens; and again without a look at the others' values, when every workgroup computes what it misses itself
 @pytest.mark.parametrize("patience", [2000, 0])
 @pytest.mark.parametrize("act", ["relu", "swiglu"])
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 def test_small_decode_shared(lib, act, dt, patience):
     vec = 4 if dt == torch.float32 else 8
+    calls, alone, gave_up = 20, 0, lib.dev_decode_small_gave_up()   # more calls than rows of words
     lib.dev_set_param("decode_small_patience", patience)
     try:
         for vecs in (1, 16, 33, 64, 128):
@@ -145,15 +146,52 @@ def test_small_decode_shared(lib, act, dt, patience):
                 lib.dev_set_param("decode_small", 0)
                 two = lib.ffn_decode(x, desc, act)
                 lib.dev_set_param("decode_small", 3)
+                assert lib.dev_decode_small(B, K, d, dt, act) == "shared"
                 y = torch.full((B * d + 64,), -7.0, dtype=dt, device=DEV)
-                for _ in range(20):   # more calls than rows of words
+                ws = torch.full((lib.ffn_decode_workspace_size(B, K, d),), 255, dtype=torch.uint8, device=DEV)
+                for _ in range(calls):
                     y[:B * d] = 0
-                    lib.ffn_decode(x, desc, act, y=y[:B * d].view(B, d))
+                    lib.ffn_decode(x, desc, act, y=y[:B * d].view(B, d), ws=ws)
                     assert torch.equal(y[:B * d].view(B, d).nan_to_num(nan=3.0), two.nan_to_num(nan=3.0)), (d, K, B)
                 assert bool((y[B * d:] == -7.0).all()), "stored past the end"
+                assert bool((ws == 255).all()), "two launches"
+                n = -(-vecs // 4)   # workgroups of a token, each of an equal part of the neurons
+                alone += calls * B * sum(K * (i + 1) // n - K * i // n < K for i in range(n))
     finally:
         lib.dev_set_param("decode_small", 1)
         lib.dev_set_param("decode_small_patience", 2000)
+    gave_up = lib.dev_decode_small_gave_up() - gave_up
+    assert gave_up == alone if patience == 0 else gave_up < alone // 2, (gave_up, alone)
+
+
+# Which way a call takes, with the setting that every program has: both sides of the lines for elements (64 K and 128 K) and for batches of
+# rows (four), and of a captured stream, whose calls are two launches wherever their values would be shared
+@pytest.mark.parametrize("act,dt,d,K,B,way", [("relu", torch.float32, 256, 256, 1, "all"), ("relu", torch.float32, 256, 257, 1, "shared"),
+                                              ("relu", torch.float32, 512, 192, 4, "all"), ("relu", torch.float32, 512, 193, 4, "shared"),
+                                              ("relu", torch.float32, 256, 512, 1, "shared"), ("relu", torch.float32, 256, 513, 1, "two launches"),
+                                              ("swiglu", torch.float32, 256, 192, 1, "all"), ("swiglu", torch.float32, 256, 193, 1, "shared"),
+                                              ("relu", torch.float16, 512, 192, 1, "all"), ("relu", torch.bfloat16, 512, 193, 1, "shared"),
+                                              ("relu", torch.float32, 512, 225, 5, "two launches")])
+def test_small_decode_ways(lib, act, dt, d, K, B, way):
+    assert lib.dev_decode_small(B, K, d, dt, act) == way
+    w = _layer(dt, act, d, K, d + K)
+    desc = lib.make_weights(w["up"], w["gate"], w["b_up"], w["down"], w["b_down"])
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(1)).to(dt).to(DEV)
+    got, took_one = _one_launch(lib, x, desc, act)
+    assert took_one == (way != "two launches")
+    assert_close_rms(got, _reference(w, act, x), dt, "y")
+    y, ws = torch.empty_like(x), lib.decode_workspace(B, K, d, DEV)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        captured = lib.dev_decode_small(B, K, d, dt, act, torch.cuda.current_stream().cuda_stream)
+        lib.ffn_decode(x, desc, act, y=y, ws=ws)
+    elements = (2 if act == "swiglu" else 1) * K * d
+    assert captured == ("all" if way == "all" and elements <= 65536 else "two launches")
+    for _ in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, got)
 
 
 # Calls of several threads, each on a stream of its own, take the same rows of words in turn
@@ -167,6 +205,7 @@ def test_small_decode_shared_by_threads(lib):
     want = torch.cat([lib.ffn_decode(xs[i:i + 1], desc, "relu") for i in range(6)])
     lib.dev_set_param("decode_small", 1)
     torch.cuda.synchronize()
+    assert lib.dev_decode_small(1, K, d, torch.float32, "relu") == "shared"
     wrong = [None] * 6
 
     def run(i):
@@ -174,6 +213,7 @@ def test_small_decode_shared_by_threads(lib):
         with torch.cuda.stream(s):
             ws, y, n = lib.decode_workspace(1, K, d, DEV), torch.empty(1, d, device=DEV), torch.zeros((), dtype=torch.int64, device=DEV)
             for _ in range(200):
+                assert lib.dev_decode_small(1, K, d, torch.float32, "relu", s.cuda_stream) == "shared"
                 lib.ffn_decode(xs[i:i + 1], desc, "relu", y=y, ws=ws)
                 n += (y != want[i:i + 1]).sum()
             s.synchronize()
