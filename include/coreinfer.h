@@ -15,7 +15,10 @@
  *   - Every tensor pointer is a DEVICE pointer owned by the caller.  The
  *     library allocates and frees nothing; scratch memory is the caller's
  *     workspace, sized by the matching *_workspace_size query (a pure host
- *     function that needs no GPU).  Inputs are never modified.
+ *     function that needs no GPU).  Two exceptions are static device memory
+ *     that the library holds on every GPU it runs on until the process ends:
+ *     the array of coreinfer_ffn_decode_static, and 4 MiB for the decode of
+ *     small layers (see coreinfer_ffn_decode).  Inputs are never modified.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All work is enqueued on it; no call synchronises the device, so outputs
  *     are valid only after the caller synchronises the stream.
@@ -321,7 +324,15 @@ typedef struct {
  * Two kernel paths, chosen by the layout of the compact down matrix:
  *   CI_DOWN_NEURON_MAJOR (and every gathered call): neuron slices produce fp32
  *     partial outputs in ws, a second launch sums them in a fixed order.  ws
- *     needs no initialisation.  A gathered call of up to
+ *     needs no initialisation.  Compacted layers of up to 128 K elements in
+ *     w_up (and w_gate) and up to four sentences run in one launch instead and
+ *     leave ws as it is (a rule on sizes and types; not where y lies over x);
+ *     the outputs are the same to the bit.  From 64 K elements on, unless the
+ *     stream is being captured, its workgroups may hand the hidden values to
+ *     each other through 4 MiB of static device memory.  Calls from any number
+ *     of threads and streams may use it at the same time: a value carries the
+ *     tag of its call, and a workgroup whose values are overwritten, or do not
+ *     come within 20 us, computes them itself.  A gathered call of up to
  *     CI_MAX_UNION_SENTENCES large, overlapping lists reads each row of their
  *     union once, as coreinfer_ffn_decode_union does (a rule on B, K, N, d and
  *     the types; a neuron that a list names r times still counts r times).

@@ -1,15 +1,20 @@
-// Decode-stage FFN of small layers in one launch without an exchange between workgroups (neuron-major compact weights):
+// Decode-stage FFN of small layers in one launch (neuron-major compact weights):
 //   y = W_down_c^T act(W_up_c x [+ b]) [+ b_down]
 // The two launches of ffn_decode.hip cost the host about 3.9 us each, more than the GPU needs for both where the weights
-// are a few hundred kilobytes.  So every workgroup here computes ALL hidden values, from weights that lie in its L2, keeps
-// them in LDS and sums its own columns of y over all neurons: no partial sums, no second launch, nothing to agree on.
+// are a few hundred kilobytes.  So every workgroup here has ALL hidden values in LDS and sums its own columns of y over all neurons: no
+// partial sums and no second launch.  It computes them itself, from weights that lie in its L2, or a part of them, and takes the others' from
+// memory (SHARE, below).
 // What bounds it is the fill of a compute unit's L1 with the up (and gate) rows: by the slope of its time over their size 124 GB/s
 // in fp32 and 85 in 16 bits, with twice the products a byte (256 x 96 to 256 x 512).  The down rows of the workgroup's columns
 // are requested ahead of them and wait in registers.
 // Where that fill takes longer than to hand a value on (SHARE), a workgroup computes its part of the hidden values only and stores each
 // as words that say themselves that they are this call's; the others read them until they are (about 1.5 us).  Nothing depends on the
 // others being there: a workgroup whose values have not come in 20 us computes them itself.  256 x 410 fp32, call by call, 6.95 ->
-// 5.39 us, 256 x 512 7.6 -> 5.4, 4 tokens of 256 x 448 7.2 -> 5.8, fp16 512 x 256 6.7 -> 5.8.
+// 5.39 us, 256 x 512 7.6 -> 5.4, 4 tokens of 256 x 448 7.2 -> 5.8, fp16 512 x 256 6.7 -> 5.8.  The words are the library's own and shared by
+// all streams, which costs little: 256 x 410 on two and three streams at once, enqueued so that calls take the same words, 5.0 to 5.2 us a
+// call where one stream alone takes 4.8 and every workgroup computing all 7.3 to 14; beside dense FFNs of 2048 x 5120 x 13824, whose
+// workgroups leave no room, 19 us where that takes 21 and two launches 20, and the dense FFNs the same 790 us; a wait of 4 us
+// for 20 makes no difference there.
 // A call gives the same bits whichever way it goes (launched or captured, apart or in place; finite weights): dot products are
 // added up over the lanes as there, down rows slice by slice, and the slices in the order of decode_reduce_kernel.  That costs
 // nothing measurable: 256 x 424 fp32 from a graph 6.91 us, and 6.89 with the rows spread over all threads.
