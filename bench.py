@@ -533,7 +533,7 @@ def main():
     import torch
 
     from paper_2410_18311_amd import build as _build
-    if not (os.path.exists(_build.LIB_PATH) and os.path.exists(_build.BINDING_PATH)):
+    if not os.path.exists(_build.LIB_PATH):
         _build.build_library()
     from paper_2410_18311_amd import workloads as wl
 

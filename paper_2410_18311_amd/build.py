@@ -17,7 +17,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libcoreinfer.so")
-BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")   # a Python module, linked against the library beside it
+# a Python module for this interpreter, linked against the library beside it
+BINDING_PATH = os.path.join(PKG_DIR, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["api.hip", "ffn_decode.hip", "ffn_decode_small.hip", "ffn_decode_fused.hip", "ffn_union.hip", "select.hip", "compact.hip", "centroid.hip", "gemv.hip", "gemm_mfma.hip", "gemm_f32.hip", "gemm_wide.hip", "gemm_mid.hip", "gemm_slim_f16.hip", "gemm_slim_bf16.hip", "stream_probe.hip"]
 
@@ -44,6 +45,23 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_binding() -> bool:
+    """The per-token call's C module.  Where there is no C compiler or no Python.h the library serves without it, through ctypes."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+           os.path.join(CSRC, "binding.c"), "-o", BINDING_PATH, "-L", PKG_DIR, "-lcoreinfer", "-Wl,-rpath,$ORIGIN"]
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        why = r.stderr if r.returncode != 0 else None
+    except OSError as e:
+        why = str(e)
+    if why is None:
+        return True
+    if os.path.exists(BINDING_PATH):
+        os.remove(BINDING_PATH)   # of another library
+    sys.stderr.write("no C module for the per-token call, which goes through ctypes instead (about 1 us more):\n" + why + "\n")
+    return False
+
+
 def build_library(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
@@ -57,11 +75,7 @@ def build_library(verbose: bool = False) -> str:
         os.remove(LIB_PATH)
         raise RuntimeError("loads into LDS or matrix products that read a register too soon after it was written, or a product's result read too soon:\n" +
                            "\n".join(bad))
-    cmd = [os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
-           os.path.join(CSRC, "binding.c"), "-o", BINDING_PATH, "-L", PKG_DIR, "-lcoreinfer", "-Wl,-rpath,$ORIGIN"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("binding failed:\n" + r.stderr)
+    build_binding()
     if verbose:
         print("built", LIB_PATH)
     return LIB_PATH

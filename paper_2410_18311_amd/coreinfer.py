@@ -1,4 +1,4 @@
-"""Binding over libcoreinfer.so -- argument marshalling only: ctypes, and for the per-token call csrc/binding.c.
+"""Binding over libcoreinfer.so -- argument marshalling only: ctypes, and for the per-token call csrc/binding.c where it is built.
 
 Function names mirror the C ABI (include/coreinfer.h).  Tensors are torch
 tensors on the GPU; torch supplies device memory and the current stream,
@@ -33,14 +33,12 @@ DTYPE_CODE = {torch.float32: CI_F32, torch.float16: CI_F16, torch.bfloat16: CI_B
 ACT_CODE = {"relu": CI_ACT_RELU, "swiglu": CI_ACT_SWIGLU}
 LAYOUT_CODE = {"out_major": CI_DOWN_OUT_MAJOR, "neuron_major": CI_DOWN_NEURON_MAJOR}
 
-if not (os.path.exists(LIB_PATH) and os.path.exists(BINDING_PATH)):
+if not os.path.exists(LIB_PATH):
     raise ImportError(
-        f"{LIB_PATH} or {BINDING_PATH} is not built; run `python -m paper_2410_18311_amd.build` "
+        f"{LIB_PATH} is not built; run `python -m paper_2410_18311_amd.build` "
         "(there is no CPU or PyTorch fallback for the CoreInfer kernels)")
 
 _lib = ctypes.CDLL(LIB_PATH)
-
-from . import _binding  # noqa: E402  (linked against the library that is now loaded)
 
 _vp, _i64, _int, _dbl, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_double, ctypes.c_size_t
 
@@ -96,6 +94,15 @@ for _name, (_res, _args) in _SIGNATURES.items():
     _f.restype, _f.argtypes = _res, _args
 
 EXPORTS = tuple(_SIGNATURES)
+
+# the per-token call, with addresses as integers: the C module if it was built for this interpreter, or the same through ctypes
+if os.path.exists(BINDING_PATH):
+    from . import _binding  # linked against the library that is now loaded
+    _decode_call = _binding.ffn_decode
+else:
+    _binding = None
+    _decode_call = ctypes.CFUNCTYPE(_int, _vp, _i64, _vp, _int, _int, _vp, _vp, _sz, _vp)(("coreinfer_ffn_decode", _lib))
+
 raw = _lib  # the bare C entry points, for tests of the error paths
 
 # development hook (csrc/coreinfer_dev.h): launch-shape parameters for sweeps, not part of the interface
@@ -516,8 +523,8 @@ def ffn_decode(x: torch.Tensor, weights: ci_ffn_weights, act: str, y: Optional[t
         ws = decode_workspace(B, weights.K, d, x.device)
     if not isinstance(weights, ci_ffn_weights):
         raise TypeError("weights: a descriptor of make_weights")
-    status = _binding.ffn_decode(x2.data_ptr(), B, ctypes.addressof(weights), DTYPE_CODE[x.dtype], ACT_CODE[act],
-                                 y.data_ptr(), ws.data_ptr(), ws.numel(), _stream(x))
+    status = _decode_call(x2.data_ptr(), B, ctypes.addressof(weights), DTYPE_CODE[x.dtype], ACT_CODE[act], y.data_ptr(),
+                          ws.data_ptr(), ws.numel(), _stream(x))
     if status != CI_OK:
         raise CoreInferError(status, "coreinfer_ffn_decode")
     return y if x2 is x else y.squeeze(0)

@@ -16,7 +16,7 @@ def pytest_configure(config):
 def lib():
     """The ctypes binding over the C-ABI library (built in-tree if absent)."""
     from paper_2410_18311_amd import build as _build
-    if not (os.path.exists(_build.LIB_PATH) and os.path.exists(_build.BINDING_PATH)):
+    if not os.path.exists(_build.LIB_PATH):
         _build.build_library()
     from paper_2410_18311_amd import coreinfer
     return coreinfer

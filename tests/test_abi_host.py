@@ -688,3 +688,32 @@ def test_nothing_in_the_library_throws(lib):
     wanted = [line.split()[-1] for line in out.splitlines() if "*UND*" in line]
     assert any(s.startswith("hip") for s in wanted), "no symbols were read"
     assert not [s for s in wanted if s.startswith(("__cxa_throw", "__cxa_rethrow", "_Znw", "_Zna")) or "random_device" in s]
+
+
+def test_per_token_call_without_the_c_module(lib, monkeypatch, tmp_path):
+    """The C module is for one interpreter and is left out where it cannot be compiled: the package then builds and imports as before,
+    and the per-token call gives the same statuses through ctypes."""
+    import importlib.util
+    import sysconfig
+    import torch
+    from paper_2410_18311_amd import build
+    assert build.BINDING_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    built = tmp_path / "_binding.so"
+    built.write_bytes(b"of another library")
+    monkeypatch.setattr(build, "BINDING_PATH", str(built))
+    monkeypatch.setenv("CC", str(tmp_path / "no compiler"))
+    assert build.build_binding() is False and not built.exists()
+    spec = importlib.util.spec_from_file_location("paper_2410_18311_amd.coreinfer_without", lib.__file__)
+    without = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(without)
+    assert without._binding is None
+    w = torch.zeros(4, 8)
+    for args, kw in (((w, without.make_weights(w, None, None, w, None), "relu"), dict(y=w, ws=w)),
+                     ((w, without.make_weights(w, None, None, None, None), "relu"), dict(y=w, ws=w.to(torch.uint8)))):
+        mine = without.ci_ffn_weights.from_buffer_copy(args[1])
+        theirs = lib.ci_ffn_weights.from_buffer_copy(args[1])
+        with pytest.raises(without.CoreInferError) as a:
+            without.ffn_decode(args[0], mine, args[2], **kw)
+        with pytest.raises(lib.CoreInferError) as b:
+            lib.ffn_decode(args[0], theirs, args[2], **kw)
+        assert a.value.status == b.value.status != lib.CI_OK
