@@ -152,7 +152,8 @@ struct WholeRoundsTime {
 // round reads from memory (a maximum, or a power mean of any higher order, fits worse).  It is a fit, not a model of the chip: the
 // constants of kFewShapes are those that come closest to 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to
 // 36864, odd lengths among them, all shapes and splits.  (For tiles of 256 x 256 a fill that costs nothing came closest, with
-// fewer flop/s.)
+// fewer flop/s.  Only down projections of layers much wider than their N take those: none of 600000 drawn plans with N of 2.6 to 4 d, three
+// of 600000 of any proportions, e.g. 128 x 21752 x 4744.)
 struct FewRowsTime {
   int tiles_m, out_bytes;
   double k, fill, columns_fill, inv_tiles_m, fixed, store, t_sums;
@@ -256,7 +257,7 @@ GemmPlan plan_gemm(int64_t M, int64_t Nn, int64_t Kk, bool up, bool dual, bool b
 // 104.7 -> 102.8, but 145 x 2816 x 9728 gated 71 -> 77.6.
 bool read_once(const GemmPlan& p, int64_t M, int64_t Nn, int64_t Kk, bool dual, bool b_kmajor, bool gated) {
   const int mode = params().gemm_once;
-  if (mode == 0 || b_kmajor || is_wide(p.shape)) return false;
+  if (mode == 0 || b_kmajor || is_wide(p.shape) || only_up(p.shape)) return false;
   const int64_t one = Nn * Kk * 2;  // bytes of a matrix of the layer
   return mode == 2 || (M <= 128 && (dual ? 2 : 1) * one >= 80000000 && Kk % 64 == 0 &&
                        (M <= 32 || (gated ? 3 : 2) * one > (int64_t)256 << 20));

@@ -221,10 +221,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   store_blocks<D, TI, TJ>(g, epi, dual, acc, m0 + wm * TI * 16, n0, wn, w.sums, bno, lane);
 }
 
-template <class D, bool BNN, int TI, int TJ>
+// ONCE: with a build for weights that are not read again
+template <class D, bool BNN, int TI, int TJ, bool ONCE = !BNN>
 int launch_shape(int epi, const GemmArgs& g, hipStream_t s) {
   const dim3 grid((unsigned)(g.full + g.tail * g.splits));
-  if (!BNN && g.once) hipLaunchKernelGGL((gemm_mid_kernel<D, BNN, TI, TJ, !BNN>), grid, dim3(256), 0, s, g, epi);
+  if (ONCE && g.once) hipLaunchKernelGGL((gemm_mid_kernel<D, BNN, TI, TJ, ONCE>), grid, dim3(256), 0, s, g, epi);
   else hipLaunchKernelGGL((gemm_mid_kernel<D, BNN, TI, TJ, false>), grid, dim3(256), 0, s, g, epi);
   CI_HIP_CHECK_LAUNCH();
   return CI_OK;
@@ -238,11 +239,11 @@ int launch_typed(int shape, int epi, const GemmArgs& g, hipStream_t s) {
     case kMid128x64: return launch_shape<D, BNN, 4, 2>(epi, g, s);
   }
   if constexpr (!BNN) {
-    switch (shape) {
-      case kMid192x128: return launch_shape<D, BNN, 6, 4>(epi, g, s);
-      case kMid128x96: return launch_shape<D, BNN, 4, 3>(epi, g, s);
-      case kMid128x160: return launch_shape<D, BNN, 4, 5>(epi, g, s);
-      case kMid128x192: return launch_shape<D, BNN, 4, 6>(epi, g, s);
+    switch (shape) {  // of more than 128 rows only, which read_once() leaves out
+      case kMid192x128: return launch_shape<D, BNN, 6, 4, false>(epi, g, s);
+      case kMid128x96: return launch_shape<D, BNN, 4, 3, false>(epi, g, s);
+      case kMid128x160: return launch_shape<D, BNN, 4, 5, false>(epi, g, s);
+      case kMid128x192: return launch_shape<D, BNN, 4, 6, false>(epi, g, s);
     }
   }
   return CI_ERR_UNSUPPORTED;

@@ -164,6 +164,21 @@ def test_dense_plan_reads_large_weights_once(lib):
         assert (plan["up_once"], plan["down_once"]) == (up, down), (M, d, N, act, layout, plan)
 
 
+def test_shapes_of_more_than_128_rows_have_no_read_once_loads(lib):
+    """Tiles of 256 rows, and those for up projections of more than 128 rows, are never planned where the rule takes such loads, and are
+    built without them: no setting asks for them."""
+    import torch
+    lib.dev_set_param("gemm_once", 2)
+    try:
+        for tile in range(11):
+            lib.dev_set_param("gemm_tile", tile)
+            plan = lib.dev_dense_plan(256, 4096, 16384, torch.float16, "relu", "out_major")
+            assert plan["up"] == tile and plan["up_once"] == (tile in (0, 1, 3)), tile
+    finally:
+        lib.dev_set_param("gemm_tile", -1)
+        lib.dev_set_param("gemm_once", 1)
+
+
 def test_hidden_call_makes_no_plans_to_check_its_arguments(lib):
     """A call that is refused for want of a workspace has cost what the same refusal of coreinfer_ffn_dense does, far less
     than the size query, which plans both layouts (fastest of many rounds of each)."""
