@@ -54,8 +54,8 @@ __device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n, int* tm
 }
 
 // Tile shapes for 16-bit types, rows of A x rows of B per workgroup: 128 x 64 .. 256 and 192 x 128 (gemm_mid.hip), 256 x 160 .. 256
-// (gemm_wide.hip).  The last four are for up projections, whose k is not split: a down projection's splits fill the chip as well (their
-// best plans of the other shapes are 1.3 % behind the best of all shapes, those of up projections 5.2 %).
+// (gemm_wide.hip).  The last four are for up projections, whose k is not split: a down projection's splits fill the chip as well.  (Without
+// them the best of the other shapes is on average 5.2 % behind the best of all for an up projection, and 1.3 % for a down projection.)
 enum { kMid128x128 = 0, kMid128x256 = 1, kWide192 = 2, kMid128x64 = 3, kWide = 4, kWide224 = 5, kWide160 = 6, kMid192x128 = 7,
        kMid128x96 = 8, kMid128x160 = 9, kMid128x192 = 10, kShapes };
 constexpr bool only_up(int shape) { return shape >= kMid192x128 && shape < kShapes; }

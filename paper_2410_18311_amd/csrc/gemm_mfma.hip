@@ -73,13 +73,13 @@ struct Product {
 
 // More than 128 rows.  A round of n tiles takes their multiplications, faster the fewer run side by side (they share the chip's
 // power and caches), a fixed part (first loads, results) and the stores; the sums of split tiles are written, read back
-// and added by another launch.  The constants are those that come closest to 4900 measured products of 129 to 4096 rows, d
-// 1024 to 9216 and N 2048 to 36864, odd lengths among them, all shapes and splits (7.6 % off on average).  Of 271 pairs of products the plans by
-// it are on average 0.2 % (up) and 2.2 % (down) behind the fastest of all; those by the former estimate of whole rounds were 1.0 and 5.3 %.
-// The last four shapes came later, with 394 more up projections of 129 to 1536 rows, layers in turn; their constants are 2 % on the slow
-// side, so that they are taken where they promise that much.  24 % of 5800 other up projections of 129 to 2048 rows take them: layers in
-// turn 13 % faster on average, one in a hundred by more than 3 % slower (small ones, 17 % at most), one layer again and again 12 %
-// and 6 % at most.
+// and added by another launch.  The constants are those that came closest to 4900 measured products of 129 to 4096 rows, d
+// 1024 to 9216 and N 2048 to 36864, odd lengths among them, all shapes and splits (7.6 % off on average), the last four shapes' to 394 more
+// up projections.  The tiles of 128 rows were measured with an earlier kernel, 4 to 8 % slower than gemm_mid.hip's.  That costs
+// little: over 222 other products of 129 to 2048 rows on the present kernels, layers in turn, the up plans are on average 0.9 % behind the fastest
+// of all shapes and the down plans 0.9 % behind the fastest of all shapes and splits (one in ten by more than 2 and 3.5 %, at most by 21 and 17 %),
+// both projections together 1.4 %.  A quarter of the up plans take one of the last four, and 15 % less time than the fastest other shape,
+// one of 55 more than it (3.4 %).
 struct ManyShape {
   int shape;
   int bm, bn;        // rows of A, rows of B (SwiGLU: half of them gate, half up)
@@ -151,7 +151,9 @@ struct WholeRoundsTime {
 // The second is a sum rather than a maximum of three parts: what an L1 is filled with, the multiplications, and the weights that a
 // round reads from memory (a maximum, or a power mean of any higher order, fits worse).  It is a fit, not a model of the chip: the
 // constants of kFewShapes are those that come closest to 26000 measured products of 5 to 512 rows, d 1024 to 9216 and N 2816 to
-// 36864, odd lengths among them, all shapes and splits.  (For tiles of 256 x 256 a fill that costs nothing came closest, with
+// 36864, odd lengths among them, all shapes and splits, those of 128 rows with the same earlier kernel.  On the present ones the plans for 299 other
+// products of 5 to 128 rows are on average 1.6 % (up) and 4.1 % (down) behind the fastest of all, one in ten by more than 4 and 14 %, at
+// most by 50 and 28 %.  (For tiles of 256 x 256 a fill that costs nothing came closest, with
 // fewer flop/s.  Only down projections of layers much wider than their N take those: none of 600000 drawn plans with N of 2.6 to 4 d, three
 // of 600000 of any proportions, e.g. 128 x 21752 x 4744.)
 struct FewRowsTime {
@@ -211,7 +213,7 @@ void consider(const Shape& ts, const Product& p, size_t room, GemmPlan& best, do
 // tokens, 7168 x 28672, neuron-major 2446 -> 715 us; 8 x 512 tokens, 9216 x 36864 4.9 -> 4.0 ms (its down projection: 576 tiles =
 // two rounds and 64 tiles in four parts, where the former plan split all 576).
 // Up to 128 rows the plan is made again by FewRowsTime, for a k-contiguous B with the tiles of 16 tm x 16 tn too, and taken if
-// that estimate promises 6 % or more: over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
+// that estimate promises 6 % or more (a line drawn with that earlier kernel of the 128-row tiles): over 578 measured products 7 % faster on average, one in a hundred by more than 5 % (at
 // most 14 %) slower; without the line at 6 % 8 % and three in a hundred, up to 32 %.  (The line was drawn on these products.  164
 // others, both projections together, layers of 120 to 330 MB in turn: 13 % faster on average, at most 2.5 % slower.)  From 129 rows on the slim tiles are 3 to
 // 50 % slower than the others (their rows of B are read by several workgroups), and a k-major B, whose rows would be pieces of 32
