@@ -58,7 +58,7 @@ def build_binding() -> bool:
         return True
     if os.path.exists(BINDING_PATH):
         os.remove(BINDING_PATH)   # of another library
-    sys.stderr.write("no C module for the per-token call, which goes through ctypes instead (about 1 us more):\n" + why + "\n")
+    sys.stderr.write("no C module for the per-token call, which goes through ctypes instead (0.4 to 1 us more):\n" + why + "\n")
     return False
 
 

@@ -14,10 +14,11 @@
 //   - they are written out, sums in place: the compiler gives a product's result other registers than its
 //     sum has and moves them back, up to one move a product (the build looks for what it then no longer does, isa_check.py);
 //   - the operand tiles go from global memory straight into LDS, as buffer loads
-//     with a 32-bit offset per lane (with 64-bit addresses an issuing wave stood
-//     still for longer: 1325 against 1374 TFLOP/s at 4096 x 36864 x 9216), in rows
-//     of 128 bytes (rows of 64 bytes cost twice the tag look-ups of the L1:
-//     1156 TFLOP/s), a constant offset apart for one place in LDS;
+//     with a 32-bit offset per lane (with 64-bit addresses an issuing wave stands
+//     still for longer), in rows of 128 bytes (rows of 64 bytes cost twice the tag
+//     look-ups of the L1), a constant offset apart for one place in LDS.  Both were
+//     measured with 32x32x16 products, at 4096 x 36864 x 9216: 1374 TFLOP/s, 1325 with
+//     64-bit addresses, 1156 with rows of 64 bytes;
 //   - fragments are read half a k-tile before they are multiplied, and the one barrier per k-tile sits in its middle;
 //   - LDS holds five operand tiles of 32 KB: A and B of the k-tile that is
 //     multiplied and of the next one, and room for B of the one after;
