@@ -332,13 +332,18 @@ uint64_t next_call() noexcept {
 //   four tokens   fp32  256 x 256   7.9 / 5.2, 5.9 / 5.2     256 x 512  7.8 / 7.8, 6.7 / 8.1   gated 512 x 72 7.8 / 6.9, 6.3 / 7.0
 //                 fp16  256 x 512   7.9 / 6.8, 6.9 / 6.9     gated 256 x 256  7.8 / 5.6, 6.6 / 5.7
 // (of 208 such layers none of up to 64 K elements was slower in either way).  Both ways give the same bits.
-// Call by call the hidden values of more than 64 K elements are shared where a workgroup would read four batches of rows or more (a call's
-// words are its own only once, so a captured call, which runs many times, has none).  us, every workgroup all / shared:
+// Call by call the hidden values of more than 64 K elements are shared where that saves a workgroup three batches of rows or more and
+// there are three workgroups or more (a call's words are its own only once, so a captured call, which runs many times, has none).  us,
+// every workgroup all / shared:
 //   fp32  256 x 256 (4 batches, 64 K) 5.38 / 5.33    256 x 288 (5) 5.81 / 5.33    256 x 384 (6) 6.37 / 5.31   128 x 576 (5) 5.95 / 5.69
 //         512 x 192 (3) 5.84 / 6.08   512 x 224 (4) 6.86 / 6.10   gated 256 x 192 (3) 5.92 / 5.65   256 x 224 (4) 6.73 / 5.71   512 x 112 (2) 6.65 / 6.37
 //         four tokens   256 x 288 6.02 / 5.80    512 x 192 5.84 / 6.11   512 x 224 6.93 / 6.20
 //   fp16  256 x 384 (3) 5.59 / 5.98   256 x 448 (4) 6.26 / 5.86   512 x 224 (4) 6.62 / 5.81   1024 x 128 (2) 5.84 / 6.14   bf16 gated 256 x 256 (2) 6.11 / 6.42
-constexpr int64_t kSmallElements = 128 * 1024, kSmallElementsGraph = 64 * 1024, kSmallBatchesShare = 4;
+//   one workgroup    fp32  16 x 1025 6.49 / 7.83, 16 x 2048 8.83 / 10.65    fp16  32 x 769 6.59 / 7.61
+//   two              fp32  32 x 1025 (5 batches, 2 saved) 6.51 / 7.14   32 x 1537 (7, 3) 8.08 / 8.42   32 x 2048 (8, 4) 8.96 / 8.86
+//   three            fp32  48 x 1025 (5, 3) 6.51 / 6.45   48 x 1537 (7, 4) 8.18 / 7.65   gated 48 x 1024 (4, 2) 6.84 / 7.12
+// Of 164 such layers in the range of the rule none is more than 0.7 % slower shared, and with layers in turn all are 7 % faster or more.
+constexpr int64_t kSmallElements = 128 * 1024, kSmallElementsGraph = 64 * 1024, kSmallBatchesSaved = 3, kSmallSharers = 3;
 DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act, int n_wg, hipStream_t s) {
   const int mode = params().decode_small;
   const int64_t vec = 16 / elem_bytes(dtype), vecs = d / vec;
@@ -351,7 +356,9 @@ DecodeSmall decode_small_way(int64_t B, int64_t K, int64_t d, int dtype, int act
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;  // the null stream is never captured
   if (s && !(hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)) return DecodeSmall::kNo;
   const int64_t lanes = vecs <= 16 ? 16 : vecs <= 32 ? 32 : 64, rows = kSmallRows * kSmallWaves * (64 / lanes);
-  return mode == 3 || (K + rows - 1) / rows >= kSmallBatchesShare ? DecodeSmall::kShare : DecodeSmall::kAll;
+  const int64_t sharers = (vecs + kSmallQuads - 1) / kSmallQuads, batches = (K + rows - 1) / rows;
+  const bool pays = sharers >= kSmallSharers && batches - (batches + sharers - 1) / sharers >= kSmallBatchesSaved;
+  return mode == 3 || pays ? DecodeSmall::kShare : DecodeSmall::kAll;
 }
 
 int decode_small_gave_up(uint32_t* out) {

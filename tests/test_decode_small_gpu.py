@@ -164,14 +164,17 @@ def test_small_decode_shared(lib, act, dt, patience):
     assert gave_up == alone if patience == 0 else gave_up < alone // 2, (gave_up, alone)
 
 
-# Which way a call takes, with the setting that every program has: both sides of the lines for elements (64 K and 128 K) and for batches of
-# rows (four), and of a captured stream, whose calls are two launches wherever their values would be shared
+# Which way a call takes, with the setting that every program has: both sides of the lines for elements (64 K and 128 K), for batches of
+# rows that sharing saves (three) and for workgroups (three), and of a captured stream, whose calls are two launches above 64 K elements
 @pytest.mark.parametrize("act,dt,d,K,B,way", [("relu", torch.float32, 256, 256, 1, "all"), ("relu", torch.float32, 256, 257, 1, "shared"),
                                               ("relu", torch.float32, 512, 192, 4, "all"), ("relu", torch.float32, 512, 193, 4, "shared"),
                                               ("relu", torch.float32, 256, 512, 1, "shared"), ("relu", torch.float32, 256, 513, 1, "two launches"),
                                               ("swiglu", torch.float32, 256, 192, 1, "all"), ("swiglu", torch.float32, 256, 193, 1, "shared"),
                                               ("relu", torch.float16, 512, 192, 1, "all"), ("relu", torch.bfloat16, 512, 193, 1, "shared"),
-                                              ("relu", torch.float32, 512, 225, 5, "two launches")])
+                                              ("relu", torch.float32, 512, 225, 5, "two launches"),
+                                              ("relu", torch.float32, 16, 2048, 1, "all"), ("relu", torch.float32, 32, 2048, 4, "all"),
+                                              ("relu", torch.float32, 36, 1025, 1, "shared"), ("swiglu", torch.float32, 36, 1024, 1, "all"),
+                                              ("relu", torch.float16, 104, 1024, 1, "shared"), ("relu", torch.bfloat16, 96, 1024, 1, "all")])
 def test_small_decode_ways(lib, act, dt, d, K, B, way):
     assert lib.dev_decode_small(B, K, d, dt, act) == way
     w = _layer(dt, act, d, K, d + K)
@@ -185,7 +188,9 @@ def test_small_decode_ways(lib, act, dt, d, K, B, way):
     with torch.cuda.graph(g):
         captured = lib.dev_decode_small(B, K, d, dt, act, torch.cuda.current_stream().cuda_stream)
         lib.ffn_decode(x, desc, act, y=y, ws=ws)
-    elements = (2 if act == "swiglu" else 1) * K * d
+    vec = 4 if dt == torch.float32 else 8
+    held = max(16 * vec, 1 << (d - 1).bit_length())   # what the lanes of a row's loads hold
+    elements = (2 if act == "swiglu" else 1) * K * held
     assert captured == ("all" if way == "all" and elements <= 65536 else "two launches")
     for _ in range(3):
         y.zero_()
