@@ -185,11 +185,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int k = 0; k < 4; ++k) bv[k] = to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]);
       }
-      const float4 c0 = make_float4(z[0], z[1], z[2], z[3]), c1 = make_float4(u[0], u[1], u[2], u[3]);
       const size_t o = (size_t)row * g.ldo + col;
-      if (dual) store_quad<D, EPI_SWIGLU>(g, c0, c1, bv, o);
-      else if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, c0, c1, bv, o);
-      else store_quad<D, EPI_LINEAR>(g, c0, c1, bv, o);
+      if (dual) store_quad<D, EPI_SWIGLU>(g, z, u, bv, o);
+      else if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, z, u, bv, o);
+      else store_quad<D, EPI_LINEAR>(g, z, u, bv, o);
     }
   }
 }

@@ -12,6 +12,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int WK = 64;             // k per tile
@@ -39,30 +41,38 @@ __device__ __forceinline__ void mfma16_in_place(const uint4& a, const uint4& b, 
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
 }
 
-// Four consecutive columns of one output row: epilogue, then one 16-byte and / or one 8-byte store.
+// Four consecutive columns of one output row: the score and the element type's bits of each.
+struct Quad {
+  f32x4 score;
+  uint2 bits;
+};
 template <class D, int EPI>
-__device__ __forceinline__ void store_quad(const GemmArgs& g, float4 c0, float4 c1, const float (&bv)[4], size_t o) {
+__device__ __forceinline__ Quad epilogue_quad(f32x4 z, f32x4 u, const float (&bv)[4]) {
   using T = typename D::T;
-  const float z[4] = {c0.x, c0.y, c0.z, c0.w}, u[4] = {c1.x, c1.y, c1.z, c1.w};
-  float h[4], score[4];
+  Quad q;
   T e[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
+    float h;
     if (EPI == EPI_SWIGLU) {
-      h[k] = silu(z[k]) * u[k];
-      score[k] = fabsf(h[k]);
+      h = silu(z[k]) * u[k];
+      q.score[k] = fabsf(h);
     } else {
-      h[k] = EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
-      score[k] = h[k];
+      h = EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
+      q.score[k] = h;
     }
-    e[k] = from_float<D>(h[k]);
+    e[k] = from_float<D>(h);
   }
-  if (g.out_f) *reinterpret_cast<float4*>(g.out_f + o) = make_float4(score[0], score[1], score[2], score[3]);
-  if (g.out_e) {
-    uint2 pack;
-    __builtin_memcpy(&pack, e, 8);
-    *reinterpret_cast<uint2*>(reinterpret_cast<T*>(g.out_e) + o) = pack;
-  }
+  __builtin_memcpy(&q.bits, e, 8);
+  return q;
+}
+
+// One 16-byte and / or one 8-byte store of them.
+template <class D, int EPI>
+__device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 z, f32x4 u, const float (&bv)[4], size_t o) {
+  const Quad q = epilogue_quad<D, EPI>(z, u, bv);
+  if (g.out_f) *reinterpret_cast<f32x4*>(g.out_f + o) = q.score;
+  if (g.out_e) *reinterpret_cast<uint2*>(reinterpret_cast<typename D::T*>(g.out_e) + o) = q.bits;
 }
 
 // Buffer descriptor over everything from a uniform address on: a load then takes one 32-bit offset per lane.
@@ -165,39 +175,12 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
     for (int j = 0; j < TJ; ++j) asm volatile("" : "+a"(acc[i][j]));
   };
 
-  // Element v of lane l is row l % 16, column 4 (l / 16) + v of a block: four neighbouring columns go out as they are.
   const int l15 = lane & 15, quarter = lane >> 4;
-  row0 += l15;
-  if (dual) {
-    // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
-    const int col0 = n0 + wn * 8 * TJ + 4 * (quarter & 1) + 8 * (quarter >> 1);
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      const int row = row0 + 16 * i;
-      settled(i);
-#pragma unroll
-      for (int j = 0; j < TJ; j += 2) {
-        const int j1 = j + 1 < TJ ? j + 1 : j;
-        float z[4], u[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[i][j][v]), f2u(acc[i][j1][v]), false, false);
-          z[v] = u2f(sw[0]);
-          u[v] = u2f(sw[1]);
-        }
-        const int col = col0 + 8 * j;
-        const float none[4] = {0.f, 0.f, 0.f, 0.f};
-        if (row < g.M && col < g.Nn && (j + 1 < TJ || quarter < 2))
-          store_quad<D, EPI_SWIGLU>(g, make_float4(z[0], z[1], z[2], z[3]), make_float4(u[0], u[1], u[2], u[3]), none, (size_t)row * g.ldo + col);
-      }
-    }
-    return;
-  }
-  const int col0 = n0 + wn * 16 * TJ + 4 * quarter;
   if (sums) {
+    const int col0 = n0 + wn * 16 * TJ + 4 * quarter;
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
-      const int row = row0 + 16 * i;
+      const int row = row0 + l15 + 16 * i;
       settled(i);
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
@@ -207,28 +190,81 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
     }
     return;
   }
+  // Outputs go through descriptors: an output that is not wanted has none of its bytes in range, and rows and columns past the edge get
+  // an offset that is in range of neither, so that nothing branches between one quad and the next.  With a test of the kind, of each
+  // output and of the edge at every quad, and 16-bit values in pieces of 32 bytes, 248 x 128 x 384 ReLU fp16 with both outputs took 11.8 us
+  // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, and 256 x 4096 x 16384 101.1 for
+  // 102.0.  128 rows of 2^20 columns at most: offsets stay below 2^29.
+  const size_t origin = (size_t)row0 * g.ldo + n0;
+  const auto to_f = __builtin_amdgcn_make_buffer_rsrc(g.out_f + origin, 0, g.out_f ? 0x7fffffff : 0, 0x00020000);
+  const auto to_e = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<T*>(g.out_e) + origin, 0, g.out_e ? 0x3fffffff : 0, 0x00020000);
+  auto at = [&](int i, int c, bool there) {  // element offset of column n0 + c in this lane's row of block i
+    return there && row0 + l15 + 16 * i < g.M && n0 + c < g.Nn ? (uint32_t)(l15 + 16 * i) * (uint32_t)g.ldo + (uint32_t)c : 0x3fffffffu;
+  };
+  auto put_scores = [&](const Quad& q, uint32_t o) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q.score), to_f, (int)(o * 4u), 0, 0);
+  };
+  // Two neighbouring sixteens of columns from c on, four a lane, of which there are `n`: they go out eight a lane, so that a row's
+  // piece is 64 bytes.
+  auto put_bits = [&](uint2 a, uint2 b, int i, int c, int n) {
+    const auto x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false), y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(x[0], x[1], false, false), hi = __builtin_amdgcn_permlane16_swap(y[0], y[1], false, false);
+    const u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+    __builtin_amdgcn_raw_buffer_store_b128(v, to_e, (int)(at(i, c + 8 * quarter, 8 * quarter < n) * 2u), 0, 0);
+  };
+  if (dual) {
+    // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
+    const int c0 = wn * 8 * TJ;
+    const float none[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      settled(i);
+      uint2 bits[2];
+#pragma unroll
+      for (int j = 0; j < TJ; j += 2) {
+        const bool pair = j + 1 < TJ;
+        f32x4 z, u;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[i][j][v]), f2u(acc[i][pair ? j + 1 : j][v]), false, false);
+          z[v] = u2f(sw[0]);
+          u[v] = u2f(sw[1]);
+        }
+        const Quad q = epilogue_quad<D, EPI_SWIGLU>(z, u, none);
+        put_scores(q, at(i, c0 + 8 * j + 4 * quarter, pair || quarter < 2));
+        bits[j >> 1 & 1] = q.bits;
+        if (j & 2) put_bits(bits[0], bits[1], i, c0 + 8 * (j - 2), pair ? 32 : 24);
+        else if (j + 2 >= TJ) put_bits(bits[0], bits[0], i, c0 + 8 * j, pair ? 16 : 8);
+      }
+    }
+    return;
+  }
+  const int c0 = wn * 16 * TJ;
   float bv[TJ][4];
 #pragma unroll
   for (int j = 0; j < TJ; ++j)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int col = col0 + 16 * j;
+      const int col = n0 + c0 + 16 * j + 4 * quarter;
       bv[j][k] = g.bias && col < g.Nn ? to_float<D>(reinterpret_cast<const T*>(g.bias)[col + k]) : 0.f;
     }
+  auto all = [&](auto kind) {
 #pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    const int row = row0 + 16 * i;
-    settled(i);
+    for (int i = 0; i < TI; ++i) {
+      settled(i);
+      uint2 bits[2];
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const int col = col0 + 16 * j;
-      const float4 c = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      if (row < g.M && col < g.Nn) {  // Nn is a multiple of 8: a quad is inside or outside as a whole
-        if (epi == EPI_RELU) store_quad<D, EPI_RELU>(g, c, c, bv[j], (size_t)row * g.ldo + col);
-        else store_quad<D, EPI_LINEAR>(g, c, c, bv[j], (size_t)row * g.ldo + col);
+      for (int j = 0; j < TJ; ++j) {
+        const Quad q = epilogue_quad<D, kind.value>(acc[i][j], acc[i][j], bv[j]);
+        if (kind.value == EPI_RELU) put_scores(q, at(i, c0 + 16 * j + 4 * quarter, true));
+        bits[j & 1] = q.bits;
+        if (j & 1) put_bits(bits[0], bits[1], i, c0 + 16 * (j - 1), 32);
+        else if (j + 1 == TJ) put_bits(bits[0], bits[0], i, c0 + 16 * j, 16);
       }
     }
-  }
+  };
+  if (epi == EPI_RELU) all(Const<EPI_RELU>{});
+  else all(Const<EPI_LINEAR>{});  // a down projection, which has no scores
 }
 
 // Which tile and which part of k a workgroup has: the first g.full tiles are computed whole, each of the
