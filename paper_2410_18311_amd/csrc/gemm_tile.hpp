@@ -61,6 +61,9 @@ __device__ __forceinline__ Quad epilogue_quad(f32x4 z, f32x4 u, const float (&bv
       h = EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
       q.score[k] = h;
     }
+    // opaque: else the compiler makes a product and its conversion to fp16 one instruction with one rounding, and the bits are no longer
+    // those of the score, rounded
+    asm("" : "+v"(h));
     e[k] = from_float<D>(h);
   }
   __builtin_memcpy(&q.bits, e, 8);

@@ -341,7 +341,9 @@ def test_dense_odd_rows_wide_tiles(lib, act, dtype, M, d, N):
 # values and outputs are the same bits whichever of them a call asks for.
 @pytest.mark.parametrize("act,dtype,M,d,N", [("swiglu", torch.bfloat16, 13, 496, 2624), ("relu", torch.float16, 53, 1000, 2224),
                                              ("relu", torch.bfloat16, 21, 568, 2816), ("swiglu", torch.float16, 21, 560, 2048),
-                                             ("relu", torch.float16, 57, 6856, 18768)])
+                                             ("relu", torch.float16, 57, 6856, 18768),
+                                             # and a plan of 256-row tiles
+                                             ("swiglu", torch.float16, 1000, 1160, 8192)])
 def test_outputs_asked_for_change_no_bits(lib, act, dtype, M, d, N):
     w = rand_weights(d, N, dtype, act, "out_major", seed=M, device=DEV)
     X = torch.randn(M, d, generator=torch.Generator().manual_seed(M)).to(dtype).to(DEV)
