@@ -197,12 +197,17 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   // an offset that is in range of neither, so that nothing branches between one quad and the next.  With a test of the kind, of each
   // output and of the edge at every quad, and 16-bit values in pieces of 32 bytes, 248 x 128 x 384 ReLU fp16 with both outputs took 11.8 us
   // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, and 256 x 4096 x 16384 101.1 for
-  // 102.0.  128 rows of 2^20 columns at most: offsets stay below 2^29.
+  // 102.0.  128 rows of 2^20 columns at most: elements below 2^27.  The offset past the edge is 2^29 elements, as far from every range's end
+  // as from 2^32, where the last words of a store would come round to the first bytes of the range.
+  constexpr uint32_t kNowhere = 1u << 29;
+  constexpr int kRange = 1 << 30;  // bytes, of either output
   const size_t origin = (size_t)row0 * g.ldo + n0;
-  const auto to_f = __builtin_amdgcn_make_buffer_rsrc(g.out_f + origin, 0, g.out_f ? 0x7fffffff : 0, 0x00020000);
-  const auto to_e = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<T*>(g.out_e) + origin, 0, g.out_e ? 0x3fffffff : 0, 0x00020000);
+  auto output = [&](const void* p, size_t bytes) {  // integers: a null pointer is not added to
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(p) + origin * bytes), 0, p ? kRange : 0, 0x00020000);
+  };
+  const auto to_f = output(g.out_f, sizeof(float)), to_e = output(g.out_e, sizeof(T));
   auto at = [&](int i, int c, bool there) {  // element offset of column n0 + c in this lane's row of block i
-    return there && row0 + l15 + 16 * i < g.M && n0 + c < g.Nn ? (uint32_t)(l15 + 16 * i) * (uint32_t)g.ldo + (uint32_t)c : 0x3fffffffu;
+    return there && row0 + l15 + 16 * i < g.M && n0 + c < g.Nn ? (uint32_t)(l15 + 16 * i) * (uint32_t)g.ldo + (uint32_t)c : kNowhere;
   };
   auto put_scores = [&](const Quad& q, uint32_t o) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q.score), to_f, (int)(o * 4u), 0, 0);
