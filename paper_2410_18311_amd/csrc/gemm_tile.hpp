@@ -197,8 +197,9 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   // an offset that is in range of neither, so that nothing branches between one quad and the next.  With a test of the kind, of each
   // output and of the edge at every quad, and 16-bit values in pieces of 32 bytes, 248 x 128 x 384 ReLU fp16 with both outputs took 11.8 us
   // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, and 256 x 4096 x 16384 101.1 for
-  // 102.0.  128 rows of 2^20 columns at most: elements below 2^27.  The offset past the edge is 2^29 elements, as far from every range's end
-  // as from 2^32, where the last words of a store would come round to the first bytes of the range.
+  // 102.0.  Blocks of 16 rows behind the last one are left out, or a prompt of a few tokens works out and drops as many quads as one of 128
+  // (14 x 128 x 144 gated bf16 10.6 us, 8.8 without them).  128 rows of 2^20 columns at most: elements below 2^27.  The offset past the edge is 2^29
+  // elements, outside both ranges and far from 2^32 bytes, where the last words of a store would come round to the first of the range.
   constexpr uint32_t kNowhere = 1u << 29;
   constexpr int kRange = 1 << 30;  // bytes, of either output
   const size_t origin = (size_t)row0 * g.ldo + n0;
@@ -223,9 +224,11 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   if (dual) {
     // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
     const int c0 = wn * 8 * TJ;
+    if (n0 + c0 >= g.Nn) return;
     const float none[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
+      if (row0 + 16 * i >= g.M) break;
       settled(i);
       uint2 bits[2];
 #pragma unroll
@@ -248,6 +251,7 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
     return;
   }
   const int c0 = wn * 16 * TJ;
+  if (row0 >= g.M || n0 + c0 >= g.Nn) return;
   float bv[TJ][4];
 #pragma unroll
   for (int j = 0; j < TJ; ++j)
@@ -259,6 +263,7 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   auto all = [&](auto kind) {
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
+      if (row0 + 16 * i >= g.M) break;
       settled(i);
       uint2 bits[2];
 #pragma unroll
