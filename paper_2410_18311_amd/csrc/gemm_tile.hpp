@@ -53,17 +53,11 @@ __device__ __forceinline__ Quad epilogue_quad(f32x4 z, f32x4 u, const float (&bv
   T e[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    float h;
-    if (EPI == EPI_SWIGLU) {
-      h = silu(z[k]) * u[k];
-      q.score[k] = fabsf(h);
-    } else {
-      h = EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
-      q.score[k] = h;
-    }
+    float h = EPI == EPI_SWIGLU ? silu(z[k]) * u[k] : EPI == EPI_RELU ? fmaxf(z[k] + bv[k], 0.f) : z[k] + bv[k];
     // opaque: else the compiler makes a product and its conversion to fp16 one instruction with one rounding, and the bits are no longer
     // those of the score, rounded
     asm("" : "+v"(h));
+    q.score[k] = EPI == EPI_SWIGLU ? fabsf(h) : h;
     e[k] = from_float<D>(h);
   }
   __builtin_memcpy(&q.bits, e, 8);
@@ -198,28 +192,31 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   // output and of the edge at every quad, and 16-bit values in pieces of 32 bytes, 248 x 128 x 384 ReLU fp16 with both outputs took 11.8 us
   // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, and 256 x 4096 x 16384 101.1 for
   // 102.0.  Blocks of 16 rows behind the last one are left out, or a prompt of a few tokens works out and drops as many quads as one of 128
-  // (14 x 128 x 144 gated bf16 10.6 us, 8.8 without them).  128 rows of 2^20 columns at most: elements below 2^27.  The offset past the edge is 2^29
-  // elements, outside both ranges and far from 2^32 bytes, where the last words of a store would come round to the first of the range.
-  constexpr uint32_t kNowhere = 1u << 29;
-  constexpr int kRange = 1 << 30;  // bytes, of either output
+  // (14 x 128 x 144 gated bf16 10.6 us, 8.8 without them).  128 rows of 2^20 columns at most: elements below 2^27.  A row or a column past the
+  // edge is 2^28 elements off and both 2^29: outside the ranges, and far from 2^32 bytes, where the last words of a store would come
+  // round to the first of the range.
+  constexpr uint32_t kNowhere = 1u << 28;
+  constexpr int kRange = 1 << 29;  // bytes, of either output
   const size_t origin = (size_t)row0 * g.ldo + n0;
   auto output = [&](const void* p, size_t bytes) {  // integers: a null pointer is not added to
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(p) + origin * bytes), 0, p ? kRange : 0, 0x00020000);
   };
   const auto to_f = output(g.out_f, sizeof(float)), to_e = output(g.out_e, sizeof(T));
-  auto at = [&](int i, int c, bool there) {  // element offset of column n0 + c in this lane's row of block i
-    return there && row0 + l15 + 16 * i < g.M && n0 + c < g.Nn ? (uint32_t)(l15 + 16 * i) * (uint32_t)g.ldo + (uint32_t)c : kNowhere;
+  auto row_at = [&](int i) {  // element offset of this lane's row of block i
+    const uint32_t r = l15 + 16 * i, o = r * (uint32_t)g.ldo;
+    return row0 + (int)r < g.M ? o : kNowhere;
   };
+  auto column_at = [&](int c, bool there) { return there & (n0 + c < g.Nn) ? (uint32_t)c : kNowhere; };
   auto put_scores = [&](const Quad& q, uint32_t o) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q.score), to_f, (int)(o * 4u), 0, 0);
   };
   // Two neighbouring sixteens of columns from c on, four a lane, of which there are `n`: they go out eight a lane, so that a row's
   // piece is 64 bytes.
-  auto put_bits = [&](uint2 a, uint2 b, int i, int c, int n) {
+  auto put_bits = [&](uint2 a, uint2 b, uint32_t row, int c, int n) {
     const auto x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false), y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
     const auto lo = __builtin_amdgcn_permlane16_swap(x[0], x[1], false, false), hi = __builtin_amdgcn_permlane16_swap(y[0], y[1], false, false);
     const u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
-    __builtin_amdgcn_raw_buffer_store_b128(v, to_e, (int)(at(i, c + 8 * quarter, 8 * quarter < n) * 2u), 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, to_e, (int)((row + column_at(c + 8 * quarter, 8 * quarter < n)) * 2u), 0, 0);
   };
   if (dual) {
     // lanes 0 .. 31 hold the gate, 32 .. 63 the up values of a block's eight columns: two blocks change halves
@@ -230,6 +227,7 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
     for (int i = 0; i < TI; ++i) {
       if (row0 + 16 * i >= g.M) break;
       settled(i);
+      const uint32_t row = row_at(i);
       uint2 bits[2];
 #pragma unroll
       for (int j = 0; j < TJ; j += 2) {
@@ -242,10 +240,10 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
           u[v] = u2f(sw[1]);
         }
         const Quad q = epilogue_quad<D, EPI_SWIGLU>(z, u, none);
-        put_scores(q, at(i, c0 + 8 * j + 4 * quarter, pair || quarter < 2));
+        put_scores(q, row + column_at(c0 + 8 * j + 4 * quarter, pair | (quarter < 2)));
         bits[j >> 1 & 1] = q.bits;
-        if (j & 2) put_bits(bits[0], bits[1], i, c0 + 8 * (j - 2), pair ? 32 : 24);
-        else if (j + 2 >= TJ) put_bits(bits[0], bits[0], i, c0 + 8 * j, pair ? 16 : 8);
+        if (j & 2) put_bits(bits[0], bits[1], row, c0 + 8 * (j - 2), pair ? 32 : 24);
+        else if (j + 2 >= TJ) put_bits(bits[0], bits[0], row, c0 + 8 * j, pair ? 16 : 8);
       }
     }
     return;
@@ -265,14 +263,15 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
     for (int i = 0; i < TI; ++i) {
       if (row0 + 16 * i >= g.M) break;
       settled(i);
+      const uint32_t row = row_at(i);
       uint2 bits[2];
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
         const Quad q = epilogue_quad<D, kind.value>(acc[i][j], acc[i][j], bv[j]);
-        if (kind.value == EPI_RELU) put_scores(q, at(i, c0 + 16 * j + 4 * quarter, true));
+        if (kind.value == EPI_RELU) put_scores(q, row + column_at(c0 + 16 * j + 4 * quarter, true));
         bits[j & 1] = q.bits;
-        if (j & 1) put_bits(bits[0], bits[1], i, c0 + 16 * (j - 1), 32);
-        else if (j + 1 == TJ) put_bits(bits[0], bits[0], i, c0 + 16 * j, 16);
+        if (j & 1) put_bits(bits[0], bits[1], row, c0 + 16 * (j - 1), 32);
+        else if (j + 1 == TJ) put_bits(bits[0], bits[0], row, c0 + 16 * j, 16);
       }
     }
   };
