@@ -190,8 +190,8 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int epi, bool du
   // Outputs go through descriptors: an output that is not wanted has none of its bytes in range, and rows and columns past the edge get
   // an offset that is in range of neither, so that nothing branches between one quad and the next.  With a test of the kind, of each
   // output and of the edge at every quad, and 16-bit values in pieces of 32 bytes, 248 x 128 x 384 ReLU fp16 with both outputs took 11.8 us
-  // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, and 256 x 4096 x 16384 101.1 for
-  // 102.0.  Blocks of 16 rows behind the last one are left out, or a prompt of a few tokens works out and drops as many quads as one of 128
+  // and bf16 13.3 (two kernels with the kind built in, rows through LDS: 11.1 and 12.9); so 11.0 and 12.2, 256 x 4096 x 16384 101.1 for
+  // 102.0, and 1024 x 5120 x 13824 gated bf16 345.1 for 352.8 (with offsets that the compiler chose by branches 356).  Blocks of 16 rows behind the last one are left out, or a prompt of a few tokens works out and drops as many quads as one of 128
   // (14 x 128 x 144 gated bf16 10.6 us, 8.8 without them).  128 rows of 2^20 columns at most: elements below 2^27.  A row or a column past the
   // edge is 2^28 elements off and both 2^29: outside the ranges, and far from 2^32 bytes, where the last words of a store would come
   // round to the first of the range.
