@@ -444,3 +444,28 @@ def test_dense_values_that_are_not_finite_in_a_ragged_k_tile(lib, tile, splits):
     assert bool(torch.isinf(Y2[:, 2]).all()) and bool(torch.isnan(Y2[:, 4]).all())
     rest = [c for c in range(d) if c not in (2, 4)]
     assert bool(torch.isfinite(Y2[:, rest]).all())
+
+
+# What an output's conversion to 16 bits does with ties, the largest and smallest numbers, infinities and NaN, in the kernels for few tokens,
+# in slim, middle and wide tiles: hidden values of one and two weights a column, so that the fp32 sum is exact.
+@pytest.mark.parametrize("M", [1, 16, 200, 1100])
+@pytest.mark.parametrize("layout", ["out_major", "neuron_major"])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_dense_outputs_are_rounded_to_nearest_even(lib, M, layout, dtype):
+    d, N = 512, 64
+    g = torch.Generator().manual_seed(M)
+    fi = torch.finfo(dtype)
+    a = torch.randn(d, generator=g).to(dtype)
+    b = (a.float() * torch.tensor([0.5, -0.5, 0.25, 1.0])[torch.randint(4, (d,), generator=g)] * fi.eps).to(dtype)   # halfway, and beside it
+    a[:8] = torch.tensor([fi.max, -fi.max, float("inf"), -float("inf"), float("nan"), 0.0, fi.tiny, -fi.tiny], dtype=dtype)
+    b[:8] = torch.tensor([fi.max * fi.eps / 4, -fi.max * fi.eps / 4, 1.0, 1.0, 1.0, -0.0, fi.tiny / 2, fi.tiny / 2], dtype=dtype)
+    down = torch.zeros(d, N, dtype=dtype)
+    down[:, 0], down[:, 1] = a, b
+    X = torch.zeros(M, d, dtype=dtype, device=DEV)
+    w_up, b_up = torch.zeros(N, d, dtype=dtype, device=DEV), torch.ones(N, dtype=dtype, device=DEV)
+    w_down = (down if layout == "out_major" else down.t()).contiguous().to(DEV)
+    Y, _ = lib.ffn_dense(X, w_up, None, b_up, w_down, None, layout, "relu", want_y=True, want_a=True)
+    want = (a.float() + b.float()).to(dtype).expand(M, d)
+    got = Y.cpu()
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got[~got.isnan()], want[~want.isnan()])
